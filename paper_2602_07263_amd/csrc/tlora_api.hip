@@ -90,6 +90,8 @@ struct Plan {
   int64_t atp_elems = 0;
   int r_total = 0;                                      // sum of rpad_j
   int64_t sx_elems = 0;                                 // elements of the per-tile K-extension operands
+  int shrink_splits_x = 1, shrink_splits_dy = 1;        // contraction splits of the shrinks over d_in (S) and d_out (dS)
+  size_t partial_bytes = 0;                             // what off_partial holds: dA / dB tiles, or sums of split launches
   // workspace byte offsets
   size_t off_tables = 0, off_S = 0, off_dS = 0, off_Shi = 0, off_Slo = 0, off_dShi = 0, off_dSlo = 0, off_Sx = 0, off_dSx = 0, off_atp = 0, off_wt = 0, off_ap = 0, off_bp = 0,
          off_partial = 0, total = 0;
@@ -184,6 +186,23 @@ bool build_grad_units(const Plan& pl, int D, std::vector<GradUnit>& units, std::
     return ca > cb;
   });
   return true;
+}
+
+// Splits of a streaming shrink over K of a plan whose units have 32 rows: enough that units x splits fill the 512
+// workgroup slots (80 KB of LDS each, two per CU), while a split keeps at least 4 K-steps of 64 (three are in flight
+// before the first is multiplied).  Fewer if the fp32 sums (4 bytes per packed S element and split) would not fit.
+constexpr int kShrinkSlots = 512, kShrinkMinSteps = 4, kShrinkMaxSplits = 32;
+int shrink_splits(const Plan& pl, int K, size_t max_bytes) {
+  if (pl.shrink_rows != 32 || g_opt.shrink_rows != 0 || K % 64 || pl.stream_units.empty()) return 1;
+  int64_t s = std::min<int64_t>(kShrinkSlots / (int64_t)pl.stream_units.size(), K / 64 / kShrinkMinSteps);
+  s = std::min<int64_t>({s, kShrinkMaxSplits, (int64_t)(max_bytes / (4 * (size_t)pl.s_elems))});
+  return s < 2 ? 1 : (int)s;
+}
+
+// Bytes of the plan tables that the forward alone needs, each table padded to 256 bytes.
+size_t forward_table_bytes(const Plan& pl) {
+  return align_up(sizeof(JobDev) * pl.jobs.size(), 256) + align_up(sizeof(TileDev) * pl.tile_jobs.size(), 256) +
+         align_up(sizeof(ShrinkUnit) * pl.shrink_units.size(), 256) + align_up(sizeof(ShrinkUnit) * pl.stream_units.size(), 256);
 }
 
 // fwd_only: tables and workspace of the forward alone (no transposed W, no dS, no dA / dB units or partial tiles)
@@ -328,10 +347,33 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     pl.off_Sx = wplace(2 * (size_t)pl.sx_elems + 256);
     if (!fwd_only) pl.off_dSx = wplace(2 * (size_t)pl.sx_elems + 256);
     pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
-
-    pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
     pl.off_bp = wplace(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32));
-    if (!fwd_only) pl.off_partial = wplace(sizeof(float) * (size_t)std::max(pl.gradB_partial, pl.gradA_partial));
+    pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
+    // Sums of split launches.  In the full plan they share the block of the dA / dB partial tiles (the launches follow one
+    // another).  The forward-only plan has a static scratch: there they lie where a_all would, which that path does not
+    // write, and in what the scratch leaves, so that a split never makes a problem too large for it.  Both plans cut the
+    // forward's contractions alike (a problem that the scratch holds is cut as the scratch allows everywhere): a row of
+    // Y has the same bits through both entry points.
+    const size_t fwd_base = align_up(forward_table_bytes(pl), 256) + 256 + 2 * align_up(2 * (size_t)pl.s_elems, 256) +
+                            align_up(2 * (size_t)pl.sx_elems + 256, 256) +
+                            align_up(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in), 256) +
+                            align_up(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32), 256);
+    const size_t fwd_total = fwd_base + align_up(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32), 256);
+    const size_t room = fwd_total <= TLORA_NOALLOC_SCRATCH_BYTES ? TLORA_NOALLOC_SCRATCH_BYTES - fwd_base
+                        : fwd_only                               ? 0
+                                                                 : SIZE_MAX;
+    pl.shrink_splits_x = shrink_splits(pl, pl.d_in, room);
+    if (pl.shrink_splits_x > 1) pl.partial_bytes = sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_x;
+    if (fwd_only) {
+      pl.off_partial = pl.off_ap;
+      w = std::max(w, align_up(pl.off_partial + pl.partial_bytes, 256));
+    } else {
+      pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, SIZE_MAX);
+      if (pl.shrink_splits_dy > 1)
+        pl.partial_bytes = std::max(pl.partial_bytes, sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_dy);
+      pl.partial_bytes = std::max(pl.partial_bytes, sizeof(float) * (size_t)std::max(pl.gradB_partial, pl.gradA_partial));
+      pl.off_partial = wplace(pl.partial_bytes);
+    }
   }
   pl.total = std::max<size_t>(w, 256);
   return TLORA_OK;
@@ -441,7 +483,14 @@ int prof_drain() {
 // S_j = X_j.A_j (or dS_j = dY_j.B_j^T): streaming kernel when the contraction length allows, else generic
 void run_shrink(const Plan& pl, const uint8_t* tb, const JobDev* jobs, const TileDev* tiles, const uint16_t* act, int K,
                 const uint16_t* packed, bool packed_is_atp, uint16_t* hi, uint16_t* lo, uint16_t* Sx,
-                const int32_t* row_index, hipStream_t st) {
+                const int32_t* row_index, float* part, hipStream_t st) {
+  const int splits = packed_is_atp ? pl.shrink_splits_x : pl.shrink_splits_dy;
+  if (splits > 1) {
+    launch_shrink_split(jobs, tiles, reinterpret_cast<const ShrinkUnit*>(tb + pl.tb_stream), (int)pl.stream_units.size(),
+                        splits, pl.T, act, K, packed, packed_is_atp, hi, lo, Sx, row_index, part, pl.s_elems, st);
+    return;
+  }
+  launch_zero_fill(Sx, 2 * (size_t)pl.sx_elems, st);
   if (K % 32 == 0)
     launch_shrink_stream(jobs, tiles, reinterpret_cast<const ShrinkUnit*>(tb + pl.tb_stream),
                          (int)pl.stream_units.size(), pl.shrink_rows, g_opt.shrink_stages, act, K, packed, packed_is_atp,
@@ -695,13 +744,13 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
   {
     Timed t(TLORA_K_PACK, st, timed);
-    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, st);
-    launch_zero_fill(Sx, 2 * (size_t)pl.sx_elems, st);
+    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, no_alloc ? nullptr : ap, bp, st);
   }
   {
     Timed t(TLORA_K_SHRINK, st, timed);
     run_shrink(pl, tb, jobs, tiles, static_cast<const uint16_t*>(p->X), pl.d_in, atp, true,
-               reinterpret_cast<uint16_t*>(ws + pl.off_Shi), reinterpret_cast<uint16_t*>(ws + pl.off_Slo), Sx, in_index, st);
+               reinterpret_cast<uint16_t*>(ws + pl.off_Shi), reinterpret_cast<uint16_t*>(ws + pl.off_Slo), Sx, in_index,
+               reinterpret_cast<float*>(ws + pl.off_partial), st);
   }
   if (timed) launch_zero_fill(ws + pl.off_clock, 16, st);
   Timed tg(TLORA_K_GEMM_FWD, st, timed);
@@ -834,19 +883,15 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     Timed t(TLORA_K_PACK, st);
     // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace
     if (!reuse_S) launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, st);
-    if (pl.T > 0) {
-      launch_zero_fill(dSx, 2 * (size_t)pl.sx_elems, st);
-      if (redo_S) launch_zero_fill(Sx, 2 * (size_t)pl.sx_elems, st);
-    }
   }
   if (pl.T > 0) {
     if (redo_S) {
       Timed t(TLORA_K_SHRINK, st);
-      run_shrink(pl, tb, jobs, tiles, Xb, pl.d_in, atp, true, Shi, Slo, Sx, in_index, st);
+      run_shrink(pl, tb, jobs, tiles, Xb, pl.d_in, atp, true, Shi, Slo, Sx, in_index, partial, st);
     }
     {
       Timed t(TLORA_K_SHRINK, st);
-      run_shrink(pl, tb, jobs, tiles, dYb, pl.d_out, bp, false, dShi, dSlo, dSx, in_index, st);
+      run_shrink(pl, tb, jobs, tiles, dYb, pl.d_out, bp, false, dShi, dSlo, dSx, in_index, partial, st);
     }
     if (dX) {
       // dX = dY . W^T contracts over W's contiguous dimension.  Against a transposed copy of W the weight tiles
@@ -1887,9 +1932,14 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       w.push_back({pl.off_Sx, sx});
       if (!fwd_only) w.push_back({pl.off_dSx, sx});
       w.push_back({pl.off_atp, 2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)});
-      w.push_back({pl.off_ap, 2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)});
       w.push_back({pl.off_bp, 2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32)});
-      if (!fwd_only) w.push_back({pl.off_partial, 4 * (size_t)std::max(pl.gradB_partial, pl.gradA_partial)});
+      if (!fwd_only) w.push_back({pl.off_ap, 2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)});
+      if (4 * (size_t)std::max(pl.gradB_partial, pl.gradA_partial) > pl.partial_bytes) return 64;
+      for (int k : {pl.shrink_splits_x, pl.shrink_splits_dy})
+        if (k < 1 || (k > 1 && 4 * se * (size_t)k > pl.partial_bytes)) return 65;
+      w.push_back({pl.off_partial, pl.partial_bytes});
+      if (fwd_only && pl.total <= TLORA_NOALLOC_SCRATCH_BYTES && pl.off_partial + pl.partial_bytes > TLORA_NOALLOC_SCRATCH_BYTES)
+        return 66;
     }
     size_t end = 0;
     for (auto& r : w) {

@@ -39,6 +39,12 @@ void launch_shrink_stream(const JobDev* jobs, const TileDev* tiles, const Shrink
                           int shrink_rows, int stages, const uint16_t* act, int K, const uint16_t* packed,
                           bool packed_is_atp, uint16_t* S_hi, uint16_t* S_lo, uint16_t* Sx, const int32_t* row_index,
                           hipStream_t st);
+// Same result with the contraction cut into `splits` (K % 64 == 0, units of 32 rows; splits <= K / 64): `part` holds
+// `splits` copies of part_stride floats (>= the packed S elements).  Writes all of Sx, zeros included: no fill needed.
+void launch_shrink_split(const JobDev* jobs, const TileDev* tiles, const ShrinkUnit* units, int num_units, int splits, int T,
+                         const uint16_t* act, int K, const uint16_t* packed, bool packed_is_atp, uint16_t* S_hi,
+                         uint16_t* S_lo, uint16_t* Sx, const int32_t* row_index, float* part, int64_t part_stride,
+                         hipStream_t st);
 
 // out[t, n] = sum_k act[t, k] * Wop[k, n] + sum_p Sx_tile[t, p] * Eop[roff_first + p, n]
 //   w_is_kn = true : W is [K, N] row-major (forward,  Eop = b_all [R + 32, N])

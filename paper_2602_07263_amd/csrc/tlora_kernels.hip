@@ -142,6 +142,7 @@ __device__ __forceinline__ bf16x8 frag16_kn(const uint8_t* tile, int nb, int ks,
 //                                                             (shrink operand; dX K-extension operand when dX runs
 //                                                              against the transposed weight)
 //   a_all : [d_in, R + 32], job j in columns roff_j ..        (dX K-extension operand, k contiguous)
+//           (a_all null: not written, the forward alone does not read it)
 //   b_all : [R + 32, d_out], job j in rows roff_j ..          (forward K-extension operand; dS shrink operand)
 // blockIdx.y == num_jobs zero-fills the 32 trailing columns / rows, which the last tile's K-extension
 // may read (against zero activations) when its rank range is rounded up to the K-step.
@@ -159,7 +160,7 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
   const int kout8 = d_out / 8;
   const u32x4 zero = {0, 0, 0, 0};
   if ((int)blockIdx.y == num_jobs) {
-    for (int i = first; i < 4 * d_in; i += stride)
+    for (int i = first; a_all && i < 4 * d_in; i += stride)
       *reinterpret_cast<u32x4*>(a_all + (int64_t)(i >> 2) * ra + r_total + (i & 3) * 8) = zero;
     for (int i = first; i < 4 * d_in; i += stride) *reinterpret_cast<u32x4*>(atp + (int64_t)r_total * d_in + (int64_t)i * 8) = zero;
     for (int i = first; i < 4 * d_out; i += stride) *reinterpret_cast<u32x4*>(b_all + (int64_t)r_total * d_out + (int64_t)i * 8) = zero;
@@ -188,7 +189,7 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
       const int c = threadIdx.x + h * 256;                       // 512 chunks of 8 per layout
       {   // a_all: row k, rank columns p0 .. p0 + 7
         const int kk = c >> 3, p0 = (c & 7) * 8;
-        if (k_base + kk < d_in && p_base + p0 < jb.rpad) {
+        if (a_all && k_base + kk < d_in && p_base + p0 < jb.rpad) {
           uint32_t v[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = tile[kk][p0 + e];
@@ -471,13 +472,16 @@ constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 
 // stream, and since a launch is one round of units its slowest units set its duration.  Eight waves (4 row blocks
 // x 2 column halves) put two waves on every SIMD, so one's fragment reads overlap the other's MFMAs, and halve the
 // loads each wave issues.  For a 32-column unit waves 4-7 only help to load.
-template <int ROWS, int NS, int KS, int PCOLS, int WAVES>
+// SPLIT: the unit contracts only the K-steps [step0, step0 + nsteps) and leaves its fp32 sums in `part` (the packed
+// ragged layout of the planes, one copy per split), which shrink_emit_kernel adds up in split order.
+template <int ROWS, int NS, int KS, int PCOLS, int WAVES, bool SPLIT>
 __device__ __forceinline__ void shrink_stream_body(uint8_t* lds, const ShrinkUnit u, const JobDev jb,
                                                    const TileDev* __restrict__ tiles,
                                                    const uint16_t* __restrict__ act, int K,
                                                    const uint16_t* __restrict__ packed, int packed_is_atp,
                                                    uint16_t* __restrict__ Shi, uint16_t* __restrict__ Slo,
-                                                   uint16_t* __restrict__ Sx, const int32_t* __restrict__ row_index) {
+                                                   uint16_t* __restrict__ Sx, const int32_t* __restrict__ row_index,
+                                                   int step0, int nsteps, float* __restrict__ part) {
   constexpr int CW = PCOLS == 32 ? 4 : WAVES;      // waves that multiply
   constexpr int WM = PCOLS == 32 ? 4 : ROWS / 32;  // waves along token rows
   constexpr int WN = CW / WM;                      // waves along rank columns
@@ -500,7 +504,6 @@ __device__ __forceinline__ void shrink_stream_body(uint8_t* lds, const ShrinkUni
   const int p0 = u.pb * PCOLS;
   const int pvalid = min(PCOLS, jb.rpad - p0);     // > 0 by construction
   const uint16_t* P = packed + (packed_is_atp ? jb.atp_off : (int64_t)jb.roff * K) + (int64_t)p0 * K;
-  const int nsteps = K / KS;
 
   f32x16 acc[NPB];
 #pragma unroll
@@ -522,14 +525,14 @@ __device__ __forceinline__ void shrink_stream_body(uint8_t* lds, const ShrinkUni
     const int q = (wave * A_LD + i) * 64 + lane, r = q / CPR;
     const int c = KS == 32 ? (q & 3) ^ ((r >> 2) & 3) : (q & 7) ^ ((r >> 1) & 7);
     const int t = u.t0 + min(r, u.nrows - 1);      // token row of the job-sorted order; row_index: where it lies
-    asrc[i] = act + (int64_t)(row_index ? row_index[t] : t) * K + c * 8;
+    asrc[i] = act + (int64_t)(row_index ? row_index[t] : t) * K + c * 8 + (SPLIT ? (int64_t)step0 * KS : 0);
   }
 #pragma unroll
   for (int i = 0; i < P_LD; ++i) {
     pslot[i] = (wave * P_LD + i) % P_TOT;
     const int q = pslot[i] * 64 + lane, r = q / CPR;
     const int c = KS == 32 ? (q & 3) ^ ((r >> 2) & 3) : (q & 7) ^ ((r >> 1) & 7);
-    psrc[i] = P + (int64_t)min(r, pvalid - 1) * K + c * 8;
+    psrc[i] = P + (int64_t)min(r, pvalid - 1) * K + c * 8 + (SPLIT ? (int64_t)step0 * KS : 0);
     plive[i] = r < pvalid || lane == 0;
   }
   const uint32_t lds0 = lds_addr(lds);
@@ -571,6 +574,21 @@ __device__ __forceinline__ void shrink_stream_body(uint8_t* lds, const ShrinkUni
     }
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));   // drain: the stages are reused below
+  if (SPLIT) {
+    const int r = wm * 32 + (lane & 31);
+    if (multiplies && r < u.nrows) {
+      float* const row = part + jb.soff + (int64_t)(u.t0 - jb.row0 + r) * jb.rpad;
+#pragma unroll
+      for (int i = 0; i < NPB; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int p = p0 + wn * PW + i * 32 + g * 8 + (lane >> 5) * 4;
+          if (p < jb.rpad)
+            *reinterpret_cast<f32x4*>(row + p) = f32x4{acc[i][g * 4], acc[i][g * 4 + 1], acc[i][g * 4 + 2], acc[i][g * 4 + 3]};
+        }
+    }
+    return;
+  }
   __syncthreads();
 
   // Outputs: bf16 hi + lo planes (hi = bf16(x), lo = bf16(x - hi); pad rows of the job's last unit written as zeros)
@@ -643,10 +661,104 @@ __global__ void __launch_bounds__(WAVES * 64) shrink_stream_kernel(const JobDev*
   const ShrinkUnit u = units[blockIdx.x];
   const JobDev jb = jobs[u.job];
   if (LOW && jb.rpad <= 32)
-    shrink_stream_body<128, 8, 64, 32, WAVES>(lds, u, jb, tiles, act, K, packed, packed_is_atp, Shi, Slo, Sx, row_index);
+    shrink_stream_body<128, 8, 64, 32, WAVES, false>(lds, u, jb, tiles, act, K, packed, packed_is_atp, Shi, Slo, Sx,
+                                                     row_index, 0, K / KS, nullptr);
   else
-    shrink_stream_body<ROWS, NS_HIGH, KS, 128, WAVES>(lds, u, jb, tiles, act, K, packed, packed_is_atp, Shi, Slo, Sx,
-                                                      row_index);
+    shrink_stream_body<ROWS, NS_HIGH, KS, 128, WAVES, false>(lds, u, jb, tiles, act, K, packed, packed_is_atp, Shi, Slo,
+                                                             Sx, row_index, 0, K / KS, nullptr);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Shrink of a small batch, contraction cut into splits.  A unit streams 32 rows of X (8 KB per K-step of 64 with its
+// adapter tile) and is bound by the latency of its own loads, ~0.4 us per step whatever the rest of the chip does: 128
+// units of 32 rows leave half the workgroup slots empty and one 512-token job fills 16 of 256 CUs for the whole
+// 12288-long contraction.  blockIdx.y = split: each takes an even share of the K-steps, all splits run at once, and
+// shrink_emit_kernel adds their fp32 sums in split order (a fixed order: bit-reproducible) and writes what the direct
+// kernel writes.
+// ---------------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) shrink_split_kernel(const JobDev* __restrict__ jobs, const ShrinkUnit* __restrict__ units,
+                                                           const uint16_t* __restrict__ act, int K,
+                                                           const uint16_t* __restrict__ packed, int packed_is_atp,
+                                                           const int32_t* __restrict__ row_index, float* __restrict__ part,
+                                                           int64_t part_stride) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[4 * (32 + 128) * 128];
+  const ShrinkUnit u = units[blockIdx.x];
+  const JobDev jb = jobs[u.job];
+  const int total = K / 64;
+  const int s0 = (int)((int64_t)blockIdx.y * total / gridDim.y), s1 = (int)((int64_t)(blockIdx.y + 1) * total / gridDim.y);
+  shrink_stream_body<32, 4, 64, 128, 4, true>(lds, u, jb, nullptr, act, K, packed, packed_is_atp, nullptr, nullptr, nullptr,
+                                              row_index, s0, s1 - s0, part + (int64_t)blockIdx.y * part_stride);
+}
+
+// One workgroup = 8 rows of a GEMM tile, threads along the 16-byte chunks of the rows of its K-extension operand: own
+// job's columns get scale * (sum of the splits) and everything else zeros (so the operand needs no separate fill), and
+// the hi / lo planes get the sums, with the zero pad rows after a job's last token.  Bound by latency: the tile's jobs
+// come into LDS with one load per thread (walking the job table row by row took 20 us for 8 jobs, this takes 5), and the
+// loads of the splits are independent.
+constexpr int kEmitRows = 8, kEmitJobs = 256;
+__global__ void __launch_bounds__(256) shrink_emit_kernel(const JobDev* __restrict__ jobs, const TileDev* __restrict__ tiles,
+                                                          int T, const float* __restrict__ part, int64_t part_stride,
+                                                          int splits, uint16_t* __restrict__ Shi, uint16_t* __restrict__ Slo,
+                                                          uint16_t* __restrict__ Sx) {
+  constexpr int WGS = kGemmBM / kEmitRows;
+  __shared__ JobDev tile_job[kEmitJobs];
+  const TileDev td = tiles[blockIdx.x / WGS];
+  const int r0 = (int)(blockIdx.x % WGS) * kEmitRows, t0 = (int)(blockIdx.x / WGS) * kGemmBM + r0;
+  const int njobs = td.last - td.first + 1;
+  // (a span of more jobs than fit here holds mostly jobs without tokens; those beyond are looked up in the table)
+  if ((int)threadIdx.x < min(njobs, kEmitJobs)) tile_job[threadIdx.x] = jobs[td.first + threadIdx.x];
+  __syncthreads();
+  const int nch = td.kext / 8;
+  for (int q = threadIdx.x; q < kEmitRows * nch; q += 256) {
+    const int r = q / nch, col = (q - r * nch) * 8;
+    const int t = t0 + r;
+    u32x4 x = {0, 0, 0, 0};
+    if (t < T) {
+      int j = 0;
+      while (j < min(njobs, kEmitJobs) - 1 && tile_job[j].row1 <= t) ++j;
+      while (j < njobs - 1 && (j < kEmitJobs ? tile_job[j].row1 : jobs[td.first + j].row1) <= t) ++j;
+      const JobDev jb = j < kEmitJobs ? tile_job[j] : jobs[td.first + j];
+      const int p = col - (jb.roff - td.roff_first);
+      if (p >= 0 && p < jb.rpad) {
+        const int64_t at = jb.soff + (int64_t)(t - jb.row0) * jb.rpad + p;
+        float v[8] = {};
+#pragma unroll 4
+        for (int k = 0; k < splits; ++k) {
+          const f32x4* const src = reinterpret_cast<const f32x4*>(part + k * part_stride + at);
+          const f32x4 a = src[0], b = src[1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { v[e] += a[e];  v[4 + e] += b[e]; }
+        }
+        float lo[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) lo[e] = v[e] - (float)(__bf16)v[e];
+        *reinterpret_cast<u32x4*>(Shi + at) =
+            u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+        *reinterpret_cast<u32x4*>(Slo + at) =
+            u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = pack_bf16x2(jb.scale * v[2 * e], jb.scale * v[2 * e + 1]);
+        if (t == jb.row1 - 1) {                       // zero pad rows up to the next multiple of kGradStep
+          const int pad = (kGradStep - (jb.row1 - jb.row0) % kGradStep) % kGradStep;
+          for (int i = 1; i <= pad; ++i) {
+            *reinterpret_cast<u32x4*>(Shi + at + (int64_t)i * jb.rpad) = u32x4{0, 0, 0, 0};
+            *reinterpret_cast<u32x4*>(Slo + at + (int64_t)i * jb.rpad) = u32x4{0, 0, 0, 0};
+          }
+        }
+      }
+    }
+    *reinterpret_cast<u32x4*>(Sx + td.aoff + (int64_t)(r0 + r) * td.kext + col) = x;
+  }
+}
+
+void launch_shrink_split(const JobDev* jobs, const TileDev* tiles, const ShrinkUnit* units, int num_units, int splits, int T,
+                         const uint16_t* act, int K, const uint16_t* packed, bool packed_is_atp, uint16_t* S_hi,
+                         uint16_t* S_lo, uint16_t* Sx, const int32_t* row_index, float* part, int64_t part_stride,
+                         hipStream_t st) {
+  hipLaunchKernelGGL(shrink_split_kernel, dim3(num_units, splits), dim3(256), 0, st, jobs, units, act, K, packed,
+                     packed_is_atp ? 1 : 0, row_index, part, part_stride);
+  hipLaunchKernelGGL(shrink_emit_kernel, dim3((T + kGemmBM - 1) / kGemmBM * (kGemmBM / kEmitRows)), dim3(256), 0, st, jobs, tiles, T, part,
+                     part_stride, splits, S_hi, S_lo, Sx);
 }
 
 void launch_shrink(const JobDev* jobs, const TileDev* tiles, const ShrinkUnit* units, int num_units, int shrink_rows,
