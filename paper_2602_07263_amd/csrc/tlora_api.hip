@@ -91,6 +91,7 @@ struct Plan {
   int r_total = 0;                                      // sum of rpad_j
   int64_t sx_elems = 0;                                 // elements of the per-tile K-extension operands
   int shrink_splits_x = 1, shrink_splits_dy = 1;        // contraction splits of the shrinks over d_in (S) and d_out (dS)
+  GemmSplit gemm_split_fwd, gemm_split_bwd;             // tiles of the two GEMMs that are cut along the contraction
   size_t partial_bytes = 0;                             // what off_partial holds: dA / dB tiles, or sums of split launches
   // workspace byte offsets
   size_t off_tables = 0, off_S = 0, off_dS = 0, off_Shi = 0, off_Slo = 0, off_dShi = 0, off_dSlo = 0, off_Sx = 0, off_dSx = 0, off_atp = 0, off_wt = 0, off_ap = 0, off_bp = 0,
@@ -191,12 +192,45 @@ bool build_grad_units(const Plan& pl, int D, std::vector<GradUnit>& units, std::
 // Splits of a streaming shrink over K of a plan whose units have 32 rows: enough that units x splits fill the 512
 // workgroup slots (80 KB of LDS each, two per CU), while a split keeps at least 4 K-steps of 64 (three are in flight
 // before the first is multiplied).  Fewer if the fp32 sums (4 bytes per packed S element and split) would not fit.
+constexpr int kGemmMaxSplits = 16;
 constexpr int kShrinkSlots = 512, kShrinkMinSteps = 4, kShrinkMaxSplits = 32;
 int shrink_splits(const Plan& pl, int K, size_t max_bytes) {
   if (pl.shrink_rows != 32 || g_opt.shrink_rows != 0 || K % 64 || pl.stream_units.empty()) return 1;
   int64_t s = std::min<int64_t>(kShrinkSlots / (int64_t)pl.stream_units.size(), K / 64 / kShrinkMinSteps);
   s = std::min<int64_t>({s, kShrinkMaxSplits, (int64_t)(max_bytes / (4 * (size_t)pl.s_elems))});
   return s < 2 ? 1 : (int)s;
+}
+
+// Which tiles of the GEMM over [T, K] x [K, N] to cut along K.  A workgroup needs ~5 us outside its K-loop and ~0.6 us per
+// 32-wide step, whether 1 or 256 of them run (16 tiles over K = 4096 took 80 us, 32 tiles over 12288 took 188 us); 256 run
+// at once.  So the tiles beyond the last multiple of 256 cost a whole contraction however few they are.  Cut into s they
+// cost ceil(tiles s / 256) shares, plus the fp32 sums written and read once (at ~4 TB/s) and the launch that adds them.
+// The cheapest s is taken if it saves more than 15 % of the uncut time.  The sums may take 12 bytes per token and feature
+// (three times the fp32 rows of both sides), so that the workspace stays linear in T (d_in + d_out).
+GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
+  GemmSplit best;
+  if (K % kGemmBK || pl.T == 0) return best;
+  int kext = 0;
+  for (const TileDev& td : pl.tile_jobs) kext = std::max(kext, td.kext);
+  const int steps = (K + kext) / kGemmBK;
+  const int64_t nb = (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
+  const int64_t n_tail = nb % 256;
+  if (n_tail == 0) return best;
+  const size_t tile_bytes = sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM);
+  max_bytes = std::min(max_bytes, (size_t)12 * (size_t)pl.T * (size_t)(pl.d_in + pl.d_out));
+  double best_us = 0.85 * (5.0 + 0.6 * steps);
+  for (int s = 2; s <= kGemmMaxSplits && steps / s >= 4; ++s) {
+    const size_t bytes = tile_bytes * (size_t)n_tail * s;
+    if (bytes > max_bytes) break;
+    const double us = (double)((n_tail * s + 255) / 256) * (5.0 + 0.6 * ((steps + s - 1) / s)) + 2.0 * (double)bytes / 4e6 + 6.0;
+    if (us < best_us) { best_us = us;  best.splits = s;  best.n_direct = (int32_t)(nb - n_tail); }
+  }
+  return best;
+}
+size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N) {
+  if (g.splits < 2) return 0;
+  const int64_t nb = (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
+  return sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM) * (size_t)(nb - g.n_direct) * g.splits;
 }
 
 // Bytes of the plan tables that the forward alone needs, each table padded to 256 bytes.
@@ -364,6 +398,8 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
                                                                  : SIZE_MAX;
     pl.shrink_splits_x = shrink_splits(pl, pl.d_in, room);
     if (pl.shrink_splits_x > 1) pl.partial_bytes = sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_x;
+    pl.gemm_split_fwd = gemm_split(pl, pl.d_in, pl.d_out, room);
+    pl.partial_bytes = std::max(pl.partial_bytes, gemm_split_bytes(pl, pl.gemm_split_fwd, pl.d_out));
     if (fwd_only) {
       pl.off_partial = pl.off_ap;
       w = std::max(w, align_up(pl.off_partial + pl.partial_bytes, 256));
@@ -371,6 +407,8 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
       pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, SIZE_MAX);
       if (pl.shrink_splits_dy > 1)
         pl.partial_bytes = std::max(pl.partial_bytes, sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_dy);
+      pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, SIZE_MAX);
+      pl.partial_bytes = std::max(pl.partial_bytes, gemm_split_bytes(pl, pl.gemm_split_bwd, pl.d_in));
       pl.partial_bytes = std::max(pl.partial_bytes, sizeof(float) * (size_t)std::max(pl.gradB_partial, pl.gradA_partial));
       pl.off_partial = wplace(pl.partial_bytes);
     }
@@ -756,7 +794,8 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   Timed tg(TLORA_K_GEMM_FWD, st, timed);
   launch_seg_gemm(true, tiles, static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), Sx, bp,
                   pl.r_total, static_cast<uint16_t*>(Y), out_index, in_index, pl.T, pl.d_in, pl.d_out,
-                  timed ? (g_clock_slot[0] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock)) : nullptr, st);
+                  timed ? (g_clock_slot[0] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock)) : nullptr,
+                  pl.gemm_split_fwd, reinterpret_cast<float*>(ws + pl.off_partial), st);
   return launches_ok(__LINE__);
 }
 }  // namespace
@@ -908,7 +947,7 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
       launch_seg_gemm(wt, tiles, dYb, wt ? Wt : static_cast<const uint16_t*>(p->W), dSx, wt ? atp : ap, pl.r_total,
                       static_cast<uint16_t*>(dX), out_index, in_index, pl.T, pl.d_out, pl.d_in,
                       g_prof_on ? (g_clock_slot[1] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock) + 2) : nullptr,
-                      st);
+                      pl.gemm_split_bwd, partial, st);
     }
   }
   if (want_grads) {
@@ -1937,6 +1976,11 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       if (4 * (size_t)std::max(pl.gradB_partial, pl.gradA_partial) > pl.partial_bytes) return 64;
       for (int k : {pl.shrink_splits_x, pl.shrink_splits_dy})
         if (k < 1 || (k > 1 && 4 * se * (size_t)k > pl.partial_bytes)) return 65;
+      for (int d = 0; d < 2; ++d) {
+        const GemmSplit& g = d ? pl.gemm_split_bwd : pl.gemm_split_fwd;
+        if (g.splits < 1 || g.splits > kGemmMaxSplits || g.n_direct < 0 || g.n_direct % 256) return 67;
+        if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
+      }
       w.push_back({pl.off_partial, pl.partial_bytes});
       if (fwd_only && pl.total <= TLORA_NOALLOC_SCRATCH_BYTES && pl.off_partial + pl.partial_bytes > TLORA_NOALLOC_SCRATCH_BYTES)
         return 66;

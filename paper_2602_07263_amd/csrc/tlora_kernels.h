@@ -56,7 +56,8 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
                      int T, int K, int N,
                      unsigned long long* clk /* null, or 2 zeroed words: every 64th workgroup adds the shader
                                                 cycles and 100 MHz ticks of its K-loop */,
-                     hipStream_t st);
+                     const GemmSplit& split /* taken when w_is_kn and K % 32 == 0 */,
+                     float* part /* splits x cut tiles x min(T, 256) x 256 floats */, hipStream_t st);
 
 // partial[u] = sum_{t in unit u} U_j[t, p] * V[t, c]   then   G_j = scale_j * sum_u partial[u]
 void launch_rank_grad(const JobDev* jobs, const GradUnit* units, int num_units, const uint16_t* U_hi,

@@ -825,14 +825,33 @@ struct GemmParams {
   unsigned long long* clk;  // optional: every 64th workgroup adds {cycles, 100 MHz ticks} of its K-loop (pre-zeroed)
   const int32_t* out_index; // optional: output row of tile row t (scatter); null = t itself
   const int32_t* in_index;  // INDEXED instantiations: batch row that holds activation row t (gather inside the loads)
+  // SPLIT instantiations: tiles n_direct .. of the walk are cut into `splits` K-ranges whose fp32 sums go to
+  // part[split][tile - n_direct][part_rows][256]
+  int n_direct, splits, part_rows;
+  float* part;
 };
+
+// Tile L of the walk: groups of 4 row tiles, so that workgroups that run together share activation and weight panels.
+__device__ __forceinline__ void gemm_tile_of(int L, int tiles_m, int tiles_n, int& tm, int& tn) {
+  constexpr int GM = 4;
+  const int per_group = GM * tiles_n;
+  const int grp = L / per_group, first_m = grp * GM;
+  const int gsize = min(GM, tiles_m - first_m);
+  const int Lg = L - grp * per_group;
+  // (the divisions run on the vector ALU; everything derived from the tile id is wave-uniform and belongs in
+  // scalar registers)
+  tm = __builtin_amdgcn_readfirstlane(first_m + Lg % gsize);
+  tn = __builtin_amdgcn_readfirstlane(Lg / gsize);
+}
 
 // KTAIL: the instantiation for K % 32 != 0 carries the extra predicated step; keeping it out of the common one
 // keeps its register pressure away from every tile.
 // INDEXED: the activation rows are fetched through P.in_index (token-indexed calls: the batch stays in its own order).
 // A lane then keeps one byte offset per row it loads (four) instead of two offsets plus scalar row strides; offsets are
 // 32 bits, so the launcher takes this instantiation only while T * K * 2 stays below 4 GiB.
-template <bool KN, bool KTAIL, bool INDEXED>
+// SPLIT: the last tiles of the walk, which would occupy fewer workgroups than the chip has CUs for a whole contraction,
+// are cut along K (gemm_split in the planner says when); gemm_reduce_kernel adds the sums in split order.
+template <bool KN, bool KTAIL, bool INDEXED, bool SPLIT>
 __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   constexpr int NT = 512;                            // threads: 8 waves
   constexpr int NFB = 4;                             // 16-wide feature blocks per wave (64 columns)
@@ -856,20 +875,24 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   // ids, and walk tiles in groups of 4 row tiles so the 32 workgroups an XCD runs together share
   // 4 activation panels and 8 weight panels in its L2 (the weight tiles are the cheaper stream: whole 512-byte
   // rows; groups of 4 measured 1-4 % faster than 8, and 16 or 32 slower).
+  // Cut tiles: neighbours of an XCD are tiles of one split (they share its slices of the operands); n_direct is a
+  // multiple of 8, so b & 7 is the XCD there too.
   int tm, tn;
+  bool cut = false;
+  int split = 0, tail_tile = 0;
   {
     const int nb = P.tiles_m * P.tiles_n, b = blockIdx.x;
-    const int q = nb >> 3, rem = nb & 7, x = b & 7;
-    const int L = x * q + min(x, rem) + (b >> 3);
-    constexpr int GM = 4;
-    const int per_group = GM * P.tiles_n;
-    const int grp = L / per_group, first_m = grp * GM;
-    const int gsize = min(GM, P.tiles_m - first_m);
-    const int Lg = L - grp * per_group;
-    // (the divisions run on the vector ALU; everything derived from the tile id is wave-uniform and belongs in
-    // scalar registers)
-    tm = __builtin_amdgcn_readfirstlane(first_m + Lg % gsize);
-    tn = __builtin_amdgcn_readfirstlane(Lg / gsize);
+    cut = SPLIT && b >= P.n_direct;
+    const int first = cut ? P.n_direct : 0;
+    const int n = !SPLIT ? nb : cut ? (nb - P.n_direct) * P.splits : P.n_direct;
+    const int q = n >> 3, rem = n & 7, x = b & 7;
+    int L = x * q + min(x, rem) + ((b - first) >> 3);
+    if (cut) {
+      split = __builtin_amdgcn_readfirstlane(L / (nb - first));
+      tail_tile = __builtin_amdgcn_readfirstlane(L - split * (nb - first));
+      L = first + tail_tile;
+    }
+    gemm_tile_of(L, P.tiles_m, P.tiles_n, tm, tn);
   }
   const int row0 = tm * BM, col0 = tn * BN;
   const int rows_valid = min(BM, P.T - row0);
@@ -893,10 +916,17 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   // ---- the K-loop: K / 32 backbone steps, then kext / 32 adapter steps, one software pipeline ----------------
   const int nfull = P.K / 32;
   const int ntot = nfull + td.kext / 32;
+  // steps of this workgroup: all of them, or an even-sized share (the ring's phase assumes an even first step)
+  int step0 = 0, step1 = ntot;
+  if (cut) {
+    const int share = ((ntot + P.splits - 1) / P.splits + 1) & ~1;
+    step0 = min(split * share, ntot);
+    step1 = min(step0 + share, ntot);
+  }
   const bool clocked = P.clk != nullptr && (blockIdx.x & 63) == 0;   // a sample of workgroups across the grid
   unsigned long long cyc0 = 0, tick0 = 0;
   if (clocked) { cyc0 = __builtin_readcyclecounter();  tick0 = __builtin_amdgcn_s_memrealtime(); }
-  if (ntot > 0) {
+  if (step1 > step0) {
     // Loads.  A tile is 2048 16-byte slots; wave w issues four 1 KB loads per tile, lane l's 16 bytes landing at
     // slot (4 w + i) 64 + l.  Which k-values and which row / column that slot holds follows from the tile
     // layout, so the source address is recomputed per load from the step index t of the lane's half of the
@@ -1066,26 +1096,26 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
     gate();                                  /* fragments are in registers */                              \
     mma_slice(xf, wf);                                                                                       \
   }
-    issue_wgt(0, -1);
-    issue_act(1, 0);
-    issue_wgt(2, 1);
-    issue_act(3, 2);
+    issue_wgt(0, step0 - 1);
+    issue_act(1, step0);
+    issue_wgt(2, step0 + 1);
+    issue_act(3, step0 + 2);
     if (late) gate();              // its share of L_0, L_1 must have landed before the early group reads them
-    int s = 0;
-    for (; s + 10 <= ntot; s += 10) {
+    int s = step0;
+    for (; s + 10 <= step1; s += 10) {
       TLORA_GEMM_STEP(0, s)      TLORA_GEMM_STEP(1, s + 1)  TLORA_GEMM_STEP(2, s + 2)  TLORA_GEMM_STEP(3, s + 3)
       TLORA_GEMM_STEP(4, s + 4)  TLORA_GEMM_STEP(5, s + 5)  TLORA_GEMM_STEP(6, s + 6)  TLORA_GEMM_STEP(7, s + 7)
       TLORA_GEMM_STEP(8, s + 8)  TLORA_GEMM_STEP(9, s + 9)
     }
-    if (s + 0 < ntot) TLORA_GEMM_STEP(0, s)
-    if (s + 1 < ntot) TLORA_GEMM_STEP(1, s + 1)
-    if (s + 2 < ntot) TLORA_GEMM_STEP(2, s + 2)
-    if (s + 3 < ntot) TLORA_GEMM_STEP(3, s + 3)
-    if (s + 4 < ntot) TLORA_GEMM_STEP(4, s + 4)
-    if (s + 5 < ntot) TLORA_GEMM_STEP(5, s + 5)
-    if (s + 6 < ntot) TLORA_GEMM_STEP(6, s + 6)
-    if (s + 7 < ntot) TLORA_GEMM_STEP(7, s + 7)
-    if (s + 8 < ntot) TLORA_GEMM_STEP(8, s + 8)
+    if (s + 0 < step1) TLORA_GEMM_STEP(0, s)
+    if (s + 1 < step1) TLORA_GEMM_STEP(1, s + 1)
+    if (s + 2 < step1) TLORA_GEMM_STEP(2, s + 2)
+    if (s + 3 < step1) TLORA_GEMM_STEP(3, s + 3)
+    if (s + 4 < step1) TLORA_GEMM_STEP(4, s + 4)
+    if (s + 5 < step1) TLORA_GEMM_STEP(5, s + 5)
+    if (s + 6 < step1) TLORA_GEMM_STEP(6, s + 6)
+    if (s + 7 < step1) TLORA_GEMM_STEP(7, s + 7)
+    if (s + 8 < step1) TLORA_GEMM_STEP(8, s + 8)
 #undef TLORA_GEMM_STEP
     __builtin_amdgcn_sched_barrier(0);
     if (!late) __builtin_amdgcn_s_barrier();
@@ -1138,6 +1168,20 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
     }
   }
 
+  if (SPLIT && cut) {       // fp32 sums, rows of 256 columns: a wave's stores fill whole 256-byte runs across j
+    float* const dst = P.part + ((int64_t)split * (P.tiles_m * P.tiles_n - P.n_direct) + tail_tile) * P.part_rows * BN;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int R = wm * 128 + i * 16 + (lane & 15);
+      if (R < rows_valid) {
+#pragma unroll
+        for (int j = 0; j < NFB; ++j)
+          *reinterpret_cast<f32x4*>(dst + (int64_t)R * BN + wn * 64 + j * 16 + (lane >> 4) * 4) = acc[j][i];
+      }
+    }
+    return;
+  }
+
   // ---- epilogue: accumulators -> bf16 -> LDS (slots 0-3 hold 64 output rows each, 512 B per row, 16-byte
   // chunk c of row R at slot c ^ (R & 31)) -> full 512-byte rows to global memory. -----------------------------
   __syncthreads();
@@ -1168,9 +1212,32 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   }
 }
 
+// out = bf16(sum of the splits in order): one workgroup = 8 rows of a cut tile, 8 columns per thread
+__global__ void __launch_bounds__(256) gemm_reduce_kernel(const float* __restrict__ part, int n_direct, int splits,
+                                                          int part_rows, uint16_t* __restrict__ out,
+                                                          const int32_t* __restrict__ out_index, int T, int N, int tiles_m,
+                                                          int tiles_n) {
+  int tm, tn;
+  gemm_tile_of(n_direct + (int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+  const int R = (int)blockIdx.y * 8 + (int)(threadIdx.x >> 5), c = (int)(threadIdx.x & 31) * 8;
+  const int t = tm * kGemmBM + R, col = tn * kGemmBN + c;
+  if (t >= T || col >= N) return;
+  const int64_t stride = (int64_t)gridDim.x * part_rows * kGemmBN;
+  const float* src = part + ((int64_t)blockIdx.x * part_rows + R) * kGemmBN + c;
+  f32x4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+  for (int k = 0; k < splits; ++k, src += stride) {
+    a += *reinterpret_cast<const f32x4*>(src);
+    b += *reinterpret_cast<const f32x4*>(src + 4);
+  }
+  const int64_t orow = out_index ? out_index[t] : t;
+  *reinterpret_cast<u32x4*>(out + orow * N + col) =
+      u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
+}
+
 void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, const uint16_t* W, const uint16_t* Sx,
                      const uint16_t* packed, int r_total, uint16_t* out, const int32_t* out_index,
-                     const int32_t* in_index, int T, int K, int N, unsigned long long* clk, hipStream_t st) {
+                     const int32_t* in_index, int T, int K, int N, unsigned long long* clk, const GemmSplit& split,
+                     float* part, hipStream_t st) {
   GemmParams P;
   P.clk = clk;
   P.out_index = out_index;
@@ -1182,8 +1249,18 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
   const int nb = P.tiles_m * P.tiles_n;
   if (nb == 0) return;
   const bool tail = K % kGemmBK != 0;
+  P.n_direct = split.n_direct;  P.splits = split.splits;  P.part_rows = std::min(T, kGemmBM);  P.part = part;
+  if (split.splits > 1 && w_is_kn && !tail) {
+    const int n_tail = nb - P.n_direct;
+    const dim3 grid(P.n_direct + n_tail * P.splits);
+    if (in_index) hipLaunchKernelGGL((seg_gemm_kernel<true, false, true, true>), grid, dim3(512), 0, st, P);
+    else          hipLaunchKernelGGL((seg_gemm_kernel<true, false, false, true>), grid, dim3(512), 0, st, P);
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(n_tail, (P.part_rows + 7) / 8), dim3(256), 0, st, part, P.n_direct, P.splits,
+                       P.part_rows, out, out_index, T, N, P.tiles_m, P.tiles_n);
+    return;
+  }
 #define TLORA_GEMM_LAUNCH(KN, TAIL, IDX) \
-  hipLaunchKernelGGL((seg_gemm_kernel<KN, TAIL, IDX>), dim3(nb), dim3(512), 0, st, P)
+  hipLaunchKernelGGL((seg_gemm_kernel<KN, TAIL, IDX, false>), dim3(nb), dim3(512), 0, st, P)
   if (in_index) {
     if (w_is_kn) { if (tail) TLORA_GEMM_LAUNCH(true, true, true);  else TLORA_GEMM_LAUNCH(true, false, true); }
     else         { if (tail) TLORA_GEMM_LAUNCH(false, true, true); else TLORA_GEMM_LAUNCH(false, false, true); }

@@ -17,6 +17,10 @@ CASES = [
     ("ragged_row_tiles", 1088, 4160, [16, 4, 100], [257, 511, 1]),
     ("many_jobs_in_a_tile", 512, 512, [2, 5] * 150, [1, 0] * 149 + [20, 9]),   # 300 jobs within one row tile
     ("no_rank_at_all", 1024, 2048, [0, 0], [40, 300]),
+    # backbone GEMM: 288 tiles forward, of which the last 32 are cut (65 to 69 steps); 72 of 257 backward, all cut
+    ("cut_tiles_after_whole_ones", 2048, 8192, [8, 64, 16], [1000, 3, 1100]),
+    ("one_step_too_many", 2080, 264, [8], [255]),                        # 66 steps: an odd share, ragged columns
+    ("k_tail_is_not_cut", 2056, 512, [8, 5], [100, 29]),
 ]
 
 
@@ -28,3 +32,31 @@ def test_split_launches_meet_the_oracle(case):
         Y, dX, dA, dB, _ = pu.run_gpu(p, reuse_S=reuse)
         res = pu.compare(p, Y, dX, dA, dB)
         assert all(v <= 1.0 for v in res.values()), f"{name} reuse={reuse}: worst error / tolerance ratios {res}"
+
+
+def test_row_list_calls_are_cut_like_the_plain_ones():
+    """Same plan, rows fetched and stored through a list: the same bits as the plain call on the sorted rows."""
+    import torch
+    from paper_2602_07263_amd import tlora
+    p = wk.generate(wk.custom("cut_indexed", "bf16", 2048, 1024, [8, 40], [700, 301], [2.0, 1.0]), seed=52)
+    lp = tlora.LayerProblem.from_numpy(p)
+    T = lp.X.shape[0]
+    dY = torch.from_numpy(p.dY).to(device="cuda", dtype=torch.bfloat16)
+    Y, dX, dA, dB = lp.new_outputs()
+    lp.fwd(Y)
+    lp.bwd(dY, dX, dA, dB, reuse_S=True)
+    index = torch.randperm(T, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()
+    at = index.long()
+    X2, dY2 = torch.empty_like(lp.X), torch.empty_like(dY)
+    X2[at], dY2[at] = lp.X, dY
+    lq = tlora.LayerProblem("bf16", 2048, 1024, [8, 40], p.offsets, [2.0, 1.0], X2, lp.W, lp.A, lp.B)
+    Y2, dX2, dA2, dB2 = lq.new_outputs()
+    n = tlora.tlora_indexed_workspace_bytes(lq.prob)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    st = int(torch.cuda.current_stream().cuda_stream)
+    tlora.tlora_fwd_indexed(lq.prob, index.data_ptr(), Y2.data_ptr(), ws.data_ptr(), n, st)
+    tlora.tlora_bwd_indexed(lq.prob, index.data_ptr(), dY2.data_ptr(), dX2.data_ptr(), [t.data_ptr() for t in dA2],
+                            [t.data_ptr() for t in dB2], tlora.TLORA_BWD_REUSE_S, ws.data_ptr(), n, st)
+    torch.cuda.synchronize()
+    assert torch.equal(Y2[at], Y) and torch.equal(dX2[at], dX)
+    assert all(torch.equal(a, b) for a, b in zip(dA2 + dB2, dA + dB))
