@@ -140,6 +140,22 @@ __device__ __forceinline__ void load_row_frags(const uint16_t* row, int lane, bf
   for (int s = 0; s < 8; ++s)
     f[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(row + 16 * s + 8 * (lane >> 5)));
 }
+// Orders the matrix products of a straight piece of code against their LDS reads: `AHEAD` reads first, then `PER_STEP`
+// reads after every `MM` products until `READS` are issued, then the remaining products.  Left to itself the compiler
+// spends as few registers as it can and puts read, wait and product one after the other, which shows the LDS latency
+// (100 - 200 cycles against 32 of a product) once per product.
+template <int READS, int AHEAD, int MM, int PER_STEP, int PRODUCTS>
+__device__ __forceinline__ void pipeline_reads() {
+  static_assert((READS - AHEAD) % PER_STEP == 0, "whole steps");
+  constexpr int STEPS = (READS - AHEAD) / PER_STEP;
+  __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+#pragma unroll
+  for (int i = 0; i < STEPS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, MM, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, PER_STEP, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, PRODUCTS - STEPS * MM, 0);
+}
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // x of this lane and x of lane ^ 32, in unspecified order: one v_permlane32_swap (the upper half of the first operand
 // trades places with the lower half of the second) instead of a round trip through the LDS crossbar.  Both callers
@@ -222,12 +238,15 @@ attn_fwd_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restrict__
       const uint8_t* vb = vt[buf];
       f32x16 sacc[2];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) sacc[j][e] = 0.f;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) sacc[j] = mfma32(frag_rows(kb, 32 * j, s, P), qf[s], sacc[j]);
-      }
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) sacc[j] = mfma32(frag_rows(kb, 32 * j, s, P), qf[s], sacc[j]);
+      pipeline_reads<16, 6, 1, 1, 16>();
+      __builtin_amdgcn_sched_barrier(0);
       if (kvbase + 63 > qmin) {                                       // the tile reaches past some query of the wave
 #pragma unroll
         for (int j = 0; j < 2; ++j)
@@ -376,6 +395,8 @@ attn_bwd_dq_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restric
           sacc = mfma32(frag_rows(kb, 32 * j, s, P), qf[s], sacc);
           dp = mfma32(frag_rows(vb, 32 * j, s, P), dof[s], dp);
         }
+        pipeline_reads<16, 6, 1, 1, 16>();
+        __builtin_amdgcn_sched_barrier(0);
         if (diag) {
 #pragma unroll
           for (int i = 0; i < 16; ++i)
@@ -389,6 +410,7 @@ attn_bwd_dq_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restric
 #pragma unroll
           for (int db = 0; db < 4; ++db) dq[db] = mfma32(frag_cols(kb, db, 32 * j + 16 * s2, P), dsf, dq[db]);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -409,40 +431,48 @@ attn_bwd_dq_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restric
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Backward, dK and dV.  One workgroup = 128 keys of one sequence and key/value head (4 waves x 32 keys); it walks
-// the query heads of the group and, for each, the queries at or after its keys in steps of 64 (two blocks of 32):
+// Backward, dK and dV.  One workgroup = 128 keys of one sequence and key/value head; it walks the query heads of the
+// group and, for each, the queries at or after its keys in steps of 64 (two blocks of 32):
 //   S = Q K^T,  P = exp2(c S - lse_q),  dV^T += dO^T P,  dP = dO V^T,  dS = P (dP - D_q),  dK^T += Q^T dS.
+// Eight waves: waves w and w + 4 (which share a SIMD) hold the same 32 keys and take the first and the second query block
+// of every step, so that one's exponentials run beside the other's matrix products; their sums are added through LDS at the
+// end.  Two waves per SIMD leave each 256 registers: dK and dV take 128, the K fragments 32, and the V fragments (32 more)
+// are read from LDS instead, which costs 8 reads beside the 32 of Q and dO per block.  (With four waves of 366 registers
+// the kernel waited half its time: LDS and MFMA latencies with one wave per SIMD, and in every step the loads just issued.)
+// Measured, 32 query / 8 key-value heads, 16 sequences of 2048: 1.73 -> 1.43 ms (770 TFLOP/s of its four products); a
+// whole pass over one sequence of 4096 with 8 / 1 heads, 32 workgroups: 1.33 -> 0.98 ms.
 // A lane owns one key column; Q, dO, lse and D of a step arrive in LDS through asynchronous loads issued two
-// steps ahead (three stages; every wave issues the same 10 loads per step so that one counter value means
+// steps ahead (three stages; every wave issues the same 6 loads per step so that one counter value means
 // "everything but the newest step has landed").  Sums run in a fixed order.  Tiles are taken from the end of the
 // table: there the first keys of the long sequences come first, which have the most queries to walk.
 // ---------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const AttnTile* __restrict__ tiles, int n_tiles,
-                                                           const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                                                           const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
-                                                           const float* __restrict__ lse, const float* __restrict__ D,
-                                                           uint16_t* __restrict__ dK, uint16_t* __restrict__ dV, int Hq,
-                                                           int Hkv, float c, float scale) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_bwd_dkv_kernel(const AttnTile* __restrict__ tiles, int n_tiles, const uint16_t* __restrict__ Q,
+                    const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
+                    const float* __restrict__ lse, const float* __restrict__ D, uint16_t* __restrict__ dK,
+                    uint16_t* __restrict__ dV, int Hq, int Hkv, float c, float scale) {
   constexpr int NS = 3, QS = 64;                                     // stages, queries per step
-  constexpr int kLoads = 10;                                         // asynchronous loads per wave and step
-  __shared__ __attribute__((aligned(1024))) uint8_t qt[NS][QS * ROWB];
-  __shared__ __attribute__((aligned(1024))) uint8_t dot[NS][QS * ROWB];
+  constexpr int kLoads = 6;                                          // asynchronous loads per wave and step
+  constexpr int VT = 128 * ROWB, TILE = QS * ROWB, STAGE = 2 * TILE;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[VT + NS * STAGE];   // V rows; stages of (Q, dO)
   __shared__ __attribute__((aligned(256))) float ls[NS][QS], ds[NS][QS];
   const AttnTile t = tiles[n_tiles - 1 - (int)blockIdx.x];
   const int hk = blockIdx.y, G = Hq / Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hl = lane >> 5;
-  const int k0w = t.t0 + wave * 32;
+  const int half = wave >> 2, kw = wave & 3;                         // query block of a step, key block
+  const int k0w = t.t0 + kw * 32;
   const bool active = k0w < t.seq_len;
   const int kpos = min(k0w + (lane & 31), t.seq_len - 1);
   const int kmax = min(k0w + 31, t.seq_len - 1);
   const bool kvalid = k0w + (lane & 31) < t.seq_len;
   const int64_t qs = (int64_t)Hq * HD, ks = (int64_t)Hkv * HD;
   const int64_t krow = t.seq_start + kpos;
-  bf16x8 kf[8], vf[8];
-  load_row_frags(K + krow * ks + hk * HD, lane, kf);
-  load_row_frags(V + krow * ks + hk * HD, lane, vf);
   const uint32_t q_row_bytes = (uint32_t)qs * 2u;
-  const uint32_t qt_lds = lds_addr(qt), dot_lds = lds_addr(dot), ls_lds = lds_addr(ls), ds_lds = lds_addr(ds);
+  const uint32_t lds0 = lds_addr(lds), ls_lds = lds_addr(ls), ds_lds = lds_addr(ds);
+  tile_dma<4>(uniform_ptr(V + (int64_t)(t.seq_start + t.t0) * ks + hk * HD), (uint32_t)ks * 2u, 16 * wave,
+              t.seq_len - 1 - t.t0, lds0, lane);
+  bf16x8 kf[8];
+  load_row_frags(K + krow * ks + hk * HD, lane, kf);
   f32x16 dk[4], dv[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -455,8 +485,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const AttnTile* __res
     const int hq = hk * G + st / nq, q0 = q_first + (st % nq) * QS;
     const int stage = st % NS, last = t.seq_len - 1 - q0;
     const int64_t base = (int64_t)(t.seq_start + q0) * qs + hq * HD;
-    tile_dma<4>(uniform_ptr(Q + base), q_row_bytes, 16 * wave, last, qt_lds + (uint32_t)stage * QS * ROWB, lane);
-    tile_dma<4>(uniform_ptr(dO + base), q_row_bytes, 16 * wave, last, dot_lds + (uint32_t)stage * QS * ROWB, lane);
+    const uint32_t at = lds0 + VT + (uint32_t)stage * STAGE;
+    tile_dma<2>(uniform_ptr(Q + base), q_row_bytes, 8 * wave, last, at, lane);
+    tile_dma<2>(uniform_ptr(dO + base), q_row_bytes, 8 * wave, last, at + TILE, lane);
     // per-query statistics, one word per lane (rows past the sequence repeat its last row); all waves write the
     // same words
     const uint32_t off = (uint32_t)min(lane, last) * (uint32_t)Hq * 4u;
@@ -465,8 +496,13 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const AttnTile* __res
     dma4s(off, uniform_ptr(D + sbase), ds_lds + (uint32_t)stage * QS * 4);
   };
   const FragPat P = make_frag_pat(lane);
+  const uint8_t* const vb = lds + kw * 32 * ROWB;                    // the wave's V rows
+  const uint8_t* const stage0 = lds + VT + half * 32 * ROWB;         // the wave's query block in stage 0
   if (nsteps > 0) issue(0);
   if (nsteps > 1) issue(1);
+  // (the K fragments are registers from here on: without this the compiler waits for them at their first use, inside the
+  // loop, and so in every step for the loads that the step has just issued)
+  __builtin_amdgcn_s_waitcnt(0);
   auto q_step = [&](auto stagec, int st) {
     constexpr int stage = decltype(stagec)::value;                   // = st % NS
     // everything but the loads of step st + 1 has landed (vmcnt in bits 3:0 and 15:14, the other counters 0)
@@ -474,49 +510,60 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const AttnTile* __res
     else                 __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_s_barrier();
     if (st + 2 < nsteps) issue(st + 2);
-    const int q0s = q_first + (st % nq) * QS;
+    const int q0 = q_first + (st % nq) * QS + 32 * half;
+    if (active && q0 + 31 >= k0w && q0 < t.seq_len) {                // wave-uniform: some query at or after a key
+      const uint8_t* const qb = stage0 + stage * STAGE;
+      const uint8_t* const dob = qb + TILE;
+      // The k-slice is bits 1 .. 3 of a chunk's number before the swizzle: one register and an exclusive or per slice in
+      // place of eight registers (the loop has none to spare; hidden from the optimiser so that it stays inside the step).
+      int row0 = P.row[0];
+      asm volatile("" : "+v"(row0));
+      auto row_frag = [&](const uint8_t* tile, int s) {
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(tile + (row0 ^ (s << 5))));
+      };
+      f32x16 sacc, dp;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int q0 = q0s + 32 * half;
-      if (active && q0 + 31 >= k0w && q0 < t.seq_len) {              // wave-uniform: some query at or after a key
-        const uint8_t* qb = qt[stage];
-        const uint8_t* dob = dot[stage];
-        f32x16 sacc, dp;
+      for (int e = 0; e < 16; ++e) { sacc[e] = 0.f;  dp[e] = 0.f; }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) { sacc[e] = 0.f;  dp[e] = 0.f; }
+      for (int s = 0; s < 8; ++s) {
+        sacc = mfma32(row_frag(qb, s), kf[s], sacc);
+        dp = mfma32(row_frag(dob, s), row_frag(vb, s), dp);
+      }
+      pipeline_reads<24, 6, 2, 3, 16>();
+      __builtin_amdgcn_sched_barrier(0);
+      if (q0 < kmax || q0 + 31 >= t.seq_len) {                       // some query before a key of the wave, or padding
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          sacc = mfma32(frag_rows(qb, 32 * half, s, P), kf[s], sacc);
-          dp = mfma32(frag_rows(dob, 32 * half, s, P), vf[s], dp);
+        for (int i = 0; i < 16; ++i) {
+          const int q = q0 + acc_row(i, hl);
+          if (q < kpos || q >= t.seq_len) sacc[i] = kNegInf;
         }
-        if (q0 < kmax || q0 + 31 >= t.seq_len) {                     // some query before a key of the wave, or padding
+      }
+      u32x4 pf[2];                                                     // P, packed at once: 8 registers instead of 16
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int q = q0 + acc_row(i, hl);
-            if (q < kpos || q >= t.seq_len) sacc[i] = kNegInf;
-          }
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&ls[stage][32 * half + 8 * g + 4 * hl]);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&ds[stage][32 * half + 8 * g + 4 * hl]);
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          p[e] = fast_exp2(fmaf(sacc[4 * g + e], c, -l4[e]));
+          sacc[4 * g + e] = p[e] * (dp[4 * g + e] - d4[e]);            // dS
         }
-        f32x16 pm;
+        pf[g >> 1][2 * (g & 1)] = pack2(p[0], p[1]);
+        pf[g >> 1][2 * (g & 1) + 1] = pack2(p[2], p[3]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(&ls[stage][32 * half + 8 * g + 4 * hl]);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(&ds[stage][32 * half + 8 * g + 4 * hl]);
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const bf16x8 dsf = pack8(sacc, 8 * s2);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float p = fast_exp2(fmaf(sacc[4 * g + e], c, -l4[e]));
-            pm[4 * g + e] = p;
-            sacc[4 * g + e] = p * (dp[4 * g + e] - d4[e]);             // dS
-          }
+        for (int db = 0; db < 4; ++db) {
+          dv[db] = mfma32(frag_cols(dob, db, 16 * s2, P), __builtin_bit_cast(bf16x8, pf[s2]), dv[db]);
+          dk[db] = mfma32(frag_cols(qb, db, 16 * s2, P), dsf, dk[db]);
         }
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const bf16x8 pf = pack8(pm, 8 * s2), dsf = pack8(sacc, 8 * s2);
-#pragma unroll
-          for (int db = 0; db < 4; ++db) {
-            dv[db] = mfma32(frag_cols(dob, db, 32 * half + 16 * s2, P), pf, dv[db]);
-            dk[db] = mfma32(frag_cols(qb, db, 32 * half + 16 * s2, P), dsf, dk[db]);
-          }
-        }
+      }
+      pipeline_reads<32, 8, 1, 2, 16>();
+      {
       }
     }
   };
@@ -525,19 +572,37 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const AttnTile* __res
     if (st + 1 < nsteps) q_step(IntC<1>{}, st + 1);
     if (st + 2 < nsteps) q_step(IntC<2>{}, st + 2);
   }
-  if (kvalid) {
-    uint16_t* krow_o = dK + krow * ks + hk * HD;
-    uint16_t* vrow_o = dV + krow * ks + hk * HD;
+  // Waves w and w + 4 trade halves of their sums: the lower wave ends with dK of the 32 keys, the upper one with dV.
+  // 8 x 16 KB fill what held the tiles (all loads have landed: the last step waited for everything).
+  static_assert(8 * 64 * 64 * 4 <= VT + NS * STAGE, "the sums fit into the tiles' place");
+  wait_all_and_sync();
+  {
+    f32x4* const mine = reinterpret_cast<f32x4*>(lds + wave * 16384) + lane;
+    const f32x4* const other = reinterpret_cast<const f32x4*>(lds + (wave ^ 4) * 16384) + lane;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int d = db * 32 + 8 * g + 4 * hl;
-        *reinterpret_cast<u32x2*>(krow_o + d) = u32x2{pack2(dk[db][4 * g] * scale, dk[db][4 * g + 1] * scale),
-                                                      pack2(dk[db][4 * g + 2] * scale, dk[db][4 * g + 3] * scale)};
-        *reinterpret_cast<u32x2*>(vrow_o + d) = u32x2{pack2(dv[db][4 * g], dv[db][4 * g + 1]),
-                                                      pack2(dv[db][4 * g + 2], dv[db][4 * g + 3])};
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = half ? dk[db][4 * g + e] : dv[db][4 * g + e];
+        mine[(db * 4 + g) * 64] = v;
       }
+    wait_all_and_sync();
+    if (kvalid) {
+      uint16_t* const out = (half ? dV : dK) + krow * ks + hk * HD;
+      const float f = half ? 1.f : scale;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 o = other[(db * 4 + g) * 64];
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = ((half ? dv[db][4 * g + e] : dk[db][4 * g + e]) + o[e]) * f;
+          *reinterpret_cast<u32x2*>(out + db * 32 + 8 * g + 4 * hl) = u32x2{pack2(v[0], v[1]), pack2(v[2], v[3])};
+        }
+    }
   }
 }
 
@@ -602,7 +667,7 @@ void launch_attn_bwd(const AttnTile* tiles, int n_tiles, const uint16_t* Q, cons
   hipLaunchKernelGGL(attn_rowdot_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, dO, O, D, rows);
   hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(n_tiles, Hq), dim3(256), 0, st, tiles, Q, K, V, dO, lse, D, dQ, Hq, Hkv, c,
                      scale);
-  hipLaunchKernelGGL(attn_bwd_dkv_kernel, dim3(n_tiles, Hkv), dim3(256), 0, st, tiles, n_tiles, Q, K, V, dO, lse, D, dK, dV,
+  hipLaunchKernelGGL(attn_bwd_dkv_kernel, dim3(n_tiles, Hkv), dim3(512), 0, st, tiles, n_tiles, Q, K, V, dO, lse, D, dK, dV,
                      Hq, Hkv, c, scale);
 }
 void launch_rope_table(float* table, int positions, float base, hipStream_t st) {
