@@ -103,8 +103,8 @@ int tlora_fwd(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_byte
 /* tlora_fwd for callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as tlora_fwd
  * (bit-identical Y), but the forward's intermediates (plan tables, S_j, the packed adapters) live in a device array
- * of TLORA_NOALLOC_SCRATCH_BYTES that is part of the library image; every GPU the library runs on holds it until the
- * process ends.  The call allocates nothing -- no hipMalloc / hipFree / hipHostMalloc, no event or stream creation,
+ * of TLORA_NOALLOC_SCRATCH_BYTES that is part of the library image (TLORA_NOALLOC_SUM_BYTES behind it hold the fp32 sums
+ * of launches whose contraction is cut); every GPU the library runs on holds it until the process ends.  The call allocates nothing -- no hipMalloc / hipFree / hipHostMalloc, no event or stream creation,
  * no allocating library routine -- and records no copy or memset: the plan tables travel as kernel arguments and
  * everything that must start at zero is cleared by store kernels on `hip_stream`.
  *   Limits: the forward-only workspace of the problem (about 4 sum_j T_j r_j + 2 * 256 ceil(T / 256) * (padded
@@ -116,6 +116,7 @@ int tlora_fwd(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_byte
  *   The address of the array on the current device is looked up (and the device's architecture checked) on the first
  *   call on that device: a caller that captures the stream makes one call before the capture begins. */
 #define TLORA_NOALLOC_SCRATCH_BYTES (16u << 20)
+#define TLORA_NOALLOC_SUM_BYTES (64u << 20)
 int tlora_fwd_noalloc(const tlora_problem_t* p, void* Y, void* hip_stream);
 
 /* flags for tlora_bwd */

@@ -22,7 +22,8 @@
 // library runs on holds its own copy of this array at its own address until the process ends.  In host code the
 // name is only a handle for hipGetSymbolAddress: the address that kernels and fills get is the per-device pointer
 // looked up below, never the name.
-static __device__ __align__(256) unsigned char scratch[TLORA_NOALLOC_SCRATCH_BYTES];
+// (its first part holds what decides whether a problem fits; the fp32 sums of split launches lie behind)
+static __device__ __align__(256) unsigned char scratch[TLORA_NOALLOC_SCRATCH_BYTES + TLORA_NOALLOC_SUM_BYTES];
 
 namespace tlora {
 namespace {
@@ -204,7 +205,8 @@ int shrink_splits(const Plan& pl, int K, size_t max_bytes) {
 // Which tiles of the GEMM over [T, K] x [K, N] to cut along K.  A workgroup needs ~5 us outside its K-loop and ~0.6 us per
 // 32-wide step, whether 1 or 256 of them run (16 tiles over K = 4096 took 80 us, 32 tiles over 12288 took 188 us); 256 run
 // at once.  So the tiles beyond the last multiple of 256 cost a whole contraction however few they are.  Cut into s they
-// cost ceil(tiles s / 256) shares, plus the fp32 sums written and read once (at ~4 TB/s) and the launch that adds them.
+// cost ceil(tiles s / 256) shares, plus the fp32 sums written (at ~5 TB/s), read (at ~7 TB/s, they are still cached) and
+// added by a launch of ~2 us on top (32 tiles in 7 shares: 58 MB, 11 us of the products' 50, and 10 us).
 // The cheapest s is taken if it saves more than 15 % of the uncut time.  The sums may take 12 bytes per token and feature
 // (three times the fp32 rows of both sides), so that the workspace stays linear in T (d_in + d_out).
 GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
@@ -222,7 +224,7 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   for (int s = 2; s <= kGemmMaxSplits && steps / s >= 4; ++s) {
     const size_t bytes = tile_bytes * (size_t)n_tail * s;
     if (bytes > max_bytes) break;
-    const double us = (double)((n_tail * s + 255) / 256) * (5.0 + 0.6 * ((steps + s - 1) / s)) + 2.0 * (double)bytes / 4e6 + 6.0;
+    const double us = (double)((n_tail * s + 255) / 256) * (5.0 + 0.6 * ((steps + s - 1) / s)) + (double)bytes / 5.2e6 + (double)bytes / 7e6 + 2.0;
     if (us < best_us) { best_us = us;  best.splits = s;  best.n_direct = (int32_t)(nb - n_tail); }
   }
   return best;
@@ -384,25 +386,23 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     pl.off_bp = wplace(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32));
     pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
     // Sums of split launches.  In the full plan they share the block of the dA / dB partial tiles (the launches follow one
-    // another).  The forward-only plan has a static scratch: there they lie where a_all would, which that path does not
-    // write, and in what the scratch leaves, so that a split never makes a problem too large for it.  Both plans cut the
-    // forward's contractions alike (a problem that the scratch holds is cut as the scratch allows everywhere): a row of
-    // Y has the same bits through both entry points.
+    // another).  The forward-only plan has them behind the static scratch, so that a split never makes a problem too large
+    // for it.  Both plans cut the forward's contractions alike (a problem that the scratch holds is cut as the room behind
+    // it allows everywhere): a row of Y has the same bits through both entry points.  That room holds one round of 256
+    // whole tiles; while it was what the scratch itself left (2 to 14 MiB), 128 tiles over K = 12288 (1900 tokens, 4096
+    // features) ran uncut: 269 us against 176 for two halves and their sum.
     const size_t fwd_base = align_up(forward_table_bytes(pl), 256) + 256 + 2 * align_up(2 * (size_t)pl.s_elems, 256) +
                             align_up(2 * (size_t)pl.sx_elems + 256, 256) +
                             align_up(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in), 256) +
                             align_up(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32), 256);
     const size_t fwd_total = fwd_base + align_up(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32), 256);
-    const size_t room = fwd_total <= TLORA_NOALLOC_SCRATCH_BYTES ? TLORA_NOALLOC_SCRATCH_BYTES - fwd_base
-                        : fwd_only                               ? 0
-                                                                 : SIZE_MAX;
+    const size_t room = fwd_total <= TLORA_NOALLOC_SCRATCH_BYTES ? TLORA_NOALLOC_SUM_BYTES : fwd_only ? 0 : SIZE_MAX;
     pl.shrink_splits_x = shrink_splits(pl, pl.d_in, room);
     if (pl.shrink_splits_x > 1) pl.partial_bytes = sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_x;
     pl.gemm_split_fwd = gemm_split(pl, pl.d_in, pl.d_out, room);
     pl.partial_bytes = std::max(pl.partial_bytes, gemm_split_bytes(pl, pl.gemm_split_fwd, pl.d_out));
     if (fwd_only) {
-      pl.off_partial = pl.off_ap;
-      w = std::max(w, align_up(pl.off_partial + pl.partial_bytes, 256));
+      pl.off_partial = TLORA_NOALLOC_SCRATCH_BYTES;      // (beyond pl.total)
     } else {
       pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, SIZE_MAX);
       if (pl.shrink_splits_dy > 1)
@@ -1981,9 +1981,8 @@ static int check_plan(const Plan& pl, bool fwd_only) {
         if (g.splits < 1 || g.splits > kGemmMaxSplits || g.n_direct < 0 || g.n_direct % 256) return 67;
         if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
       }
-      w.push_back({pl.off_partial, pl.partial_bytes});
-      if (fwd_only && pl.total <= TLORA_NOALLOC_SCRATCH_BYTES && pl.off_partial + pl.partial_bytes > TLORA_NOALLOC_SCRATCH_BYTES)
-        return 66;
+      if (!fwd_only) w.push_back({pl.off_partial, pl.partial_bytes});
+      else if (pl.partial_bytes > TLORA_NOALLOC_SUM_BYTES || pl.off_partial < TLORA_NOALLOC_SCRATCH_BYTES) return 66;
     }
     size_t end = 0;
     for (auto& r : w) {
