@@ -366,6 +366,12 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
   // the transposed W first: its place depends on nothing but d_in x d_out, so a copy made by one call is found
   // by later calls on other token batches (nano-batches) that share the workspace
   if (pl.dtype == TLORA_BF16 && !fwd_only) pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
+  // so do the packed adapters, whose places depend on the feature sizes and ranks
+  if (pl.dtype == TLORA_BF16) {
+    pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
+    pl.off_bp = wplace(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32));
+    pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
+  }
   pl.off_tables = wplace(pl.tables_bytes);
   pl.off_clock = wplace(64);
   if (pl.dtype == TLORA_F32) {
@@ -382,9 +388,6 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     // + 256: a 64-wide K-step over a last 32-wide slice reads (and ignores) 64 bytes past each operand row
     pl.off_Sx = wplace(2 * (size_t)pl.sx_elems + 256);
     if (!fwd_only) pl.off_dSx = wplace(2 * (size_t)pl.sx_elems + 256);
-    pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
-    pl.off_bp = wplace(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32));
-    pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
     // Sums of split launches.  In the full plan they share the block of the dA / dB partial tiles (the launches follow one
     // another).  The forward-only plan has them behind the static scratch, so that a split never makes a problem too large
     // for it.  Both plans cut the forward's contractions alike (a problem that the scratch holds is cut as the room behind
@@ -714,8 +717,9 @@ namespace {
 // Token-indexed calls (bf16): out_index = the batch row of every token row of the job-sorted order -- the GEMM scatters
 // its output rows there; in_index = the same list when X is the batch in its own order, fetched through the list
 // inside the kernels' loads (null: X already lies in job-sorted order).
+// packed: this workspace already holds the packed copies of the same adapters (a nano-batch after the first).
 int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes, void* hip_stream, bool no_alloc,
-             const int32_t* out_index = nullptr, const int32_t* in_index = nullptr) {
+             const int32_t* out_index = nullptr, const int32_t* in_index = nullptr, bool packed = false) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, no_alloc);
@@ -777,12 +781,11 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   if (rc != TLORA_OK) return rc;
   uint16_t* Sx = reinterpret_cast<uint16_t*>(ws + pl.off_Sx);
   uint16_t* atp = reinterpret_cast<uint16_t*>(ws + pl.off_atp);
-  uint16_t* ap = reinterpret_cast<uint16_t*>(ws + pl.off_ap);
   uint16_t* bp = reinterpret_cast<uint16_t*>(ws + pl.off_bp);
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
-  {
+  if (!packed) {
     Timed t(TLORA_K_PACK, st, timed);
-    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, no_alloc ? nullptr : ap, bp, st);
+    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, nullptr, bp, st);
   }
   {
     Timed t(TLORA_K_SHRINK, st, timed);
@@ -823,7 +826,8 @@ namespace {
 // The backward's launch sequence (out_index / in_index as in fwd_impl: dX rows are scattered; X and dY are fetched
 // through the list).
 int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags,
-             void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index) {
+             void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index,
+             bool packed = false) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes);
@@ -918,10 +922,14 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
   const uint16_t* dYb = static_cast<const uint16_t*>(dY);
   const bool redo_S = want_grads && !reuse_S;
 
+  const bool wt = g_opt.dx_transposed_w != 0;
   {
     Timed t(TLORA_K_PACK, st);
-    // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace
-    if (!reuse_S) launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, st);
+    // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace; a_all,
+    // which only a dX product against W as it lies reads, is made here when it is needed
+    const bool need_a_all = dX && !wt;
+    if (!(reuse_S || packed) || need_a_all)
+      launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, need_a_all ? ap : nullptr, bp, st);
   }
   if (pl.T > 0) {
     if (redo_S) {
@@ -936,7 +944,6 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
       // dX = dY . W^T contracts over W's contiguous dimension.  Against a transposed copy of W the weight tiles
       // are 64 rows of 512 contiguous bytes instead of 256 rows of 128, which the load stream handles markedly
       // better (the copy costs one read and one write of W; W is frozen, so REUSE_WT skips it).
-      const bool wt = g_opt.dx_transposed_w != 0;
       uint16_t* Wt = reinterpret_cast<uint16_t*>(ws + pl.off_wt);
       if (wt && !(flags & TLORA_BWD_REUSE_WT)) {
         Timed t(TLORA_K_WT, st);
@@ -1072,14 +1079,16 @@ int tlora_fwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, vo
   if (need == 0) return validate(p) != TLORA_OK ? validate(p) : TLORA_EINVAL;
   if (!workspace || ws_bytes < need) return TLORA_EWORKSPACE;
   const size_t elt = p->dtype == TLORA_F32 ? 4 : 2;
+  bool packed = false;                            // the adapters are packed once: their copies lie where no batch size moves them
   for (int32_t n = 0; n < n_nano; ++n) {          // one after the other, on the caller's stream
     NanoSub s;
     int rc = make_sub(p, n_nano, granule, n, s);
     if (rc != TLORA_OK) return rc;
     if (s.b1 == s.b0) continue;
-    rc = tlora_fwd(&s.p, Y ? static_cast<uint8_t*>(Y) + (size_t)s.b0 * p->d_out * elt : nullptr, workspace, ws_bytes,
-                   hip_stream);
+    rc = fwd_impl(&s.p, Y ? static_cast<uint8_t*>(Y) + (size_t)s.b0 * p->d_out * elt : nullptr, workspace, ws_bytes,
+                  hip_stream, false, nullptr, nullptr, packed);
     if (rc != TLORA_OK) return rc;
+    packed = true;
   }
   return TLORA_OK;
 }
@@ -1093,7 +1102,7 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
   if (need == 0) return validate(p) != TLORA_OK ? validate(p) : TLORA_EINVAL;
   if (!workspace || ws_bytes < need) return TLORA_EWORKSPACE;
   const size_t elt = p->dtype == TLORA_F32 ? 4 : 2;
-  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0;
+  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0, packed = false;
   for (int32_t n = 0; n < n_nano; ++n) {
     NanoSub s;
     int rc = make_sub(p, n_nano, granule, n, s);
@@ -1101,10 +1110,11 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
     if (s.b1 == s.b0 && !(first && n == n_nano - 1)) continue;      // (an all-empty batch still zeroes dA / dB once)
     // the adapter gradients are sums over the job's tokens: the first nano-batch overwrites, the others add
     int f = (first ? (flags & TLORA_BWD_ACCUMULATE) : TLORA_BWD_ACCUMULATE) | (wt_made ? TLORA_BWD_REUSE_WT : 0);
-    rc = tlora_bwd(&s.p, dY ? static_cast<const uint8_t*>(dY) + (size_t)s.b0 * p->d_out * elt : nullptr,
-                   dX ? static_cast<uint8_t*>(dX) + (size_t)s.b0 * p->d_in * elt : nullptr, dA, dB, f, workspace,
-                   ws_bytes, hip_stream);
+    rc = bwd_impl(&s.p, dY ? static_cast<const uint8_t*>(dY) + (size_t)s.b0 * p->d_out * elt : nullptr,
+                  dX ? static_cast<uint8_t*>(dX) + (size_t)s.b0 * p->d_in * elt : nullptr, dA, dB, f, workspace, ws_bytes,
+                  hip_stream, nullptr, nullptr, packed);
     if (rc != TLORA_OK) return rc;
+    packed = true;
     first = false;
     if (dX && s.b1 > s.b0) wt_made = true;
   }
@@ -1959,6 +1969,11 @@ static int check_plan(const Plan& pl, bool fwd_only) {
     std::vector<std::pair<size_t, size_t>> w;
     const size_t se = (size_t)pl.s_elems, sx = 2 * (size_t)pl.sx_elems + 256;
     if (bf16 && !fwd_only) w.push_back({pl.off_wt, 2 * (size_t)pl.d_in * (size_t)pl.d_out});
+    if (bf16) {
+      w.push_back({pl.off_atp, 2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)});
+      w.push_back({pl.off_bp, 2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32)});
+      w.push_back({pl.off_ap, 2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)});
+    }
     w.push_back({pl.off_tables, pl.tables_bytes});
     w.push_back({pl.off_clock, 64});
     if (!bf16) {
@@ -1970,9 +1985,6 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       if (!fwd_only) { w.push_back({pl.off_dShi, 2 * se});  w.push_back({pl.off_dSlo, 2 * se}); }
       w.push_back({pl.off_Sx, sx});
       if (!fwd_only) w.push_back({pl.off_dSx, sx});
-      w.push_back({pl.off_atp, 2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)});
-      w.push_back({pl.off_bp, 2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32)});
-      if (!fwd_only) w.push_back({pl.off_ap, 2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)});
       if (4 * (size_t)std::max(pl.gradB_partial, pl.gradA_partial) > pl.partial_bytes) return 64;
       for (int k : {pl.shrink_splits_x, pl.shrink_splits_dy})
         if (k < 1 || (k > 1 && 4 * se * (size_t)k > pl.partial_bytes)) return 65;
