@@ -142,7 +142,7 @@ __device__ __forceinline__ bf16x8 frag16_kn(const uint8_t* tile, int nb, int ks,
 //                                                             (shrink operand; dX K-extension operand when dX runs
 //                                                              against the transposed weight)
 //   a_all : [d_in, R + 32], job j in columns roff_j ..        (dX K-extension operand, k contiguous)
-//           (a_all null: not written, the forward alone does not read it)
+//           (a_all null: not written; the forward and a dX product against the transposed weight do not read it)
 //   b_all : [R + 32, d_out], job j in rows roff_j ..          (forward K-extension operand; dS shrink operand)
 // blockIdx.y == num_jobs zero-fills the 32 trailing columns / rows, which the last tile's K-extension
 // may read (against zero activations) when its rank range is rounded up to the K-step.
@@ -150,6 +150,7 @@ __device__ __forceinline__ bf16x8 frag16_kn(const uint8_t* tile, int nb, int ks,
 // Every thread assembles 8 consecutive output elements and stores them as one 16-byte chunk (d_in, d_out, rpad,
 // roff and R are multiples of 8, so every chunk is aligned); A_j is read element by element (its rows are r_j
 // elements long, any alignment), B_j in 16-byte chunks when its base is aligned.
+constexpr int kPackPiece = 1024;               // 16-byte chunks of B_j a workgroup copies at a time
 __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __restrict__ jobs, int num_jobs, int d_in,
                                                             int d_out, int r_total, uint16_t* __restrict__ atp,
                                                             uint16_t* __restrict__ a_all,
@@ -171,18 +172,49 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
   const uint16_t* A = static_cast<const uint16_t*>(jb.A);
   const uint16_t* B = static_cast<const uint16_t*>(jb.B);
   const int rank = jb.rank;
+  // Work of a job: tiles of A_j, then pieces of B_j (1024 chunks, four independent loads per thread).  The launch is bound
+  // by latency, not bytes, until the ranks add up to thousands, so a workgroup should meet one tile or one piece (rank 16,
+  // 4096 -> 12288: 21 - 27 us when 24 workgroups walked several tiles and then their share of B_j, 5 us this way; 32 jobs of
+  // ranks 1 to 256, 5120 -> 17408: 127 - 157 us, now 70).
   // A_j is read once, in tiles of 64 k-rows x 64 rank columns, row by row (contiguous elements), into LDS; both
   // packed layouts are written from there: a_all chunks along the rank, A_j^T chunks along k.
   __shared__ uint16_t tile[64][66];
   const int tk = (d_in + 63) / 64, tp = (jb.rpad + 63) / 64;
-  for (int t = blockIdx.x; t < tk * tp; t += gridDim.x) {
+  const int n_tiles = tk * tp, n_chunks = jb.rpad * kout8, n_units = n_tiles + (n_chunks + kPackPiece - 1) / kPackPiece;
+  uint16_t* const bdst = b_all + (int64_t)jb.roff * d_out;
+  const bool b_aligned = (reinterpret_cast<uintptr_t>(B) & 15) == 0;
+  for (int t = blockIdx.x; t < n_units; t += gridDim.x) {
+    if (t >= n_tiles) {              // B_j into its rows of b_all
+      const int i0 = (t - n_tiles) * kPackPiece + threadIdx.x;
+      u32x4 v[kPackPiece / 256];
+#pragma unroll
+      for (int h = 0; h < kPackPiece / 256; ++h) {
+        const int i = i0 + h * 256, p = i / kout8, c0 = (i - p * kout8) * 8;
+        v[h] = zero;
+        if (p < rank) {              // (p < rank <= rpad: within the job's chunks)
+          const uint16_t* src = B + (int64_t)p * d_out + c0;
+          if (b_aligned) {
+            v[h] = *reinterpret_cast<const u32x4*>(src);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[h][e] = (uint32_t)src[2 * e] | ((uint32_t)src[2 * e + 1] << 16);
+          }
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < kPackPiece / 256; ++h)
+        if (i0 + h * 256 < n_chunks) *reinterpret_cast<u32x4*>(bdst + (int64_t)(i0 + h * 256) * 8) = v[h];
+      continue;
+    }
     const int k_base = (t / tp) * 64, p_base = (t % tp) * 64;
+    uint16_t a[16];
 #pragma unroll
     for (int h = 0; h < 16; ++h) {
-      const int kk = (threadIdx.x >> 6) + h * 4, pp = threadIdx.x & 63;
-      const int k = k_base + kk, pcol = p_base + pp;
-      tile[kk][pp] = (k < d_in && pcol < rank) ? A[(int64_t)k * rank + pcol] : (uint16_t)0;
+      const int k = k_base + (threadIdx.x >> 6) + h * 4, pcol = p_base + (threadIdx.x & 63);
+      a[h] = (k < d_in && pcol < rank) ? A[(int64_t)k * rank + pcol] : (uint16_t)0;
     }
+#pragma unroll
+    for (int h = 0; h < 16; ++h) tile[(threadIdx.x >> 6) + h * 4][threadIdx.x & 63] = a[h];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -210,32 +242,16 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
     }
     __syncthreads();
   }
-  // B_j into its rows of b_all
-  uint16_t* bdst = b_all + (int64_t)jb.roff * d_out;
-  const bool b_aligned = (reinterpret_cast<uintptr_t>(B) & 15) == 0;
-  for (int i = first; i < jb.rpad * kout8; i += stride) {
-    const int p = i / kout8, c0 = (i - p * kout8) * 8;
-    u32x4 v = zero;
-    if (p < rank) {
-      const uint16_t* src = B + (int64_t)p * d_out + c0;
-      if (b_aligned) {
-        v = *reinterpret_cast<const u32x4*>(src);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (uint32_t)src[2 * e] | ((uint32_t)src[2 * e + 1] << 16);
-      }
-    }
-    *reinterpret_cast<u32x4*>(bdst + (int64_t)p * d_out + c0) = v;
-  }
 }
 
+// Workgroups per job: one per tile and piece of the largest job, but no more than 8192 in all (those of smaller jobs find
+// nothing and end; beyond that the loop over the job's units is cheaper than the empty workgroups).
 void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total,
                           uint16_t* atp, uint16_t* a_all, uint16_t* b_all, hipStream_t st) {
   if (max_rpad == 0) return;
-  const int64_t n = (int64_t)max_rpad * (d_in > d_out ? d_in : d_out) / 8;     // 16-byte chunks of the largest layout
-  int bx = (int)((n + 256 * 4 - 1) / (256 * 4));
-  if (bx > 512) bx = 512;
-  if (bx < 1) bx = 1;
+  const int64_t units = (int64_t)((d_in + 63) / 64) * ((max_rpad + 63) / 64) +
+                        ((int64_t)max_rpad * (d_out / 8) + kPackPiece - 1) / kPackPiece;
+  const int bx = (int)std::min<int64_t>(units, std::max(64, 8192 / (num_jobs + 1)));
   hipLaunchKernelGGL(pack_adapters_kernel, dim3(bx, num_jobs + 1), dim3(256), 0, st, jobs, num_jobs, d_in, d_out,
                      r_total, atp, a_all, b_all);
 }
