@@ -1576,59 +1576,112 @@ void launch_grad_reduce(const JobDev* jobs, const GradGroup* groups, int num_gro
 }
 
 // ---------------------------------------------------------------------------------------------------
-// fp32 configuration: strided products C (+)= alpha * A.B, 64 x 64 tile per workgroup.  Operands and
+// fp32 configuration: strided products C (+)= alpha * A.B.  Operands and
 // results are fp32; the running sums are kept in fp64 so that long token reductions (dA, dB) stay
 // within 1e-5 of the exact value even where the result is close to zero.
+// A workgroup makes a TS x TS tile of C, each thread (TS / 16)^2 of its elements, in K-steps of 1024 / TS whose operands
+// (four elements of A and of B per thread) are fetched while the step before is multiplied.  The table lists tiles of 64;
+// TS = 32 runs four workgroups per entry.  Small problems are bound by latency: with ten workgroups (128 tokens, 256 x 256)
+// each K-step of 16 took 2.3 us, nearly all of it its eight loads, one after the other:
+// 37 us the launch, 15 us now; 2048 tokens of 1024 -> 512 at rank 64, a pass 780 -> 503 us.
 // ---------------------------------------------------------------------------------------------------
+template <int TS>
 __global__ void __launch_bounds__(256) f32_units_kernel(const F32Unit* __restrict__ units,
                                                         const F32Tile* __restrict__ tiles) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const F32Tile t = tiles[blockIdx.x];
+  constexpr int BK = 1024 / TS, E = TS / 16, SUB = 64 / TS;
+  __shared__ float As[2][BK][TS + 1];
+  __shared__ float Bs[2][BK][TS + 1];
+  const F32Tile t = tiles[blockIdx.x / (SUB * SUB)];
   const F32Unit u = units[t.unit];
+  const int sub = (int)(blockIdx.x % (SUB * SUB));
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = t.tm * 64, n0 = t.tn * 64;
-  double acc[4][4] = {};
-  for (int k0 = 0; k0 < u.K; k0 += 16) {
-    for (int i = threadIdx.x; i < 16 * 64; i += 256) {
-      const int kk = i & 15, mm = i >> 4;             // A tile: 64 rows x 16 k
-      const int m = m0 + mm, k = k0 + kk;
-      As[kk][mm] = (m < u.M && k < u.K) ? u.A[(int64_t)m * u.a_rs + (int64_t)k * u.a_cs] : 0.f;
-      const int nn = i & 63, kb = i >> 6;             // B tile: 16 k x 64 cols
-      const int n = n0 + nn, k2 = k0 + kb;
-      Bs[kb][nn] = (n < u.N && k2 < u.K) ? u.B[(int64_t)k2 * u.b_rs + (int64_t)n * u.b_cs] : 0.f;
+  const int m0 = t.tm * 64 + sub / SUB * TS, n0 = t.tn * 64 + sub % SUB * TS;
+  if (m0 >= u.M || n0 >= u.N) return;
+  // element i of a thread's four: consecutive threads follow the operand's contiguous direction
+  const bool a_along_m = u.a_rs == 1 && u.a_cs != 1, b_along_k = u.b_rs == 1 && u.b_cs != 1;
+  auto a_at = [&](int i, int& kk, int& mm) {
+    const int q = threadIdx.x + i * 256;
+    kk = a_along_m ? q / TS : q % BK;  mm = a_along_m ? q % TS : q / BK;
+  };
+  auto b_at = [&](int i, int& kk, int& nn) {
+    const int q = threadIdx.x + i * 256;
+    kk = b_along_k ? q % BK : q / TS;  nn = b_along_k ? q / BK : q % TS;
+  };
+  // Loads without branches (clamped to the operand, zeroed on the way to LDS) and through pointers known to be global: a load
+  // under a condition, or one that might be an LDS access, is waited for before the next is issued.
+  typedef const __attribute__((address_space(1))) float* GlobalPtr;
+  const GlobalPtr gA = (GlobalPtr)u.A, gB = (GlobalPtr)u.B;
+  float ra[4], rb[4];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int kk, mm, kb, nn;
+      a_at(i, kk, mm);  b_at(i, kb, nn);
+      const int m = m0 + mm, n = n0 + nn, k = k0 + kk, k2 = k0 + kb;
+      ra[i] = gA[(int64_t)min(m, u.M - 1) * u.a_rs + (int64_t)min(k, u.K - 1) * u.a_cs];
+      rb[i] = gB[(int64_t)min(k2, u.K - 1) * u.b_rs + (int64_t)min(n, u.N - 1) * u.b_cs];
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf, int k0) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fma((double)a[i], (double)b[j], acc[i][j]);
+    for (int i = 0; i < 4; ++i) {
+      int kk, mm, kb, nn;
+      a_at(i, kk, mm);  b_at(i, kb, nn);
+      As[buf][kk][mm] = m0 + mm < u.M && k0 + kk < u.K ? ra[i] : 0.f;
+      Bs[buf][kb][nn] = n0 + nn < u.N && k0 + kb < u.K ? rb[i] : 0.f;
     }
+  };
+  double acc[E][E] = {};
+  if (u.K > 0) {
+    fetch(0);
+    store(0, 0);
     __syncthreads();
   }
+  for (int k0 = 0, buf = 0; k0 < u.K; k0 += BK, buf ^= 1) {
+    const bool more = k0 + BK < u.K;
+    if (more) fetch(k0 + BK);
+#pragma unroll 8
+    for (int kk = 0; kk < BK; ++kk) {
+      float a[E], b[E];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < E; ++i) a[i] = As[buf][kk][ty * E + i];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < u.M && n < u.N) {
-        float* c = u.C + (int64_t)m * u.c_rs + n;
-        const double v = (double)u.alpha * acc[i][j];
-        *c = (float)(u.accumulate ? (double)*c + v : v);
-      }
+      for (int j = 0; j < E; ++j) b[j] = Bs[buf][kk][tx * E + j];
+#pragma unroll
+      for (int i = 0; i < E; ++i)
+#pragma unroll
+        for (int j = 0; j < E; ++j) acc[i][j] = __builtin_fma((double)a[i], (double)b[j], acc[i][j]);
+    }
+    if (more) store(buf ^ 1, k0 + BK);
+    __syncthreads();
+  }
+  __attribute__((address_space(1))) float* const gC = (__attribute__((address_space(1))) float*)u.C;
+  float old[E][E] = {};
+  if (u.accumulate) {
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+#pragma unroll
+      for (int j = 0; j < E; ++j)
+        old[i][j] = gC[(int64_t)min(m0 + ty * E + i, u.M - 1) * u.c_rs + min(n0 + tx * E + j, u.N - 1)];
+  }
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int m = m0 + ty * E + i, n = n0 + tx * E + j;
+      const double v = (double)u.alpha * acc[i][j];
+      if (m < u.M && n < u.N) gC[(int64_t)m * u.c_rs + n] = (float)(u.accumulate ? (double)old[i][j] + v : v);
     }
 }
 
+// Tiles of 32 while tiles of 64 would leave CUs without a workgroup; from 256 on the larger tile's fewer LDS reads and
+// conversions per product count for more.
 void launch_f32_units(const F32Unit* units, const F32Tile* tiles, int num_tiles, hipStream_t st) {
   if (num_tiles == 0) return;
-  hipLaunchKernelGGL(f32_units_kernel, dim3(num_tiles), dim3(256), 0, st, units, tiles);
+  if (num_tiles < 256)
+    hipLaunchKernelGGL(f32_units_kernel<32>, dim3(num_tiles * 4), dim3(256), 0, st, units, tiles);
+  else
+    hipLaunchKernelGGL(f32_units_kernel<64>, dim3(num_tiles), dim3(256), 0, st, units, tiles);
 }
 
 // ---------------------------------------------------------------------------------------------------
