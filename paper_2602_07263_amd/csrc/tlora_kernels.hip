@@ -1688,28 +1688,66 @@ void launch_f32_units(const F32Unit* units, const F32Tile* tiles, int num_tiles,
 // Per-job optimizer step (AdamW with decoupled weight decay) over a table of tensors: blockIdx.y = tensor,
 // blockIdx.x = chunk of 4096 elements.  fp32 arithmetic on the fp32 master copy; the tensor the layer reads is
 // rewritten from it (round-to-nearest-even for bf16).  Reads 16 and writes 14 (bf16) bytes per element.
+// Bound by HBM: where the bases allow it a thread takes four neighbouring elements with 16-byte accesses and has all its
+// loads in flight before the first is used (48 adapters, 10 M elements: 66.2 -> 64.5 us).
 // ---------------------------------------------------------------------------------------------------
+struct AdamwVal {
+  float m, v, w;
+};
+__device__ __forceinline__ AdamwVal adamw_one(const AdamwDev& t, float g, float m0, float v0, float w0) {
+  const float m = t.beta1 * m0 + (1.f - t.beta1) * g;
+  const float v = t.beta2 * v0 + (1.f - t.beta2) * g * g;
+  return {m, v, w0 - t.lr * ((m * t.c1) / (sqrtf(v * t.c2) + t.eps) + t.weight_decay * w0)};
+}
 __global__ void __launch_bounds__(256) adamw_kernel(const AdamwDev* __restrict__ tensors) {
   const AdamwDev t = tensors[blockIdx.y];
   const int64_t base = (int64_t)blockIdx.x * 4096;
   if (base >= t.n) return;
   float* const wsrc = t.master ? t.master : static_cast<float*>(t.param);
+  const uintptr_t bases = reinterpret_cast<uintptr_t>(t.grad) | reinterpret_cast<uintptr_t>(t.m) |
+                          reinterpret_cast<uintptr_t>(t.v) | reinterpret_cast<uintptr_t>(wsrc) |
+                          reinterpret_cast<uintptr_t>(t.param) << (t.param_is_bf16 ? 1 : 0);
+  if ((bases & 15) == 0 && base + 4096 <= t.n) {
+    f32x4 g[4], m[4], v[4], w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = base + k * 1024 + threadIdx.x * 4;
+      g[k] = *reinterpret_cast<const f32x4*>(t.grad + i);
+      m[k] = *reinterpret_cast<const f32x4*>(t.m + i);
+      v[k] = *reinterpret_cast<const f32x4*>(t.v + i);
+      w[k] = *reinterpret_cast<const f32x4*>(wsrc + i);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = base + k * 1024 + threadIdx.x * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const AdamwVal r = adamw_one(t, g[k][e], m[k][e], v[k][e], w[k][e]);
+        m[k][e] = r.m;  v[k][e] = r.v;  w[k][e] = r.w;
+      }
+      *reinterpret_cast<f32x4*>(t.m + i) = m[k];
+      *reinterpret_cast<f32x4*>(t.v + i) = v[k];
+      *reinterpret_cast<f32x4*>(wsrc + i) = w[k];
+      if (t.param_is_bf16)
+        *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(t.param) + i) =
+            u32x2{pack_bf16x2(w[k][0], w[k][1]), pack_bf16x2(w[k][2], w[k][3])};
+      else if (t.master)
+        *reinterpret_cast<f32x4*>(static_cast<float*>(t.param) + i) = w[k];
+    }
+    return;
+  }
 #pragma unroll 4
   for (int k = 0; k < 16; ++k) {
     const int64_t i = base + k * 256 + threadIdx.x;
     if (i >= t.n) break;
-    const float g = t.grad[i];
-    const float m = t.beta1 * t.m[i] + (1.f - t.beta1) * g;
-    const float v = t.beta2 * t.v[i] + (1.f - t.beta2) * g * g;
-    const float w0 = wsrc[i];
-    const float w = w0 - t.lr * ((m * t.c1) / (sqrtf(v * t.c2) + t.eps) + t.weight_decay * w0);
-    t.m[i] = m;
-    t.v[i] = v;
-    wsrc[i] = w;
+    const AdamwVal r = adamw_one(t, t.grad[i], t.m[i], t.v[i], wsrc[i]);
+    t.m[i] = r.m;
+    t.v[i] = r.v;
+    wsrc[i] = r.w;
     if (t.param_is_bf16) {
-      static_cast<uint16_t*>(t.param)[i] = (uint16_t)(pack_bf16x2(w, 0.f) & 0xffffu);
+      static_cast<uint16_t*>(t.param)[i] = (uint16_t)(pack_bf16x2(r.w, 0.f) & 0xffffu);
     } else if (t.master) {
-      static_cast<float*>(t.param)[i] = w;
+      static_cast<float*>(t.param)[i] = r.w;
     }
   }
 }
