@@ -1868,8 +1868,8 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const void* __restrict
 template <bool BF>
 __global__ void __launch_bounds__(256) swiglu_fwd_kernel(const void* __restrict__ G, const void* __restrict__ U,
                                                          void* __restrict__ Z, int64_t n8) {
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n8) {
     float g[8], u[8];
     load8<BF>(G, i * 8, g);  load8<BF>(U, i * 8, u);
 #pragma unroll
@@ -1882,8 +1882,8 @@ template <bool BF>
 __global__ void __launch_bounds__(256) swiglu_bwd_kernel(const void* __restrict__ G, const void* __restrict__ U,
                                                          const void* __restrict__ dZ, void* __restrict__ dG,
                                                          void* __restrict__ dU, int64_t n8) {
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n8) {
     float g[8], u[8], z[8], dg[8], du[8];
     load8<BF>(G, i * 8, g);  load8<BF>(U, i * 8, u);  load8<BF>(dZ, i * 8, z);
 #pragma unroll
@@ -1899,8 +1899,8 @@ __global__ void __launch_bounds__(256) swiglu_bwd_kernel(const void* __restrict_
 template <bool BF>
 __global__ void __launch_bounds__(256) residual_add_kernel(const void* __restrict__ X, const void* __restrict__ D,
                                                            void* __restrict__ Out, int64_t n8) {
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n8) {
     float x[8], y[8];
     load8<BF>(X, i * 8, x);  load8<BF>(D, i * 8, y);
 #pragma unroll
@@ -1909,7 +1909,10 @@ __global__ void __launch_bounds__(256) residual_add_kernel(const void* __restric
   }
 }
 
-static unsigned ew_blocks(int64_t n8) { return (unsigned)std::min<int64_t>((n8 + 255) / 256, 256 * 32); }
+// One chunk per thread.  8192 workgroups that walked the tensors in strides kept the loads of an iteration behind the stores
+// of the one before: residual sum of 83968 x 4096 427 us (now 333: 6.2 TB/s), SwiGLU of 83968 x 12288 1286 us forward and
+// 2150 us backward (now 1055 and 1815: 5.8 and 5.7 TB/s).
+static unsigned ew_blocks(int64_t n8) { return (unsigned)((n8 + 255) / 256); }
 
 void launch_rmsnorm_fwd(bool bf16, const void* X, const void* gamma, float eps, int T, int d, void* Xn, float* rstd,
                         hipStream_t st) {
