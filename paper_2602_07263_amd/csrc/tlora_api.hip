@@ -1439,7 +1439,7 @@ int tlora_attention_bwd(const void* Q, const void* K, const void* V, const void*
     launch_attn_bwd(reinterpret_cast<const AttnTile*>(ws + A.off_tiles), (int)A.tiles.size(), static_cast<const uint16_t*>(Q),
                     static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), static_cast<const uint16_t*>(O),
                     static_cast<const uint16_t*>(dO), lse, reinterpret_cast<float*>(ws + A.off_D),
-                    static_cast<uint16_t*>(dQ), static_cast<uint16_t*>(dK), static_cast<uint16_t*>(dV), A.T, n_heads,
+                    static_cast<uint16_t*>(dQ), static_cast<uint16_t*>(dK), static_cast<uint16_t*>(dV), n_heads,
                     n_kv_heads, st);
   }
   return launches_ok(__LINE__);
@@ -1591,7 +1591,7 @@ int tlora_attn_bwd(const tlora_attn_t* p, const void* dOut, void* dX, void* cons
                       reinterpret_cast<const uint16_t*>(ws + L.off_v), reinterpret_cast<const uint16_t*>(ws + L.off_o),
                       reinterpret_cast<const uint16_t*>(ws + L.off_do), reinterpret_cast<const float*>(ws + L.off_lse),
                       reinterpret_cast<float*>(aw + L.A.off_D), reinterpret_cast<uint16_t*>(ws + L.off_dq),
-                      reinterpret_cast<uint16_t*>(ws + L.off_dk), reinterpret_cast<uint16_t*>(ws + L.off_dv), L.T,
+                      reinterpret_cast<uint16_t*>(ws + L.off_dk), reinterpret_cast<uint16_t*>(ws + L.off_dv),
                       p->n_heads, p->n_kv_heads, st);
     }
     {

@@ -314,33 +314,17 @@ attn_fwd_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restrict__
   }
 }
 
-// D[t, h] = sum_d dO[t, h, d] * O[t, h, d]   (16 lanes x 16 bytes per (token, head) row, 16 rows per workgroup)
-__global__ void __launch_bounds__(256) attn_rowdot_kernel(const uint16_t* __restrict__ dO, const uint16_t* __restrict__ O,
-                                                          float* __restrict__ D, int64_t n_rows) {
-  const int64_t r = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int sub = threadIdx.x & 15;
-  float s = 0.f;
-  if (r < n_rows) {
-    const u32x4 a = *reinterpret_cast<const u32x4*>(dO + r * HD + sub * 8);
-    const u32x4 b = *reinterpret_cast<const u32x4*>(O + r * HD + sub * 8);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      s += __builtin_bit_cast(float, a[e] << 16) * __builtin_bit_cast(float, b[e] << 16) +
-           __builtin_bit_cast(float, a[e] & 0xffff0000u) * __builtin_bit_cast(float, b[e] & 0xffff0000u);
-  }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (sub == 0 && r < n_rows) D[r] = s;
-}
-
 // ---------------------------------------------------------------------------------------------------
 // Backward, dQ.  Same decomposition as the forward: per 32 keys
 //   S^T = K Q^T,  P^T = exp2(c S^T - lse),  dP^T = V dO^T,  dS^T = P^T (dP^T - D),  dQ^T += K^T dS^T,  dQ = dQ / sqrt(128).
+// D[t, h] = sum_d dO[t, h, d] O[t, h, d] is made here, from the dO fragments the kernel holds anyway, and stored for the
+// dK / dV kernel that follows (a kernel of its own read dO a second time: 92 us for 32768 tokens and 32 heads).
 // ---------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_bwd_dq_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                   const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO, const float* __restrict__ lse,
-                   const float* __restrict__ D, uint16_t* __restrict__ dQ, int Hq, int Hkv, float c, float scale) {
+                   const uint16_t* __restrict__ V, const uint16_t* __restrict__ O, const uint16_t* __restrict__ dO,
+                   const float* __restrict__ lse, float* __restrict__ D, uint16_t* __restrict__ dQ, int Hq, int Hkv,
+                   float c, float scale) {
   __shared__ __attribute__((aligned(1024))) uint8_t kt[2][64 * ROWB];
   __shared__ __attribute__((aligned(1024))) uint8_t vt[2][64 * ROWB];
   const AttnTile t = tiles[blockIdx.x];
@@ -356,7 +340,7 @@ attn_bwd_dq_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restric
   bf16x8 qf[8], dof[8];
   load_row_frags(Q + qrow * qs + h * HD, lane, qf);
   load_row_frags(dO + qrow * qs + h * HD, lane, dof);
-  const float L = lse[qrow * Hq + h], Dq = D[qrow * Hq + h];
+  const float L = lse[qrow * Hq + h];
   const uint16_t* Kh = K + (int64_t)t.seq_start * ks + hk * HD;
   const uint16_t* Vh = V + (int64_t)t.seq_start * ks + hk * HD;
   const uint32_t kv_row_bytes = (uint32_t)ks * 2u;
@@ -376,6 +360,20 @@ attn_bwd_dq_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restric
   };
   const FragPat P = make_frag_pat(lane);
   issue(0);
+  float Dq;
+  {                                                                  // 64 products per lane (8 sums of 8), then lane ^ 32's
+    bf16x8 of[8];
+    load_row_frags(O + qrow * qs + h * HD, lane, of);
+    float d[8] = {};
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[e] = fmaf((float)dof[s][e], (float)of[s][e], d[e]);
+    float a, b;
+    with_partner32(((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7])), a, b);
+    Dq = a + b;
+    if (qvalid && hl == 0) D[qrow * Hq + h] = Dq;
+  }
   auto tile_step = [&](auto bufc, int it) {
     constexpr int buf = decltype(bufc)::value;
     wait_all_and_sync();
@@ -660,13 +658,11 @@ void launch_attn_fwd(const AttnTile* tiles, int n_tiles, const uint16_t* Q, cons
 }
 void launch_attn_bwd(const AttnTile* tiles, int n_tiles, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
                      const uint16_t* O, const uint16_t* dO, const float* lse, float* D, uint16_t* dQ, uint16_t* dK,
-                     uint16_t* dV, int64_t T, int Hq, int Hkv, hipStream_t st) {
+                     uint16_t* dV, int Hq, int Hkv, hipStream_t st) {
   if (n_tiles == 0) return;
   const float scale = 1.f / sqrtf((float)HD), c = 1.4426950408889634f * scale;
-  const int64_t rows = T * Hq;
-  hipLaunchKernelGGL(attn_rowdot_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, dO, O, D, rows);
-  hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(n_tiles, Hq), dim3(256), 0, st, tiles, Q, K, V, dO, lse, D, dQ, Hq, Hkv, c,
-                     scale);
+  hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(n_tiles, Hq), dim3(256), 0, st, tiles, Q, K, V, O, dO, lse, D, dQ, Hq, Hkv,
+                     c, scale);
   hipLaunchKernelGGL(attn_bwd_dkv_kernel, dim3(n_tiles, Hkv), dim3(512), 0, st, tiles, n_tiles, Q, K, V, dO, lse, D, dK, dV,
                      Hq, Hkv, c, scale);
 }
