@@ -1689,7 +1689,8 @@ void launch_f32_units(const F32Unit* units, const F32Tile* tiles, int num_tiles,
 // blockIdx.x = chunk of 4096 elements.  fp32 arithmetic on the fp32 master copy; the tensor the layer reads is
 // rewritten from it (round-to-nearest-even for bf16).  Reads 16 and writes 14 (bf16) bytes per element.
 // Bound by HBM: where the bases allow it a thread takes four neighbouring elements with 16-byte accesses and has all its
-// loads in flight before the first is used (48 adapters, 10 M elements: 66.2 -> 64.5 us).
+// loads in flight before the first is used (48 adapter tensors, 14.4 M elements: 66.2 -> 64.5 us,
+// 6.7 TB/s).
 // ---------------------------------------------------------------------------------------------------
 struct AdamwVal {
   float m, v, w;
@@ -1800,67 +1801,126 @@ __device__ __forceinline__ float block_sum(float x, float* red) {
 }
 
 // Xn[t, :] = X[t, :] * rstd_t * gamma,  rstd_t = 1 / sqrt(mean(X[t, :]^2) + eps).  One workgroup per row.
-template <bool BF>
+// CH: the row is kept in registers between the sum and the result, CH chunks of 8 per thread (rows of up to 2048 CH features;
+// loads past the row repeat its last chunk and are not used).  CH = 0: any width, the row is read twice.  A CU's eight
+// workgroups have 64 KB per operand between them, so with the five operands of the backward the second reading no longer
+// found the row in the L2 (83968 x 4096: forward 246 -> 217 us, backward 690 -> 597 us with two gradients and 905 -> 745 us
+// with three, 5.5 TB/s).
+template <bool BF, int CH>
 __global__ void __launch_bounds__(256) rmsnorm_fwd_kernel(const void* __restrict__ X, const void* __restrict__ gamma,
                                                           float eps, int d, void* __restrict__ Xn,
                                                           float* __restrict__ rstd) {
   __shared__ float red[4];
   const int64_t row = (int64_t)blockIdx.x * d;
+  const int c0 = threadIdx.x * 8;
+  float keep[CH ? CH : 1][8];
   float ss = 0.f;
-  for (int c = threadIdx.x * 8; c < d; c += 2048) {
-    float v[8];
-    load8<BF>(X, row + c, v);
+  if (CH) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
+    for (int h = 0; h < CH; ++h) load8<BF>(X, row + min(c0 + h * 2048, d - 8), keep[h]);
+#pragma unroll
+    for (int h = 0; h < CH; ++h)
+      if (c0 + h * 2048 < d) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += keep[h][e] * keep[h][e];
+      }
+  } else {
+    for (int c = c0; c < d; c += 2048) {
+      float v[8];
+      load8<BF>(X, row + c, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
+    }
   }
   const float r = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
   if (threadIdx.x == 0) rstd[blockIdx.x] = r;
-  for (int c = threadIdx.x * 8; c < d; c += 2048) {
-    float v[8], g[8];
-    load8<BF>(X, row + c, v);
+  auto finish = [&](int c, float (&v)[8]) {
+    float g[8];
     load8<BF>(gamma, c, g);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = v[e] * r * g[e];
     store8<BF>(Xn, row + c, v);
+  };
+  if (CH) {
+#pragma unroll
+    for (int h = 0; h < CH; ++h)
+      if (c0 + h * 2048 < d) finish(c0 + h * 2048, keep[h]);
+  } else {
+    for (int c = c0; c < d; c += 2048) {
+      float v[8];
+      load8<BF>(X, row + c, v);
+      finish(c, v);
+    }
   }
 }
 
-// dX[t, :] = dOut[t, :] + rstd_t * gd - X[t, :] * rstd_t^3 * sum(gd * X[t, :]) / d,   gd = (dXa + dXb) * gamma
-template <bool BF>
+// dX[t, :] = dOut[t, :] + rstd_t * gd - X[t, :] * rstd_t^3 * sum(gd * X[t, :]) / d,   gd = (dXa + dXb + dXc) * gamma
+// (C3: with dXc, which is null otherwise).  CH as above.
+template <bool BF, int CH, bool C3>
 __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const void* __restrict__ X, const void* __restrict__ gamma,
                                                           const float* __restrict__ rstd, const void* __restrict__ dXa,
                                                           const void* __restrict__ dXb, const void* __restrict__ dXc,
                                                           const void* __restrict__ dOut, int d, void* __restrict__ dX) {
   __shared__ float red[4];
   const int64_t row = (int64_t)blockIdx.x * d;
-  float dot = 0.f;
-  for (int c = threadIdx.x * 8; c < d; c += 2048) {
-    float x[8], a[8], b[8], g[8];
-    load8<BF>(X, row + c, x);  load8<BF>(dXa, row + c, a);  load8<BF>(dXb, row + c, b);  load8<BF>(gamma, c, g);
-    if (dXc) {
+  const int c0 = threadIdx.x * 8;
+  constexpr int N = CH ? CH : 1;
+  float x[N][8], a[N][8], o[N][8];
+  auto load_row = [&](int c, float (&xv)[8], float (&av)[8]) {        // X and the sum of its gradients
+    float b[8];
+    load8<BF>(X, row + c, xv);  load8<BF>(dXa, row + c, av);  load8<BF>(dXb, row + c, b);
+    if (C3) {
       float cc[8];
       load8<BF>(dXc, row + c, cc);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] = a[e] + b[e] + cc[e], b[e] = 0.f;
+      for (int e = 0; e < 8; ++e) av[e] = av[e] + b[e] + cc[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) av[e] = av[e] + b[e];
+    }
+  };
+  float dot = 0.f;
+  auto add_dot = [&](int c, const float (&xv)[8], const float (&av)[8]) {
+    float g[8];
+    load8<BF>(gamma, c, g);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dot += av[e] * g[e] * xv[e];
+  };
+  if (CH) {
+#pragma unroll
+    for (int h = 0; h < N; ++h) {
+      const int c = min(c0 + h * 2048, d - 8);
+      load_row(c, x[h], a[h]);
+      load8<BF>(dOut, row + c, o[h]);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) dot += (a[e] + b[e]) * g[e] * x[e];
+    for (int h = 0; h < N; ++h)
+      if (c0 + h * 2048 < d) add_dot(c0 + h * 2048, x[h], a[h]);
+  } else {
+    for (int c = c0; c < d; c += 2048) {
+      load_row(c, x[0], a[0]);
+      add_dot(c, x[0], a[0]);
+    }
   }
   const float r = rstd[blockIdx.x];
   const float k = block_sum(dot, red) * r * r * r / (float)d;
-  for (int c = threadIdx.x * 8; c < d; c += 2048) {
-    float x[8], a[8], b[8], g[8], o[8];
-    load8<BF>(X, row + c, x);  load8<BF>(dXa, row + c, a);  load8<BF>(dXb, row + c, b);  load8<BF>(gamma, c, g);
-    load8<BF>(dOut, row + c, o);
-    if (dXc) {
-      float cc[8];
-      load8<BF>(dXc, row + c, cc);
+  auto finish = [&](int c, const float (&xv)[8], const float (&av)[8], float (&ov)[8]) {
+    float g[8];
+    load8<BF>(gamma, c, g);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] = a[e] + b[e] + cc[e], b[e] = 0.f;
+    for (int e = 0; e < 8; ++e) ov[e] = ov[e] + r * av[e] * g[e] - xv[e] * k;
+    store8<BF>(dX, row + c, ov);
+  };
+  if (CH) {
+#pragma unroll
+    for (int h = 0; h < N; ++h)
+      if (c0 + h * 2048 < d) finish(c0 + h * 2048, x[h], a[h], o[h]);
+  } else {
+    for (int c = c0; c < d; c += 2048) {
+      load_row(c, x[0], a[0]);
+      load8<BF>(dOut, row + c, o[0]);
+      finish(c, x[0], a[0], o[0]);
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = o[e] + r * (a[e] + b[e]) * g[e] - x[e] * k;
-    store8<BF>(dX, row + c, o);
   }
 }
 
@@ -1914,18 +1974,35 @@ __global__ void __launch_bounds__(256) residual_add_kernel(const void* __restric
 // 2150 us backward (now 1055 and 1815: 5.8 and 5.7 TB/s).
 static unsigned ew_blocks(int64_t n8) { return (unsigned)((n8 + 255) / 256); }
 
+// bf16 rows of up to 8192 features stay in registers (fp32 blocks are the small ones: no instantiations of their own).
+#define TLORA_BY_WIDTH(LAUNCH)                                                                                         \
+  do {                                                                                                                \
+    if (bf16 && d <= 2048) LAUNCH(true, 1);                                                                           \
+    else if (bf16 && d <= 4096) LAUNCH(true, 2);                                                                      \
+    else if (bf16 && d <= 8192) LAUNCH(true, 4);                                                                      \
+    else if (bf16) LAUNCH(true, 0);                                                                                   \
+    else LAUNCH(false, 0);                                                                                            \
+  } while (0)
 void launch_rmsnorm_fwd(bool bf16, const void* X, const void* gamma, float eps, int T, int d, void* Xn, float* rstd,
                         hipStream_t st) {
   if (T == 0) return;
-  if (bf16) hipLaunchKernelGGL(rmsnorm_fwd_kernel<true>, dim3(T), dim3(256), 0, st, X, gamma, eps, d, Xn, rstd);
-  else      hipLaunchKernelGGL(rmsnorm_fwd_kernel<false>, dim3(T), dim3(256), 0, st, X, gamma, eps, d, Xn, rstd);
+#define TLORA_FWD(BF, CH) hipLaunchKernelGGL((rmsnorm_fwd_kernel<BF, CH>), dim3(T), dim3(256), 0, st, X, gamma, eps, d, Xn, rstd)
+  TLORA_BY_WIDTH(TLORA_FWD);
+#undef TLORA_FWD
 }
 void launch_rmsnorm_bwd(bool bf16, const void* X, const void* gamma, const float* rstd, const void* dXa,
                         const void* dXb, const void* dXc, const void* dOut, int T, int d, void* dX, hipStream_t st) {
   if (T == 0) return;
-  if (bf16) hipLaunchKernelGGL(rmsnorm_bwd_kernel<true>, dim3(T), dim3(256), 0, st, X, gamma, rstd, dXa, dXb, dXc, dOut, d, dX);
-  else      hipLaunchKernelGGL(rmsnorm_bwd_kernel<false>, dim3(T), dim3(256), 0, st, X, gamma, rstd, dXa, dXb, dXc, dOut, d, dX);
+#define TLORA_BWD2(BF, CH) \
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<BF, CH, false>), dim3(T), dim3(256), 0, st, X, gamma, rstd, dXa, dXb, dXc, dOut, d, dX)
+#define TLORA_BWD3(BF, CH) \
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<BF, CH, true>), dim3(T), dim3(256), 0, st, X, gamma, rstd, dXa, dXb, dXc, dOut, d, dX)
+  if (dXc) TLORA_BY_WIDTH(TLORA_BWD3);
+  else     TLORA_BY_WIDTH(TLORA_BWD2);
+#undef TLORA_BWD2
+#undef TLORA_BWD3
 }
+#undef TLORA_BY_WIDTH
 void launch_swiglu_fwd(bool bf16, const void* G, const void* U, void* Z, int64_t n, hipStream_t st) {
   if (n == 0) return;
   if (bf16) hipLaunchKernelGGL(swiglu_fwd_kernel<true>, dim3(ew_blocks(n / 8)), dim3(256), 0, st, G, U, Z, n / 8);

@@ -59,3 +59,10 @@ def test_optimizer_step_does_not_depend_on_alignment(dtype, shift):
 
     for a, b in zip(step(0), step(shift)):
         assert torch.allclose(a, b, rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("d", [8, 2048, 2056, 4104, 8200])
+def test_norm_rows_at_the_register_widths(d):
+    """The norms hold rows of up to 2048, 4096 and 8192 features in registers and read wider ones twice."""
+    from tests import test_mlp_gpu as tm
+    tm.test_mlp_block_matches_oracle(("bf16", d, 64, [8, 3], [5, 2], [1.0, 2.0]))
