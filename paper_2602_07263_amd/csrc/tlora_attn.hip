@@ -561,8 +561,6 @@ attn_bwd_dkv_kernel(const AttnTile* __restrict__ tiles, int n_tiles, const uint1
         }
       }
       pipeline_reads<32, 8, 1, 2, 16>();
-      {
-      }
     }
   };
   for (int st = 0; st < nsteps; st += NS) {                          // NS steps per trip: the stage is a constant
@@ -572,8 +570,10 @@ attn_bwd_dkv_kernel(const AttnTile* __restrict__ tiles, int n_tiles, const uint1
   }
   // Waves w and w + 4 trade halves of their sums: the lower wave ends with dK of the 32 keys, the upper one with dV.
   // 8 x 16 KB fill what held the tiles (all loads have landed: the last step waited for everything).
+  // The stores and loads of the trade are ordinary ones, so the barriers are __syncthreads(): the bare barrier of the loop
+  // orders only the asynchronous loads (whose asm the compiler may not move memory accesses across).
   static_assert(8 * 64 * 64 * 4 <= VT + NS * STAGE, "the sums fit into the tiles' place");
-  wait_all_and_sync();
+  __syncthreads();
   {
     f32x4* const mine = reinterpret_cast<f32x4*>(lds + wave * 16384) + lane;
     const f32x4* const other = reinterpret_cast<const f32x4*>(lds + (wave ^ 4) * 16384) + lane;
@@ -586,7 +586,7 @@ attn_bwd_dkv_kernel(const AttnTile* __restrict__ tiles, int n_tiles, const uint1
         for (int e = 0; e < 4; ++e) v[e] = half ? dk[db][4 * g + e] : dv[db][4 * g + e];
         mine[(db * 4 + g) * 64] = v;
       }
-    wait_all_and_sync();
+    __syncthreads();
     if (kvalid) {
       uint16_t* const out = (half ? dV : dK) + krow * ks + hk * HD;
       const float f = half ? 1.f : scale;
