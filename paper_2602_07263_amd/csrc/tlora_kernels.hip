@@ -11,6 +11,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "tlora_kernels.h"
 
@@ -1494,8 +1495,11 @@ void launch_rank_grad(const JobDev* jobs, const GradUnit* units, int num_units, 
 // dA_j is the transpose of the computed tile: [D, r]).  One workgroup = 32 rank rows x 64 feature columns.  Bound by
 // memory: the partial tiles are read as 256-byte runs; a dB row leaves the same way, and a dA block is turned in LDS, so
 // that the 32 ranks of a feature leave as one run of 128 bytes.  (Stored as 16 bytes per feature from workgroups that
-// each held 4 ranks, the lines of dA were put together from pieces of several L2s: 368 us for the dA of 32 jobs at 17408
-// features, now 110; the dB of the same jobs 130, as before.)
+// each held 4 ranks, the lines of dA were put together from pieces of several L2s: 356 us for the dA of 32 jobs at
+// 17408 features, now 104.)  Where few blocks walk long chains of partial tiles the latency of the loads decides, so
+// they carry no condition (a row beyond the job's rank repeats its last one) and those of up to 8 tiles are in flight: loads
+// under a per-row condition were waited for one by one, 15.0 us for four jobs at 4096 features, 5.5 now (the kernel of
+// 4-rank slabs: 7.9).
 template <bool DA>
 __global__ void __launch_bounds__(256) grad_reduce_kernel(const JobDev* __restrict__ jobs,
                                                           const GradGroup* __restrict__ groups,
@@ -1512,14 +1516,28 @@ __global__ void __launch_bounds__(256) grad_reduce_kernel(const JobDev* __restri
   if (live <= 0 || c0 >= D) return;
   const int sub = (threadIdx.x & 15) * 4, r = threadIdx.x >> 4;   // the thread's 4 columns; its rows r and r + 16
   const int64_t tile_elems = (int64_t)g.mb * kGradRanks * kGradCols;
-  const float* src = partial + g.part_off + (int64_t)(m * kGradRanks + r) * kGradCols + blockIdx.y * COLS + sub;
+  const float* const block = partial + g.part_off + (int64_t)m * kGradRanks * kGradCols + blockIdx.y * COLS + sub;
+  const float* const src[2] = {block + min(r, live - 1) * kGradCols, block + min(r + 16, live - 1) * kGradCols};
   f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
   const bool on[2] = {r < live, r + 16 < live};
-#pragma unroll 4
-  for (int k = 0; k < g.nunits; ++k) {
-    if (on[0]) s[0] += *reinterpret_cast<const f32x4*>(src + k * tile_elems);
-    if (on[1]) s[1] += *reinterpret_cast<const f32x4*>(src + k * tile_elems + 16 * kGradCols);
-  }
+  auto add = [&](auto n, int k) {                          // the next n partial tiles, their loads in flight together
+    constexpr int N = decltype(n)::value;
+    f32x4 v[N][2];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) v[i][h] = *reinterpret_cast<const f32x4*>(src[h] + (k + i) * tile_elems);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      s[0] += v[i][0];
+      s[1] += v[i][1];
+    }
+  };
+  int k = 0;
+  for (; k + 8 <= g.nunits; k += 8) add(std::integral_constant<int, 8>{}, k);
+  if (g.nunits & 4) { add(std::integral_constant<int, 4>{}, k);  k += 4; }
+  if (g.nunits & 2) { add(std::integral_constant<int, 2>{}, k);  k += 2; }
+  if (g.nunits & 1) add(std::integral_constant<int, 1>{}, k);
   float* const dst = static_cast<float*>(DA ? jb.dA : jb.dB);
   const bool aligned = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
   auto store4 = [&](float* d, f32x4 v) {
