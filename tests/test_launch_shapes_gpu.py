@@ -1,5 +1,5 @@
 """Launches whose workgroups depend on the size: fp32 products in tiles of 32 (few tiles) and of 64, adapter packing in
-tiles and pieces, the optimizer's 16-byte path.  Sizes at the edges of each, against the fp64 oracle."""
+tiles and pieces, chains of partial tiles, the optimizer's 16-byte path.  Sizes at the edges of each, against the fp64 oracle."""
 import pytest
 
 from paper_2602_07263_amd import workloads as wk
@@ -16,6 +16,8 @@ CASES = [
     # bf16: adapter tiles of 64 x 64 with one row or column over, pieces of 1024 chunks with one over, no chunk at all
     ("pack_one_rank", "bf16", 72, 8, [1], [3]),
     ("pack_over_the_edge", "bf16", 136, 1096, [65, 64, 0, 8, 129], [40, 1, 7, 0, 300]),
+    # dA / dB in chunks of 256 tokens: chains of 1 to 16 partial tiles (added 8, 4, 2 and 1 at a time), blocks of one rank
+    ("reduction_chains", "bf16", 64, 264, [8, 3, 33, 20, 1, 65, 16], [1, 257, 600, 1000, 1900, 2300, 3900]),
     ("pack_more_units_than_workgroups", "bf16", 1032, 520, [1] * 150 + [256], [2] * 151),
 ]
 
