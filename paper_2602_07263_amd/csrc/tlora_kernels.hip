@@ -709,59 +709,65 @@ __global__ void __launch_bounds__(256) shrink_split_kernel(const JobDev* __restr
 
 // One workgroup = 8 rows of a GEMM tile, threads along the 16-byte chunks of the rows of its K-extension operand: own
 // job's columns get scale * (sum of the splits) and everything else zeros (so the operand needs no separate fill), and
-// the hi / lo planes get the sums, with the zero pad rows after a job's last token.  Bound by latency: the tile's jobs
-// come into LDS with one load per thread (walking the job table row by row took 20 us for 8 jobs, this takes 5), and the
-// loads of the splits are independent.
-constexpr int kEmitRows = 8, kEmitJobs = 256;
+// the hi / lo planes get the sums, with the zero pad rows after a job's last token.  Bound by latency: the threads look at
+// the tile's jobs side by side and each job enters itself for its rows (walking the job table row by row took 20 us for 8
+// jobs, this takes 5, and a table of thousands of jobs, most of them idle, is read once per workgroup), and the loads of
+// the splits are independent.
+constexpr int kEmitRows = 8;
+struct EmitRow {
+  int64_t at;       // the row's first element in the planes
+  int32_t col;      // its first column in the operand
+  int32_t rpad;     // its width (0: a row past the batch)
+  int32_t pad;      // zero rows that follow it in the planes
+  float scale;
+};
 __global__ void __launch_bounds__(256) shrink_emit_kernel(const JobDev* __restrict__ jobs, const TileDev* __restrict__ tiles,
                                                           int T, const float* __restrict__ part, int64_t part_stride,
                                                           int splits, uint16_t* __restrict__ Shi, uint16_t* __restrict__ Slo,
                                                           uint16_t* __restrict__ Sx) {
   constexpr int WGS = kGemmBM / kEmitRows;
-  __shared__ JobDev tile_job[kEmitJobs];
+  __shared__ EmitRow row[kEmitRows];
   const TileDev td = tiles[blockIdx.x / WGS];
   const int r0 = (int)(blockIdx.x % WGS) * kEmitRows, t0 = (int)(blockIdx.x / WGS) * kGemmBM + r0;
-  const int njobs = td.last - td.first + 1;
-  // (a span of more jobs than fit here holds mostly jobs without tokens; those beyond are looked up in the table)
-  if ((int)threadIdx.x < min(njobs, kEmitJobs)) tile_job[threadIdx.x] = jobs[td.first + threadIdx.x];
+  if ((int)threadIdx.x < kEmitRows && t0 + (int)threadIdx.x >= T) row[threadIdx.x] = EmitRow{0, 0, 0, 0, 0.f};
+  for (int j = td.first + threadIdx.x; j <= td.last; j += 256) {     // (the jobs' segments are disjoint: one entry per row)
+    const int row0 = jobs[j].row0, row1 = jobs[j].row1;
+    const int lo = max(row0, t0), hi = min(row1, t0 + kEmitRows);
+    if (lo >= hi) continue;
+    const JobDev jb = jobs[j];
+    for (int t = lo; t < hi; ++t)
+      row[t - t0] = EmitRow{jb.soff + (int64_t)(t - row0) * jb.rpad, jb.roff - td.roff_first, jb.rpad,
+                            t == row1 - 1 ? (kGradStep - (row1 - row0) % kGradStep) % kGradStep : 0, jb.scale};
+  }
   __syncthreads();
   const int nch = td.kext / 8;
   for (int q = threadIdx.x; q < kEmitRows * nch; q += 256) {
     const int r = q / nch, col = (q - r * nch) * 8;
-    const int t = t0 + r;
+    const EmitRow e = row[r];
+    const int p = col - e.col;
     u32x4 x = {0, 0, 0, 0};
-    if (t < T) {
-      int j = 0;
-      while (j < min(njobs, kEmitJobs) - 1 && tile_job[j].row1 <= t) ++j;
-      while (j < njobs - 1 && (j < kEmitJobs ? tile_job[j].row1 : jobs[td.first + j].row1) <= t) ++j;
-      const JobDev jb = j < kEmitJobs ? tile_job[j] : jobs[td.first + j];
-      const int p = col - (jb.roff - td.roff_first);
-      if (p >= 0 && p < jb.rpad) {
-        const int64_t at = jb.soff + (int64_t)(t - jb.row0) * jb.rpad + p;
-        float v[8] = {};
+    if (p >= 0 && p < e.rpad) {
+      const int64_t at = e.at + p;
+      float v[8] = {};
 #pragma unroll 4
-        for (int k = 0; k < splits; ++k) {
-          const f32x4* const src = reinterpret_cast<const f32x4*>(part + k * part_stride + at);
-          const f32x4 a = src[0], b = src[1];
+      for (int k = 0; k < splits; ++k) {
+        const f32x4* const src = reinterpret_cast<const f32x4*>(part + k * part_stride + at);
+        const f32x4 a = src[0], b = src[1];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) { v[e] += a[e];  v[4 + e] += b[e]; }
-        }
-        float lo[8];
+        for (int i = 0; i < 4; ++i) { v[i] += a[i];  v[4 + i] += b[i]; }
+      }
+      float lo[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) lo[e] = v[e] - (float)(__bf16)v[e];
-        *reinterpret_cast<u32x4*>(Shi + at) =
-            u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-        *reinterpret_cast<u32x4*>(Slo + at) =
-            u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+      for (int i = 0; i < 8; ++i) lo[i] = v[i] - (float)(__bf16)v[i];
+      *reinterpret_cast<u32x4*>(Shi + at) =
+          u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+      *reinterpret_cast<u32x4*>(Slo + at) =
+          u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = pack_bf16x2(jb.scale * v[2 * e], jb.scale * v[2 * e + 1]);
-        if (t == jb.row1 - 1) {                       // zero pad rows up to the next multiple of kGradStep
-          const int pad = (kGradStep - (jb.row1 - jb.row0) % kGradStep) % kGradStep;
-          for (int i = 1; i <= pad; ++i) {
-            *reinterpret_cast<u32x4*>(Shi + at + (int64_t)i * jb.rpad) = u32x4{0, 0, 0, 0};
-            *reinterpret_cast<u32x4*>(Slo + at + (int64_t)i * jb.rpad) = u32x4{0, 0, 0, 0};
-          }
-        }
+      for (int i = 0; i < 4; ++i) x[i] = pack_bf16x2(e.scale * v[2 * i], e.scale * v[2 * i + 1]);
+      for (int i = 1; i <= e.pad; ++i) {            // zero pad rows up to the next multiple of kGradStep
+        *reinterpret_cast<u32x4*>(Shi + at + (int64_t)i * e.rpad) = u32x4{0, 0, 0, 0};
+        *reinterpret_cast<u32x4*>(Slo + at + (int64_t)i * e.rpad) = u32x4{0, 0, 0, 0};
       }
     }
     *reinterpret_cast<u32x4*>(Sx + td.aoff + (int64_t)(r0 + r) * td.kext + col) = x;

@@ -16,6 +16,9 @@ CASES = [
     ("two_column_blocks", 832, 1216, [256, 129, 5], [64, 255, 3]),       # 13 and 19 K-steps
     ("ragged_row_tiles", 1088, 4160, [16, 4, 100], [257, 511, 1]),
     ("many_jobs_in_a_tile", 512, 512, [2, 5] * 150, [1, 0] * 149 + [20, 9]),   # 300 jobs within one row tile
+    # a row's job is found among all those of its tile: 257 with one idle, and thousands of idle ones between two active
+    ("one_idle_of_257", 512, 512, [1] * 257, [1] * 100 + [0] + [1] * 155 + [2]),
+    ("idle_jobs_between_active", 512, 512, [8] * 2500, [5] + [0] * 2498 + [7]),
     ("no_rank_at_all", 1024, 2048, [0, 0], [40, 300]),
     # backbone GEMM: 288 tiles forward, of which the last 32 are cut (65 to 69 steps); 72 of 257 backward, all cut
     ("cut_tiles_after_whole_ones", 2048, 8192, [8, 64, 16], [1000, 3, 1100]),
