@@ -132,8 +132,13 @@ int validate(const tlora_problem_t* p) {
 // bytes that is written and read once more, so the default chunk is 32 * live_rows tokens (partial traffic
 // <= ~12 %).  If that gives too few units to fill the GPU the chunks are shortened (not below `grad_tokens`).
 // Units are issued longest first.
+constexpr int64_t kGradUnitsWanted = 1024;
+// Upper bounds over every batch in which no job has more tokens than in this one (see Reserve).
+struct GradBounds {
+  int64_t units = 0, floats = 0;
+};
 bool build_grad_units(const Plan& pl, int D, std::vector<GradUnit>& units, std::vector<GradGroup>& groups,
-                      int64_t& partial_floats) {
+                      int64_t& partial_floats, GradBounds& bounds) {
   const int ncb = (D + kGradCols - 1) / kGradCols;
   const int pb_rows = kGradMaxBlocks * kGradRanks;
   auto live_blocks = [&](const JobDev& jb, int pb) {
@@ -144,21 +149,40 @@ bool build_grad_units(const Plan& pl, int D, std::vector<GradUnit>& units, std::
     chunk = (chunk + kGradStep - 1) / kGradStep * kGradStep;
     return std::min(chunk, kGradMaxTokens);          // the kernel stages at most that many row indices per unit
   };
-  auto count_units = [&](double shrink) {
-    int64_t n = 0;
+  auto count = [&](double shrink) {
+    GradBounds n;
     for (const JobDev& jb : pl.jobs) {
       if (jb.rank == 0 || jb.row1 == jb.row0) continue;
       for (int pb = 0; pb * pb_rows < jb.rpad; ++pb) {
-        const int chunk = chunk_of(live_blocks(jb, pb), shrink);
-        n += (int64_t)((jb.row1 - jb.row0 + chunk - 1) / chunk) * ncb;
+        const int mb = live_blocks(jb, pb), chunk = chunk_of(mb, shrink);
+        const int64_t u = (int64_t)((jb.row1 - jb.row0 + chunk - 1) / chunk) * ncb;
+        n.units += u;
+        n.floats += u * mb * kGradRanks * kGradCols;
       }
     }
     return n;
   };
   double shrink = 1.0;
-  const int64_t want = 1024;
-  while (shrink > 1.0 / 64 && count_units(shrink) < want) shrink *= 0.5;
-  if (count_units(shrink) > kMaxUnits) return false;      // refused before the tables are built
+  while (shrink > 1.0 / 64 && count(shrink).units < kGradUnitsWanted) shrink *= 0.5;
+  if (count(shrink).units > kMaxUnits) return false;      // refused before the tables are built
+  {
+    // A smaller batch with shrink 1 has what this one counts at 1, or less.  With a smaller factor it has at most twice the
+    // units of the factor before (a chunk is at least half as long), which were too few, and of each tile height at most those
+    // of the shortest chunks: the tallest tiles first, that many units at most.
+    const GradBounds whole = count(1.0);
+    int64_t by_height[kGradMaxBlocks + 1] = {}, left = 2 * (kGradUnitsWanted - 1);
+    for (const JobDev& jb : pl.jobs)
+      for (int pb = 0; jb.rank > 0 && pb * pb_rows < jb.rpad; ++pb) {
+        const int mb = live_blocks(jb, pb), chunk = chunk_of(mb, 0.0);
+        by_height[mb] += (int64_t)((jb.row1 - jb.row0 + chunk - 1) / chunk) * ncb;
+      }
+    for (int mb = kGradMaxBlocks; mb > 0; --mb) {
+      const int64_t u = std::min(by_height[mb], left);
+      bounds.units += u;  bounds.floats += u * mb * kGradRanks * kGradCols;  left -= u;
+    }
+    bounds.units = std::max(whole.units, bounds.units);
+    bounds.floats = std::max(whole.floats, bounds.floats);
+  }
   partial_floats = 0;
   for (int j = 0; j < pl.J; ++j) {
     const JobDev& jb = pl.jobs[j];
@@ -207,8 +231,7 @@ int shrink_splits(const Plan& pl, int K, size_t max_bytes) {
 // at once.  So the tiles beyond the last multiple of 256 cost a whole contraction however few they are.  Cut into s they
 // cost ceil(tiles s / 256) shares, plus the fp32 sums written (at ~5 TB/s), read (at ~7 TB/s, they are still cached) and
 // added by a launch of ~2 us on top (32 tiles in 7 shares: 58 MB, 11 us of the products' 50, and 10 us).
-// The cheapest s is taken if it saves more than 15 % of the uncut time.  The sums may take 12 bytes per token and feature
-// (three times the fp32 rows of both sides), so that the workspace stays linear in T (d_in + d_out).
+// The cheapest s is taken if it saves more than 15 % of the uncut time.
 GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   GemmSplit best;
   if (K % kGemmBK || pl.T == 0) return best;
@@ -219,7 +242,6 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   const int64_t n_tail = nb % 256;
   if (n_tail == 0) return best;
   const size_t tile_bytes = sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM);
-  max_bytes = std::min(max_bytes, (size_t)12 * (size_t)pl.T * (size_t)(pl.d_in + pl.d_out));
   double best_us = 0.85 * (5.0 + 0.6 * steps);
   for (int s = 2; s <= kGemmMaxSplits && steps / s >= 4; ++s) {
     const size_t bytes = tile_bytes * (size_t)n_tail * s;
@@ -235,10 +257,44 @@ size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N) {
   return sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM) * (size_t)(nb - g.n_direct) * g.splits;
 }
 
-// Bytes of the plan tables that the forward alone needs, each table padded to 256 bytes.
-size_t forward_table_bytes(const Plan& pl) {
-  return align_up(sizeof(JobDev) * pl.jobs.size(), 256) + align_up(sizeof(TileDev) * pl.tile_jobs.size(), 256) +
-         align_up(sizeof(ShrinkUnit) * pl.shrink_units.size(), 256) + align_up(sizeof(ShrinkUnit) * pl.stream_units.size(), 256);
+// Room for the sums of cut launches: a round of 256 whole tiles (64 MiB), or less for few tokens, whose workspace has to
+// stay far from another dense matrix: 12 bytes per token and feature for the GEMMs (12 T (d_in + d_out) < 2 d_in d_out up to
+// T = d / 12; it holds 61 tokens over 4096 -> 4096 at 6 shares, 22.8 us, where 14 would take about 17), and what the most
+// shares of all shrink units take.  It grows with the tokens of each job and is the same in both plans, so both cut alike: a
+// row of Y has the same bits through tlora_fwd and tlora_fwd_noalloc.
+size_t sums_room(const Plan& pl) {
+  const size_t gemm = 12 * (size_t)pl.T * (size_t)(pl.d_in + pl.d_out);
+  const size_t shrink = sizeof(float) * (size_t)pl.s_elems * kShrinkMaxSplits;
+  return std::min<size_t>(std::max(gemm, shrink), TLORA_NOALLOC_SUM_BYTES);
+}
+
+// What the full plan reserves where a smaller batch can need more than a larger one (fewer, longer units; jobs that happen
+// to share row tiles): upper bounds over every batch of the same jobs in which none has more tokens.  So a workspace that
+// serves a batch serves every smaller one, as callers that keep one (and W^T inside it) for all their batches expect.
+struct Reserve {
+  size_t tables = 0;                                    // bytes of the table blob
+  int64_t sx_elems = 0;
+  size_t partial = 0;                                   // bytes of dA / dB partial tiles or sums of cut launches
+};
+Reserve reserve_of(const Plan& pl, const GradBounds& gB, const GradBounds& gA) {
+  Reserve r;
+  // a job's rows touch at most (T_j + 254) / 256 + 1 row tiles; one without tokens lies inside one at most
+  for (const JobDev& jb : pl.jobs) r.sx_elems += (int64_t)jb.rpad * (jb.row1 == jb.row0 ? 1 : (jb.row1 - jb.row0 + 254) / kGemmBM + 1);
+  r.sx_elems = kGemmBM * (r.sx_elems + (int64_t)pl.tile_jobs.size() * kGemmBK);
+  const int rows = g_opt.shrink_rows != 0 ? pl.shrink_rows : pl.d_in % 64 == 0 && pl.d_out % 64 == 0 ? 32 : 64;
+  int64_t stream = 0;
+  for (const JobDev& jb : pl.jobs) stream += (int64_t)((jb.row1 - jb.row0 + rows - 1) / rows) * ((jb.rpad + 127) / 128);
+  auto table = [&](size_t bytes) { r.tables += align_up(bytes, 256); };
+  table(sizeof(JobDev) * pl.jobs.size());
+  table(sizeof(TileDev) * pl.tile_jobs.size());
+  table(sizeof(ShrinkUnit) * pl.shrink_units.size());
+  table(sizeof(ShrinkUnit) * (size_t)stream);
+  table(sizeof(GradUnit) * (size_t)gB.units);
+  table(sizeof(GradGroup) * pl.gradB_groups.size());
+  table(sizeof(GradUnit) * (size_t)gA.units);
+  table(sizeof(GradGroup) * pl.gradA_groups.size());
+  r.partial = std::max(sums_room(pl), sizeof(float) * (size_t)std::max(gB.floats, gA.floats));
+  return r;
 }
 
 // fwd_only: tables and workspace of the forward alone (no transposed W, no dS, no dA / dB units or partial tiles)
@@ -288,6 +344,7 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
       pl.sx_elems += (int64_t)kGemmBM * td.kext;
     }
   }
+  GradBounds gB, gA;
   if (pl.dtype == TLORA_BF16) {
     // Rows per unit of the streaming shrink: 128 when that still gives enough workgroups for the 256 CUs, else 64, else
     // 32 (a small batch would otherwise stream its activations through a few dozen CUs).  The 32-row kernel exists for
@@ -326,8 +383,8 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
         }
     }
     if (!fwd_only) {
-      if (!build_grad_units(pl, pl.d_out, pl.gradB_units, pl.gradB_groups, pl.gradB_partial) ||
-          !build_grad_units(pl, pl.d_in, pl.gradA_units, pl.gradA_groups, pl.gradA_partial))
+      if (!build_grad_units(pl, pl.d_out, pl.gradB_units, pl.gradB_groups, pl.gradB_partial, gB) ||
+          !build_grad_units(pl, pl.d_in, pl.gradA_units, pl.gradA_groups, pl.gradA_partial, gA))
         return TLORA_EINVAL;
     }
   }
@@ -361,18 +418,20 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
   pl.tables_bytes = o;
 
   // workspace layout
+  const bool full = pl.dtype == TLORA_BF16 && !fwd_only;
+  const Reserve res = full ? reserve_of(pl, gB, gA) : Reserve();
   size_t w = 0;
   auto wplace = [&](size_t bytes) { const size_t at = w;  w = align_up(w + bytes, 256);  return at; };
   // the transposed W first: its place depends on nothing but d_in x d_out, so a copy made by one call is found
   // by later calls on other token batches (nano-batches) that share the workspace
-  if (pl.dtype == TLORA_BF16 && !fwd_only) pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
+  if (full) pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
   // so do the packed adapters, whose places depend on the feature sizes and ranks
   if (pl.dtype == TLORA_BF16) {
     pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
     pl.off_bp = wplace(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32));
     pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
   }
-  pl.off_tables = wplace(pl.tables_bytes);
+  pl.off_tables = wplace(full ? res.tables : pl.tables_bytes);
   pl.off_clock = wplace(64);
   if (pl.dtype == TLORA_F32) {
     pl.off_S = wplace(sizeof(float) * (size_t)pl.s_elems);
@@ -386,33 +445,22 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
       pl.off_dSlo = wplace(2 * (size_t)pl.s_elems);
     }
     // + 256: a 64-wide K-step over a last 32-wide slice reads (and ignores) 64 bytes past each operand row
-    pl.off_Sx = wplace(2 * (size_t)pl.sx_elems + 256);
-    if (!fwd_only) pl.off_dSx = wplace(2 * (size_t)pl.sx_elems + 256);
-    // Sums of split launches.  In the full plan they share the block of the dA / dB partial tiles (the launches follow one
-    // another).  The forward-only plan has them behind the static scratch, so that a split never makes a problem too large
-    // for it.  Both plans cut the forward's contractions alike (a problem that the scratch holds is cut as the room behind
-    // it allows everywhere): a row of Y has the same bits through both entry points.  That room holds one round of 256
-    // whole tiles; while it was what the scratch itself left (2 to 14 MiB), 128 tiles over K = 12288 (1900 tokens, 4096
-    // features) ran uncut: 269 us against 176 for two halves and their sum.
-    const size_t fwd_base = align_up(forward_table_bytes(pl), 256) + 256 + 2 * align_up(2 * (size_t)pl.s_elems, 256) +
-                            align_up(2 * (size_t)pl.sx_elems + 256, 256) +
-                            align_up(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in), 256) +
-                            align_up(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32), 256);
-    const size_t fwd_total = fwd_base + align_up(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32), 256);
-    const size_t room = fwd_total <= TLORA_NOALLOC_SCRATCH_BYTES ? TLORA_NOALLOC_SUM_BYTES : fwd_only ? 0 : SIZE_MAX;
+    pl.off_Sx = wplace(2 * (size_t)(full ? res.sx_elems : pl.sx_elems) + 256);
+    if (!fwd_only) pl.off_dSx = wplace(2 * (size_t)res.sx_elems + 256);
+    // Sums of cut launches: in the full plan in the block of the dA / dB partial tiles (the launches follow one another); in
+    // the forward-only plan behind the static scratch, so that a cut never makes a problem too large for it.  While they
+    // had what the scratch itself left (2 to 14 MiB), 128 tiles over K = 12288 (1900 tokens, 4096 features) ran uncut:
+    // 269 us against 176 for two halves and their sum.
+    const size_t room = sums_room(pl);
     pl.shrink_splits_x = shrink_splits(pl, pl.d_in, room);
-    if (pl.shrink_splits_x > 1) pl.partial_bytes = sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_x;
     pl.gemm_split_fwd = gemm_split(pl, pl.d_in, pl.d_out, room);
-    pl.partial_bytes = std::max(pl.partial_bytes, gemm_split_bytes(pl, pl.gemm_split_fwd, pl.d_out));
     if (fwd_only) {
+      pl.partial_bytes = room;
       pl.off_partial = TLORA_NOALLOC_SCRATCH_BYTES;      // (beyond pl.total)
     } else {
-      pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, SIZE_MAX);
-      if (pl.shrink_splits_dy > 1)
-        pl.partial_bytes = std::max(pl.partial_bytes, sizeof(float) * (size_t)pl.s_elems * pl.shrink_splits_dy);
-      pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, SIZE_MAX);
-      pl.partial_bytes = std::max(pl.partial_bytes, gemm_split_bytes(pl, pl.gemm_split_bwd, pl.d_in));
-      pl.partial_bytes = std::max(pl.partial_bytes, sizeof(float) * (size_t)std::max(pl.gradB_partial, pl.gradA_partial));
+      pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, room);
+      pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, room);
+      pl.partial_bytes = res.partial;
       pl.off_partial = wplace(pl.partial_bytes);
     }
   }

@@ -133,6 +133,28 @@ def test_workspace_grows_with_rank_work_not_with_dense_weights():
     assert tlora.tlora_workspace_bytes(b) < 2.1 * tlora.tlora_workspace_bytes(a)
 
 
+def test_workspace_of_a_batch_serves_every_smaller_one():
+    """One workspace (with W^T inside it) is kept for all batches of a job table: what a batch needs must not fall while no
+    job's tokens fall, and no nano-batch may need more than the whole batch."""
+    rng = np.random.default_rng(11)
+    for _ in range(40):
+        J = int(rng.integers(1, 7))
+        ranks = [int(r) for r in rng.choice([0, 1, 3, 8, 16, 32, 64, 128, 256], J)]
+        d_in, d_out = int(rng.choice([72, 512, 1024, 4096, 5120])), int(rng.choice([136, 512, 1024, 4096, 12288]))
+        tokens = [int(t) for t in rng.integers(0, 40, J)]
+        dtype = tlora.TLORA_BF16 if rng.random() < 0.9 else tlora.TLORA_F32
+        last = 0
+        for step in range(30):
+            prob, _keep = _problem(ranks, tokens, d_in=d_in, d_out=d_out, dtype=dtype)
+            need = tlora.tlora_workspace_bytes(prob)
+            assert need >= last, (ranks, tokens, d_in, d_out, need, last)
+            last = need
+            if step % 10 == 9:
+                for n in (2, 3, 7):
+                    assert tlora.tlora_nano_workspace_bytes(prob, n, 37) <= need
+            tokens[int(rng.integers(0, J))] += int(rng.choice([1, 37, 256, 1000, 3000]))
+
+
 def test_header_is_plain_c():
     """The boundary is a C ABI: the header must compile as C99 and as C++ with no other includes."""
     import os
