@@ -719,9 +719,10 @@ int f32_place(const Plan& pl, std::vector<uint8_t>& blob, std::vector<F32Unit> u
 }
 
 // static_scratch: the "workspace" is the library's static scratch array and only the forward will run.
+// shared_sums: the workspace ends where the sums begin (a block's projections have one place for them).
 // Gives the (cached) plan and this call's job table: the plan's with the caller's scales and adapter pointers.
 int common_checks(const tlora_problem_t* p, const PlanEntry** entry, std::vector<JobDev>& hjobs, void* ws, size_t ws_bytes,
-                  bool static_scratch = false) {
+                  bool static_scratch = false, bool shared_sums = false) {
   int rc = get_plan(p, static_scratch, entry);
   if (rc != TLORA_OK) return rc;
   const Plan& pl = (*entry)->pl;
@@ -730,7 +731,8 @@ int common_checks(const tlora_problem_t* p, const PlanEntry** entry, std::vector
     if (pl.jobs[j].rank > 0 && (!p->A[j] || !p->B[j])) return TLORA_ENULL;
   if (misaligned16(p->X) || misaligned16(p->W)) return TLORA_EALIGN;
   if (static_scratch && ws_bytes < pl.total) return TLORA_ESCRATCH;
-  if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) || ws_bytes < pl.total) return TLORA_EWORKSPACE;
+  const size_t need = shared_sums ? pl.off_partial : pl.total;
+  if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) || ws_bytes < need) return TLORA_EWORKSPACE;
   hjobs = pl.jobs;
   for (int j = 0; j < pl.J; ++j) {
     hjobs[j].scale = p->scales[j];
@@ -766,11 +768,13 @@ namespace {
 // its output rows there; in_index = the same list when X is the batch in its own order, fetched through the list
 // inside the kernels' loads (null: X already lies in job-sorted order).
 // packed: this workspace already holds the packed copies of the same adapters (a nano-batch after the first).
+// shared_sums: where the sums of cut launches go instead of the workspace's own last part.
 int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes, void* hip_stream, bool no_alloc,
-             const int32_t* out_index = nullptr, const int32_t* in_index = nullptr, bool packed = false) {
+             const int32_t* out_index = nullptr, const int32_t* in_index = nullptr, bool packed = false,
+             uint8_t* shared_sums = nullptr) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
-  int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, no_alloc);
+  int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, no_alloc, shared_sums != nullptr);
   if (rc != TLORA_OK) return rc;
   const Plan& pl = entry->pl;
   if (pl.T > 0 && !Y) return TLORA_ENULL;
@@ -830,6 +834,7 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   uint16_t* Sx = reinterpret_cast<uint16_t*>(ws + pl.off_Sx);
   uint16_t* atp = reinterpret_cast<uint16_t*>(ws + pl.off_atp);
   uint16_t* bp = reinterpret_cast<uint16_t*>(ws + pl.off_bp);
+  float* sums = reinterpret_cast<float*>(shared_sums ? shared_sums : ws + pl.off_partial);
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
   if (!packed) {
     Timed t(TLORA_K_PACK, st, timed);
@@ -839,14 +844,14 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
     Timed t(TLORA_K_SHRINK, st, timed);
     run_shrink(pl, tb, jobs, tiles, static_cast<const uint16_t*>(p->X), pl.d_in, atp, true,
                reinterpret_cast<uint16_t*>(ws + pl.off_Shi), reinterpret_cast<uint16_t*>(ws + pl.off_Slo), Sx, in_index,
-               reinterpret_cast<float*>(ws + pl.off_partial), st);
+               sums, st);
   }
   if (timed) launch_zero_fill(ws + pl.off_clock, 16, st);
   Timed tg(TLORA_K_GEMM_FWD, st, timed);
   launch_seg_gemm(true, tiles, static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), Sx, bp,
                   pl.r_total, static_cast<uint16_t*>(Y), out_index, in_index, pl.T, pl.d_in, pl.d_out,
                   timed ? (g_clock_slot[0] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock)) : nullptr,
-                  pl.gemm_split_fwd, reinterpret_cast<float*>(ws + pl.off_partial), st);
+                  pl.gemm_split_fwd, sums, st);
   return launches_ok(__LINE__);
 }
 }  // namespace
@@ -872,13 +877,13 @@ int tlora_fwd_noalloc(const tlora_problem_t* p, void* Y, void* hip_stream) {
 namespace tlora {
 namespace {
 // The backward's launch sequence (out_index / in_index as in fwd_impl: dX rows are scattered; X and dY are fetched
-// through the list).
+// through the list; packed and shared_sums as there, the latter also for the partial tiles of dA / dB).
 int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags,
              void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index,
-             bool packed = false) {
+             bool packed = false, uint8_t* shared_sums = nullptr) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
-  int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes);
+  int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, false, shared_sums != nullptr);
   if (rc != TLORA_OK) return rc;
   const Plan& pl = entry->pl;
   if (pl.T > 0 && !dY) return TLORA_ENULL;
@@ -964,7 +969,7 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
   uint16_t* atp = reinterpret_cast<uint16_t*>(ws + pl.off_atp);
   uint16_t* ap = reinterpret_cast<uint16_t*>(ws + pl.off_ap);
   uint16_t* bp = reinterpret_cast<uint16_t*>(ws + pl.off_bp);
-  float* partial = reinterpret_cast<float*>(ws + pl.off_partial);
+  float* partial = reinterpret_cast<float*>(shared_sums ? shared_sums : ws + pl.off_partial);
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
   const uint16_t* Xb = static_cast<const uint16_t*>(p->X);
   const uint16_t* dYb = static_cast<const uint16_t*>(dY);
@@ -1216,12 +1221,35 @@ int tlora_adamw_step(const tlora_adamw_tensor_t* tensors, int32_t count, int32_t
 
 // ---- MLP block: RMSNorm -> gate / up (fused multi-LoRA) -> silu(G) * U -> down (fused multi-LoRA) -> + X -------
 namespace {
+// One projection of a block.  The projections run one after the other on one stream, so the block has one place for their
+// sums and partial tiles (the last part of a workspace); everything else of a workspace is the projection's own.
+struct LayerBytes {
+  size_t own = 0, sums = 0;
+};
+bool layer_bytes(const tlora_problem_t* p, LayerBytes& b) {
+  std::lock_guard<std::recursive_mutex> lk(g_mu);
+  const PlanEntry* e = nullptr;
+  if (get_plan(p, false, &e) != TLORA_OK) return false;
+  const bool bf16 = e->pl.dtype == TLORA_BF16;
+  b.own = bf16 ? e->pl.off_partial : e->pl.total;
+  b.sums = bf16 ? e->pl.partial_bytes : 0;
+  return true;
+}
+int layer_fwd(const tlora_problem_t* p, void* Y, uint8_t* ws, size_t own, uint8_t* sums, void* hip_stream) {
+  return fwd_impl(p, Y, ws, own, hip_stream, false, nullptr, nullptr, false, p->dtype == TLORA_BF16 ? sums : nullptr);
+}
+int layer_bwd(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags, uint8_t* ws,
+              size_t own, uint8_t* sums, void* hip_stream) {
+  return bwd_impl(p, dY, dX, dA, dB, flags, ws, own, hip_stream, nullptr, nullptr, false,
+                  p->dtype == TLORA_BF16 ? sums : nullptr);
+}
+
 struct MlpLayout {
   tlora_problem_t gate, up, down;      // the three fused layers (X pointers filled in below)
   size_t elt = 2;
   int64_t T = 0;
   size_t off_xn = 0, off_rstd = 0, off_g = 0, off_u = 0, off_z = 0, off_d = 0, off_dz = 0, off_dg = 0, off_du = 0,
-         off_dxa = 0, off_dxb = 0, off_ws_gate = 0, off_ws_up = 0, off_ws_down = 0;
+         off_dxa = 0, off_dxb = 0, off_ws_gate = 0, off_ws_up = 0, off_ws_down = 0, off_sums = 0;
   size_t ws_gate = 0, ws_up = 0, ws_down = 0, total = 0;
 };
 int mlp_layout(const tlora_mlp_t* p, MlpLayout& L) {
@@ -1253,10 +1281,11 @@ int mlp_layout(const tlora_mlp_t* p, MlpLayout& L) {
   L.off_xn = place(td);  L.off_rstd = place(sizeof(float) * (size_t)L.T);
   L.off_g = place(tf);  L.off_u = place(tf);  L.off_z = place(tf);  L.off_d = place(td);
   L.off_dz = place(tf);  L.off_dg = place(tf);  L.off_du = place(tf);  L.off_dxa = place(td);  L.off_dxb = place(td);
-  L.ws_gate = tlora_workspace_bytes(&L.gate);  L.ws_up = tlora_workspace_bytes(&L.up);
-  L.ws_down = tlora_workspace_bytes(&L.down);
-  if (!L.ws_gate || !L.ws_up || !L.ws_down) return TLORA_EINVAL;
+  LayerBytes gate, up, down;
+  if (!layer_bytes(&L.gate, gate) || !layer_bytes(&L.up, up) || !layer_bytes(&L.down, down)) return TLORA_EINVAL;
+  L.ws_gate = gate.own;  L.ws_up = up.own;  L.ws_down = down.own;
   L.off_ws_gate = place(L.ws_gate);  L.off_ws_up = place(L.ws_up);  L.off_ws_down = place(L.ws_down);
+  L.off_sums = place(std::max({gate.sums, up.sums, down.sums}));
   L.total = w;
   return TLORA_OK;
 }
@@ -1287,16 +1316,16 @@ int tlora_mlp_fwd(const tlora_mlp_t* p, void* Out, void* workspace, size_t ws_by
                        reinterpret_cast<float*>(ws + L.off_rstd), st);
   }
   L.gate.X = L.up.X = ws + L.off_xn;
-  rc = tlora_fwd(&L.gate, ws + L.off_g, ws + L.off_ws_gate, L.ws_gate, hip_stream);
+  rc = layer_fwd(&L.gate, ws + L.off_g, ws + L.off_ws_gate, L.ws_gate, ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
-  rc = tlora_fwd(&L.up, ws + L.off_u, ws + L.off_ws_up, L.ws_up, hip_stream);
+  rc = layer_fwd(&L.up, ws + L.off_u, ws + L.off_ws_up, L.ws_up, ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   {
     Timed t(TLORA_K_GLUE, st);
     launch_swiglu_fwd(bf, ws + L.off_g, ws + L.off_u, ws + L.off_z, L.T * p->d_ff, st);
   }
   L.down.X = ws + L.off_z;
-  rc = tlora_fwd(&L.down, ws + L.off_d, ws + L.off_ws_down, L.ws_down, hip_stream);
+  rc = layer_fwd(&L.down, ws + L.off_d, ws + L.off_ws_down, L.ws_down, ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   {
     Timed t(TLORA_K_GLUE, st);
@@ -1326,15 +1355,15 @@ int tlora_mlp_bwd(const tlora_mlp_t* p, const void* dOut, void* dX, void* const*
   const int lf = flags | TLORA_BWD_REUSE_S;
   L.gate.X = L.up.X = ws + L.off_xn;
   L.down.X = ws + L.off_z;
-  rc = tlora_bwd(&L.down, dOut, ws + L.off_dz, dA_down, dB_down, lf, ws + L.off_ws_down, L.ws_down, hip_stream);
+  rc = layer_bwd(&L.down, dOut, ws + L.off_dz, dA_down, dB_down, lf, ws + L.off_ws_down, L.ws_down, ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   if (L.T > 0) {
     Timed t(TLORA_K_GLUE, st);
     launch_swiglu_bwd(bf, ws + L.off_g, ws + L.off_u, ws + L.off_dz, ws + L.off_dg, ws + L.off_du, L.T * p->d_ff, st);
   }
-  rc = tlora_bwd(&L.gate, ws + L.off_dg, ws + L.off_dxa, dA_gate, dB_gate, lf, ws + L.off_ws_gate, L.ws_gate, hip_stream);
+  rc = layer_bwd(&L.gate, ws + L.off_dg, ws + L.off_dxa, dA_gate, dB_gate, lf, ws + L.off_ws_gate, L.ws_gate, ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
-  rc = tlora_bwd(&L.up, ws + L.off_du, ws + L.off_dxb, dA_up, dB_up, lf, ws + L.off_ws_up, L.ws_up, hip_stream);
+  rc = layer_bwd(&L.up, ws + L.off_du, ws + L.off_dxb, dA_up, dB_up, lf, ws + L.off_ws_up, L.ws_up, ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   if (L.T > 0) {
     Timed t(TLORA_K_GLUE, st);
@@ -1499,7 +1528,7 @@ struct AttnLayout {
   AttnPlan A;
   int64_t T = 0;
   size_t off_attn = 0, off_xn = 0, off_rstd = 0, off_q = 0, off_k = 0, off_v = 0, off_o = 0, off_lse = 0, off_d = 0,
-         off_do = 0, off_dq = 0, off_dk = 0, off_dv = 0, off_dxa = 0, off_dxb = 0, off_dxc = 0, off_ws[4] = {0, 0, 0, 0};
+         off_do = 0, off_dq = 0, off_dk = 0, off_dv = 0, off_dxa = 0, off_dxb = 0, off_dxc = 0, off_ws[4] = {0, 0, 0, 0}, off_sums = 0;
   size_t ws_l[4] = {0, 0, 0, 0}, total = 0;
 };
 int attn_layout(const tlora_attn_t* p, bool want_tables, AttnLayout& L) {
@@ -1542,11 +1571,15 @@ int attn_layout(const tlora_attn_t* p, bool want_tables, AttnLayout& L) {
   L.off_d = place(td);
   L.off_do = place(tq);  L.off_dq = place(tq);  L.off_dk = place(tk);  L.off_dv = place(tk);
   L.off_dxa = place(td);  L.off_dxb = place(td);  L.off_dxc = place(td);
+  size_t sums = 0;
   for (int i = 0; i < 4; ++i) {
-    L.ws_l[i] = tlora_workspace_bytes(ls[i]);
-    if (!L.ws_l[i]) return TLORA_EINVAL;
-    L.off_ws[i] = place(L.ws_l[i]);
+    LayerBytes b;
+    if (!layer_bytes(ls[i], b)) return TLORA_EINVAL;
+    L.ws_l[i] = b.own;
+    L.off_ws[i] = place(b.own);
+    sums = std::max(sums, b.sums);
   }
+  L.off_sums = place(sums);
   L.total = w;
   return TLORA_OK;
 }
@@ -1578,9 +1611,9 @@ int tlora_attn_fwd(const tlora_attn_t* p, void* Out, void* workspace, size_t ws_
                        reinterpret_cast<float*>(ws + L.off_rstd), st);
   }
   L.q.X = L.k.X = L.v.X = ws + L.off_xn;
-  rc = tlora_fwd(&L.q, ws + L.off_q, ws + L.off_ws[0], L.ws_l[0], hip_stream);
-  if (rc == TLORA_OK) rc = tlora_fwd(&L.k, ws + L.off_k, ws + L.off_ws[1], L.ws_l[1], hip_stream);
-  if (rc == TLORA_OK) rc = tlora_fwd(&L.v, ws + L.off_v, ws + L.off_ws[2], L.ws_l[2], hip_stream);
+  rc = layer_fwd(&L.q, ws + L.off_q, ws + L.off_ws[0], L.ws_l[0], ws + L.off_sums, hip_stream);
+  if (rc == TLORA_OK) rc = layer_fwd(&L.k, ws + L.off_k, ws + L.off_ws[1], L.ws_l[1], ws + L.off_sums, hip_stream);
+  if (rc == TLORA_OK) rc = layer_fwd(&L.v, ws + L.off_v, ws + L.off_ws[2], L.ws_l[2], ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   const int32_t* pos = reinterpret_cast<const int32_t*>(aw + L.A.off_pos);
   {
@@ -1598,7 +1631,7 @@ int tlora_attn_fwd(const tlora_attn_t* p, void* Out, void* workspace, size_t ws_
                     reinterpret_cast<float*>(ws + L.off_lse), p->n_heads, p->n_kv_heads, st);
   }
   L.o.X = ws + L.off_o;
-  rc = tlora_fwd(&L.o, ws + L.off_d, ws + L.off_ws[3], L.ws_l[3], hip_stream);
+  rc = layer_fwd(&L.o, ws + L.off_d, ws + L.off_ws[3], L.ws_l[3], ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   {
     Timed t(TLORA_K_GLUE, st);
@@ -1628,7 +1661,7 @@ int tlora_attn_bwd(const tlora_attn_t* p, const void* dOut, void* dX, void* cons
   const int lf = flags | TLORA_BWD_REUSE_S;            // every projection's workspace still holds its S_j
   L.q.X = L.k.X = L.v.X = ws + L.off_xn;
   L.o.X = ws + L.off_o;
-  rc = tlora_bwd(&L.o, dOut, ws + L.off_do, dA[3], dB[3], lf, ws + L.off_ws[3], L.ws_l[3], hip_stream);
+  rc = layer_bwd(&L.o, dOut, ws + L.off_do, dA[3], dB[3], lf, ws + L.off_ws[3], L.ws_l[3], ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   if (L.T > 0) {
     const int32_t* pos = reinterpret_cast<const int32_t*>(aw + L.A.off_pos);   // tables uploaded by tlora_attn_fwd
@@ -1649,9 +1682,9 @@ int tlora_attn_bwd(const tlora_attn_t* p, const void* dOut, void* dX, void* cons
       launch_rope(reinterpret_cast<uint16_t*>(ws + L.off_dk), pos, tab, L.T, p->n_kv_heads, true, st);
     }
   }
-  rc = tlora_bwd(&L.q, ws + L.off_dq, ws + L.off_dxa, dA[0], dB[0], lf, ws + L.off_ws[0], L.ws_l[0], hip_stream);
-  if (rc == TLORA_OK) rc = tlora_bwd(&L.k, ws + L.off_dk, ws + L.off_dxb, dA[1], dB[1], lf, ws + L.off_ws[1], L.ws_l[1], hip_stream);
-  if (rc == TLORA_OK) rc = tlora_bwd(&L.v, ws + L.off_dv, ws + L.off_dxc, dA[2], dB[2], lf, ws + L.off_ws[2], L.ws_l[2], hip_stream);
+  rc = layer_bwd(&L.q, ws + L.off_dq, ws + L.off_dxa, dA[0], dB[0], lf, ws + L.off_ws[0], L.ws_l[0], ws + L.off_sums, hip_stream);
+  if (rc == TLORA_OK) rc = layer_bwd(&L.k, ws + L.off_dk, ws + L.off_dxb, dA[1], dB[1], lf, ws + L.off_ws[1], L.ws_l[1], ws + L.off_sums, hip_stream);
+  if (rc == TLORA_OK) rc = layer_bwd(&L.v, ws + L.off_dv, ws + L.off_dxc, dA[2], dB[2], lf, ws + L.off_ws[2], L.ws_l[2], ws + L.off_sums, hip_stream);
   if (rc != TLORA_OK) return rc;
   if (L.T > 0) {
     Timed t(TLORA_K_GLUE, st);

@@ -155,6 +155,22 @@ def test_workspace_of_a_batch_serves_every_smaller_one():
             tokens[int(rng.integers(0, J))] += int(rng.choice([1, 37, 256, 1000, 3000]))
 
 
+def test_a_block_has_one_place_for_its_projections_sums():
+    """The projections of an MLP block run one after the other: their partial tiles and sums (64 MiB at this size) are
+    reserved once, so the block needs less than its activations and three whole workspaces by two such places."""
+    T, d, f = 600, 4096, 12288
+    ranks, off = (ctypes.c_int32 * 2)(16, 8), (ctypes.c_int64 * 3)(0, 500, T)
+    scales, ptrs = (ctypes.c_float * 2)(1.0, 1.0), (ctypes.c_void_p * 2)(0x3000, 0x3000)
+    mlp = tlora.tlora_mlp_t(tlora.TLORA_BF16, 2, d, f, ranks, off, scales, 0x1000, 0x2000, 1e-5, 0x5000, 0x6000, 0x7000,
+                            *([ptrs] * 6))
+    block = tlora.lib().tlora_mlp_workspace_bytes(ctypes.byref(mlp))
+    wide, _k = _problem([16, 8], [500, 100], d_in=d, d_out=f)
+    down, _l = _problem([16, 8], [500, 100], d_in=f, d_out=d)
+    layers = 2 * tlora.tlora_workspace_bytes(wide) + tlora.tlora_workspace_bytes(down)
+    activations = T * (4 * 2 * d + 6 * 2 * f + 4)
+    assert activations < block <= activations + layers - 2 * (64 << 20) + 16 * 256
+
+
 def test_header_is_plain_c():
     """The boundary is a C ABI: the header must compile as C99 and as C++ with no other includes."""
     import os
