@@ -226,12 +226,22 @@ int shrink_splits(const Plan& pl, int K, size_t max_bytes) {
   return s < 2 ? 1 : (int)s;
 }
 
-// Which tiles of the GEMM over [T, K] x [K, N] to cut along K.  A workgroup needs ~5 us outside its K-loop and ~0.6 us per
-// 32-wide step, whether 1 or 256 of them run (16 tiles over K = 4096 took 80 us, 32 tiles over 12288 took 188 us); 256 run
-// at once.  So the tiles beyond the last multiple of 256 cost a whole contraction however few they are.  Cut into s they
-// cost ceil(tiles s / 256) shares, plus the fp32 sums written (at ~5 TB/s), read (at ~7 TB/s, they are still cached) and
-// added by a launch of ~2 us on top (32 tiles in 7 shares: 58 MB, 11 us of the products' 50, and 10 us).
-// The cheapest s is taken if it saves more than 15 % of the uncut time.
+// Microseconds of `units` workgroups of the GEMM, `steps` 32-wide K-steps each, 256 at a time: ~6.5 outside the K-loop, and
+// per step 0.43 for one workgroup and 0.64 when all CUs run (16 tiles over K = 1024, 4096, 12288: 26, 69, 183 with the
+// launch's ~5; 240 tiles: 33, 92, 253).
+double gemm_us(int64_t units, int steps) {
+  double us = 0.0;
+  for (; units > 0; units -= 256) us += 6.5 + steps * (0.432 + 0.205 * (double)std::min<int64_t>(units, 256) / 256.0);
+  return us;
+}
+// Which tiles of the GEMM over [T, K] x [K, N] to cut along K, and into how many shares.  256 tiles run at once, so those
+// beyond the last multiple of 256 cost a whole contraction however few they are.  Cut, they cost their shares, and for the
+// fp32 sums a launch (4 us) and a microsecond per 4.7 MB written, read and added (32 tiles over K = 4096: 69 us, in 5 shares
+// 38; 64 over 12288: 189, in 4 shares 95).  The kernel that can cut is slower in its whole tiles too (K = 2048, 24 rounds of
+// 256: 1199 -> 1232 to 1243 us; K = 4096: 2251 -> 2265; over 12288 it was not slower): 2 us per round are charged, and the
+// cheapest number of shares is taken if that saves 3 % of the uncut tail.  Over 5 contractions, 0 to 24 rounds and 16 to 240
+// tiles beyond them this is never slower than no cut, and on average 0.25 % from the best choice (without a charge per
+// round: up to 3.5 % slower).
 GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   GemmSplit best;
   if (K % kGemmBK || pl.T == 0) return best;
@@ -242,12 +252,15 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   const int64_t n_tail = nb % 256;
   if (n_tail == 0) return best;
   const size_t tile_bytes = sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM);
-  double best_us = 0.85 * (5.0 + 0.6 * steps);
+  const double uncut = gemm_us(n_tail, steps), rounds = 2.0 * (double)(nb / 256);
+  double best_gain = 0.03 * uncut;
   for (int s = 2; s <= kGemmMaxSplits && steps / s >= 4; ++s) {
+    const int share = ((steps + s - 1) / s + 1) & ~1;
+    if ((steps + share - 1) / share != s) continue;           // even shares of this size are fewer: tried under their number
     const size_t bytes = tile_bytes * (size_t)n_tail * s;
     if (bytes > max_bytes) break;
-    const double us = (double)((n_tail * s + 255) / 256) * (5.0 + 0.6 * ((steps + s - 1) / s)) + (double)bytes / 5.2e6 + (double)bytes / 7e6 + 2.0;
-    if (us < best_us) { best_us = us;  best.splits = s;  best.n_direct = (int32_t)(nb - n_tail); }
+    const double gain = uncut - rounds - gemm_us(n_tail * s, share) - 4.0 - (double)bytes / 4.7e6;
+    if (gain > best_gain) { best_gain = gain;  best.splits = s;  best.share = share;  best.n_direct = (int32_t)(nb - n_tail); }
   }
   return best;
 }
@@ -2072,6 +2085,12 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       for (int d = 0; d < 2; ++d) {
         const GemmSplit& g = d ? pl.gemm_split_bwd : pl.gemm_split_fwd;
         if (g.splits < 1 || g.splits > kGemmMaxSplits || g.n_direct < 0 || g.n_direct % 256) return 67;
+        if (g.splits > 1) {                              // even shares; all of them have work in the longest tile
+          int kext = 0;
+          for (const TileDev& td : pl.tile_jobs) kext = std::max(kext, td.kext);
+          const int64_t steps = ((d ? pl.d_out : pl.d_in) + kext) / kGemmBK;
+          if (g.share < 2 || g.share % 2 || (int64_t)g.share * g.splits < steps || (int64_t)g.share * (g.splits - 1) >= steps) return 69;
+        }
         if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
       }
       if (!fwd_only) w.push_back({pl.off_partial, pl.partial_bytes});

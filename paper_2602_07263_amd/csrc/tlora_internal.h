@@ -44,10 +44,12 @@ struct TileDev {
   int64_t aoff;
 };
 
-// Which tiles of a backbone GEMM are cut along the contraction: all from n_direct (a multiple of 256) on, into `splits`.
+// Which tiles of a backbone GEMM are cut along the contraction: all from n_direct (a multiple of 256) on, into `splits` shares
+// of `share` K-steps (even; the last share of the longest tile may be shorter but is not empty).
 struct GemmSplit {
   int32_t n_direct = 0;
   int32_t splits = 1;
+  int32_t share = 0;
 };
 
 // Work unit of the shrink kernels (S_j = X_j.A_j and dS_j = dY_j.B_j^T): a block of token rows of
