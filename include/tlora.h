@@ -412,6 +412,12 @@ int tlora_plan_dump(const tlora_problem_t* p, int32_t* rpad, int64_t* soff, int3
  * first failed check in *failed_check (may be NULL; 0 when nothing failed).  Used by the CPU tests on random problems. */
 int tlora_plan_check(const tlora_problem_t* p, int32_t fwd_only, int32_t* failed_check);
 
+/* How the plan of `p` (of the forward alone if fwd_only != 0) cuts contractions into shares whose fp32 sums are added by a
+ * launch of their own (host only): cuts[0], cuts[1] = shares of S_j = X_j.A_j and of dS_j = dY_j.B_j^T; cuts[2], cuts[3] =
+ * whole tiles of the forward's backbone product and shares of each of the others; cuts[4], cuts[5] = the same of dX.  One
+ * share means not cut (every tile is whole). */
+int tlora_plan_cuts(const tlora_problem_t* p, int32_t fwd_only, int32_t* cuts);
+
 /* Tuning knobs (process-wide, for experiments and for the tiling-independence tests).
  *   "shrink_rows"  : token rows per work unit of the shrink kernels        (0 = chosen per problem (default) | 32 | 64 | 128)
  *   "shrink_stages": LDS stages of the streaming shrink kernel             (4 | 8)

@@ -2117,6 +2117,23 @@ int tlora_plan_check(const tlora_problem_t* p, int32_t fwd_only, int32_t* failed
   return bad ? TLORA_EINVAL : TLORA_OK;
 }
 
+int tlora_plan_cuts(const tlora_problem_t* p, int32_t fwd_only, int32_t* cuts) {
+  std::lock_guard<std::recursive_mutex> lk(g_mu);
+  if (!cuts) return TLORA_ENULL;
+  Plan pl;
+  const int rc = build_plan(p, pl, fwd_only != 0);
+  if (rc != TLORA_OK) return rc;
+  cuts[0] = pl.shrink_splits_x;
+  cuts[1] = pl.shrink_splits_dy;
+  for (int d = 0; d < 2; ++d) {
+    const GemmSplit& g = d ? pl.gemm_split_bwd : pl.gemm_split_fwd;
+    const int N = d ? pl.d_in : pl.d_out;
+    cuts[2 + 2 * d] = g.splits > 1 ? g.n_direct : (int32_t)(pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN));
+    cuts[3 + 2 * d] = g.splits;
+  }
+  return TLORA_OK;
+}
+
 int tlora_profile(int enable) {
   std::lock_guard<std::recursive_mutex> lk(g_mu);
   const int rc = prof_drain();

@@ -99,7 +99,7 @@ EXPORTS = ["tlora_workspace_bytes", "tlora_fwd", "tlora_fwd_noalloc", "tlora_bwd
            "tlora_indexed_workspace_bytes", "tlora_fwd_indexed", "tlora_bwd_indexed",
            "tlora_aimd_init", "tlora_aimd_update",
            "tlora_nano_split", "tlora_nano_workspace_bytes", "tlora_fwd_nano", "tlora_bwd_nano",
-           "tlora_plan_dump", "tlora_plan_check", "tlora_set_option",
+           "tlora_plan_dump", "tlora_plan_check", "tlora_plan_cuts", "tlora_set_option",
            "tlora_profile", "tlora_profile_read", "tlora_profile_clock", "tlora_strerror", "tlora_last_hip_error",
            "tlora_version"]
 KERNEL_CLASSES = ["pack", "shrink", "gemm_fwd", "gemm_bwd", "rank_grad", "grad_reduce", "f32", "w_transpose", "optimizer", "glue", "permute",
@@ -211,6 +211,8 @@ def lib() -> ctypes.CDLL:
                                   ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int64)]
     L.tlora_plan_check.restype = ctypes.c_int
     L.tlora_plan_check.argtypes = [P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+    L.tlora_plan_cuts.restype = ctypes.c_int
+    L.tlora_plan_cuts.argtypes = [P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
     L.tlora_set_option.restype = ctypes.c_int
     L.tlora_set_option.argtypes = [ctypes.c_char_p, ctypes.c_int64]
     L.tlora_profile.restype = ctypes.c_int
@@ -427,6 +429,14 @@ def tlora_plan_check(prob: tlora_problem_t, fwd_only: bool = False):
     bad = ctypes.c_int32(0)
     rc = lib().tlora_plan_check(ctypes.byref(prob), 1 if fwd_only else 0, ctypes.byref(bad))
     return int(rc), int(bad.value)
+
+
+def tlora_plan_cuts(prob: tlora_problem_t, fwd_only: bool = False):
+    """How the plan cuts contractions: shares of the shrinks over X and over dY, then (whole tiles, shares of the others) of
+    the forward's and of dX's backbone product."""
+    cuts = (ctypes.c_int32 * 6)()
+    _check(lib().tlora_plan_cuts(ctypes.byref(prob), 1 if fwd_only else 0, cuts), "tlora_plan_cuts")
+    return {"shrink_x": cuts[0], "shrink_dy": cuts[1], "fwd": (cuts[2], cuts[3]), "bwd": (cuts[4], cuts[5])}
 
 
 # ---- torch-backed convenience holder ---------------------------------------------------------------------

@@ -322,6 +322,42 @@ def test_planner_self_check_on_random_problems():
         tlora.tlora_set_option("grad_tokens", 256)
 
 
+def test_both_plans_cut_the_forward_alike():
+    """A row of Y has the same bits through tlora_fwd and tlora_fwd_noalloc: the full and the forward-only plan cut alike."""
+    rng = np.random.default_rng(31)
+    cut = 0
+    for i in range(400):
+        J = int(rng.integers(1, 9))
+        tokens = [int(t) for t in np.exp(rng.uniform(0, 8.5, J))]
+        ranks = [int(r) for r in rng.choice([0, 1, 8, 16, 64, 130, 256], J)]
+        prob, _keep = _problem(ranks, tokens, d_in=int(rng.choice([512, 2048, 4096, 5120, 12288])),
+                               d_out=int(rng.choice([256, 1000, 4096, 8192])))
+        full, fwd = tlora.tlora_plan_cuts(prob), tlora.tlora_plan_cuts(prob, True)
+        assert full["fwd"] == fwd["fwd"] and full["shrink_x"] == fwd["shrink_x"], (ranks, tokens, full, fwd)
+        assert tlora.tlora_plan_check(prob) == (0, 0) and tlora.tlora_plan_check(prob, True) == (0, 0)
+        cut += full["fwd"][1] > 1
+    assert 50 < cut < 350                                                # both kinds are there
+
+
+def test_problems_of_the_cut_tests_are_cut():
+    """What the GPU tests of cut launches name must be in the plans of their problems, whatever the cost model becomes."""
+    from tests import test_split_launches_gpu as sl, test_zz_no_alloc as na
+    cuts = lambda c: tlora.tlora_plan_cuts(_problem(c[3], c[4], d_in=c[1], d_out=c[2])[0])
+    split = {c[0]: cuts(c) for c in sl.CASES}
+    for name in ("fewest_steps", "one_token", "tiny_jobs_in_a_tile", "two_column_blocks", "ragged_row_tiles",
+                 "many_jobs_in_a_tile", "idle_jobs_between_active"):
+        assert split[name]["shrink_x"] > 1 and split[name]["shrink_dy"] > 1, (name, split[name])
+    whole, shares = split["cut_tiles_after_whole_ones"]["fwd"]
+    assert whole == 256 and shares > 1
+    assert split["cut_tiles_after_whole_ones"]["bwd"][0] == 0 and split["cut_tiles_after_whole_ones"]["bwd"][1] > 1
+    assert split["one_step_too_many"]["fwd"][1] > 1 and split["k_tail_is_not_cut"]["fwd"][1] == 1
+    assert cuts(("cut_indexed", *sl.CUT_INDEXED))["fwd"][1] > 1
+    for c in na.CUT:
+        assert cuts(c)["fwd"][1] > 1, (c[0], cuts(c))
+    assert cuts(na.CUT[0])["fwd"][0] == 0 and cuts(na.CUT[2])["fwd"][0] == 256
+    assert cuts(na.FIRST)["fwd"][1] == 1 and cuts(na.SECOND)["fwd"][1] == 1
+
+
 @pytest.mark.parametrize("cfg", [0, 1, 2, 3, 4])
 def test_planner_self_check_on_the_five_configurations(cfg):
     wl = wk.config(cfg)

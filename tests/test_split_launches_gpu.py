@@ -26,6 +26,8 @@ CASES = [
     ("k_tail_is_not_cut", 2056, 512, [8, 5], [100, 29]),
 ]
 
+CUT_INDEXED = (2048, 1024, [8, 40], [700, 301])
+
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_split_launches_meet_the_oracle(case):
@@ -41,7 +43,7 @@ def test_row_list_calls_are_cut_like_the_plain_ones():
     """Same plan, rows fetched and stored through a list: the same bits as the plain call on the sorted rows."""
     import torch
     from paper_2602_07263_amd import tlora
-    p = wk.generate(wk.custom("cut_indexed", "bf16", 2048, 1024, [8, 40], [700, 301], [2.0, 1.0]), seed=52)
+    p = wk.generate(wk.custom("cut_indexed", "bf16", *CUT_INDEXED, [2.0, 1.0]), seed=52)
     lp = tlora.LayerProblem.from_numpy(p)
     T = lp.X.shape[0]
     dY = torch.from_numpy(p.dY).to(device="cuda", dtype=torch.bfloat16)

@@ -2,8 +2,9 @@
 is part of the library) against tlora_fwd on a caller-provided workspace: same kernels, so Y must agree bit for
 bit -- on two calls in a row, the second on a smaller problem (the array keeps the first call's contents), in
 both dtypes; the result is also held to the oracle's tolerance.  A problem beyond the array's size is refused
-before anything is launched.  Last: the call recorded into a captured stream (what the entry point exists for) and
-replayed three times, with eager calls on another problem through the same array in between."""
+before anything is launched.  Problems whose backbone product is cut along the contraction leave fp32 sums behind the
+array; their calls, too, must give tlora_fwd's bits.  Last: the call recorded into a captured stream (what the entry point
+exists for) and replayed three times, with eager calls on another problem through the same array in between."""
 import numpy as np
 import pytest
 
@@ -15,6 +16,14 @@ pytestmark = pytest.mark.gpu
 # name, d_in, d_out, ranks, tokens, scales: several 256-row tiles with ragged tails, then a smaller problem
 FIRST = ("noalloc_first", 512, 768, [3, 16, 40, 0, 130], [300, 700, 129, 40, 260], [2.0, 0.5, 1.0, 2.0, 1.5])
 SECOND = ("noalloc_second", 256, 384, [8, 5], [70, 33], [2.0, 3.0])
+
+# backbone products that are cut (tests/test_abi_cpu.py holds the planner to that): a serving step, all tiles in shares; whole
+# tiles and then cut ones, the last row tile nearly empty; shares whose number the steps do not divide
+CUT = [
+    ("noalloc_serving", 4096, 1024, [8, 16, 3], [1, 4, 7], [2.0, 0.5, 1.0]),
+    ("noalloc_all_cut", 2048, 1024, [8, 40], [700, 301], [2.0, 1.0]),
+    ("noalloc_whole_then_cut", 2048, 8192, [8, 3], [2000, 53], [2.0, 1.0]),
+]
 
 
 def _both_ways(case, dtype, seed):
@@ -48,6 +57,13 @@ def test_two_calls_in_a_row_second_smaller(dtype):
     _both_ways(FIRST, dtype, seed=23)      # and back up: stale contents of the smaller call in between
 
 
+@pytest.mark.parametrize("case", CUT, ids=[c[0] for c in CUT])
+def test_cut_products_have_the_bits_of_the_workspace_call(case):
+    _both_ways(case, "bf16", seed=24)
+    _both_ways(SECOND, "bf16", seed=25)    # an uncut problem between two cut ones
+    _both_ways(case, "bf16", seed=26)
+
+
 def test_problem_beyond_the_scratch_is_refused():
     import torch
     from paper_2602_07263_amd import tlora
@@ -67,11 +83,13 @@ def test_problem_beyond_the_scratch_is_refused():
     assert bool((Y == 7.0).all()), "a refused call must not launch anything"
 
 
-def test_noalloc_forward_replays_from_a_captured_stream():
+@pytest.mark.parametrize("first,second", [(FIRST, SECOND), (CUT[0], CUT[1]), (CUT[2], CUT[0])],
+                         ids=["uncut", "cut", "whole_then_cut"])
+def test_noalloc_forward_replays_from_a_captured_stream(first, second):
     import torch
     from paper_2602_07263_amd import tlora
     mk = lambda case, seed: tlora.LayerProblem.from_numpy(wk.generate(wk.custom(case[0], "bf16", *case[1:]), seed=seed))
-    lp, other = mk(FIRST, 31), mk(SECOND, 32)
+    lp, other = mk(first, 31), mk(second, 32)
     Y_ref, _, _, _ = lp.new_outputs()
     Y_other, _, _, _ = other.new_outputs()
     lp.fwd(Y_ref)
