@@ -239,8 +239,8 @@ double gemm_us(int64_t units, int steps) {
 // fp32 sums a launch (4 us) and a microsecond per 4.7 MB written, read and added (32 tiles over K = 4096: 69 us, in 5 shares
 // 38; 64 over 12288: 189, in 4 shares 95).  The kernel that can cut is slower in its whole tiles too (K = 2048, 24 rounds of
 // 256: 1199 -> 1232 to 1243 us; K = 4096: 2251 -> 2265; over 12288 it was not slower): 2 us per round are charged, and the
-// cheapest number of shares is taken if that saves 3 % of the uncut tail.  Over 5 contractions, 0 to 24 rounds and 16 to 240
-// tiles beyond them this is never slower than no cut, and on average 0.25 % from the best choice (without a charge per
+// cheapest number of shares is taken if that saves 2 us and 3 % of the uncut tail.  Over 5 contractions, 0 to 24 rounds and 16 to 240
+// tiles beyond them this is never slower than no cut, and on average 0.28 % from the best choice (without a charge per
 // round: up to 3.5 % slower).
 GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   GemmSplit best;
@@ -253,7 +253,7 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   if (n_tail == 0) return best;
   const size_t tile_bytes = sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM);
   const double uncut = gemm_us(n_tail, steps), rounds = 2.0 * (double)(nb / 256);
-  double best_gain = 0.03 * uncut;
+  double best_gain = std::max(2.0, 0.03 * uncut);
   for (int s = 2; s <= kGemmMaxSplits && steps / s >= 4; ++s) {
     const int share = ((steps + s - 1) / s + 1) & ~1;
     if ((steps + share - 1) / share != s) continue;           // even shares of this size are fewer: tried under their number
