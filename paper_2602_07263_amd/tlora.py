@@ -499,8 +499,7 @@ class LayerProblem:
                   (TLORA_BWD_REUSE_S if reuse_S else 0) | flags, self.ws.data_ptr(), self.ws_bytes, self._stream())
 
     def _nano_ws(self, n_nano: int, granule: int) -> None:
-        """Grow the workspace to what this partition needs (its tiles start at other rows than the whole batch's, so a
-        tile may hold more jobs and its K-extension operand may be wider)."""
+        """Grow the workspace if this partition needs more (the whole batch's covers every partition of it)."""
         need = tlora_nano_workspace_bytes(self.prob, n_nano, granule)
         if need == 0:
             raise TloraError("tlora_nano_workspace_bytes: invalid problem or partition")

@@ -75,7 +75,7 @@ def test_accumulate_flag_adds_to_the_existing_gradients(dtype):
 
 
 def test_reuse_of_the_transposed_weight():
-    """A second backward with TLORA_BWD_REUSE_WT on another batch that shares workspace and W finds the copy."""
+    """A second backward with TLORA_BWD_REUSE_WT on the same workspace and W finds the copy."""
     import torch
     from paper_2602_07263_amd import tlora
     p = wk.generate(wk.custom("wt", "bf16", 256, 320, [8, 24], [200, 300]), seed=2)
@@ -88,6 +88,29 @@ def test_reuse_of_the_transposed_weight():
     torch.cuda.synchronize()
     _assert_ok(pu.compare(p, Y.float().cpu().numpy(), dX.float().cpu().numpy(), [a.cpu().numpy() for a in dA],
                           [b.cpu().numpy() for b in dB]), "reuse Wt")
+
+
+def test_transposed_weight_of_a_large_batch_serves_a_smaller_one():
+    """The same jobs' next batch is smaller and takes the workspace, and W^T inside it, of the large one."""
+    import torch
+    from paper_2602_07263_amd import tlora
+    large = wk.generate(wk.custom("wt_large", "bf16", 1024, 2048, [8, 24], [6000, 2192]), seed=3)
+    small = wk.generate(wk.custom("wt_small", "bf16", 1024, 2048, [8, 24], [500, 401]), seed=4)
+    lp = tlora.LayerProblem.from_numpy(large)
+    lq = tlora.LayerProblem.from_numpy(small)
+    lq = tlora.LayerProblem("bf16", 1024, 2048, small.ranks, small.offsets, small.scales, lq.X, lp.W, lp.A, lp.B)
+    lq.ws, lq.ws_bytes = lp.ws, lp.ws_bytes
+    up = lambda a: torch.from_numpy(a).to(device="cuda", dtype=torch.bfloat16)
+    out = lp.new_outputs()
+    lp.fwd(out[0]); lp.bwd(up(large.dY), *out[1:], reuse_S=True)
+    Y, dX, dA, dB = lq.new_outputs()
+    for t in (Y, dX, *dA, *dB):
+        t.fill_(float("nan"))
+    lq.fwd(Y); lq.bwd(up(small.dY), dX, dA, dB, reuse_S=True, flags=tlora.TLORA_BWD_REUSE_WT)
+    torch.cuda.synchronize()
+    small.W, small.A, small.B = large.W, large.A, large.B
+    _assert_ok(pu.compare(small, Y.float().cpu().numpy(), dX.float().cpu().numpy(), [a.cpu().numpy() for a in dA],
+                          [b.cpu().numpy() for b in dB]), "W^T of a larger batch")
 
 
 def test_controller_in_the_loop():
