@@ -40,8 +40,13 @@
  *     tlora_bwd validate everything before their first launch: on an argument error nothing has been launched.
  *     The composite entry points (nano-batched, token-indexed, MLP / attention block, decoder layer) check their
  *     own arguments first but run their sub-calls one after the other: if a later sub-call fails (a HIP error,
- *     an invalid per-projection pointer) the kernels of the earlier ones are already queued.  The results are independent of the internal tiling and are bit-identical from
- *     run to run (no floating-point atomics).
+ *     an invalid per-projection pointer) the kernels of the earlier ones are already queued.
+ *   - Results are bit-identical from run to run (every sum in a fixed order, no floating-point atomics).  The order follows
+ *     from the shapes of the call: how tokens are dealt to the work units of dA_j / dB_j, and, where a call has too
+ *     few tiles to fill the chip, which contractions of S_j, dS_j, Y and dX are cut into shares (tlora_plan_cuts).  So a
+ *     token's row of Y or dX may differ by the rounding of its fp32 sums -- at most the last bit of a bf16 result, save where
+ *     terms cancel -- between a call of its job alone, a fused call and a nano-batch, and between whole and cut tiles
+ *     of one call.  Values of other jobs never enter a job's results.
  */
 #ifndef TLORA_H
 #define TLORA_H
@@ -108,8 +113,8 @@ int tlora_fwd(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_byte
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as tlora_fwd
  * (bit-identical Y), but the forward's intermediates (plan tables, S_j, the packed adapters) live in a device array
  * of TLORA_NOALLOC_SCRATCH_BYTES that is part of the library image (TLORA_NOALLOC_SUM_BYTES behind it hold the fp32 sums
- * of launches whose contraction is cut); every GPU the library runs on holds it until the process ends.  The call allocates nothing -- no hipMalloc / hipFree / hipHostMalloc, no event or stream creation,
- * no allocating library routine -- and records no copy or memset: the plan tables travel as kernel arguments and
+ * of launches whose contraction is cut); every GPU the library runs on holds it until the process ends.  The call
+ * allocates nothing -- no hipMalloc / hipFree / hipHostMalloc, no event or stream creation, no allocating library routine -- and records no copy or memset: the plan tables travel as kernel arguments and
  * everything that must start at zero is cleared by store kernels on `hip_stream`.
  *   Limits: the forward-only workspace of the problem (about 4 sum_j T_j r_j + 2 * 256 ceil(T / 256) * (padded
  *   ranks met per 256-row tile) + 6 (sum_j r_j + 32) (d_in + d_out) bytes + tables) must fit in
@@ -175,7 +180,8 @@ int tlora_nano_split(const tlora_problem_t* p, int32_t n_nano, int64_t granule, 
 size_t tlora_nano_workspace_bytes(const tlora_problem_t* p, int32_t n_nano, int64_t granule);
 /* tlora_fwd / tlora_bwd over the n_nano nano-batches, one after the other on `hip_stream`, sharing one
  * workspace.  Same arguments and results as the plain calls (the results do not depend on n_nano beyond
- * floating-point summation order: dA_j, dB_j are accumulated over the nano-batches in order).  Flags of
+ * floating-point summation order: dA_j, dB_j are accumulated over the nano-batches in order, and smaller batches may
+ * have their contractions cut, see above).  Flags of
  * tlora_bwd_nano: TLORA_BWD_ACCUMULATE, TLORA_BWD_REUSE_WT (S of a nano-batch is not kept, so no REUSE_S). */
 int tlora_fwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, void* Y, void* workspace, size_t ws_bytes,
                    void* hip_stream);
@@ -458,7 +464,7 @@ typedef enum {
   TLORA_K_GLUE = 9,         /* RMSNorm, gated SiLU, residual of the MLP block   */
   TLORA_K_PERMUTE = 10,     /* row gather / scatter of the token-indexed calls  */
   TLORA_K_ATTN_FWD = 11,    /* causal attention, forward                        */
-  TLORA_K_ATTN_BWD = 12,    /* causal attention, backward (3 kernels)           */
+  TLORA_K_ATTN_BWD = 12,    /* causal attention, backward (2 kernels)           */
   TLORA_K_ROPE = 13,        /* rotary embedding                                 */
   TLORA_K_COUNT = 14
 } tlora_kernel_class_t;

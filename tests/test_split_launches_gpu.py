@@ -65,3 +65,33 @@ def test_row_list_calls_are_cut_like_the_plain_ones():
     torch.cuda.synchronize()
     assert torch.equal(Y2[at], Y) and torch.equal(dX2[at], dX)
     assert all(torch.equal(a, b) for a, b in zip(dA2 + dB2, dA + dB))
+
+
+def test_a_job_that_is_cut_otherwise_alone_agrees_to_a_rounding():
+    """Whether and how a contraction is cut follows from the whole call's shape, so a job's rows may differ between a fused call
+    and one of its own by the order of fp32 sums: one unit in the last place of a bf16 value, or, where terms cancel, the
+    error of a sum of 2048 products of size |x w| ~ 0.013 (worst order 2048^2 2^-24 0.013 = 3e-3, typically 1e-5)."""
+    import torch
+    from paper_2602_07263_amd import tlora
+    p = wk.generate(wk.custom("fused", "bf16", 2048, 2048, [8, 40, 16], [300, 700, 1900], [2.0, 1.0, 0.5]), seed=53)
+    lp = tlora.LayerProblem.from_numpy(p)
+    dY = torch.from_numpy(p.dY).to(device="cuda", dtype=torch.bfloat16)
+    Y, dX, dA, dB = lp.new_outputs()
+    lp.fwd(Y)
+    lp.bwd(dY, dX, dA, dB, reuse_S=True)
+    fused = tlora.tlora_plan_cuts(lp.prob)
+    for j in range(2):
+        lo, hi = lp.offsets[j], lp.offsets[j + 1]
+        one = lp.job_slice(j)
+        alone = tlora.tlora_plan_cuts(one.prob)
+        assert alone["fwd"][1] > 1 and alone["fwd"] != fused["fwd"] and alone["shrink_x"] != fused["shrink_x"]
+        Y1, dX1, dA1, dB1 = one.new_outputs()
+        one.fwd(Y1)
+        one.bwd(dY[lo:hi], dX1, dA1, dB1, reuse_S=True)
+        torch.cuda.synchronize()
+        for a, b in ((Y1, Y[lo:hi]), (dX1, dX[lo:hi])):
+            a, b = a.float(), b.float()
+            assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-4).all())
+            assert float((a != b).float().mean()) < 0.02                 # few sums lie that close to a rounding edge
+        for a, b in zip(dA1 + dB1, [dA[j], dB[j]]):
+            assert bool(((a - b).abs() <= 1e-4 * (1.0 + b.abs())).all())
