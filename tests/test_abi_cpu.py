@@ -350,6 +350,7 @@ def test_problems_of_the_cut_tests_are_cut():
     whole, shares = split["cut_tiles_after_whole_ones"]["fwd"]
     assert whole == 256 and shares > 1
     assert split["cut_tiles_after_whole_ones"]["bwd"][0] == 0 and split["cut_tiles_after_whole_ones"]["bwd"][1] > 1
+    assert split["short_tile_beside_a_long_one"]["fwd"][1] > 2
     assert split["one_step_too_many"]["fwd"][1] > 1 and split["k_tail_is_not_cut"]["fwd"][1] == 1
     assert cuts(("cut_indexed", *sl.CUT_INDEXED))["fwd"][1] > 1
     for c in na.CUT:
