@@ -177,7 +177,10 @@ __device__ __forceinline__ int acc_row(int i, int hl) { return 8 * (i >> 2) + 4 
 // c = log2(e) / sqrt(128) the probabilities are exp2(c s - c m), one multiply-add and one exponential per score.
 // The running maximum only rescales the output accumulators when it moved in some lane of the wave, and only
 // tiles on the diagonal are masked.  lse = c m + log2(sum)  (base-2 domain).  Two workgroups share a CU so that
-// one's softmax overlaps the other's matrix products.
+// one's softmax overlaps the other's matrix products.  The two score blocks of a tile alternate, their LDS reads issued six
+// ahead (one block after the other, as the compiler orders it / alternating, same bits: 4096 tokens in one sequence,
+// 8 / 1 heads 84.4 / 79.6 us; 8192, 32 / 8 heads 705 / 690; 16 sequences of 2048 657 / 651; 512 271 / 267; of 777, 16 / 4
+// heads, and of 100 no difference beyond the spread).
 // ---------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_fwd_kernel(const AttnTile* __restrict__ tiles, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,

@@ -245,8 +245,8 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
   }
 }
 
-// Workgroups per job: one per tile and piece of the largest job, but no more than 8192 in all (those of smaller jobs find
-// nothing and end; beyond that the loop over the job's units is cheaper than the empty workgroups).
+// Workgroups per job: one per tile and piece of the largest job, but no more than 8192 in all, or 64 per job from 128 jobs on
+// (those of smaller jobs find nothing and end; beyond that the loop over the job's units is cheaper than the empty workgroups).
 void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total,
                           uint16_t* atp, uint16_t* a_all, uint16_t* b_all, hipStream_t st) {
   if (max_rpad == 0) return;
