@@ -270,15 +270,28 @@ size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N) {
   return sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM) * (size_t)(nb - g.n_direct) * g.splits;
 }
 
-// Room for the sums of cut launches: a round of 256 whole tiles (64 MiB), or less for few tokens, whose workspace has to
-// stay far from another dense matrix: 12 bytes per token and feature for the GEMMs (12 T (d_in + d_out) < 2 d_in d_out up to
-// T = d / 12; it holds 61 tokens over 4096 -> 4096 at 6 shares, 22.8 us, where 14 would take about 17), and what the most
-// shares of all shrink units take.  It grows with the tokens of each job and is the same in both plans, so both cut alike: a
-// row of Y has the same bits through tlora_fwd and tlora_fwd_noalloc.
+// Room for the sums of cut launches in the full plan: two rounds of 256 whole tiles (128 MiB: 144 tiles over K = 15072 in
+// three shares take 23 us off a dX of 400 tiles), or less for few tokens, whose workspace has to stay far from another dense
+// matrix: 12 bytes per token and feature for the GEMMs (12 T (d_in + d_out) < 2 d_in d_out up to T = d / 12; it holds 61 tokens
+// over 4096 -> 4096 at 6 shares, 22.8 us, where 14 would take about 17), and what the most shares of all shrink units take.
+// It grows with the tokens of each job.
 size_t sums_room(const Plan& pl) {
   const size_t gemm = 12 * (size_t)pl.T * (size_t)(pl.d_in + pl.d_out);
   const size_t shrink = sizeof(float) * (size_t)pl.s_elems * kShrinkMaxSplits;
-  return std::min<size_t>(std::max(gemm, shrink), TLORA_NOALLOC_SUM_BYTES);
+  return std::min<size_t>(std::max(gemm, shrink), 2 * (size_t)TLORA_NOALLOC_SUM_BYTES);
+}
+// Bytes of the forward-only plan's workspace (the self-check holds the layout to this sum).
+size_t forward_bytes(const Plan& pl) {
+  auto a = [](size_t bytes) { return align_up(bytes, 256); };
+  return a(sizeof(JobDev) * pl.jobs.size()) + a(sizeof(TileDev) * pl.tile_jobs.size()) +
+         a(sizeof(ShrinkUnit) * pl.shrink_units.size()) + a(sizeof(ShrinkUnit) * pl.stream_units.size()) + a(64) +
+         2 * a(2 * (size_t)pl.s_elems) + a(2 * (size_t)pl.sx_elems + 256) + a(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)) +
+         (a(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)) + a(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32)));
+}
+// The forward's part of that room, the same in both plans, so that both cut alike and a row of Y has the same bits through
+// tlora_fwd and tlora_fwd_noalloc: what lies behind the static scratch where the scratch holds the problem.
+size_t forward_sums_room(const Plan& pl) {
+  return std::min<size_t>(sums_room(pl), forward_bytes(pl) <= TLORA_NOALLOC_SCRATCH_BYTES ? TLORA_NOALLOC_SUM_BYTES : SIZE_MAX);
 }
 
 // What the full plan reserves where a smaller batch can need more than a larger one (fewer, longer units; jobs that happen
@@ -464,15 +477,15 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     // the forward-only plan behind the static scratch, so that a cut never makes a problem too large for it.  While they
     // had what the scratch itself left (2 to 14 MiB), 128 tiles over K = 12288 (1900 tokens, 4096 features) ran uncut:
     // 269 us against 176 for two halves and their sum.
-    const size_t room = sums_room(pl);
+    const size_t room = forward_sums_room(pl);
     pl.shrink_splits_x = shrink_splits(pl, pl.d_in, room);
     pl.gemm_split_fwd = gemm_split(pl, pl.d_in, pl.d_out, room);
     if (fwd_only) {
-      pl.partial_bytes = room;
+      pl.partial_bytes = room;                           // (more than there is only in a plan that does not fit)
       pl.off_partial = TLORA_NOALLOC_SCRATCH_BYTES;      // (beyond pl.total)
     } else {
-      pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, room);
-      pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, room);
+      pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, sums_room(pl));
+      pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, sums_room(pl));
       pl.partial_bytes = res.partial;
       pl.off_partial = wplace(pl.partial_bytes);
     }
@@ -2094,7 +2107,9 @@ static int check_plan(const Plan& pl, bool fwd_only) {
         if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
       }
       if (!fwd_only) w.push_back({pl.off_partial, pl.partial_bytes});
-      else if (pl.partial_bytes > TLORA_NOALLOC_SUM_BYTES || pl.off_partial < TLORA_NOALLOC_SCRATCH_BYTES) return 66;
+      else if (pl.total != forward_bytes(pl)) return 70;
+      else if (pl.off_partial < TLORA_NOALLOC_SCRATCH_BYTES ||
+               (pl.total <= TLORA_NOALLOC_SCRATCH_BYTES && pl.partial_bytes > TLORA_NOALLOC_SUM_BYTES)) return 66;
     }
     size_t end = 0;
     for (auto& r : w) {
