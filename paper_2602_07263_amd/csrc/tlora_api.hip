@@ -237,11 +237,14 @@ double gemm_us(int64_t units, int steps) {
 // Which tiles of the GEMM over [T, K] x [K, N] to cut along K, and into how many shares.  256 tiles run at once, so those
 // beyond the last multiple of 256 cost a whole contraction however few they are.  Cut, they cost their shares, and for the
 // fp32 sums a launch (4 us) and a microsecond per 4.7 MB written, read and added (32 tiles over K = 4096: 69 us, in 5 shares
-// 38; 64 over 12288: 189, in 4 shares 95).  The kernel that can cut is slower in its whole tiles too (K = 2048, 24 rounds of
-// 256: 1199 -> 1232 to 1243 us; K = 4096: 2251 -> 2265; over 12288 it was not slower): 2 us per round are charged, and the
-// cheapest number of shares is taken if that saves 2 us and 3 % of the uncut tail.  Over 5 contractions, 0 to 24 rounds and 16 to 240
-// tiles beyond them this is never slower than no cut, and on average 0.28 % from the best choice (without a charge per
-// round: up to 3.5 % slower).
+// 38; 64 over 12288: 189, in 4 shares 95).  After many rounds the workgroups are out of step and a tail hides among them,
+// while the kernel that can cut is slower per tile (23 scalars in vector registers); over short contractions cuts then lose
+// (2048 -> 2048, 30 rounds and 80 tiles: 1539 us, cut 1594; 4096 -> 4096, 24 and 128: 2270, 2299), over long ones they never do
+// (17408 -> 5120, 30 and 80: 12461, 12083).  So rounds beyond the sixth are charged 5 us each, less with the length, nothing
+// from 6144 on, and the cheapest number of shares is taken if that saves 2 us and 3 % of the uncut tail.  Over 581 sizes
+// (K = 1024 ... 17408, 0 to 30 rounds, 12 to 240 tiles beyond them) that is 0.22 % from the best choice on average and slower
+// than no cut at three, by at most 1.5 %; without the charge at thirteen, by up to 3.5 %; a charge of 2 us for every round loses
+// nothing but leaves 0.49 %.
 GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   GemmSplit best;
   if (K % kGemmBK || pl.T == 0) return best;
@@ -252,15 +255,16 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   const int64_t n_tail = nb % 256;
   if (n_tail == 0) return best;
   const size_t tile_bytes = sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM);
-  const double uncut = gemm_us(n_tail, steps), rounds = 2.0 * (double)(nb / 256);
+  const double uncut = gemm_us(n_tail, steps);
+  const double rounds = (double)std::max<int64_t>(0, nb / 256 - 6) * std::max(0.0, 5.0 * (1.0 - steps / 192.0));
   double best_gain = std::max(2.0, 0.03 * uncut);
   for (int s = 2; s <= kGemmMaxSplits && steps / s >= 4; ++s) {
-    const int share = ((steps + s - 1) / s + 1) & ~1;
+    const int share = gemm_share(steps, s);
     if ((steps + share - 1) / share != s) continue;           // even shares of this size are fewer: tried under their number
     const size_t bytes = tile_bytes * (size_t)n_tail * s;
     if (bytes > max_bytes) break;
     const double gain = uncut - rounds - gemm_us(n_tail * s, share) - 4.0 - (double)bytes / 4.7e6;
-    if (gain > best_gain) { best_gain = gain;  best.splits = s;  best.share = share;  best.n_direct = (int32_t)(nb - n_tail); }
+    if (gain > best_gain) { best_gain = gain;  best.splits = s;  best.n_direct = (int32_t)(nb - n_tail); }
   }
   return best;
 }
@@ -2098,11 +2102,11 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       for (int d = 0; d < 2; ++d) {
         const GemmSplit& g = d ? pl.gemm_split_bwd : pl.gemm_split_fwd;
         if (g.splits < 1 || g.splits > kGemmMaxSplits || g.n_direct < 0 || g.n_direct % 256) return 67;
-        if (g.splits > 1) {                              // even shares; all of them have work in the longest tile
+        if (g.splits > 1) {                              // all shares have work in the longest tile
           int kext = 0;
           for (const TileDev& td : pl.tile_jobs) kext = std::max(kext, td.kext);
-          const int64_t steps = ((d ? pl.d_out : pl.d_in) + kext) / kGemmBK;
-          if (g.share < 2 || g.share % 2 || (int64_t)g.share * g.splits < steps || (int64_t)g.share * (g.splits - 1) >= steps) return 69;
+          const int steps = ((d ? pl.d_out : pl.d_in) + kext) / kGemmBK;
+          if (gemm_share(steps, g.splits) * (g.splits - 1) >= steps) return 69;
         }
         if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
       }

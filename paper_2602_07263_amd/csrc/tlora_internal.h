@@ -45,12 +45,14 @@ struct TileDev {
 };
 
 // Which tiles of a backbone GEMM are cut along the contraction: all from n_direct (a multiple of 256) on, into `splits` shares
-// of `share` K-steps (even; the last share of the longest tile may be shorter but is not empty).
+// of their K-steps.
 struct GemmSplit {
   int32_t n_direct = 0;
   int32_t splits = 1;
-  int32_t share = 0;
 };
+// K-steps of a share of a tile of `steps` steps, the last share apart, which has what is left: an even number, which the GEMM's
+// ring of tile slots asks of a first step.
+__host__ __device__ inline int gemm_share(int steps, int splits) { return ((steps + splits - 1) / splits + 1) & ~1; }
 
 // Work unit of the shrink kernels (S_j = X_j.A_j and dS_j = dY_j.B_j^T): a block of token rows of
 // one job times a block of kShrinkCols padded rank columns.

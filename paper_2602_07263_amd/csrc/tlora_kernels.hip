@@ -848,9 +848,9 @@ struct GemmParams {
   unsigned long long* clk;  // optional: every 64th workgroup adds {cycles, 100 MHz ticks} of its K-loop (pre-zeroed)
   const int32_t* out_index; // optional: output row of tile row t (scatter); null = t itself
   const int32_t* in_index;  // INDEXED instantiations: batch row that holds activation row t (gather inside the loads)
-  // SPLIT instantiations: tiles n_direct .. of the walk are cut into `splits` ranges of `share` K-steps whose fp32 sums go to
+  // SPLIT instantiations: tiles n_direct .. of the walk are cut into `splits` K-ranges whose fp32 sums go to
   // part[split][tile - n_direct][part_rows][256]
-  int n_direct, splits, share, part_rows;
+  int n_direct, splits, part_rows;
   float* part;
 };
 
@@ -942,8 +942,9 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   // steps of this workgroup: all of them, or a share (an even number: the ring's phase assumes an even first step)
   int step0 = 0, step1 = ntot;
   if (cut) {
-    step0 = min(split * P.share, ntot);
-    step1 = min(step0 + P.share, ntot);
+    const int share = gemm_share(ntot, P.splits);
+    step0 = min(split * share, ntot);
+    step1 = min(step0 + share, ntot);
   }
   const bool clocked = P.clk != nullptr && (blockIdx.x & 63) == 0;   // a sample of workgroups across the grid
   unsigned long long cyc0 = 0, tick0 = 0;
@@ -1271,7 +1272,7 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
   const int nb = P.tiles_m * P.tiles_n;
   if (nb == 0) return;
   const bool tail = K % kGemmBK != 0;
-  P.n_direct = split.n_direct;  P.splits = split.splits;  P.share = split.share;  P.part_rows = std::min(T, kGemmBM);  P.part = part;
+  P.n_direct = split.n_direct;  P.splits = split.splits;  P.part_rows = std::min(T, kGemmBM);  P.part = part;
   if (split.splits > 1 && w_is_kn && !tail) {
     const int n_tail = nb - P.n_direct;
     const dim3 grid(P.n_direct + n_tail * P.splits);

@@ -23,7 +23,7 @@ CASES = [
     # backbone GEMM: 288 tiles forward, of which the last 32 are cut (65 to 69 steps); 72 of 257 backward, all cut
     ("cut_tiles_after_whole_ones", 2048, 8192, [8, 64, 16], [1000, 3, 1100]),
     ("one_step_too_many", 2080, 264, [8], [255]),                        # 66 steps: eleven shares of 6, ragged columns
-    ("short_tile_beside_a_long_one", 512, 512, [8] * 251, [1] * 250 + [40]),   # 79 and 17 steps in shares of 12: some are empty
+    ("short_tile_beside_a_long_one", 512, 512, [8] * 251, [1] * 250 + [40]),   # 79 and 17 steps in seven shares: two are empty
     ("k_tail_is_not_cut", 2056, 512, [8, 5], [100, 29]),
 ]
 
