@@ -133,9 +133,9 @@ int tlora_fwd_noalloc(const tlora_problem_t* p, void* Y, void* hip_stream);
                                  problem; X, A_j, B_j have not changed since */
 #define TLORA_BWD_ACCUMULATE 4 /* dA_j += ..., dB_j += ... instead of overwriting them (gradient accumulation over the
                                  nano-batches or micro-batches of one step); dX is always overwritten */
-#define TLORA_BWD_REUSE_WT 2  /* the workspace still holds the transposed copy of W that an earlier tlora_bwd with
-                                 the same W, d_in, d_out, job table and workspace made (W is frozen: one copy
-                                 serves every later step) */
+#define TLORA_BWD_REUSE_WT 2  /* an earlier tlora_bwd with the same W, d_in, d_out, job table and workspace has computed dX
+                                 (W is frozen: the transposed copy that a large batch makes serves every later step; if
+                                 the calls before did without one, the first call with this flag makes it) */
 
 /* Backward (derivatives of L = sum(dY * Y); Sec. 3.2 fixes only that each job's backward is
  * independent and that W gets no gradient).
@@ -427,8 +427,9 @@ int tlora_plan_cuts(const tlora_problem_t* p, int32_t fwd_only, int32_t* cuts);
 /* Tuning knobs (process-wide, for experiments and for the tiling-independence tests).
  *   "shrink_rows"  : token rows per work unit of the shrink kernels        (0 = chosen per problem (default) | 32 | 64 | 128)
  *   "shrink_stages": LDS stages of the streaming shrink kernel             (4 | 8)
- *   "dx_transposed_w": 1 (default): dX runs against a transposed copy of W kept in the workspace | 0: against W
- *                    as it lies in memory (no copy, slower weight stream)
+ *   "dx_transposed_w": 1 (default): dX of a large batch, or with TLORA_BWD_REUSE_WT, runs against a transposed copy of W
+ *                    kept in the workspace, of a small one against W as it lies in memory (no copy, slower weight
+ *                    stream) | 0: always against W as it lies.  The results are the same.
  *   "grad_tokens"  : minimum tokens per work unit of the dA / dB kernels   (multiple of 64, at most 4096)
  *   "indexed_direct": 1 (default): bf16 token-indexed calls read the batch rows through the index list inside the
  *                    kernels' loads (while T * max(d_in, d_out) * 2 bytes stays below 4 GiB) | 0: always gather the

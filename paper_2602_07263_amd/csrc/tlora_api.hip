@@ -95,7 +95,8 @@ struct Plan {
   GemmSplit gemm_split_fwd, gemm_split_bwd;             // tiles of the two GEMMs that are cut along the contraction
   size_t partial_bytes = 0;                             // what off_partial holds: dA / dB tiles, or sums of split launches
   // workspace byte offsets
-  size_t off_tables = 0, off_S = 0, off_dS = 0, off_Shi = 0, off_Slo = 0, off_dShi = 0, off_dSlo = 0, off_Sx = 0, off_dSx = 0, off_atp = 0, off_wt = 0, off_ap = 0, off_bp = 0,
+  size_t off_tables = 0, off_S = 0, off_dS = 0, off_Shi = 0, off_Slo = 0, off_dShi = 0, off_dSlo = 0, off_Sx = 0, off_dSx = 0, off_atp = 0, off_wt = 0, off_wt_state = 0, off_ap = 0,
+         off_bp = 0,
          off_partial = 0, total = 0;
   size_t tables_bytes = 0;
   // offsets of each table inside the table blob
@@ -268,6 +269,13 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
   }
   return best;
 }
+// Whether dX = dY.W^T of a batch runs against W as it lies instead of against a transposed copy.  Whole rounds of tiles are
+// 2 to 9 % faster against the copy (its tiles are 64 rows of 512 contiguous bytes, those of W 256 rows of 128), but the copy
+// reads and writes W once: forward and backward of 512 tokens, 4096 -> 12288, 215 us with the copy, 176 without; 17408 -> 5120,
+// 256 tokens, 262 and 175.  They meet between 6000 tokens (gains of 0.9 to 3 % over nine pairs of feature sizes) and 8192 (0.8 %
+// gained at 4096 -> 4096, 2.7 % lost at 17408 -> 5120).  A weight below 2^19 elements keeps the copy, a launch of 3 us: of
+// 1024 x 1024 on, the smallest measured, leaving it out gains 2 to 4 us.  Same bits either way.
+inline bool dx_direct(int64_t tokens, int64_t d_in, int64_t d_out) { return tokens <= 6144 && d_in * d_out >= (1 << 19); }
 size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N) {
   if (g.splits < 2) return 0;
   const int64_t nb = (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
@@ -454,7 +462,10 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
   auto wplace = [&](size_t bytes) { const size_t at = w;  w = align_up(w + bytes, 256);  return at; };
   // the transposed W first: its place depends on nothing but d_in x d_out, so a copy made by one call is found
   // by later calls on other token batches (nano-batches) that share the workspace
-  if (full) pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
+  if (full) {
+    pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
+    pl.off_wt_state = wplace(sizeof(WtState));
+  }
   // so do the packed adapters, whose places depend on the feature sizes and ranks
   if (pl.dtype == TLORA_BF16) {
     pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
@@ -511,7 +522,7 @@ constexpr int kSlots = 16;
 Slot g_slots[kSlots];
 int g_next_slot = 0;
 
-int upload_tables(const std::vector<uint8_t>& blob, void* dst, hipStream_t st) {
+int upload_tables(const std::vector<uint8_t>& blob, void* dst, hipStream_t st, const WtCall& wt = WtCall()) {
   Slot& s = g_slots[g_next_slot];
   g_next_slot = (g_next_slot + 1) % kSlots;
   if (s.busy) {
@@ -532,10 +543,12 @@ int upload_tables(const std::vector<uint8_t>& blob, void* dst, hipStream_t st) {
   if (!s.ev) TLORA_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
   memcpy(s.host, blob.data(), blob.size());
   if (g_opt.table_copy_kernel && s.dev_view && blob.size() % 16 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-    launch_table_copy(s.dev_view, dst, blob.size(), st);
+    launch_table_copy(s.dev_view, dst, blob.size(), wt, st);
     TLORA_HIP(hipGetLastError());
   } else {
     TLORA_HIP(hipMemcpyAsync(dst, s.host, blob.size(), hipMemcpyHostToDevice, st));
+    launch_table_copy(nullptr, nullptr, 0, wt, st);
+    TLORA_HIP(hipGetLastError());
   }
   TLORA_HIP(hipEventRecord(s.ev, st));
   s.busy = true;
@@ -868,7 +881,9 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
   if (!packed) {
     Timed t(TLORA_K_PACK, st, timed);
-    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, nullptr, bp, st);
+    // (a backward that reuses this packing may need A_j side by side)
+    uint16_t* const ap = !no_alloc && dx_direct(pl.T, pl.d_in, pl.d_out) ? reinterpret_cast<uint16_t*>(ws + pl.off_ap) : nullptr;
+    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, st);
   }
   {
     Timed t(TLORA_K_SHRINK, st, timed);
@@ -908,9 +923,11 @@ namespace tlora {
 namespace {
 // The backward's launch sequence (out_index / in_index as in fwd_impl: dX rows are scattered; X and dY are fetched
 // through the list; packed and shared_sums as there, the latter also for the partial tiles of dA / dB).
+// batch_tokens: of the whole batch, if the call is one of its nano-batches, which share one copy of W^T or do without alike.
+// wt_there: the same entry point has made the copy for an earlier nano-batch.
 int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags,
              void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index,
-             bool packed = false, uint8_t* shared_sums = nullptr) {
+             bool packed = false, uint8_t* shared_sums = nullptr, int64_t batch_tokens = 0, bool wt_there = false) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, false, shared_sums != nullptr);
@@ -988,7 +1005,20 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     return launches_ok(__LINE__);
   }
 
-  rc = upload_tables(blob, tb, st);
+  const bool direct = dx_direct(std::max<int64_t>(batch_tokens, pl.T), pl.d_in, pl.d_out);
+  const bool reuse_wt = (flags & TLORA_BWD_REUSE_WT) != 0;
+  const bool wt = g_opt.dx_transposed_w != 0 && (reuse_wt || !direct);
+  uint16_t* Wt = reinterpret_cast<uint16_t*>(ws + pl.off_wt);
+  WtCall wc;
+  if (dX && pl.T > 0) {
+    if (!reuse_wt) wc.action = wt ? kWtMade : kWtNone;
+    else if (wt && !wt_there) wc.action = kWtEnsure;
+    wc.state = reinterpret_cast<WtState*>(ws + pl.off_wt_state);
+    wc.W = static_cast<const uint16_t*>(p->W);
+    wc.Wt = Wt;
+    wc.rows = pl.d_in;  wc.cols = pl.d_out;
+  }
+  rc = upload_tables(blob, tb, st, wc);
   if (rc != TLORA_OK) return rc;
   uint16_t* Sx = reinterpret_cast<uint16_t*>(ws + pl.off_Sx);
   uint16_t* dSx = reinterpret_cast<uint16_t*>(ws + pl.off_dSx);
@@ -1005,13 +1035,13 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
   const uint16_t* dYb = static_cast<const uint16_t*>(dY);
   const bool redo_S = want_grads && !reuse_S;
 
-  const bool wt = g_opt.dx_transposed_w != 0;
   {
     Timed t(TLORA_K_PACK, st);
-    // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace; a_all,
-    // which only a dX product against W as it lies reads, is made here when it is needed
+    // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace, and a_all,
+    // which only a dX product against W as it lies reads, if the forward's batch is one for it
     const bool need_a_all = dX && !wt;
-    if (!(reuse_S || packed) || need_a_all)
+    const bool have_a_all = reuse_S ? dx_direct(pl.T, pl.d_in, pl.d_out) : packed;
+    if (!(reuse_S || packed) || (need_a_all && !have_a_all))
       launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, need_a_all ? ap : nullptr, bp, st);
   }
   if (pl.T > 0) {
@@ -1027,8 +1057,7 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
       // dX = dY . W^T contracts over W's contiguous dimension.  Against a transposed copy of W the weight tiles
       // are 64 rows of 512 contiguous bytes instead of 256 rows of 128, which the load stream handles markedly
       // better (the copy costs one read and one write of W; W is frozen, so REUSE_WT skips it).
-      uint16_t* Wt = reinterpret_cast<uint16_t*>(ws + pl.off_wt);
-      if (wt && !(flags & TLORA_BWD_REUSE_WT)) {
+      if (wt && !reuse_wt) {
         Timed t(TLORA_K_WT, st);
         launch_transpose_bf16(static_cast<const uint16_t*>(p->W), Wt, pl.d_in, pl.d_out, st);
       }
@@ -1185,7 +1214,8 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
   if (need == 0) return validate(p) != TLORA_OK ? validate(p) : TLORA_EINVAL;
   if (!workspace || ws_bytes < need) return TLORA_EWORKSPACE;
   const size_t elt = p->dtype == TLORA_F32 ? 4 : 2;
-  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0, packed = false;
+  const int64_t T = p->offsets[p->num_jobs];
+  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0, wt_there = false, packed = false;
   for (int32_t n = 0; n < n_nano; ++n) {
     NanoSub s;
     int rc = make_sub(p, n_nano, granule, n, s);
@@ -1195,11 +1225,12 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
     int f = (first ? (flags & TLORA_BWD_ACCUMULATE) : TLORA_BWD_ACCUMULATE) | (wt_made ? TLORA_BWD_REUSE_WT : 0);
     rc = bwd_impl(&s.p, dY ? static_cast<const uint8_t*>(dY) + (size_t)s.b0 * p->d_out * elt : nullptr,
                   dX ? static_cast<uint8_t*>(dX) + (size_t)s.b0 * p->d_in * elt : nullptr, dA, dB, f, workspace, ws_bytes,
-                  hip_stream, nullptr, nullptr, packed);
+                  hip_stream, nullptr, nullptr, packed, nullptr, T, wt_there);
     if (rc != TLORA_OK) return rc;
     packed = true;
     first = false;
-    if (dX && s.b1 > s.b0) wt_made = true;
+    // (a batch that does without the copy does so in every nano-batch)
+    if (dX && s.b1 > s.b0 && (wt_made || !dx_direct(T, p->d_in, p->d_out))) wt_made = wt_there = true;
   }
   return TLORA_OK;
 }
@@ -2079,7 +2110,10 @@ static int check_plan(const Plan& pl, bool fwd_only) {
   {
     std::vector<std::pair<size_t, size_t>> w;
     const size_t se = (size_t)pl.s_elems, sx = 2 * (size_t)pl.sx_elems + 256;
-    if (bf16 && !fwd_only) w.push_back({pl.off_wt, 2 * (size_t)pl.d_in * (size_t)pl.d_out});
+    if (bf16 && !fwd_only) {
+      w.push_back({pl.off_wt, 2 * (size_t)pl.d_in * (size_t)pl.d_out});
+      w.push_back({pl.off_wt_state, sizeof(WtState)});
+    }
     if (bf16) {
       w.push_back({pl.off_atp, 2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)});
       w.push_back({pl.off_bp, 2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32)});

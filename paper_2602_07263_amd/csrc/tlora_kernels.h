@@ -23,8 +23,26 @@ void launch_zero_fill(void* ptr, size_t bytes, hipStream_t st);
 // Copy `bytes` of HOST memory to device memory `dst` (4-byte aligned, room for bytes rounded up to 4) by value,
 // through the arguments of small store kernels: no staging buffer, no copy node, nothing allocated.
 void launch_table_write(const void* host_src, size_t bytes, void* dst, hipStream_t st);
-// Copy `bytes` (a multiple of 16) from pinned host memory, given by its device address, to device memory.
-void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, hipStream_t st);
+// What a backward does about the transposed copy of W in its workspace.
+enum WtAction {
+  kWtKeep = 0,       // nothing: no dX product, or a copy that this very call has made before
+  kWtMade = 1,       // notes that the call makes it
+  kWtNone = 2,       // notes that the call does without, so that what lies there is not taken for a copy of its W
+  kWtEnsure = 3,     // the caller promises that an earlier call made it: made now if that call did without
+};
+struct WtState {     // in the workspace, at a place that depends on d_in x d_out alone
+  uint32_t made;
+  uint32_t done;     // workgroups of a kWtEnsure launch that have finished
+};
+struct WtCall {
+  int action = kWtKeep;
+  WtState* state = nullptr;
+  const uint16_t* W = nullptr;     // [rows, cols]
+  uint16_t* Wt = nullptr;
+  int rows = 0, cols = 0;
+};
+// Copy `bytes` (a multiple of 16) from pinned host memory, given by its device address, to device memory; and wt.
+void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, const WtCall& wt, hipStream_t st);
 
 // out_j[t, p] = sum_k act[t, k] * P_j[p, k]   (P_j = A_j^T packed, or B_j packed)
 // row_index (null = identity): the row of `act` that holds token row t of the job-sorted order (token-indexed calls).
@@ -56,7 +74,7 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
                      int T, int K, int N,
                      unsigned long long* clk /* null, or 2 zeroed words: every 64th workgroup adds the shader
                                                 cycles and 100 MHz ticks of its K-loop */,
-                     const GemmSplit& split /* taken when w_is_kn and K % 32 == 0 */,
+                     const GemmSplit& split /* taken when K % 32 == 0 */,
                      float* part /* splits x cut tiles x min(T, 256) x 256 floats */, hipStream_t st);
 
 // partial[u] = sum_{t in unit u} U_j[t, p] * V[t, c]   then   G_j = scale_j * sum_u partial[u]

@@ -259,10 +259,9 @@ void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out,
 
 // out[c, r] = in[r, c] for a row-major bf16 matrix [rows, cols] (both multiples of 8): 64 x 64 tiles through LDS,
 // 16-byte global accesses on both sides.
-__global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
-                                                             int rows, int cols) {
-  __shared__ uint16_t tile[64][72];        // [c][r]; 144-byte pitch keeps the 16-byte row reads aligned
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+typedef uint16_t TurnTile[64][72];         // [c][r]; 144-byte pitch keeps the 16-byte row reads aligned
+__device__ __forceinline__ void transpose_tile(TurnTile& tile, const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
+                                               int rows, int cols, int r0, int c0) {
   const int tid = threadIdx.x;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -282,6 +281,11 @@ __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __r
     if (c0 + c < cols && r0 + rr < rows)
       *reinterpret_cast<u32x4*>(out + (int64_t)(c0 + c) * rows + r0 + rr) = *reinterpret_cast<const u32x4*>(&tile[c][rr]);
   }
+}
+__global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
+                                                             int rows, int cols) {
+  __shared__ TurnTile tile;
+  transpose_tile(tile, in, out, rows, cols, blockIdx.y * 64, blockIdx.x * 64);
 }
 
 void launch_transpose_bf16(const uint16_t* in, uint16_t* out, int rows, int cols, hipStream_t st) {
@@ -330,17 +334,42 @@ void launch_table_write(const void* host_src, size_t bytes, void* dst, hipStream
 // Plan tables from a pinned staging buffer (host memory, read through its device address) into the workspace, as an
 // ordinary kernel on the caller's stream: a host-to-device copy command makes the stream's next kernel wait for the
 // copy engine's signal (~20 us of idle stream per call), a kernel in the same queue does not.
-__global__ void __launch_bounds__(256) table_copy_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
-                                                         size_t n16) {
-  const size_t stride = (size_t)gridDim.x * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) dst[i] = src[i];
+// The launch also keeps the state of the transposed copy of W (see WtState): a call that makes the copy or does without it
+// notes which; a call that was promised a copy makes it here if the calls before did without.
+constexpr int kWtBlocks = 1024;
+__global__ void __launch_bounds__(256) table_copy_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16,
+                                                         int copy_blocks, WtState* state, int action,
+                                                         const uint16_t* __restrict__ W, uint16_t* __restrict__ Wt, int rows,
+                                                         int cols) {
+  if ((int)blockIdx.x < copy_blocks) {
+    const size_t stride = (size_t)copy_blocks * 256;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) dst[i] = src[i];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (action == kWtMade || action == kWtNone)) {
+      state->made = action == kWtMade;
+      state->done = 0;
+    }
+    return;
+  }
+  // kWtEnsure: every workgroup has read the word before the last of them sets it
+  if (__builtin_nontemporal_load(&state->made) != 0) return;
+  __shared__ TurnTile tile;
+  const int tx = (cols + 63) / 64, ty = (rows + 63) / 64;
+  for (int64_t t = (int)blockIdx.x - copy_blocks; t < (int64_t)tx * ty; t += kWtBlocks) {
+    transpose_tile(tile, W, Wt, rows, cols, (int)(t / tx) * 64, (int)(t % tx) * 64);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0 && atomicAdd(&state->done, 1u) == kWtBlocks - 1) {
+    state->done = 0;
+    state->made = 1;
+  }
 }
-void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, hipStream_t st) {
+void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, const WtCall& wt, hipStream_t st) {
   const size_t n16 = bytes / 16;                 // the caller passes a multiple of 16 bytes
-  if (n16 == 0) return;
-  const unsigned blocks = (unsigned)std::min<size_t>((n16 + 255) / 256, 256);
-  hipLaunchKernelGGL(table_copy_kernel, dim3(blocks), dim3(256), 0, st, static_cast<const u32x4*>(src_device_view),
-                     static_cast<u32x4*>(dst), n16);
+  const unsigned blocks = (unsigned)std::min<size_t>((n16 + 255) / 256 + (n16 == 0 && wt.action != kWtKeep), 256);
+  if (blocks == 0) return;
+  hipLaunchKernelGGL(table_copy_kernel, dim3(blocks + (wt.action == kWtEnsure ? kWtBlocks : 0)), dim3(256), 0, st,
+                     static_cast<const u32x4*>(src_device_view), static_cast<u32x4*>(dst), n16, (int)blocks, wt.state, wt.action,
+                     wt.W, wt.Wt, wt.rows, wt.cols);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1273,11 +1302,13 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
   if (nb == 0) return;
   const bool tail = K % kGemmBK != 0;
   P.n_direct = split.n_direct;  P.splits = split.splits;  P.part_rows = std::min(T, kGemmBM);  P.part = part;
-  if (split.splits > 1 && w_is_kn && !tail) {
+  if (split.splits > 1 && !tail) {
     const int n_tail = nb - P.n_direct;
     const dim3 grid(P.n_direct + n_tail * P.splits);
-    if (in_index) hipLaunchKernelGGL((seg_gemm_kernel<true, false, true, true>), grid, dim3(512), 0, st, P);
-    else          hipLaunchKernelGGL((seg_gemm_kernel<true, false, false, true>), grid, dim3(512), 0, st, P);
+#define TLORA_GEMM_CUT(KN, IDX) hipLaunchKernelGGL((seg_gemm_kernel<KN, false, IDX, true>), grid, dim3(512), 0, st, P)
+    if (w_is_kn) { if (in_index) TLORA_GEMM_CUT(true, true);  else TLORA_GEMM_CUT(true, false); }
+    else         { if (in_index) TLORA_GEMM_CUT(false, true); else TLORA_GEMM_CUT(false, false); }
+#undef TLORA_GEMM_CUT
     hipLaunchKernelGGL(gemm_reduce_kernel, dim3(n_tail, (P.part_rows + 7) / 8), dim3(256), 0, st, part, P.n_direct, P.splits,
                        P.part_rows, out, out_index, T, N, P.tiles_m, P.tiles_n);
     return;
