@@ -93,6 +93,7 @@ struct Plan {
   int64_t sx_elems = 0;                                 // elements of the per-tile K-extension operands
   int shrink_splits_x = 1, shrink_splits_dy = 1;        // contraction splits of the shrinks over d_in (S) and d_out (dS)
   GemmSplit gemm_split_fwd, gemm_split_bwd;             // tiles of the two GEMMs that are cut along the contraction
+  int small_x = 0, small_dy = 0;                        // splits of a small batch's two-launch form (0: not taken), X and dY side
   size_t partial_bytes = 0;                             // what off_partial holds: dA / dB tiles, or sums of split launches
   // workspace byte offsets
   size_t off_tables = 0, off_S = 0, off_dS = 0, off_Shi = 0, off_Slo = 0, off_dShi = 0, off_dSlo = 0, off_Sx = 0, off_dSx = 0, off_atp = 0, off_wt = 0, off_wt_state = 0, off_ap = 0,
@@ -281,6 +282,54 @@ size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N) {
   const int64_t nb = (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
   return sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM) * (size_t)(nb - g.n_direct) * g.splits;
 }
+
+// Bytes of the sums of a small batch and of its activations as fragments.
+size_t small_part_bytes(const Plan& pl, int N, int splits) {
+  return sizeof(float) * (size_t)pl.T * (size_t)small_ld(N, pl.r_total) * (size_t)splits;
+}
+size_t small_frag_bytes(const Plan& pl, int K) {
+  const int rb = small_blocks(pl.T);
+  return small_frags(rb) ? align_up((size_t)rb * 32 * (size_t)K, 256) : 0;
+}
+// Where the fragments of X (side 0) and dY (side 1) lie in the room of the sums: behind those of either direction.
+FragPack small_frag_pack(const Plan& pl, int side, const void* act, const int32_t* in_index, void* sums) {
+  FragPack f;
+  f.act = static_cast<const uint16_t*>(act);  f.in_index = in_index;
+  f.T = pl.T;  f.K = side ? pl.d_out : pl.d_in;  f.rb = small_blocks(pl.T);
+  if (!small_frags(f.rb)) return f;
+  const size_t x = std::max(pl.small_x ? small_part_bytes(pl, pl.d_out, pl.small_x) : 0,
+                            pl.small_dy ? small_part_bytes(pl, pl.d_in, pl.small_dy) : 0);
+  f.out = reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(sums) + align_up(x, 256) + (side ? small_frag_bytes(pl, pl.d_in) : 0));
+  return f;
+}
+// Splits of the two-launch form of a small batch over [T, K] x [K, N] (0: the general kernels); kn: against a weight as the
+// forward reads it.  A direction takes about 20 us, 0.115 us per MB of W and rank rows, and `piece` us per workgroup of the busiest
+// CU and piece of 128 k-values of a wave, with 4 waves to a workgroup and 64 columns and a split each; the general kernels (cut
+// shrink, sums, cut product, sums) about 29, or 32 in the backward, 0.26 us per MB and 2 us per 64 tokens.  Fitted to 608 launches of
+// 16 to 128 tokens (K and N 1024 to 17408, 64 and 512 rank rows, 1 to 8 splits; 4 to 6 % off each, W from memory); the rule is
+// 2 % off the best choice on average.  Measured, general / this, forward and backward without gradients: 4096 -> 4096, 64 tokens, 45 /
+// 34 and 47 / 32 us; 4096 -> 12288, 16 tokens, 52 / 43 and 61 / 42; 1024 -> 1024, 128 tokens, 33 / 24; 17408 -> 5120, 128 tokens,
+// 80 / 81 (general).  Each wave should have a piece (K >= 512), and idle jobs' rank rows, which are contracted too, must not be the bulk.
+int small_splits(const Plan& pl, int K, int N, bool kn, size_t max_bytes) {
+  if (pl.T < 1 || pl.T > kSmallRows || pl.d_in % 64 || pl.d_out % 64 || K < 512 || g_opt.shrink_rows != 0) return 0;
+  int active = 0;
+  for (const JobDev& jb : pl.jobs) active += jb.row1 > jb.row0 ? jb.rpad : 0;
+  if (pl.r_total > 2 * active) return 0;
+  const int steps = K / 64, tiles = N / 64 + (pl.r_total + 63) / 64, rb = small_blocks(pl.T);
+  const size_t bytes = small_part_bytes(pl, N, 1), frags = 2 * small_frag_bytes(pl, std::max(pl.d_in, pl.d_out));
+  const double piece = kn ? (rb == 1 ? 1.84 : rb == 2 ? 2.33 : rb == 4 ? 2.6 : 4.0) : (rb == 1 ? 1.04 : rb == 2 ? 1.47 : rb == 4 ? 1.8 : 2.97);
+  int best = 0;
+  double best_us = 0.95 * ((kn ? 9.0 : 11.0) + 0.144e-6 * 2 * (double)K * N + pl.T / 32.0);
+  for (int s = 1; s <= kGemmMaxSplits && s <= steps && align_up(bytes * s, 256) + frags <= max_bytes; ++s) {
+    const int pieces = ((steps + s - 1) / s + 7) / 8;
+    const double us = piece * ((tiles * s + 255) / 256) * pieces + 0.15e-6 * (double)bytes * s;
+    if (us < best_us) { best = s;  best_us = us; }
+  }
+  return best;
+}
+
+// Whether the forward of the full plan packs A_j side by side as well: for a dX product of the same batch against W as it lies.
+bool packs_a_all(const Plan& pl) { return dx_direct(pl.T, pl.d_in, pl.d_out) && !pl.small_dy; }
 
 // Room for the sums of cut launches in the full plan: two rounds of 256 whole tiles (128 MiB: 144 tiles over K = 15072 in
 // three shares take 23 us off a dX of 400 tiles), or less for few tokens, whose workspace has to stay far from another dense
@@ -495,12 +544,14 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     const size_t room = forward_sums_room(pl);
     pl.shrink_splits_x = shrink_splits(pl, pl.d_in, room);
     pl.gemm_split_fwd = gemm_split(pl, pl.d_in, pl.d_out, room);
+    pl.small_x = small_splits(pl, pl.d_in, pl.d_out, true, room);
     if (fwd_only) {
       pl.partial_bytes = room;                           // (more than there is only in a plan that does not fit)
       pl.off_partial = TLORA_NOALLOC_SCRATCH_BYTES;      // (beyond pl.total)
     } else {
       pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, sums_room(pl));
       pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, sums_room(pl));
+      pl.small_dy = small_splits(pl, pl.d_out, pl.d_in, false, sums_room(pl));
       pl.partial_bytes = res.partial;
       pl.off_partial = wplace(pl.partial_bytes);
     }
@@ -522,7 +573,8 @@ constexpr int kSlots = 16;
 Slot g_slots[kSlots];
 int g_next_slot = 0;
 
-int upload_tables(const std::vector<uint8_t>& blob, void* dst, hipStream_t st, const WtCall& wt = WtCall()) {
+int upload_tables(const std::vector<uint8_t>& blob, void* dst, hipStream_t st, const WtCall& wt = WtCall(),
+                  const FragPack& frags = FragPack()) {
   Slot& s = g_slots[g_next_slot];
   g_next_slot = (g_next_slot + 1) % kSlots;
   if (s.busy) {
@@ -543,11 +595,11 @@ int upload_tables(const std::vector<uint8_t>& blob, void* dst, hipStream_t st, c
   if (!s.ev) TLORA_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
   memcpy(s.host, blob.data(), blob.size());
   if (g_opt.table_copy_kernel && s.dev_view && blob.size() % 16 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-    launch_table_copy(s.dev_view, dst, blob.size(), wt, st);
+    launch_table_copy(s.dev_view, dst, blob.size(), wt, frags, st);
     TLORA_HIP(hipGetLastError());
   } else {
     TLORA_HIP(hipMemcpyAsync(dst, s.host, blob.size(), hipMemcpyHostToDevice, st));
-    launch_table_copy(nullptr, nullptr, 0, wt, st);
+    launch_table_copy(nullptr, nullptr, 0, wt, frags, st);
     TLORA_HIP(hipGetLastError());
   }
   TLORA_HIP(hipEventRecord(s.ev, st));
@@ -879,11 +931,21 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   uint16_t* bp = reinterpret_cast<uint16_t*>(ws + pl.off_bp);
   float* sums = reinterpret_cast<float*>(shared_sums ? shared_sums : ws + pl.off_partial);
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
-  if (!packed) {
+  const FragPack frags = pl.small_x ? small_frag_pack(pl, 0, p->X, in_index, sums) : FragPack();
+  if (packed) {
+    launch_frag_pack(frags, st);
+  } else {
     Timed t(TLORA_K_PACK, st, timed);
     // (a backward that reuses this packing may need A_j side by side)
-    uint16_t* const ap = !no_alloc && dx_direct(pl.T, pl.d_in, pl.d_out) ? reinterpret_cast<uint16_t*>(ws + pl.off_ap) : nullptr;
-    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, st);
+    uint16_t* const ap = !no_alloc && packs_a_all(pl) ? reinterpret_cast<uint16_t*>(ws + pl.off_ap) : nullptr;
+    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, frags, st);
+  }
+  if (pl.small_x) {
+    Timed tg(TLORA_K_GEMM_FWD, st, timed);
+    launch_small(true, jobs, tiles, frags.out ? frags.out : static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), atp, bp, pl.r_total,
+                 static_cast<uint16_t*>(Y), out_index, in_index, pl.T, pl.d_in, pl.d_out, pl.small_x, sums,
+                 no_alloc ? nullptr : reinterpret_cast<uint16_t*>(ws + pl.off_Shi), reinterpret_cast<uint16_t*>(ws + pl.off_Slo), st);
+    return launches_ok(__LINE__);
   }
   {
     Timed t(TLORA_K_SHRINK, st, timed);
@@ -1007,7 +1069,9 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
 
   const bool direct = dx_direct(std::max<int64_t>(batch_tokens, pl.T), pl.d_in, pl.d_out);
   const bool reuse_wt = (flags & TLORA_BWD_REUSE_WT) != 0;
-  const bool wt = g_opt.dx_transposed_w != 0 && (reuse_wt || !direct);
+  // (the nano-batches of a large batch share its copy)
+  const bool small = pl.small_dy && (batch_tokens <= pl.T || direct);
+  const bool wt = g_opt.dx_transposed_w != 0 && !small && (reuse_wt || !direct);
   uint16_t* Wt = reinterpret_cast<uint16_t*>(ws + pl.off_wt);
   WtCall wc;
   if (dX && pl.T > 0) {
@@ -1018,7 +1082,9 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     wc.Wt = Wt;
     wc.rows = pl.d_in;  wc.cols = pl.d_out;
   }
-  rc = upload_tables(blob, tb, st, wc);
+  float* partial = reinterpret_cast<float*>(shared_sums ? shared_sums : ws + pl.off_partial);
+  const FragPack frags = small && pl.T > 0 ? small_frag_pack(pl, 1, dY, in_index, partial) : FragPack();
+  rc = upload_tables(blob, tb, st, wc, frags);
   if (rc != TLORA_OK) return rc;
   uint16_t* Sx = reinterpret_cast<uint16_t*>(ws + pl.off_Sx);
   uint16_t* dSx = reinterpret_cast<uint16_t*>(ws + pl.off_dSx);
@@ -1029,7 +1095,6 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
   uint16_t* atp = reinterpret_cast<uint16_t*>(ws + pl.off_atp);
   uint16_t* ap = reinterpret_cast<uint16_t*>(ws + pl.off_ap);
   uint16_t* bp = reinterpret_cast<uint16_t*>(ws + pl.off_bp);
-  float* partial = reinterpret_cast<float*>(shared_sums ? shared_sums : ws + pl.off_partial);
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
   const uint16_t* Xb = static_cast<const uint16_t*>(p->X);
   const uint16_t* dYb = static_cast<const uint16_t*>(dY);
@@ -1039,21 +1104,33 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     Timed t(TLORA_K_PACK, st);
     // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace, and a_all,
     // which only a dX product against W as it lies reads, if the forward's batch is one for it
-    const bool need_a_all = dX && !wt;
-    const bool have_a_all = reuse_S ? dx_direct(pl.T, pl.d_in, pl.d_out) : packed;
+    const bool need_a_all = dX && !wt && !small;
+    const bool have_a_all = reuse_S ? packs_a_all(pl) : packed;
     if (!(reuse_S || packed) || (need_a_all && !have_a_all))
-      launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, need_a_all ? ap : nullptr, bp, st);
+      launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, need_a_all ? ap : nullptr, bp,
+                           FragPack(), st);
   }
   if (pl.T > 0) {
     if (redo_S) {
       Timed t(TLORA_K_SHRINK, st);
-      run_shrink(pl, tb, jobs, tiles, Xb, pl.d_in, atp, true, Shi, Slo, Sx, in_index, partial, st);
+      if (pl.small_x) {
+        const FragPack xf = small_frag_pack(pl, 0, Xb, in_index, partial);
+        launch_frag_pack(xf, st);
+        launch_small(true, jobs, tiles, xf.out ? xf.out : Xb, nullptr, atp, bp, pl.r_total, nullptr, nullptr, in_index, pl.T, pl.d_in, pl.d_out,
+                     pl.small_x, partial, Shi, Slo, st);
+      } else {
+        run_shrink(pl, tb, jobs, tiles, Xb, pl.d_in, atp, true, Shi, Slo, Sx, in_index, partial, st);
+      }
     }
-    {
+    if (small) {
+      Timed t(dX ? TLORA_K_GEMM_BWD : TLORA_K_SHRINK, st);
+      launch_small(false, jobs, tiles, frags.out ? frags.out : dYb, static_cast<const uint16_t*>(p->W), bp, atp, pl.r_total, static_cast<uint16_t*>(dX),
+                   out_index, in_index, pl.T, pl.d_out, pl.d_in, pl.small_dy, partial, dShi, dSlo, st);
+    } else {
       Timed t(TLORA_K_SHRINK, st);
       run_shrink(pl, tb, jobs, tiles, dYb, pl.d_out, bp, false, dShi, dSlo, dSx, in_index, partial, st);
     }
-    if (dX) {
+    if (dX && !small) {
       // dX = dY . W^T contracts over W's contiguous dimension.  Against a transposed copy of W the weight tiles
       // are 64 rows of 512 contiguous bytes instead of 256 rows of 128, which the load stream handles markedly
       // better (the copy costs one read and one write of W; W is frozen, so REUSE_WT skips it).
@@ -2144,6 +2221,16 @@ static int check_plan(const Plan& pl, bool fwd_only) {
         }
         if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
       }
+      for (int d = 0; d < 2; ++d) {
+        const int k = d ? pl.small_dy : pl.small_x, K = d ? pl.d_out : pl.d_in, N = d ? pl.d_in : pl.d_out;
+        if (k == 0) continue;
+        if (pl.T < 1 || pl.T > kSmallRows || pl.tile_jobs.size() != 1 || K % 64 || N % 64 || k < 1 || k > K / 64) return 71;
+        if (small_part_bytes(pl, N, k) > pl.partial_bytes) return 72;
+        uint8_t* const none = nullptr;                   // (offsets)
+        const FragPack f = small_frag_pack(pl, d, nullptr, nullptr, none);
+        if (f.out && (size_t)(reinterpret_cast<uint8_t*>(f.out) - none) + small_frag_bytes(pl, K) > pl.partial_bytes) return 73;
+        if (f.out && (size_t)(reinterpret_cast<uint8_t*>(f.out) - none) < small_part_bytes(pl, N, k)) return 74;
+      }
       if (!fwd_only) w.push_back({pl.off_partial, pl.partial_bytes});
       else if (pl.total != forward_bytes(pl)) return 70;
       else if (pl.off_partial < TLORA_NOALLOC_SCRATCH_BYTES ||
@@ -2183,6 +2270,12 @@ int tlora_plan_cuts(const tlora_problem_t* p, int32_t fwd_only, int32_t* cuts) {
     const int N = d ? pl.d_in : pl.d_out;
     cuts[2 + 2 * d] = g.splits > 1 ? g.n_direct : (int32_t)(pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN));
     cuts[3 + 2 * d] = g.splits;
+    const int small = d ? pl.small_dy : pl.small_x;
+    if (small) {                                         // shares of a split: its workgroups' waves
+      const int steps = (d ? pl.d_out : pl.d_in) / 64 / small;
+      cuts[d] = cuts[3 + 2 * d] = small * std::min(4, std::max(1, (steps + 1) / 2));
+      cuts[2 + 2 * d] = 0;
+    }
   }
   return TLORA_OK;
 }

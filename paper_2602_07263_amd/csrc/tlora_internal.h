@@ -54,6 +54,20 @@ struct GemmSplit {
 // ring of tile slots asks of a first step.
 __host__ __device__ inline int gemm_share(int steps, int splits) { return ((steps + splits - 1) / splits + 1) & ~1; }
 
+// Batches of at most kSmallRows tokens run in two launches per direction; a row of their sums: N columns of the backbone product
+// and the rank columns, whole tiles of 64.
+constexpr int kSmallRows = 128;
+// Blocks of 16 tokens that the kernel is built for, and whether it reads the activations as fragments laid out before.
+__host__ __device__ constexpr int small_blocks(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : 8; }
+__host__ __device__ constexpr bool small_frags(int blocks) { return blocks >= 4; }
+struct FragPack {
+  const uint16_t* act = nullptr;        // [T, K], rows through in_index if given
+  const int32_t* in_index = nullptr;
+  uint16_t* out = nullptr;              // null: nothing to do
+  int T = 0, K = 0, rb = 0;
+};
+__host__ __device__ inline int small_ld(int N, int r_total) { return N + (r_total + 63) / 64 * 64; }
+
 // Work unit of the shrink kernels (S_j = X_j.A_j and dS_j = dY_j.B_j^T): a block of token rows of
 // one job times a block of kShrinkCols padded rank columns.
 struct ShrinkUnit {

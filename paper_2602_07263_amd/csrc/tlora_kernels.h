@@ -12,7 +12,9 @@ namespace tlora {
 // atp: per job A_j^T [rpad, d_in], stacked in job order ([R + 32, d_in], trailing rows zero);  a_all: [d_in, R + 32] with job j in columns roff_j ..;  b_all: [R + 32, d_out]
 // with job j in rows roff_j ..  (R = r_total; the 32 trailing columns / rows are zero).
 void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total,
-                          uint16_t* atp, uint16_t* a_all, uint16_t* b_all, hipStream_t st);
+                          uint16_t* atp, uint16_t* a_all, uint16_t* b_all, const FragPack& frags /* in the same launch */,
+                          hipStream_t st);
+void launch_frag_pack(const FragPack& frags, hipStream_t st);
 
 // out[c, r] = in[r, c]; bf16 [rows, cols] row-major, rows and cols multiples of 8, 16-byte aligned.
 void launch_transpose_bf16(const uint16_t* in, uint16_t* out, int rows, int cols, hipStream_t st);
@@ -41,8 +43,9 @@ struct WtCall {
   uint16_t* Wt = nullptr;
   int rows = 0, cols = 0;
 };
-// Copy `bytes` (a multiple of 16) from pinned host memory, given by its device address, to device memory; and wt.
-void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, const WtCall& wt, hipStream_t st);
+// Copy `bytes` (a multiple of 16) from pinned host memory, given by its device address, to device memory; and wt or frags.
+void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, const WtCall& wt, const FragPack& frags,
+                       hipStream_t st);
 
 // out_j[t, p] = sum_k act[t, k] * P_j[p, k]   (P_j = A_j^T packed, or B_j packed)
 // row_index (null = identity): the row of `act` that holds token row t of the job-sorted order (token-indexed calls).
@@ -76,6 +79,14 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
                                                 cycles and 100 MHz ticks of its K-loop */,
                      const GemmSplit& split /* taken when K % 32 == 0 */,
                      float* part /* splits x cut tiles x min(T, 256) x 256 floats */, hipStream_t st);
+
+// A direction of a small batch (T <= kSmallRows; K and N multiples of 64): S_j (dS_j) as hi / lo planes (null: not wanted) and,
+// unless out is null, Y (dX).  act: as fragments if small_frags(small_blocks(T)).  rank_rows: A_j^T (B_j) packed, [R + 32, K];  expand_rows: B_j (A_j^T) packed, [R + 32, N].  part:
+// splits x T x small_ld(N, R) floats.
+void launch_small(bool w_is_kn, const JobDev* jobs, const TileDev* tiles, const uint16_t* act, const uint16_t* W,
+                  const uint16_t* rank_rows, const uint16_t* expand_rows, int r_total, uint16_t* out, const int32_t* out_index,
+                  const int32_t* in_index, int T, int K, int N, int splits, float* part, uint16_t* S_hi, uint16_t* S_lo,
+                  hipStream_t st);
 
 // partial[u] = sum_{t in unit u} U_j[t, p] * V[t, c]   then   G_j = scale_j * sum_u partial[u]
 void launch_rank_grad(const JobDev* jobs, const GradUnit* units, int num_units, const uint16_t* U_hi,

@@ -148,6 +148,24 @@ __device__ __forceinline__ bf16x8 frag16_kn(const uint8_t* tile, int nb, int ks,
 // blockIdx.y == num_jobs zero-fills the 32 trailing columns / rows, which the last tile's K-extension
 // may read (against zero activations) when its rank range is rounded up to the K-step.
 // ---------------------------------------------------------------------------------------------------
+// Activations of a small batch as operand fragments: [K / 32][rb][64 lanes][8], lane l of fragment (k / 32, b) holding row
+// b 16 + l % 16 (rows past the batch repeat its last one), k-values 8 (l / 16) .. + 7.
+__device__ __forceinline__ void frag_pack(const FragPack& f, int first, int stride) {
+  const int cpr = f.K / 8, n = f.rb * 16 * cpr;
+  for (int i = first; i < n; i += stride) {
+    const int r = i / cpr, c = i - r * cpr, t = min(r, f.T - 1);
+    const u32x4 v = ldg16(f.act + (int64_t)(f.in_index ? f.in_index[t] : t) * f.K + c * 8);
+    *reinterpret_cast<u32x4*>(f.out + ((int64_t)((c >> 2) * f.rb + (r >> 4)) * 64 + (c & 3) * 16 + (r & 15)) * 8) = v;
+  }
+}
+__global__ void __launch_bounds__(256) frag_pack_kernel(FragPack f) {
+  frag_pack(f, (int)(blockIdx.x * 256 + threadIdx.x), (int)gridDim.x * 256);
+}
+static int frag_blocks(const FragPack& f) { return f.out ? std::min((f.rb * 16 * (f.K / 8) + 255) / 256, 1024) : 0; }
+void launch_frag_pack(const FragPack& f, hipStream_t st) {
+  if (f.out) hipLaunchKernelGGL(frag_pack_kernel, dim3(frag_blocks(f)), dim3(256), 0, st, f);
+}
+
 // Every thread assembles 8 consecutive output elements and stores them as one 16-byte chunk (d_in, d_out, rpad,
 // roff and R are multiples of 8, so every chunk is aligned); A_j is read element by element (its rows are r_j
 // elements long, any alignment), B_j in 16-byte chunks when its base is aligned.
@@ -155,12 +173,16 @@ constexpr int kPackPiece = 1024;               // 16-byte chunks of B_j a workgr
 __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __restrict__ jobs, int num_jobs, int d_in,
                                                             int d_out, int r_total, uint16_t* __restrict__ atp,
                                                             uint16_t* __restrict__ a_all,
-                                                            uint16_t* __restrict__ b_all) {
+                                                            uint16_t* __restrict__ b_all, FragPack frags) {
   const int stride = (int)(gridDim.x * blockDim.x);
   const int first = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   const int ra = r_total + 32;
   const int kout8 = d_out / 8;
   const u32x4 zero = {0, 0, 0, 0};
+  if ((int)blockIdx.y > num_jobs) {
+    frag_pack(frags, first, stride);
+    return;
+  }
   if ((int)blockIdx.y == num_jobs) {
     for (int i = first; a_all && i < 4 * d_in; i += stride)
       *reinterpret_cast<u32x4*>(a_all + (int64_t)(i >> 2) * ra + r_total + (i & 3) * 8) = zero;
@@ -248,13 +270,13 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
 // Workgroups per job: one per tile and piece of the largest job, but no more than 8192 in all, or 64 per job from 128 jobs on
 // (those of smaller jobs find nothing and end; beyond that the loop over the job's units is cheaper than the empty workgroups).
 void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total,
-                          uint16_t* atp, uint16_t* a_all, uint16_t* b_all, hipStream_t st) {
-  if (max_rpad == 0) return;
+                          uint16_t* atp, uint16_t* a_all, uint16_t* b_all, const FragPack& frags, hipStream_t st) {
+  if (max_rpad == 0) return launch_frag_pack(frags, st);
   const int64_t units = (int64_t)((d_in + 63) / 64) * ((max_rpad + 63) / 64) +
                         ((int64_t)max_rpad * (d_out / 8) + kPackPiece - 1) / kPackPiece;
   const int bx = (int)std::min<int64_t>(units, std::max(64, 8192 / (num_jobs + 1)));
-  hipLaunchKernelGGL(pack_adapters_kernel, dim3(bx, num_jobs + 1), dim3(256), 0, st, jobs, num_jobs, d_in, d_out,
-                     r_total, atp, a_all, b_all);
+  hipLaunchKernelGGL(pack_adapters_kernel, dim3(bx, num_jobs + 1 + (frags.out ? 1 : 0)), dim3(256), 0, st, jobs, num_jobs, d_in,
+                     d_out, r_total, atp, a_all, b_all, frags);
 }
 
 // out[c, r] = in[r, c] for a row-major bf16 matrix [rows, cols] (both multiples of 8): 64 x 64 tiles through LDS,
@@ -340,7 +362,7 @@ constexpr int kWtBlocks = 1024;
 __global__ void __launch_bounds__(256) table_copy_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16,
                                                          int copy_blocks, WtState* state, int action,
                                                          const uint16_t* __restrict__ W, uint16_t* __restrict__ Wt, int rows,
-                                                         int cols) {
+                                                         int cols, FragPack frags) {
   if ((int)blockIdx.x < copy_blocks) {
     const size_t stride = (size_t)copy_blocks * 256;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) dst[i] = src[i];
@@ -348,6 +370,10 @@ __global__ void __launch_bounds__(256) table_copy_kernel(const u32x4* __restrict
       state->made = action == kWtMade;
       state->done = 0;
     }
+    return;
+  }
+  if (frags.out) {
+    frag_pack(frags, (int)((blockIdx.x - copy_blocks) * 256 + threadIdx.x), (int)(gridDim.x - copy_blocks) * 256);
     return;
   }
   // kWtEnsure: every workgroup has read the word before the last of them sets it
@@ -363,13 +389,15 @@ __global__ void __launch_bounds__(256) table_copy_kernel(const u32x4* __restrict
     state->made = 1;
   }
 }
-void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, const WtCall& wt, hipStream_t st) {
+void launch_table_copy(const void* src_device_view, void* dst, size_t bytes, const WtCall& wt, const FragPack& frags,
+                       hipStream_t st) {
   const size_t n16 = bytes / 16;                 // the caller passes a multiple of 16 bytes
   const unsigned blocks = (unsigned)std::min<size_t>((n16 + 255) / 256 + (n16 == 0 && wt.action != kWtKeep), 256);
-  if (blocks == 0) return;
-  hipLaunchKernelGGL(table_copy_kernel, dim3(blocks + (wt.action == kWtEnsure ? kWtBlocks : 0)), dim3(256), 0, st,
+  const unsigned more = wt.action == kWtEnsure ? kWtBlocks : frag_blocks(frags);      // (a small batch has no copy of W)
+  if (blocks + more == 0) return;
+  hipLaunchKernelGGL(table_copy_kernel, dim3(blocks + more), dim3(256), 0, st,
                      static_cast<const u32x4*>(src_device_view), static_cast<u32x4*>(dst), n16, (int)blocks, wt.state, wt.action,
-                     wt.W, wt.Wt, wt.rows, wt.cols);
+                     wt.W, wt.Wt, wt.rows, wt.cols, frags);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1323,6 +1351,299 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
     else         { if (tail) TLORA_GEMM_LAUNCH(false, true, false); else TLORA_GEMM_LAUNCH(false, false, false); }
   }
 #undef TLORA_GEMM_LAUNCH
+}
+
+// ---------------------------------------------------------------------------------------------------
+// A whole direction of a small batch (at most kSmallRows tokens) in two launches.  Such a batch is bound by the stream of W,
+// which the 256 x 256 tiles cannot spread over the chip (a 61-token call of 4096 -> 4096 kept 96 CUs busy for 23 us, at
+// 1.5 TB/s), and by the number of its launches.
+//  small_gemm_kernel: part[split][t][c] = the share `split` of sum_k act[t, k] * Op[k, c], where the columns c are those of the
+//    backbone operand (W, or W^T: its rows) and, behind them, all packed rank rows of the adapters (A_j^T or B_j), for every
+//    token: S_j (dS_j) is what stands in a job's own rows and columns.
+//  small_emit_kernel: adds the shares in order, rounds scale_j S_j to bf16, adds its product with the other adapter matrix, and
+//    writes the rows of Y (dX) and the hi / lo planes of S_j (dS_j).
+// Workgroup of the first: 64 columns, four waves that take 128 k-values each in turn, all tokens.  A wave fetches its 128 x 64
+// piece (16 KB, 128-byte or 256-byte runs) into LDS of its own and waits for nobody: two workgroups per CU have 128 KB
+// in flight, 32 MB on the chip.  Activations go straight from the L2 to registers; from 33 tokens on they are as many bytes as
+// W's piece, and a fragment of 16 rows by 64 bytes takes the address unit longer than 1 KB in a run, so the launch before lays them
+// out as fragments.  The four sums are added through LDS.  61 tokens of eight jobs, 4096 -> 4096: cut shrink, its sums, cut product
+// and its sums 6 + 6 + 23 + 4 us; this 13 + 7 (the call 41.5 -> 26.6 us); forward and backward of 19 tokens, 17408 -> 4096: 194
+// -> 124 us.
+// ---------------------------------------------------------------------------------------------------
+struct SmallParams {
+  const uint16_t* act;       // FRAGS: fragments (frag_pack)   else [T, K] (rows through in_index if given)
+  const uint16_t* W;         // KN: [K, N]   else [N, K]
+  const uint16_t* R;         // packed rank rows [r_rows, K]
+  float* part;               // [splits][T][ld]
+  const int32_t* in_index;
+  int T, K, N, ld, r_rows, w_tiles, splits;
+};
+template <int RB, bool KN>                              // RB: blocks of 16 tokens
+__global__ void __launch_bounds__(256, 2) small_gemm_kernel(SmallParams P) {
+  constexpr bool FRAGS = small_frags(RB);
+  constexpr int PRE = RB <= 4 ? 4 : 1;                 // slices of 32 k-values whose activations are fetched ahead
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[4 * 16384];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_tiles = gridDim.x / P.splits;
+  const int split = blockIdx.x / n_tiles, tile = blockIdx.x - split * n_tiles;
+  const bool rank_rows = tile >= P.w_tiles;            // a tile of packed rank rows: always k-contiguous
+  const int total = P.K / 64;
+  const int s0 = (int)((int64_t)split * total / P.splits), s1 = (int)((int64_t)(split + 1) * total / P.splits);
+  uint8_t* const mine = lds + wave * 16384;
+  const uint32_t mine_lds = lds_addr(mine);
+
+  uint32_t xoff[FRAGS ? 1 : RB];                       // byte offset of the lane's activation rows
+  if (!FRAGS) {
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      const int t = min(b * 16 + (lane & 15), P.T - 1);
+      xoff[b] = (uint32_t)(P.in_index ? P.in_index[t] : t) * (uint32_t)(P.K * 2) + (lane >> 4) * 16;
+    }
+  }
+  // k-contiguous operand: [64 rows][128 k] (256 B per row), 16-byte chunk c of row r at slot c ^ (r & 15).  KN operand: [128 k][64
+  // columns] (128 B per row), the pair of chunks cp of row k at cp ^ f(k), f = bits 1 and 3 of k: the rows that one transposing
+  // read touches fall into distinct 32-byte bank groups.
+  const uint16_t* const rows = rank_rows ? P.R : P.W;
+  const int row_first = rank_rows ? (tile - P.w_tiles) * 64 : tile * 64, row_last = (rank_rows ? P.r_rows : P.N) - 1;
+  const bool kn = KN && !rank_rows;
+  const char* const kn_base = uniform_ptr(reinterpret_cast<const char*>(P.W + tile * 64));
+  const char* const nt_base = uniform_ptr(reinterpret_cast<const char*>(rows));
+  uint32_t woff[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {                        // k-contiguous: rows 4 i .. + 3 of every 16 (they differ by 16 rows)
+    const int r = i * 4 + (lane >> 4);
+    woff[i] = (uint32_t)(((lane & 15) ^ r) * 16);
+  }
+  f32x4 acc[4][RB];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int b = 0; b < RB; ++b) acc[j][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int st = s0 + 2 * wave; st < s1; st += 8) {
+    const int steps = min(2, s1 - st);
+    const int64_t k0 = (int64_t)st * 64;
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));  // the fragments of the piece before are in registers
+    __builtin_amdgcn_sched_barrier(0);
+    if (kn) {
+      for (int h = 0; h < steps; ++h)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {                  // 8 k-rows per load
+          const int kl = h * 64 + i * 8 + (lane >> 3), c = lane & 7;
+          const int f = ((kl >> 1) & 1) | ((kl >> 2) & 2);
+          dma16(kn_base + (k0 + kl) * (int64_t)(P.N * 2) + (((c >> 1) ^ f) * 2 + (c & 1)) * 16, mine_lds + (h * 8 + i) * 1024);
+        }
+    } else {
+      // a piece of one step repeats its 64 k-values: the second half is not read
+      const uint32_t half = steps == 2 ? 255u : 127u;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = min(row_first + i * 4 + (lane >> 4), row_last);
+        dma16(nt_base + (int64_t)r * (P.K * 2) + k0 * 2 + (woff[i & 3] & half), mine_lds + i * 1024);
+      }
+    }
+    u32x4 xf[4][RB];
+    const char* const xb = reinterpret_cast<const char*>(P.act) + (FRAGS ? k0 * (32 * RB) + lane * 16 : k0 * 2);
+    auto fetch_act = [&](int ks) __attribute__((always_inline)) {
+      const int at = ks < 2 * steps ? ks : 0;
+#pragma unroll
+      for (int b = 0; b < RB; ++b) xf[ks][b] = ldg16(FRAGS ? xb + (at * RB + b) * 1024 : xb + xoff[FRAGS ? 0 : b] + at * 64);
+    };
+#pragma unroll
+    for (int ks = 0; ks < PRE; ++ks) fetch_act(ks);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks >= 2 * steps) break;
+      if (ks + PRE < 4) fetch_act(ks + PRE);
+      bf16x8 wf[4];
+      if (kn) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int s = lane & 15, kl = ks * 32 + (lane >> 4) * 8 + (s >> 2);     // (kl and kl + 4 share bits 1 and 3)
+          const int f = ((kl >> 1) & 1) | ((kl >> 2) & 2);
+          const uint8_t* const a = mine + kl * 128 + ((j ^ f) * 32) + (s & 3) * 8;
+          s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a));
+          s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a + 4 * 128));
+          typedef short s16x8 __attribute__((ext_vector_type(8)));
+          wf[j] = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = lane & 15, c = ks * 4 + (lane >> 4);
+          wf[j] = as_bf16x8(*reinterpret_cast<const u32x4*>(mine + (j * 16 + r) * 256 + ((c ^ r) << 4)));
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[j][b] = mfma16(wf[j], as_bf16x8(xf[ks][b]), acc[j][b]);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  // sums of the four waves, 64 tokens at a time: [64 tokens][64 columns] fp32 per wave, 16-byte chunk c of token r at c ^ (r & 15)
+  float* const dst = P.part + (int64_t)split * P.T * P.ld + (rank_rows ? P.N + row_first : row_first);
+#pragma unroll
+  for (int m = 0; m < (RB + 3) / 4; ++m) {
+    if (m) __syncthreads();
+#pragma unroll
+    for (int b = 0; b < (RB < 4 ? RB : 4); ++b)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = b * 16 + (lane & 15), c = j * 4 + (lane >> 4);
+        *reinterpret_cast<f32x4*>(mine + r * 256 + ((c ^ (r & 15)) << 4)) = acc[j][m * 4 + b];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < (RB < 4 ? RB : 4); ++h) {
+      const int r = h * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
+      if (m * 64 + r < P.T) {
+        const uint8_t* const a = lds + r * 256 + ((c ^ (r & 15)) << 4);
+        f32x4 v = *reinterpret_cast<const f32x4*>(a);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4*>(a + w * 16384);
+        *reinterpret_cast<f32x4*>(dst + (int64_t)(m * 64 + r) * P.ld + c * 4) = v;
+      }
+    }
+  }
+}
+
+// One workgroup = 4 tokens x 256 columns; its halves take the lower and the upper ranks of a token.  Bound by latency: the sums of
+// the backbone product are fetched before the tokens' jobs are known, and two times eight rank rows are in flight.  The rank sums
+// of its tokens are made by every workgroup of a token anew (they are few).
+constexpr int kSmallEmitRows = 4;
+__global__ void __launch_bounds__(256) small_emit_kernel(const JobDev* __restrict__ jobs, const TileDev* __restrict__ tiles,
+                                                         const float* __restrict__ part, int splits, int T, int N, int ld,
+                                                         const uint16_t* __restrict__ E /* [R + 32, N] */,
+                                                         uint16_t* __restrict__ out, const int32_t* __restrict__ out_index,
+                                                         uint16_t* __restrict__ Shi, uint16_t* __restrict__ Slo) {
+  __shared__ EmitRow row[kSmallEmitRows];
+  __shared__ float sv[kSmallEmitRows][1024];
+  __shared__ f32x4 upper[2][128];
+  const TileDev td = tiles[0];
+  const int t0 = (int)blockIdx.y * kSmallEmitRows;
+  const int r = (threadIdx.x >> 5) & 3, half = threadIdx.x >> 7, t = t0 + r, n = (int)blockIdx.x * 256 + (int)(threadIdx.x & 31) * 8;
+  const int64_t stride = (int64_t)T * ld;
+  const float* const prow = part + (int64_t)min(t, T - 1) * ld;
+  auto sum8 = [&](const float* src, float (&v)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < splits; ++k) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(src + k * stride), b = *reinterpret_cast<const f32x4*>(src + k * stride + 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { v[i] += a[i];  v[4 + i] += b[i]; }
+    }
+  };
+  float a[8];                                        // the backbone's sums, on their way during the search below
+  if (out && !half) {
+    sum8(prow + min(n, N - 8), a);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = 0.f;
+  }
+  if ((int)threadIdx.x < kSmallEmitRows) row[threadIdx.x] = EmitRow{0, 0, 0, 0, 0.f};
+  __syncthreads();
+  for (int j = td.first + threadIdx.x; j <= td.last; j += 256) {     // (the jobs' segments are disjoint: one entry per row)
+    const int row0 = jobs[j].row0, row1 = jobs[j].row1;
+    const int lo = max(row0, t0), hi = min(row1, t0 + kSmallEmitRows);
+    if (lo >= hi) continue;
+    const JobDev jb = jobs[j];
+    for (int t = lo; t < hi; ++t)
+      row[t - t0] = EmitRow{jb.soff + (int64_t)(t - row0) * jb.rpad, jb.roff, jb.rpad,
+                            t == row1 - 1 ? (kGradStep - (row1 - row0) % kGradStep) % kGradStep : 0, jb.scale};
+  }
+  __syncthreads();
+  const EmitRow e = row[r];
+  for (int p = (int)(half * 32 + (threadIdx.x & 31)) * 8; p < e.rpad; p += 512) {
+    float v[8];
+    sum8(prow + N + e.col + p, v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sv[r][p + i] = (float)(__bf16)(e.scale * v[i]);
+    if (blockIdx.x == 0 && Shi) {
+      float lo[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) lo[i] = v[i] - (float)(__bf16)v[i];
+      const int64_t at = e.at + p;
+      *reinterpret_cast<u32x4*>(Shi + at) =
+          u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+      *reinterpret_cast<u32x4*>(Slo + at) =
+          u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+      for (int i = 1; i <= e.pad; ++i) {            // zero pad rows up to the next multiple of kGradStep
+        *reinterpret_cast<u32x4*>(Shi + at + (int64_t)i * e.rpad) = u32x4{0, 0, 0, 0};
+        *reinterpret_cast<u32x4*>(Slo + at + (int64_t)i * e.rpad) = u32x4{0, 0, 0, 0};
+      }
+    }
+  }
+  __syncthreads();
+  if (!out) return;
+  const int mid = (e.rpad / 8 + 1) / 2 * 8, p0 = half ? mid : 0, p1 = half ? e.rpad : mid;
+  const uint16_t* const erow = E + (int64_t)e.col * N + min(n, N - 8);
+  u32x4 b[2][8];                                     // rank rows, the next eight in flight while eight are added
+  auto fetch = [&](int h, int p) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[h][i] = ldg16(erow + (int64_t)(p + i) * N);
+  };
+  if (p0 < p1) fetch(0, p0);
+  auto add = [&](int h, int p) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float x = sv[r][p + i];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[2 * q] = fmaf(x, __builtin_bit_cast(float, b[h][i][q] << 16), a[2 * q]);
+        a[2 * q + 1] = fmaf(x, __builtin_bit_cast(float, b[h][i][q] & 0xffff0000u), a[2 * q + 1]);
+      }
+    }
+  };
+  for (int p = p0; p < p1; p += 16) {
+    if (p + 8 < p1) fetch(1, p + 8);
+    add(0, p);
+    if (p + 16 < p1) fetch(0, p + 16);
+    if (p + 8 < p1) add(1, p + 8);
+  }
+  if (half) {
+    upper[0][threadIdx.x & 127] = f32x4{a[0], a[1], a[2], a[3]};
+    upper[1][threadIdx.x & 127] = f32x4{a[4], a[5], a[6], a[7]};
+  }
+  __syncthreads();
+  if (half || t >= T || n >= N) return;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] += upper[i >> 2][threadIdx.x][i & 3];
+  const int64_t orow = out_index ? out_index[t] : t;
+  *reinterpret_cast<u32x4*>(out + orow * N + n) =
+      u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7])};
+}
+
+void launch_small(bool w_is_kn, const JobDev* jobs, const TileDev* tiles, const uint16_t* act, const uint16_t* W,
+                  const uint16_t* rank_rows, const uint16_t* expand_rows, int r_total, uint16_t* out, const int32_t* out_index,
+                  const int32_t* in_index, int T, int K, int N, int splits, float* part, uint16_t* S_hi, uint16_t* S_lo,
+                  hipStream_t st) {
+  SmallParams P;
+  P.act = act;  P.W = W;  P.R = rank_rows;  P.part = part;  P.in_index = in_index;
+  P.T = T;  P.K = K;  P.N = N;  P.r_rows = r_total + 32;  P.splits = splits;
+  P.w_tiles = out ? N / 64 : 0;
+  P.ld = small_ld(N, r_total);
+  const int n_tiles = P.w_tiles + (r_total + 63) / 64;
+  if (n_tiles == 0) return;
+  const dim3 grid(n_tiles * splits);
+#define TLORA_SMALL(RB)                                                                                     \
+  do {                                                                                                       \
+    if (w_is_kn) hipLaunchKernelGGL((small_gemm_kernel<RB, true>), grid, dim3(256), 0, st, P);               \
+    else         hipLaunchKernelGGL((small_gemm_kernel<RB, false>), grid, dim3(256), 0, st, P);              \
+  } while (0)
+  switch (small_blocks(T)) {
+    case 1: TLORA_SMALL(1); break;
+    case 2: TLORA_SMALL(2); break;
+    case 4: TLORA_SMALL(4); break;
+    default: TLORA_SMALL(8); break;
+  }
+#undef TLORA_SMALL
+  hipLaunchKernelGGL(small_emit_kernel, dim3(out ? (N + 255) / 256 : 1, (T + kSmallEmitRows - 1) / kSmallEmitRows), dim3(256), 0, st, jobs,
+                     tiles, part, splits, T, N, P.ld, expand_rows, out, out_index, S_hi, S_lo);
 }
 
 // ---------------------------------------------------------------------------------------------------
