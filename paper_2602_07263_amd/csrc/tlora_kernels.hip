@@ -1952,110 +1952,160 @@ void launch_grad_reduce(const JobDev* jobs, const GradGroup* groups, int num_gro
 }
 
 // ---------------------------------------------------------------------------------------------------
-// fp32 configuration: strided products C (+)= alpha * A.B.  Operands and
-// results are fp32; the running sums are kept in fp64 so that long token reductions (dA, dB) stay
-// within 1e-5 of the exact value even where the result is close to zero.
-// A workgroup makes a TS x TS tile of C, each thread (TS / 16)^2 of its elements, in K-steps of 1024 / TS whose operands
-// (four elements of A and of B per thread) are fetched while the step before is multiplied.  The table lists tiles of 64;
-// TS = 32 runs four workgroups per entry.  Small problems are bound by latency: with ten workgroups (128 tokens, 256 x 256)
-// each K-step of 16 took 2.3 us, nearly all of it its eight loads, one after the other:
-// 37 us the launch, 15 us now; 2048 tokens of 1024 -> 512 at rank 64, a pass 780 -> 503 us.
+// fp32 configuration: strided products C (+)= alpha * A.B.  Operands and results are fp32; the products and running sums are
+// fp64, on v_mfma_f64_16x16x4_f64 (lane l feeds row / column l % 16, k = l / 16, and owns of the result column l % 16, rows
+// l / 16 + 4 i), so that long token reductions (dA, dB) stay within 1e-5 of the exact value even where the result is close to zero.
+// A workgroup makes a tile of C; the table lists tiles of 64.
+//  f32_units_kernel<64>: a 64 x 64 tile, 32 x 32 for each of four waves, in K-steps of 32 that are fetched while the one before is multiplied.
+//  f32_units_kernel<32>: four workgroups per entry, a 32 x 32 tile each; each of eight waves takes 32 of every 256 k-values and adds
+//    its sums to the others' through LDS.  Small problems are bound by the latency of one K-step after the other: 128 tokens, 256 x 256,
+//    is one step this way.
+// Measured against fp64 vector arithmetic in tiles of the same sizes: 128 tokens, 256 x 256, the first launch 14.8 -> 8.9 us and a pass
+// 48.3 -> 39.9; 1046 tokens, 752 x 584, 205 -> 156; 1563 tokens, 896 x 152, 246 -> 163 (four waves with a quarter of K each: 10.5,
+// 45.0, 152, 159 us, and slower than eight on most smaller problems).
 // ---------------------------------------------------------------------------------------------------
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+// Loads without branches (clamped to the operand, zeroed on the way to LDS) and through pointers known to be global: a load
+// under a condition, or one that might be an LDS access, is waited for before the next is issued.
+typedef const __attribute__((address_space(1))) float* F32Global;
+
+__device__ __forceinline__ void f32_store(const F32Unit& u, int m, int n, double sum) {
+  if (m >= u.M || n >= u.N) return;
+  __attribute__((address_space(1))) float* const c = (__attribute__((address_space(1))) float*)u.C + (int64_t)m * u.c_rs + n;
+  const double v = (double)u.alpha * sum;
+  *c = (float)(u.accumulate ? (double)*c + v : v);
+}
+
 template <int TS>
-__global__ void __launch_bounds__(256) f32_units_kernel(const F32Unit* __restrict__ units,
-                                                        const F32Tile* __restrict__ tiles) {
-  constexpr int BK = 1024 / TS, E = TS / 16, SUB = 64 / TS;
-  __shared__ float As[2][BK][TS + 1];
-  __shared__ float Bs[2][BK][TS + 1];
+__global__ void __launch_bounds__(TS == 32 ? 512 : 256) f32_units_kernel(const F32Unit* __restrict__ units, const F32Tile* __restrict__ tiles) {
+  constexpr bool SHARES = TS == 32;                      // the waves share the tile and split K
+  constexpr int WAVES = SHARES ? 8 : 4, SUB = 64 / TS, THREADS = SHARES ? 64 : 256, BK = 32;
+  constexpr int E = BK * TS / THREADS;                   // elements of A and of B per thread and step
+  constexpr int BUFS = SHARES ? 1 : 2, SETS = SHARES ? WAVES : 1;
+  __shared__ __attribute__((aligned(16))) float lds[SETS * BUFS * 2 * BK * (TS + 1)];
   const F32Tile t = tiles[blockIdx.x / (SUB * SUB)];
   const F32Unit u = units[t.unit];
   const int sub = (int)(blockIdx.x % (SUB * SUB));
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int m0 = t.tm * 64 + sub / SUB * TS, n0 = t.tn * 64 + sub % SUB * TS;
   if (m0 >= u.M || n0 >= u.N) return;
-  // element i of a thread's four: consecutive threads follow the operand's contiguous direction
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto at = [&](int buf, int operand) { return lds + (((SHARES ? wave : 0) * BUFS + buf) * 2 + operand) * BK * (TS + 1); };
+  // k-values of a step: BK, or for each wave its share of K while K is short (whole fours)
+  const int kq = SHARES ? min(BK, ((u.K + WAVES - 1) / WAVES + 3) / 4 * 4) : BK, step = SHARES ? WAVES * kq : BK;
+  const int kw = SHARES ? wave * kq : 0;
+  // A load instruction follows the operand's contiguous direction with CL = 64 lanes, or with 32 and takes two of the other.  So
+  // the addresses are one base, lane offsets and multiples of a row: computed per element, the addresses of a thread (27
+  // instructions each) were two thirds of a short product's time.
   const bool a_along_m = u.a_rs == 1 && u.a_cs != 1, b_along_k = u.b_rs == 1 && u.b_cs != 1;
-  auto a_at = [&](int i, int& kk, int& mm) {
-    const int q = threadIdx.x + i * 256;
-    kk = a_along_m ? q / TS : q % BK;  mm = a_along_m ? q % TS : q / BK;
-  };
-  auto b_at = [&](int i, int& kk, int& nn) {
-    const int q = threadIdx.x + i * 256;
-    kk = b_along_k ? q % BK : q / TS;  nn = b_along_k ? q / BK : q % TS;
-  };
-  // Loads without branches (clamped to the operand, zeroed on the way to LDS) and through pointers known to be global: a load
-  // under a condition, or one that might be an LDS access, is waited for before the next is issued.
-  typedef const __attribute__((address_space(1))) float* GlobalPtr;
-  const GlobalPtr gA = (GlobalPtr)u.A, gB = (GlobalPtr)u.B;
-  float ra[4], rb[4];
-  auto fetch = [&](int k0) {
+  constexpr int KL = 32, XL = TS;                        // lanes along k, along m / n
+  float ra[E], rb[E];
+  auto fetch = [&](auto cl, float (&r)[E], const float* p, int64_t sc, int64_t so, int c0, int c_end, int o0, int o_end) __attribute__((always_inline)) {
+    constexpr int CL = decltype(cl)::value, PER = 64 / CL, SPAN = SHARES ? E * PER : 4 * E * PER;
+    const int cf = min(c0, c_end - 1), of = min(o0, o_end - 1), rest = o_end - 1 - of;      // (tile-relative: 32-bit byte offsets)
+    const uint32_t one = (uint32_t)min(lane & (CL - 1), c_end - 1 - cf) * (uint32_t)sc * 4u, row = (uint32_t)so * 4u;
+    typedef const __attribute__((address_space(1))) char* Bytes;
+    const Bytes base = (Bytes)((F32Global)p + (int64_t)cf * sc + (int64_t)of * so);
+    if (rest + 1 >= SPAN) {
+      const uint32_t off = one + (uint32_t)(lane / CL) * row;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int kk, mm, kb, nn;
-      a_at(i, kk, mm);  b_at(i, kb, nn);
-      const int m = m0 + mm, n = n0 + nn, k = k0 + kk, k2 = k0 + kb;
-      ra[i] = gA[(int64_t)min(m, u.M - 1) * u.a_rs + (int64_t)min(k, u.K - 1) * u.a_cs];
-      rb[i] = gB[(int64_t)min(k2, u.K - 1) * u.b_rs + (int64_t)min(n, u.N - 1) * u.b_cs];
-    }
-  };
-  auto store = [&](int buf, int k0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int kk, mm, kb, nn;
-      a_at(i, kk, mm);  b_at(i, kb, nn);
-      As[buf][kk][mm] = m0 + mm < u.M && k0 + kk < u.K ? ra[i] : 0.f;
-      Bs[buf][kb][nn] = n0 + nn < u.N && k0 + kb < u.K ? rb[i] : 0.f;
-    }
-  };
-  double acc[E][E] = {};
-  if (u.K > 0) {
-    fetch(0);
-    store(0, 0);
-    __syncthreads();
-  }
-  for (int k0 = 0, buf = 0; k0 < u.K; k0 += BK, buf ^= 1) {
-    const bool more = k0 + BK < u.K;
-    if (more) fetch(k0 + BK);
-#pragma unroll 8
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[E], b[E];
-#pragma unroll
-      for (int i = 0; i < E; ++i) a[i] = As[buf][kk][ty * E + i];
-#pragma unroll
-      for (int j = 0; j < E; ++j) b[j] = Bs[buf][kk][tx * E + j];
+      for (int i = 0; i < E; ++i) r[i] = *(F32Global)(base + (off + (uint32_t)(PER * (SHARES ? i : 4 * i + wave)) * row));
+    } else {
 #pragma unroll
       for (int i = 0; i < E; ++i)
-#pragma unroll
-        for (int j = 0; j < E; ++j) acc[i][j] = __builtin_fma((double)a[i], (double)b[j], acc[i][j]);
+        r[i] = *(F32Global)(base + (one + (uint32_t)min(PER * (SHARES ? i : 4 * i + wave) + lane / CL, rest) * row));
     }
-    if (more) store(buf ^ 1, k0 + BK);
+  };
+  auto put = [&](auto cl, const float (&r)[E], float* dst, int dc, int dstep, int c0, int c_end, int o0, int o_end) __attribute__((always_inline)) {
+    constexpr int CL = decltype(cl)::value, PER = 64 / CL;
+    const int c = lane & (CL - 1), oo = lane / CL;
+    const bool ok = c0 + c < c_end;
+    float* const d = dst + c * dc + oo * dstep;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const int o = PER * (SHARES ? i : 4 * i + wave);
+      d[o * dstep] = ok && o0 + o + oo < o_end ? r[i] : 0.f;
+    }
+  };
+  auto fetch_both = [&](int k0) __attribute__((always_inline)) {
+    if (a_along_m) fetch(std::integral_constant<int, XL>{}, ra, u.A, u.a_rs, u.a_cs, m0, u.M, k0, u.K);
+    else           fetch(std::integral_constant<int, KL>{}, ra, u.A, u.a_cs, u.a_rs, k0, u.K, m0, u.M);
+    if (b_along_k) fetch(std::integral_constant<int, KL>{}, rb, u.B, u.b_rs, u.b_cs, k0, u.K, n0, u.N);
+    else           fetch(std::integral_constant<int, XL>{}, rb, u.B, u.b_cs, u.b_rs, n0, u.N, k0, u.K);
+  };
+  auto store_both = [&](int buf, int k0) __attribute__((always_inline)) {
+    if (a_along_m) put(std::integral_constant<int, XL>{}, ra, at(buf, 0), 1, TS + 1, m0, u.M, k0, u.K);
+    else           put(std::integral_constant<int, KL>{}, ra, at(buf, 0), TS + 1, 1, k0, u.K, m0, u.M);
+    if (b_along_k) put(std::integral_constant<int, KL>{}, rb, at(buf, 1), TS + 1, 1, k0, u.K, n0, u.N);
+    else           put(std::integral_constant<int, XL>{}, rb, at(buf, 1), 1, TS + 1, n0, u.N, k0, u.K);
+  };
+  f64x4 acc[2][2] = {};
+  const int mw = SHARES ? 0 : (wave >> 1) * 32, nw = SHARES ? 0 : (wave & 1) * 32;
+  auto multiply = [&](int buf) {
+    const float* const As = at(buf, 0) + (lane >> 4) * (TS + 1) + mw + (lane & 15);
+    const float* const Bs = at(buf, 1) + (lane >> 4) * (TS + 1) + nw + (lane & 15);
+#pragma unroll 4
+    for (int k = 0; k < kq; k += 4) {
+      double a[2], b[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        a[h] = (double)As[k * (TS + 1) + h * 16];
+        b[h] = (double)Bs[k * (TS + 1) + h * 16];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma64(a[i], b[j], acc[i][j]);
+    }
+  };
+  if (u.K > 0) {
+    fetch_both(kw);
+    store_both(0, kw);
     __syncthreads();
   }
-  __attribute__((address_space(1))) float* const gC = (__attribute__((address_space(1))) float*)u.C;
-  float old[E][E] = {};
-  if (u.accumulate) {
-#pragma unroll
-    for (int i = 0; i < E; ++i)
-#pragma unroll
-      for (int j = 0; j < E; ++j)
-        old[i][j] = gC[(int64_t)min(m0 + ty * E + i, u.M - 1) * u.c_rs + min(n0 + tx * E + j, u.N - 1)];
+  for (int k0 = 0, buf = 0; k0 < u.K; k0 += step, buf ^= BUFS - 1) {
+    const bool more = k0 + step < u.K;
+    if (more) fetch_both(k0 + step + kw);
+    multiply(buf);
+    if (SHARES && more) __syncthreads();               // (one buffer per wave: it is read before it is filled again)
+    if (more) store_both(buf ^ (BUFS - 1), k0 + step + kw);
+    __syncthreads();
   }
+  if (!SHARES) {
 #pragma unroll
-  for (int i = 0; i < E; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int m = m0 + ty * E + i, n = n0 + tx * E + j;
-      const double v = (double)u.alpha * acc[i][j];
-      if (m < u.M && n < u.N) gC[(int64_t)m * u.c_rs + n] = (float)(u.accumulate ? (double)old[i][j] + v : v);
-    }
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          f32_store(u, m0 + mw + i * 16 + (lane >> 4) + 4 * e, n0 + nw + j * 16 + (lane & 15), acc[i][j][e]);
+    return;
+  }
+  static_assert(!SHARES || sizeof(double) * WAVES * 32 * 32 <= sizeof(lds), "the shares' sums fit into the tiles' place");
+  double* const sums = reinterpret_cast<double*>(lds);     // (the last step ended in a barrier)
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        sums[(wave * 32 + i * 16 + (lane >> 4) + 4 * e) * 32 + j * 16 + (lane & 15)] = acc[i][j][e];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int q = (int)threadIdx.x + i * 512, m = q >> 5, n = q & 31;
+    double v = sums[m * 32 + n];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) v += sums[(w * 32 + m) * 32 + n];
+    f32_store(u, m0 + m, n0 + n, v);
+  }
 }
-
-// Tiles of 32 while tiles of 64 would leave CUs without a workgroup; from 256 on the larger tile's fewer LDS reads and
-// conversions per product count for more.
+// Shares of K while tiles of 64 would leave CUs without a workgroup; from 256 on the larger tile's fewer loads per product
+// count for more.
 void launch_f32_units(const F32Unit* units, const F32Tile* tiles, int num_tiles, hipStream_t st) {
   if (num_tiles == 0) return;
   if (num_tiles < 256)
-    hipLaunchKernelGGL(f32_units_kernel<32>, dim3(num_tiles * 4), dim3(256), 0, st, units, tiles);
+    hipLaunchKernelGGL(f32_units_kernel<32>, dim3(num_tiles * 4), dim3(512), 0, st, units, tiles);
   else
     hipLaunchKernelGGL(f32_units_kernel<64>, dim3(num_tiles), dim3(256), 0, st, units, tiles);
 }
