@@ -85,7 +85,8 @@ struct Plan {
   std::vector<ShrinkUnit> stream_units;                 // streaming kernel: shrink_rows x 128 rank columns
   std::vector<GradUnit> gradB_units, gradA_units;      // dB: columns over d_out;  dA: columns over d_in;
 
-  int64_t gradB_partial = 0, gradA_partial = 0;         // floats of partial tiles
+  bool grads_merged = false;                            // dB and dA share a launch
+  int64_t grad_partial = 0;                             // floats of partial tiles, those of dB first
   std::vector<GradGroup> gradB_groups, gradA_groups;
   int64_t s_elems = 0;                                  // elements of the packed S (= dS) buffer
   int64_t atp_elems = 0;
@@ -128,35 +129,39 @@ int validate(const tlora_problem_t* p) {
   return TLORA_OK;
 }
 
-// Work units of the dA / dB token reductions (rank-aware nano-batches of one job's tokens).  A job's rank
-// rows are cut into blocks of 128, of which a unit multiplies only the live 32-row sub-blocks.  A token
-// chunk streams chunk * 256 * 2 bytes of the activation and leaves a partial tile of live_rows * 256 * 4
-// bytes that is written and read once more, so the default chunk is 32 * live_rows tokens (partial traffic
-// <= ~12 %).  If that gives too few units to fill the GPU the chunks are shortened (not below `grad_tokens`).
+// Work units of the dA / dB token reductions (rank-aware nano-batches of one job's tokens).  A job's rank rows are cut into blocks
+// of 128, of which a unit multiplies only the live 32-row sub-blocks, and its tokens into chunks.  A job of one chunk stores its
+// gradient itself; the chunks of others leave partial tiles of live_rows * 256 * 4 bytes that are written and read once more.
 // Units are issued longest first.
 constexpr int64_t kGradUnitsWanted = 1024;
 // Upper bounds over every batch in which no job has more tokens than in this one (see Reserve).
 struct GradBounds {
   int64_t units = 0, floats = 0;
 };
-bool build_grad_units(const Plan& pl, int D, std::vector<GradUnit>& units, std::vector<GradGroup>& groups,
-                      int64_t& partial_floats, GradBounds& bounds) {
+constexpr int kGradBlockRanks = kGradMaxBlocks * kGradRanks;
+int grad_live_blocks(const JobDev& jb, int pb) {
+  return std::min(kGradMaxBlocks, (jb.rpad - pb * kGradBlockRanks + kGradRanks - 1) / kGradRanks);
+}
+// Output tiles of dA / dB (256 columns x 128 ranks) over D columns.
+int64_t grad_tiles(const Plan& pl, int D) {
+  int64_t n = 0;
+  for (const JobDev& jb : pl.jobs) n += jb.rank > 0 ? (jb.rpad + kGradBlockRanks - 1) / kGradBlockRanks : 0;
+  return n * ((D + kGradCols - 1) / kGradCols);
+}
+int grad_chunk(int tokens) {
+  tokens = std::max(g_opt.grad_tokens, (tokens + kGradStep - 1) / kGradStep * kGradStep);
+  return std::min(tokens, kGradMaxTokens);           // the kernel stages at most that many row indices per unit
+}
+// Bounds for D columns; false: more units than a launch may have (refused before the tables are built).
+bool grad_bounds(const Plan& pl, int D, GradBounds& bounds) {
   const int ncb = (D + kGradCols - 1) / kGradCols;
-  const int pb_rows = kGradMaxBlocks * kGradRanks;
-  auto live_blocks = [&](const JobDev& jb, int pb) {
-    return std::min(kGradMaxBlocks, (jb.rpad - pb * pb_rows + kGradRanks - 1) / kGradRanks);
-  };
-  auto chunk_of = [&](int live, double shrink) {
-    int chunk = std::max(g_opt.grad_tokens, (int)(32 * kGradRanks * live * shrink));
-    chunk = (chunk + kGradStep - 1) / kGradStep * kGradStep;
-    return std::min(chunk, kGradMaxTokens);          // the kernel stages at most that many row indices per unit
-  };
+  auto chunk_of = [&](int live, double shrink) { return grad_chunk((int)(32 * kGradRanks * live * shrink)); };
   auto count = [&](double shrink) {
     GradBounds n;
     for (const JobDev& jb : pl.jobs) {
       if (jb.rank == 0 || jb.row1 == jb.row0) continue;
-      for (int pb = 0; pb * pb_rows < jb.rpad; ++pb) {
-        const int mb = live_blocks(jb, pb), chunk = chunk_of(mb, shrink);
+      for (int pb = 0; pb * kGradBlockRanks < jb.rpad; ++pb) {
+        const int mb = grad_live_blocks(jb, pb), chunk = chunk_of(mb, shrink);
         const int64_t u = (int64_t)((jb.row1 - jb.row0 + chunk - 1) / chunk) * ncb;
         n.units += u;
         n.floats += u * mb * kGradRanks * kGradCols;
@@ -166,54 +171,97 @@ bool build_grad_units(const Plan& pl, int D, std::vector<GradUnit>& units, std::
   };
   double shrink = 1.0;
   while (shrink > 1.0 / 64 && count(shrink).units < kGradUnitsWanted) shrink *= 0.5;
-  if (count(shrink).units > kMaxUnits) return false;      // refused before the tables are built
-  {
-    // A smaller batch with shrink 1 has what this one counts at 1, or less.  With a smaller factor it has at most twice the
-    // units of the factor before (a chunk is at least half as long), which were too few, and of each tile height at most those
-    // of the shortest chunks: the tallest tiles first, that many units at most.
-    const GradBounds whole = count(1.0);
-    int64_t by_height[kGradMaxBlocks + 1] = {}, left = 2 * (kGradUnitsWanted - 1);
-    for (const JobDev& jb : pl.jobs)
-      for (int pb = 0; jb.rank > 0 && pb * pb_rows < jb.rpad; ++pb) {
-        const int mb = live_blocks(jb, pb), chunk = chunk_of(mb, 0.0);
-        by_height[mb] += (int64_t)((jb.row1 - jb.row0 + chunk - 1) / chunk) * ncb;
-      }
-    for (int mb = kGradMaxBlocks; mb > 0; --mb) {
-      const int64_t u = std::min(by_height[mb], left);
-      bounds.units += u;  bounds.floats += u * mb * kGradRanks * kGradCols;  left -= u;
+  if (count(shrink).units > kMaxUnits || grad_tiles(pl, D) > kMaxUnits) return false;
+  // Grows with every job's tokens: what chunks of 1024 tokens per live block give, or, of each tile height at most what the
+  // shortest chunks give, the tallest tiles first, 2046 units.  The chunks below are chosen within it (those of 4096 tokens always
+  // are); the units of idle jobs, which store zeros, come on top.
+  const GradBounds whole = count(1.0);
+  int64_t by_height[kGradMaxBlocks + 1] = {}, left = 2 * (kGradUnitsWanted - 1);
+  for (const JobDev& jb : pl.jobs)
+    for (int pb = 0; jb.rank > 0 && pb * kGradBlockRanks < jb.rpad; ++pb) {
+      const int mb = grad_live_blocks(jb, pb), chunk = chunk_of(mb, 0.0);
+      by_height[mb] += (int64_t)((jb.row1 - jb.row0 + chunk - 1) / chunk) * ncb;
     }
-    bounds.units = std::max(whole.units, bounds.units);
-    bounds.floats = std::max(whole.floats, bounds.floats);
+  for (int mb = kGradMaxBlocks; mb > 0; --mb) {
+    const int64_t u = std::min(by_height[mb], left);
+    bounds.units += u;  bounds.floats += u * mb * kGradRanks * kGradCols;  left -= u;
   }
-  partial_floats = 0;
+  bounds.units = std::max(whole.units, bounds.units) + grad_tiles(pl, D);
+  bounds.floats = std::max(whole.floats, bounds.floats);
+  return true;
+}
+// Chunks whose units take at most `limit` us: a step of 32 tokens takes 0.13 us and 0.155 for every live block.
+double grad_step_us(int mb) { return 0.13 + 0.155 * mb; }
+struct GradCost {
+  double longest = 0.0, sum = 0.0, bytes = 0.0;
+  int64_t units = 0, floats = 0;
+};
+int grad_chunk_of(int mb, double limit) { return grad_chunk((int)std::min<double>(kGradMaxTokens, kGradStep * limit / grad_step_us(mb))); }
+GradCost grad_cost(const Plan& pl, int D, double limit) {
+  GradCost g;
+  const int ncb = (D + kGradCols - 1) / kGradCols;
+  for (const JobDev& jb : pl.jobs) {
+    const int T = jb.row1 - jb.row0;
+    for (int pb = 0; jb.rank > 0 && pb * kGradBlockRanks < jb.rpad; ++pb) {
+      const int mb = grad_live_blocks(jb, pb), chunk = grad_chunk_of(mb, limit), n = std::max(1, (T + chunk - 1) / chunk);
+      const double step = grad_step_us(mb), fixed = 3.0 + mb;
+      g.longest = std::max(g.longest, fixed + step * ((std::min(T, chunk) + kGradStep - 1) / kGradStep));
+      g.sum += ncb * (n * fixed + step * ((T + kGradStep - 1) / kGradStep));
+      g.bytes += (double)ncb * T * kGradCols * 2;
+      g.units += (int64_t)n * ncb;
+      if (n > 1) g.floats += (int64_t)n * ncb * mb * kGradRanks * kGradCols;
+    }
+  }
+  return g;
+}
+// The limit for one launch over the given widths: the cheapest of a few, by the longest unit, the units' sum over 256 CUs, the bytes
+// of the activations at 5 TB/s, and for the partial tiles a launch of 5 us and their bytes, written and read, at 4 TB/s.
+double grad_limit(const Plan& pl, const int* widths, const GradBounds* bounds, int n) {
+  double best = 1e9, best_us = 0.0;
+  for (double limit : {1e9, 96.0, 64.0, 48.0, 32.0, 24.0, 16.0, 12.0, 8.0, 6.0}) {
+    double longest = 0.0, sum = 0.0, bytes = 0.0, extra = 0.0;
+    bool fits = true;
+    for (int i = 0; i < n; ++i) {
+      const GradCost g = grad_cost(pl, widths[i], limit);
+      fits = fits && g.units <= bounds[i].units && g.floats <= bounds[i].floats;
+      longest = std::max(longest, g.longest);  sum += g.sum;  bytes += g.bytes;
+      if (g.floats > 0) extra += 5.0 + (double)g.floats * 8 / 4.0e6;
+    }
+    const double us = std::max({longest, sum / 256, bytes / 5.0e6}) + 0.5 * longest * (sum > 256 * longest) + extra;
+    if (limit == 1e9 || (fits && us < best_us)) { best = limit;  best_us = us; }
+  }
+  return best;
+}
+void build_grad_units(const Plan& pl, int D, double limit, std::vector<GradUnit>& units, std::vector<GradGroup>& groups,
+                      int64_t& partial_floats /* in: first free float, out: past the last */) {
+  const int ncb = (D + kGradCols - 1) / kGradCols;
   for (int j = 0; j < pl.J; ++j) {
     const JobDev& jb = pl.jobs[j];
     if (jb.rank == 0) continue;
     const int Tj = jb.row1 - jb.row0;
-    for (int pb = 0; pb * pb_rows < jb.rpad; ++pb) {
-      const int mb = live_blocks(jb, pb);
-      const int chunk = chunk_of(mb, shrink);
-      const int nchunks = Tj > 0 ? (Tj + chunk - 1) / chunk : 0;
+    for (int pb = 0; pb * kGradBlockRanks < jb.rpad; ++pb) {
+      const int mb = grad_live_blocks(jb, pb), chunk = grad_chunk_of(mb, limit);
+      const int nchunks = std::max(1, (Tj + chunk - 1) / chunk);
       for (int cb = 0; cb < ncb; ++cb) {
+        if (nchunks == 1) {
+          units.push_back(GradUnit{j, jb.row0, jb.row1, cb, pb, mb, -1});
+          continue;
+        }
         GradGroup g{};
         g.job = j;  g.cb = cb;  g.pb = pb;  g.mb = mb;  g.nunits = nchunks;  g.part_off = partial_floats;
         for (int c = 0; c < nchunks; ++c) {
-          GradUnit u{};
-          u.job = j;  u.t0 = jb.row0 + c * chunk;  u.t1 = std::min(jb.row1, u.t0 + chunk);  u.cb = cb;  u.pb = pb;
-          u.mb = mb;  u.part_off = partial_floats;
+          const int t0 = jb.row0 + c * chunk;
+          units.push_back(GradUnit{j, t0, std::min(jb.row1, t0 + chunk), cb, pb, mb, partial_floats});
           partial_floats += (int64_t)mb * kGradRanks * kGradCols;
-          units.push_back(u);
         }
         groups.push_back(g);
       }
     }
   }
-  // longest (then heaviest) first: the tail of the launch is made of the short units
+  // longest first: the tail of the launch is made of the short units
   std::stable_sort(units.begin(), units.end(), [](const GradUnit& a, const GradUnit& b) {
-    const int64_t ca = (int64_t)(a.t1 - a.t0) * (4 + a.mb), cb = (int64_t)(b.t1 - b.t0) * (4 + b.mb);
-    return ca > cb;
+    return (a.t1 - a.t0) * grad_step_us(a.mb) > (b.t1 - b.t0) * grad_step_us(b.mb);
   });
-  return true;
 }
 
 // Splits of a streaming shrink over K of a plan whose units have 32 rows: enough that units x splits fill the 512
@@ -376,11 +424,12 @@ Reserve reserve_of(const Plan& pl, const GradBounds& gB, const GradBounds& gA) {
   table(sizeof(TileDev) * pl.tile_jobs.size());
   table(sizeof(ShrinkUnit) * pl.shrink_units.size());
   table(sizeof(ShrinkUnit) * (size_t)stream);
-  table(sizeof(GradUnit) * (size_t)gB.units);
-  table(sizeof(GradGroup) * pl.gradB_groups.size());
-  table(sizeof(GradUnit) * (size_t)gA.units);
-  table(sizeof(GradGroup) * pl.gradA_groups.size());
-  r.partial = std::max(sums_room(pl), sizeof(float) * (size_t)std::max(gB.floats, gA.floats));
+  for (int d = 0; d < 2; ++d) {
+    const int64_t tiles = grad_tiles(pl, d ? pl.d_in : pl.d_out);
+    table(sizeof(GradUnit) * (size_t)(d ? gA.units : gB.units));
+    table(sizeof(GradGroup) * (size_t)tiles);
+  }
+  r.partial = std::max(sums_room(pl), sizeof(float) * (size_t)(gB.floats + gA.floats));
   return r;
 }
 
@@ -470,9 +519,15 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
         }
     }
     if (!fwd_only) {
-      if (!build_grad_units(pl, pl.d_out, pl.gradB_units, pl.gradB_groups, pl.gradB_partial, gB) ||
-          !build_grad_units(pl, pl.d_in, pl.gradA_units, pl.gradA_groups, pl.gradA_partial, gA))
-        return TLORA_EINVAL;
+      if (!grad_bounds(pl, pl.d_out, gB) || !grad_bounds(pl, pl.d_in, gA)) return TLORA_EINVAL;
+      // One launch for both from 32 output tiles on; with fewer either way is a few workgroups.
+      pl.grads_merged = grad_tiles(pl, pl.d_out) + grad_tiles(pl, pl.d_in) >= 32;
+      const int widths[2] = {pl.d_out, pl.d_in};
+      const GradBounds bounds[2] = {gB, gA};
+      const double limit = grad_limit(pl, widths, bounds, pl.grads_merged ? 2 : 1);
+      build_grad_units(pl, pl.d_out, limit, pl.gradB_units, pl.gradB_groups, pl.grad_partial);
+      build_grad_units(pl, pl.d_in, pl.grads_merged ? limit : grad_limit(pl, widths + 1, bounds + 1, 1), pl.gradA_units, pl.gradA_groups,
+                       pl.grad_partial);
     }
   }
 
@@ -1147,20 +1202,21 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     }
   }
   if (want_grads) {
+    const GradSide b = {reinterpret_cast<const GradUnit*>(tb + pl.tb_gBu), Shi, Slo, dYb, pl.d_out, (int)pl.gradB_units.size()};
+    const GradSide a = {reinterpret_cast<const GradUnit*>(tb + pl.tb_gAu), dShi, dSlo, Xb, pl.d_in, (int)pl.gradA_units.size()};
+    const GradSide none;
     {
       Timed t(TLORA_K_RANK_GRAD, st);
-      launch_rank_grad(jobs, reinterpret_cast<const GradUnit*>(tb + pl.tb_gBu), (int)pl.gradB_units.size(), Shi, Slo,
-                       dYb, pl.d_out, partial, in_index, st);
+      launch_rank_grad(jobs, b, pl.grads_merged ? a : none, partial, accumulate, in_index, st);
+    }
+    if (!pl.grads_merged) {
+      Timed t(TLORA_K_RANK_GRAD, st);
+      launch_rank_grad(jobs, none, a, partial, accumulate, in_index, st);
     }
     {
       Timed t(TLORA_K_GRAD_REDUCE, st);
       launch_grad_reduce(jobs, reinterpret_cast<const GradGroup*>(tb + pl.tb_gBg), (int)pl.gradB_groups.size(), partial,
                          pl.d_out, false, accumulate, st);
-    }
-    {
-      Timed t(TLORA_K_RANK_GRAD, st);
-      launch_rank_grad(jobs, reinterpret_cast<const GradUnit*>(tb + pl.tb_gAu), (int)pl.gradA_units.size(), dShi, dSlo,
-                       Xb, pl.d_in, partial, in_index, st);
     }
     {
       Timed t(TLORA_K_GRAD_REDUCE, st);
@@ -2118,38 +2174,36 @@ static int check_plan(const Plan& pl, bool fwd_only) {
     if (int rc = check_shrink(pl.shrink_units, 64, kShrinkCols)) return rc;
     if (int rc = check_shrink(pl.stream_units, pl.shrink_rows, 128)) return rc + 100;
     // 4x: dA / dB work units and their partial tiles
-    auto check_grad = [&](const std::vector<GradUnit>& units, const std::vector<GradGroup>& groups, int64_t partial,
-                          int D) -> int {
-      const int pb_rows = kGradMaxBlocks * kGradRanks;
-      std::vector<std::pair<int64_t, int64_t>> spans;
+    std::vector<std::pair<int64_t, int64_t>> spans;
+    auto check_grad = [&](const std::vector<GradUnit>& units, const std::vector<GradGroup>& groups, int D) -> int {
+      std::map<std::tuple<int, int, int>, std::vector<const GradUnit*>> by_tile;
       for (const GradUnit& u : units) {
         if (u.job < 0 || u.job >= pl.J) return 40;
         const JobDev& jb = pl.jobs[u.job];
-        if (u.t0 < jb.row0 || u.t1 <= u.t0 || u.t1 > jb.row1 || u.t1 - u.t0 > kGradMaxTokens) return 41;
+        if (u.t0 < jb.row0 || u.t1 < u.t0 || u.t1 > jb.row1 || u.t1 - u.t0 > kGradMaxTokens) return 41;
         if ((u.t0 - jb.row0) % kGradStep) return 42;                 // the packed S rows are padded to the token step
-        if (u.cb < 0 || u.cb * kGradCols >= D || u.pb < 0 || u.pb * pb_rows >= jb.rpad) return 43;
-        const int mb = std::min(kGradMaxBlocks, (jb.rpad - u.pb * pb_rows + kGradRanks - 1) / kGradRanks);
-        if (u.mb != mb || mb < 1) return 44;
-        const int64_t n = (int64_t)mb * kGradRanks * kGradCols;
-        if (u.part_off < 0 || u.part_off + n > partial) return 45;
+        if (u.cb < 0 || u.cb * kGradCols >= D || u.pb < 0 || u.pb * kGradBlockRanks >= jb.rpad || jb.rank == 0) return 43;
+        if (u.mb != grad_live_blocks(jb, u.pb) || u.mb < 1) return 44;
+        const int64_t n = (int64_t)u.mb * kGradRanks * kGradCols;
+        by_tile[{u.job, u.cb, u.pb}].push_back(&u);
+        if (u.part_off < 0) {                                        // the whole job, also an idle one
+          if (u.t0 != jb.row0 || u.t1 != jb.row1) return 54;
+          continue;
+        }
+        if (u.t1 == u.t0) return 41;
+        if (u.part_off + n > pl.grad_partial) return 45;
         spans.push_back({u.part_off, n});
       }
-      std::sort(spans.begin(), spans.end());
-      for (size_t i = 1; i < spans.size(); ++i)
-        if (spans[i - 1].first + spans[i - 1].second > spans[i].first) return 46;
-      // every output tile (job with a rank, column block, rank block) has one group; its partial tiles are the
-      // units of the same (job, cb, pb), consecutive in memory and covering the job's tokens
-      int64_t want_groups = 0;
-      for (const JobDev& jb : pl.jobs)
-        if (jb.rank > 0) want_groups += (int64_t)((jb.rpad + pb_rows - 1) / pb_rows) * ((D + kGradCols - 1) / kGradCols);
-      if ((int64_t)groups.size() != want_groups) return 47;
-      std::map<std::tuple<int, int, int>, std::vector<const GradUnit*>> by_tile;
-      for (const GradUnit& u : units) by_tile[{u.job, u.cb, u.pb}].push_back(&u);
+      // every output tile (job with a rank, column block, rank block) has a unit of its own, or one group whose partial tiles are
+      // the units of the same (job, cb, pb), consecutive in memory and covering the job's tokens
+      size_t alone = 0;
+      for (const auto& t : by_tile) alone += t.second.size() == 1 && t.second[0]->part_off < 0;
+      if ((int64_t)by_tile.size() != grad_tiles(pl, D) || alone + groups.size() != by_tile.size()) return 47;
       for (const GradGroup& g : groups) {
         if (g.job < 0 || g.job >= pl.J) return 48;
         const JobDev& jb = pl.jobs[g.job];
         auto& us = by_tile[{g.job, g.cb, g.pb}];
-        if ((int)us.size() != g.nunits) return 49;
+        if ((int)us.size() != g.nunits || g.nunits < 2) return 49;
         std::sort(us.begin(), us.end(), [](const GradUnit* a, const GradUnit* b) { return a->t0 < b->t0; });
         int t = jb.row0;
         for (int k = 0; k < g.nunits; ++k) {
@@ -2158,15 +2212,17 @@ static int check_plan(const Plan& pl, bool fwd_only) {
           t = us[k]->t1;
         }
         if (t != jb.row1) return 52;
-        if (g.nunits == 0 && jb.row1 != jb.row0) return 53;
       }
       return 0;
     };
     if (!fwd_only) {
-      if (int rc = check_grad(pl.gradB_units, pl.gradB_groups, pl.gradB_partial, pl.d_out)) return rc;
-      if (int rc = check_grad(pl.gradA_units, pl.gradA_groups, pl.gradA_partial, pl.d_in)) return rc + 100;
+      if (int rc = check_grad(pl.gradB_units, pl.gradB_groups, pl.d_out)) return rc;
+      if (int rc = check_grad(pl.gradA_units, pl.gradA_groups, pl.d_in)) return rc + 100;
+      std::sort(spans.begin(), spans.end());                         // (both may be in use at a time)
+      for (size_t i = 1; i < spans.size(); ++i)
+        if (spans[i - 1].first + spans[i - 1].second > spans[i].first) return 46;
     } else if (!pl.gradA_units.empty() || !pl.gradB_units.empty()) {
-      return 54;
+      return 55;
     }
   }
   // 6x: tables inside the blob, regions inside the workspace, nothing overlapping
@@ -2207,7 +2263,7 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       if (!fwd_only) { w.push_back({pl.off_dShi, 2 * se});  w.push_back({pl.off_dSlo, 2 * se}); }
       w.push_back({pl.off_Sx, sx});
       if (!fwd_only) w.push_back({pl.off_dSx, sx});
-      if (4 * (size_t)std::max(pl.gradB_partial, pl.gradA_partial) > pl.partial_bytes) return 64;
+      if (4 * (size_t)pl.grad_partial > pl.partial_bytes) return 64;
       for (int k : {pl.shrink_splits_x, pl.shrink_splits_dy})
         if (k < 1 || (k > 1 && 4 * se * (size_t)k > pl.partial_bytes)) return 65;
       for (int d = 0; d < 2; ++d) {

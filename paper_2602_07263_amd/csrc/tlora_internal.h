@@ -86,15 +86,15 @@ struct GradUnit {
   int32_t cb;              // feature-column block
   int32_t pb;              // rank block (of 128 rows)
   int32_t mb;              // live 32-row blocks in it: 1 .. 4
-  int64_t part_off;
+  int64_t part_off;        // < 0: the unit has all tokens of its job and stores the gradient itself
 };
 
-// One output tile of dA_j / dB_j: the run of nunits consecutive partial tiles that sum to it.
+// One output tile of dA_j / dB_j whose tokens are several units: the run of nunits consecutive partial tiles that sum to it.
 struct GradGroup {
   int32_t job;
   int32_t cb, pb;
   int32_t mb;
-  int32_t nunits;          // number of partial tiles (token chunks); 0 for an empty segment
+  int32_t nunits;          // number of partial tiles (token chunks), at least two
   int32_t pad_;
   int64_t part_off;        // float offset of the first partial tile
 };

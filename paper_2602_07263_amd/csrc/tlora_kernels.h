@@ -88,10 +88,15 @@ void launch_small(bool w_is_kn, const JobDev* jobs, const TileDev* tiles, const 
                   const int32_t* in_index, int T, int K, int N, int splits, float* part, uint16_t* S_hi, uint16_t* S_lo,
                   hipStream_t st);
 
-// partial[u] = sum_{t in unit u} U_j[t, p] * V[t, c]   then   G_j = scale_j * sum_u partial[u]
-void launch_rank_grad(const JobDev* jobs, const GradUnit* units, int num_units, const uint16_t* U_hi,
-                      const uint16_t* U_lo, const uint16_t* V, int D, float* partial,
-                      const int32_t* row_index /* null, or the row of V behind every token row */, hipStream_t st);
+// partial[u] = sum_{t in unit u} U_j[t, p] * V[t, c], or G_j itself of a unit with all tokens of its job;  then G_j = scale_j * sum_u
+// partial[u].  b: the units of dB_j (U = S_j, V = dY), a: of dA_j (U = dS_j, V = X); either may be empty.
+struct GradSide {
+  const GradUnit* units = nullptr;
+  const uint16_t *Uhi = nullptr, *Ulo = nullptr, *V = nullptr;      // V: [T, D], rows through row_index if that is given
+  int D = 0, count = 0;
+};
+void launch_rank_grad(const JobDev* jobs, const GradSide& b, const GradSide& a, float* partial, bool accumulate,
+                      const int32_t* row_index, hipStream_t st);
 // accumulate: G_j += ... instead of G_j = ...
 void launch_grad_reduce(const JobDev* jobs, const GradGroup* groups, int num_groups, const float* partial, int D,
                         bool out_is_dA, bool accumulate, hipStream_t st);

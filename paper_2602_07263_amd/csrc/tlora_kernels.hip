@@ -1679,13 +1679,14 @@ __device__ __forceinline__ bf16x8 frag_tr_u(const uint8_t* plane, int pitch, int
 // INDEXED: the rows of V are fetched through row_index (token-indexed calls).  A separate instantiation, so that the
 // plain one carries no trace of it: even a branch around a memory load inside the load loop would make the compiler
 // wait, where the paths merge, for every asynchronous load in flight.
+// One launch may run the units of dB_j and of dA_j (side, a_side).  A unit with all tokens of its job (part_off < 0) has the gradient
+// itself and stores it: dB rows leave the registers as runs of 128 bytes, dA is turned in LDS, half of the columns at a time.  The
+// others leave partial tiles.  With partial tiles for every job and a launch for each side, dA and dB took, reductions included (mlp
+// projections of 31744 tokens 797 us / now 723; 32 skewed jobs 1695 / 1501; four jobs of 7680 tokens, 4096 -> 4096, 54 / 43; three of
+// 9082, 4096 -> 5120, 94 / 58; 4198 tokens of eleven jobs, 10848 -> 1448, 77 / 52).
 template <bool INDEXED>
-__global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict__ jobs,
-                                                        const GradUnit* __restrict__ units,
-                                                        const uint16_t* __restrict__ Uhi,
-                                                        const uint16_t* __restrict__ Ulo,
-                                                        const uint16_t* __restrict__ V, int D,
-                                                        float* __restrict__ partial,
+__global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict__ jobs, GradSide side, GradSide a_side,
+                                                        float* __restrict__ partial, int accumulate,
                                                         const int32_t* __restrict__ row_index) {
   constexpr int MB = kGradMaxBlocks;                        // the U tile always has room for 4 blocks of 32 ranks;
   constexpr int RP = kGradRanks * MB;                       // a unit multiplies only its u.mb live ones
@@ -1702,20 +1703,25 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
   constexpr int LOADS = V_LD + U_LD;                        // asynchronous loads per wave per step
   constexpr int MW = MB / 2;                                // rank blocks per wave
   static_assert(V_LD * WAVES * 1024 == VTILE && U_LD * WAVES * 1024 == 2 * UPLANE && MB == 4, "load split over the waves");
-  __shared__ __attribute__((aligned(1024))) uint8_t g0[VTILE];
-  __shared__ __attribute__((aligned(1024))) uint8_t g1[VTILE];
-  __shared__ __attribute__((aligned(1024))) uint8_t g2[VTILE];
-  __shared__ __attribute__((aligned(1024))) uint8_t g3[VTILE];
-  __shared__ __attribute__((aligned(1024))) uint8_t h0[2 * UPLANE];
-  __shared__ __attribute__((aligned(1024))) uint8_t h1[2 * UPLANE];
-  __shared__ __attribute__((aligned(1024))) uint8_t h2[2 * UPLANE];
-  __shared__ __attribute__((aligned(1024))) uint8_t h3[2 * UPLANE];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[4 * (VTILE + 2 * UPLANE)];
+  uint8_t* const g0 = lds;
+  uint8_t* const g1 = lds + VTILE;
+  uint8_t* const g2 = lds + 2 * VTILE;
+  uint8_t* const g3 = lds + 3 * VTILE;
+  uint8_t* const h0 = lds + 4 * VTILE;
+  uint8_t* const h1 = h0 + 2 * UPLANE;
+  uint8_t* const h2 = h0 + 4 * UPLANE;
+  uint8_t* const h3 = h0 + 6 * UPLANE;
   // token-indexed calls: where in the batch each token row of the unit lies (row_index of the unit's chunk, staged
   // once so that the load loop never waits for an index from memory; a unit has at most kGradMaxTokens tokens)
   __shared__ int32_t srow[INDEXED ? kGradMaxTokens : 1];
 
-  const GradUnit u = units[blockIdx.x];
+  const bool dA = (int)blockIdx.x >= side.count;
+  if (dA) side = a_side;
+  const GradUnit u = side.units[dA ? blockIdx.x - (gridDim.x - a_side.count) : blockIdx.x];
   const JobDev jb = jobs[u.job];
+  const uint16_t* const V = side.V;
+  const int D = side.D;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cg = wave & 3, rh = wave >> 2;                  // column group, rank half
@@ -1755,7 +1761,7 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
     const int c = cphys ^ (((k >> SW_SHIFT) & SW_MASK) << 2);
     ulive[i] = pbase + c * 8 < jb.rpad || lane == 0;    // lane 0 keeps every wave's load count the same
     const int p = min(pbase + c * 8, jb.rpad - 8);
-    usrc[i] = (plane ? Ulo : Uhi) + jb.soff + (int64_t)(u.t0 - jb.row0 + k) * jb.rpad + p;
+    usrc[i] = (plane ? side.Ulo : side.Uhi) + jb.soff + (int64_t)(u.t0 - jb.row0 + k) * jb.rpad + p;
     udst[i] = plane * UPLANE + within * 1024;
   }
   if (INDEXED) {
@@ -1820,6 +1826,65 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
     __builtin_amdgcn_s_waitcnt(0x0070);   // drain the trailing loads before the workgroup's LDS is released
   }
 
+  if (u.part_off < 0) {
+    const int live = min(jb.rank - pbase, u.mb * kGradRanks);            // ranks of the block that exist
+    if (!dA) {
+      float* const dst = static_cast<float*>(jb.dB) + (int64_t)pbase * D;
+#pragma unroll
+      for (int i = 0; i < MW; ++i)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int p = (rh + 2 * i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), c = col0 + cg * 64 + n * 32 + (lane & 31);
+            if (p < live && c < D) {
+              float* const d = dst + (int64_t)p * D + c;
+              const float v = jb.scale * acc[i][n][e];
+              *d = accumulate ? *d + v : v;
+            }
+          }
+      return;
+    }
+    constexpr int PITCH = RP + 1;
+    static_assert(128 * PITCH * 4 <= 4 * (VTILE + 2 * UPLANE), "half of the columns fit into the stages' place");
+    float* const turn = reinterpret_cast<float*>(lds);
+    float* const dst = static_cast<float*>(jb.dA) + pbase;
+    const bool fours = (jb.rank & 3) == 0 && (reinterpret_cast<uintptr_t>(jb.dA) & 15) == 0;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      __syncthreads();                                                   // the stages, or the first half, have been read
+#pragma unroll
+      for (int i = 0; i < MW; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          turn[(cg * 32 + (lane & 31)) * PITCH + (rh + 2 * i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)] = jb.scale * acc[i][n][e];
+      __syncthreads();
+      if (fours) {                                                       // four ranks of a column per thread
+        const int per = live / 4;
+        for (int q = tid; q < 128 * per; q += WAVES * 64) {
+          const int x = q / per, p = (q - x * per) * 4, c = col0 + (x >> 5) * 64 + n * 32 + (x & 31);
+          if (c < D) {
+            f32x4* const d = reinterpret_cast<f32x4*>(dst + (int64_t)c * jb.rank + p);
+            const float* const t = turn + x * PITCH + p;
+            f32x4 v = {t[0], t[1], t[2], t[3]};
+            if (accumulate) v += *d;
+            *d = v;
+          }
+        }
+      } else {
+        for (int q = tid; q < 128 * live; q += WAVES * 64) {
+          const int x = q / live, p = q - x * live, c = col0 + (x >> 5) * 64 + n * 32 + (x & 31);
+          if (c < D) {
+            float* const d = dst + (int64_t)c * jb.rank + p;
+            const float v = turn[x * PITCH + p];
+            *d = accumulate ? *d + v : v;
+          }
+        }
+      }
+    }
+    return;
+  }
+
   // partial tile [32 * u.mb][256]: lane holds column (lane % 32) of its n-block and 16 rank rows per m-block
   float* out = partial + u.part_off;
 #pragma unroll
@@ -1837,16 +1902,13 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
   }
 }
 
-void launch_rank_grad(const JobDev* jobs, const GradUnit* units, int num_units, const uint16_t* U_hi,
-                      const uint16_t* U_lo, const uint16_t* V, int D, float* partial, const int32_t* row_index,
-                      hipStream_t st) {
-  if (num_units == 0) return;
-  if (row_index)
-    hipLaunchKernelGGL(rank_grad_kernel<true>, dim3(num_units), dim3(512), 0, st, jobs, units, U_hi, U_lo, V, D, partial,
-                       row_index);
-  else
-    hipLaunchKernelGGL(rank_grad_kernel<false>, dim3(num_units), dim3(512), 0, st, jobs, units, U_hi, U_lo, V, D,
-                       partial, row_index);
+void launch_rank_grad(const JobDev* jobs, const GradSide& b, const GradSide& a, float* partial, bool accumulate,
+                      const int32_t* row_index, hipStream_t st) {
+  if (a.count + b.count == 0) return;
+  const dim3 grid(a.count + b.count);
+  const int add = accumulate ? 1 : 0;
+  if (row_index) hipLaunchKernelGGL(rank_grad_kernel<true>, grid, dim3(512), 0, st, jobs, b, a, partial, add, row_index);
+  else           hipLaunchKernelGGL(rank_grad_kernel<false>, grid, dim3(512), 0, st, jobs, b, a, partial, add, row_index);
 }
 
 // Sum the partial tiles of one output tile in unit order (bit-reproducible), scale, and store (dB_j row-major [r, D];
@@ -2044,7 +2106,6 @@ __global__ void __launch_bounds__(TS == 32 ? 512 : 256) f32_units_kernel(const F
   auto multiply = [&](int buf) {
     const float* const As = at(buf, 0) + (lane >> 4) * (TS + 1) + mw + (lane & 15);
     const float* const Bs = at(buf, 1) + (lane >> 4) * (TS + 1) + nw + (lane & 15);
-#pragma unroll 4
     for (int k = 0; k < kq; k += 4) {
       double a[2], b[2];
 #pragma unroll
