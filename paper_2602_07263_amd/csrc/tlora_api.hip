@@ -979,8 +979,13 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
     return launches_ok(__LINE__);
   }
 
-  rc = upload(pl.tables_bytes);
-  if (rc != TLORA_OK) return rc;
+  // The forward's tables lie in front of the backward's.  They go with the packing's launch where they fit and it has work.
+  const bool with_pack = !packed && pl.max_rpad > 0 && pl.tb_gBu <= kPackArgBytes && pl.tb_jobs == 0;
+  if (no_alloc && pl.tables_bytes > kNoAllocMaxTableBytes) return TLORA_ESCRATCH;
+  if (!with_pack) {
+    rc = upload(pl.tables_bytes);
+    if (rc != TLORA_OK) return rc;
+  }
   uint16_t* Sx = reinterpret_cast<uint16_t*>(ws + pl.off_Sx);
   uint16_t* atp = reinterpret_cast<uint16_t*>(ws + pl.off_atp);
   uint16_t* bp = reinterpret_cast<uint16_t*>(ws + pl.off_bp);
@@ -993,7 +998,8 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
     Timed t(TLORA_K_PACK, st, timed);
     // (a backward that reuses this packing may need A_j side by side)
     uint16_t* const ap = !no_alloc && packs_a_all(pl) ? reinterpret_cast<uint16_t*>(ws + pl.off_ap) : nullptr;
-    launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, frags, st);
+    launch_pack_adapters(reinterpret_cast<JobDev*>(tb), pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, ap, bp, frags,
+                         with_pack ? blob.data() : nullptr, pl.tb_gBu, st);
   }
   if (pl.small_x) {
     Timed tg(TLORA_K_GEMM_FWD, st, timed);
@@ -1162,8 +1168,8 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     const bool need_a_all = dX && !wt && !small;
     const bool have_a_all = reuse_S ? packs_a_all(pl) : packed;
     if (!(reuse_S || packed) || (need_a_all && !have_a_all))
-      launch_pack_adapters(jobs, pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp, need_a_all ? ap : nullptr, bp,
-                           FragPack(), st);
+      launch_pack_adapters(reinterpret_cast<JobDev*>(tb), pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp,
+                           need_a_all ? ap : nullptr, bp, FragPack(), nullptr, 0, st);
   }
   if (pl.T > 0) {
     if (redo_S) {

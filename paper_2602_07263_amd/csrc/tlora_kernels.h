@@ -11,9 +11,12 @@ namespace tlora {
 // bf16 copies of the adapters in the layouts the MFMA kernels read (zero padded to rpad).
 // atp: per job A_j^T [rpad, d_in], stacked in job order ([R + 32, d_in], trailing rows zero);  a_all: [d_in, R + 32] with job j in columns roff_j ..;  b_all: [R + 32, d_out]
 // with job j in rows roff_j ..  (R = r_total; the 32 trailing columns / rows are zero).
-void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total,
-                          uint16_t* atp, uint16_t* a_all, uint16_t* b_all, const FragPack& frags /* in the same launch */,
-                          hipStream_t st);
+// frags: laid out in the same launch.  host_tables (null: the job table is on the device already): HOST memory, table_bytes (a
+// multiple of 4, at most kPackArgBytes) of tables that begin with the job table; the launch takes them by value and leaves them at
+// `jobs`.  Not with max_rpad == 0, which packs nothing.
+constexpr size_t kPackArgBytes = 3328;      // with the other arguments below the 4 KB of a launch's argument block
+void launch_pack_adapters(JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total, uint16_t* atp, uint16_t* a_all,
+                          uint16_t* b_all, const FragPack& frags, const void* host_tables, size_t table_bytes, hipStream_t st);
 void launch_frag_pack(const FragPack& frags, hipStream_t st);
 
 // out[c, r] = in[r, c]; bf16 [rows, cols] row-major, rows and cols multiples of 8, 16-byte aligned.

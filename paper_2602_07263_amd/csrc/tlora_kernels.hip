@@ -170,12 +170,25 @@ void launch_frag_pack(const FragPack& f, hipStream_t st) {
 // roff and R are multiples of 8, so every chunk is aligned); A_j is read element by element (its rows are r_j
 // elements long, any alignment), B_j in 16-byte chunks when its base is aligned.
 constexpr int kPackPiece = 1024;               // 16-byte chunks of B_j a workgroup copies at a time
-__global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __restrict__ jobs, int num_jobs, int d_in,
-                                                            int d_out, int r_total, uint16_t* __restrict__ atp,
-                                                            uint16_t* __restrict__ a_all,
-                                                            uint16_t* __restrict__ b_all, FragPack frags) {
+// ARGS: the call's tables, the job table first, travel as an argument of this launch, which also leaves them in the workspace for the
+// launches that follow: a launch of their own took 2 to 4 us of a forward (13 % of one of 61 tokens).
+struct PackTables {
+  uint32_t w[kPackArgBytes / 4];
+};
+struct NoTables {};
+template <bool ARGS>
+__global__ void __launch_bounds__(256) pack_adapters_kernel(JobDev* job_table, int num_jobs, int d_in, int d_out, int r_total,
+                                                            uint16_t* __restrict__ atp, uint16_t* __restrict__ a_all,
+                                                            uint16_t* __restrict__ b_all, FragPack frags, int table_words,
+                                                            std::conditional_t<ARGS, PackTables, NoTables> tables) {
   const int stride = (int)(gridDim.x * blockDim.x);
   const int first = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  const JobDev* jobs = job_table;
+  if constexpr (ARGS) {
+    jobs = reinterpret_cast<const JobDev*>(tables.w);
+    if ((int)blockIdx.y == num_jobs && blockIdx.x == 0)
+      for (int i = threadIdx.x; i < table_words; i += 256) reinterpret_cast<uint32_t*>(job_table)[i] = tables.w[i];
+  }
   const int ra = r_total + 32;
   const int kout8 = d_out / 8;
   const u32x4 zero = {0, 0, 0, 0};
@@ -269,14 +282,23 @@ __global__ void __launch_bounds__(256) pack_adapters_kernel(const JobDev* __rest
 
 // Workgroups per job: one per tile and piece of the largest job, but no more than 8192 in all, or 64 per job from 128 jobs on
 // (those of smaller jobs find nothing and end; beyond that the loop over the job's units is cheaper than the empty workgroups).
-void launch_pack_adapters(const JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total,
-                          uint16_t* atp, uint16_t* a_all, uint16_t* b_all, const FragPack& frags, hipStream_t st) {
+void launch_pack_adapters(JobDev* jobs, int num_jobs, int d_in, int d_out, int max_rpad, int r_total, uint16_t* atp, uint16_t* a_all,
+                          uint16_t* b_all, const FragPack& frags, const void* host_tables, size_t table_bytes, hipStream_t st) {
   if (max_rpad == 0) return launch_frag_pack(frags, st);
   const int64_t units = (int64_t)((d_in + 63) / 64) * ((max_rpad + 63) / 64) +
                         ((int64_t)max_rpad * (d_out / 8) + kPackPiece - 1) / kPackPiece;
   const int bx = (int)std::min<int64_t>(units, std::max(64, 8192 / (num_jobs + 1)));
-  hipLaunchKernelGGL(pack_adapters_kernel, dim3(bx, num_jobs + 1 + (frags.out ? 1 : 0)), dim3(256), 0, st, jobs, num_jobs, d_in,
-                     d_out, r_total, atp, a_all, b_all, frags);
+  const dim3 grid(bx, num_jobs + 1 + (frags.out ? 1 : 0));
+  if (host_tables) {
+    PackTables t;
+    memset(&t, 0, sizeof(t));
+    memcpy(&t, host_tables, std::min(table_bytes, sizeof(t)));
+    hipLaunchKernelGGL(pack_adapters_kernel<true>, grid, dim3(256), 0, st, jobs, num_jobs, d_in, d_out, r_total, atp, a_all, b_all,
+                       frags, (int)(table_bytes / 4), t);
+  } else {
+    hipLaunchKernelGGL(pack_adapters_kernel<false>, grid, dim3(256), 0, st, jobs, num_jobs, d_in, d_out, r_total, atp, a_all, b_all,
+                       frags, 0, NoTables());
+  }
 }
 
 // out[c, r] = in[r, c] for a row-major bf16 matrix [rows, cols] (both multiples of 8): 64 x 64 tiles through LDS,
