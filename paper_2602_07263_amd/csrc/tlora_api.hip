@@ -94,6 +94,7 @@ struct Plan {
   int64_t sx_elems = 0;                                 // elements of the per-tile K-extension operands
   int shrink_splits_x = 1, shrink_splits_dy = 1;        // contraction splits of the shrinks over d_in (S) and d_out (dS)
   GemmSplit gemm_split_fwd, gemm_split_bwd;             // tiles of the two GEMMs that are cut along the contraction
+  GemmSplit pair_split_fwd, pair_split_bwd;             // and of two such GEMMs in one launch
   int small_x = 0, small_dy = 0;                        // splits of a small batch's two-launch form (0: not taken), X and dY side
   size_t partial_bytes = 0;                             // what off_partial holds: dA / dB tiles, or sums of split launches
   // workspace byte offsets
@@ -295,13 +296,13 @@ double gemm_us(int64_t units, int steps) {
 // (K = 1024 ... 17408, 0 to 30 rounds, 12 to 240 tiles beyond them) that is 0.22 % from the best choice on average and slower
 // than no cut at three, by at most 1.5 %; without the charge at thirteen, by up to 3.5 %; a charge of 2 us for every round loses
 // nothing but leaves 0.49 %.
-GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
+GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes, int products = 1) {
   GemmSplit best;
   if (K % kGemmBK || pl.T == 0) return best;
   int kext = 0;
   for (const TileDev& td : pl.tile_jobs) kext = std::max(kext, td.kext);
   const int steps = (K + kext) / kGemmBK;
-  const int64_t nb = (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
+  const int64_t nb = products * (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
   const int64_t n_tail = nb % 256;
   if (n_tail == 0) return best;
   const size_t tile_bytes = sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM);
@@ -325,9 +326,9 @@ GemmSplit gemm_split(const Plan& pl, int K, int N, size_t max_bytes) {
 // gained at 4096 -> 4096, 2.7 % lost at 17408 -> 5120).  A weight below 2^19 elements keeps the copy, a launch of 3 us: of
 // 1024 x 1024 on, the smallest measured, leaving it out gains 2 to 4 us.  Same bits either way.
 inline bool dx_direct(int64_t tokens, int64_t d_in, int64_t d_out) { return tokens <= 6144 && d_in * d_out >= (1 << 19); }
-size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N) {
+size_t gemm_split_bytes(const Plan& pl, const GemmSplit& g, int N, int products = 1) {
   if (g.splits < 2) return 0;
-  const int64_t nb = (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
+  const int64_t nb = products * (int64_t)pl.tile_jobs.size() * ((N + kGemmBN - 1) / kGemmBN);
   return sizeof(float) * kGemmBN * (size_t)std::min(pl.T, kGemmBM) * (size_t)(nb - g.n_direct) * g.splits;
 }
 
@@ -606,6 +607,8 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     } else {
       pl.shrink_splits_dy = shrink_splits(pl, pl.d_out, sums_room(pl));
       pl.gemm_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, sums_room(pl));
+      pl.pair_split_fwd = gemm_split(pl, pl.d_in, pl.d_out, sums_room(pl), 2);
+      pl.pair_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, sums_room(pl), 2);
       pl.small_dy = small_splits(pl, pl.d_out, pl.d_in, false, sums_room(pl));
       pl.partial_bytes = res.partial;
       pl.off_partial = wplace(pl.partial_bytes);
@@ -717,6 +720,44 @@ int prof_drain() {
   }
   g_pending.clear();
   return TLORA_OK;
+}
+
+// Two projections of a block over the same rows and sizes (gate and up, k and v).  Together they fill the rounds of 256 tiles that
+// either would leave partly empty or cut: forward and backward of an MLP block, apart / in pairs, 271 / 228 us at 300 tokens and
+// 1024 -> 2816, 1267 / 1188 at 1900 and 4096 -> 12288, 6450 / 6400 at 12000 (9 rounds each).  Over many rounds there is nothing
+// left to fill, while two weights share the caches: 12590 / 12610 at 24000 (17 rounds), 63430 / 63800 for a decoder layer of 83968
+// (61).  So pairs are for products of up to 12 rounds.
+constexpr int64_t kPairTiles = 12 * 256;
+// A backbone product that is ready to run.
+struct GemmCall {
+  int kernel = 0;                                       // what it is timed as
+  bool w_is_kn = false, timed = true;
+  const TileDev* tiles = nullptr;
+  GemmOperands op;                                      // (out null: nothing to run)
+  int r_total = 0, T = 0, K = 0, N = 0;
+  const int32_t *out_index = nullptr, *in_index = nullptr;
+  unsigned long long* clk = nullptr;
+  GemmSplit split, pair_split;
+  float* sums = nullptr;
+  bool pairs() const {
+    const int64_t tiles = (int64_t)((T + kGemmBM - 1) / kGemmBM) * ((N + kGemmBN - 1) / kGemmBN);
+    return K % kGemmBK == 0 && !out_index && !in_index && tiles <= kPairTiles;
+  }
+};
+// second: another one over the same jobs, in the same launch; their sums have one place.
+void launch_gemm(const GemmCall& g, const GemmCall* second, hipStream_t st) {
+  Timed t(g.kernel, st, g.timed);
+  launch_seg_gemm(g.w_is_kn, g.tiles, g.op.act, g.op.W, g.op.Sx, g.op.packed, g.r_total, g.op.out, g.out_index, g.in_index, g.T,
+                  g.K, g.N, g.clk, second ? g.pair_split : g.split, g.sums, second ? second->op : GemmOperands(), st);
+}
+void launch_gemm_pair(const GemmCall& a, const GemmCall& b, hipStream_t st) {
+  if (a.op.out && b.op.out && a.w_is_kn == b.w_is_kn && a.K == b.K && a.N == b.N && a.T == b.T && a.r_total == b.r_total &&
+      a.sums == b.sums) {
+    launch_gemm(a, &b, st);
+    return;
+  }
+  if (a.op.out) launch_gemm(a, nullptr, st);
+  if (b.op.out) launch_gemm(b, nullptr, st);
 }
 
 // S_j = X_j.A_j (or dS_j = dY_j.B_j^T): streaming kernel when the contraction length allows, else generic
@@ -919,9 +960,10 @@ namespace {
 // inside the kernels' loads (null: X already lies in job-sorted order).
 // packed: this workspace already holds the packed copies of the same adapters (a nano-batch after the first).
 // shared_sums: where the sums of cut launches go instead of the workspace's own last part.
+// later: where given, a product that a pair may take is written down there instead of launched.
 int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes, void* hip_stream, bool no_alloc,
              const int32_t* out_index = nullptr, const int32_t* in_index = nullptr, bool packed = false,
-             uint8_t* shared_sums = nullptr) {
+             uint8_t* shared_sums = nullptr, GemmCall* later = nullptr) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, no_alloc, shared_sums != nullptr);
@@ -1015,11 +1057,16 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
                sums, st);
   }
   if (timed) launch_zero_fill(ws + pl.off_clock, 16, st);
-  Timed tg(TLORA_K_GEMM_FWD, st, timed);
-  launch_seg_gemm(true, tiles, static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), Sx, bp,
-                  pl.r_total, static_cast<uint16_t*>(Y), out_index, in_index, pl.T, pl.d_in, pl.d_out,
-                  timed ? (g_clock_slot[0] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock)) : nullptr,
-                  pl.gemm_split_fwd, sums, st);
+  GemmCall g;
+  g.kernel = TLORA_K_GEMM_FWD;  g.w_is_kn = true;  g.timed = timed;
+  g.tiles = tiles;
+  g.op = {static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), Sx, bp, static_cast<uint16_t*>(Y)};
+  g.r_total = pl.r_total;  g.T = pl.T;  g.K = pl.d_in;  g.N = pl.d_out;
+  g.out_index = out_index;  g.in_index = in_index;
+  g.clk = timed ? (g_clock_slot[0] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock)) : nullptr;
+  g.split = pl.gemm_split_fwd;  g.pair_split = pl.pair_split_fwd;  g.sums = sums;
+  if (later && g.pairs()) *later = g;
+  else launch_gemm(g, nullptr, st);
   return launches_ok(__LINE__);
 }
 }  // namespace
@@ -1044,13 +1091,15 @@ int tlora_fwd_noalloc(const tlora_problem_t* p, void* Y, void* hip_stream) {
 
 namespace tlora {
 namespace {
+// later: as there; the product then follows the gradients.
 // The backward's launch sequence (out_index / in_index as in fwd_impl: dX rows are scattered; X and dY are fetched
 // through the list; packed and shared_sums as there, the latter also for the partial tiles of dA / dB).
 // batch_tokens: of the whole batch, if the call is one of its nano-batches, which share one copy of W^T or do without alike.
 // wt_there: the same entry point has made the copy for an earlier nano-batch.
 int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags,
              void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index,
-             bool packed = false, uint8_t* shared_sums = nullptr, int64_t batch_tokens = 0, bool wt_there = false) {
+             bool packed = false, uint8_t* shared_sums = nullptr, int64_t batch_tokens = 0, bool wt_there = false,
+             GemmCall* later = nullptr) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, false, shared_sums != nullptr);
@@ -1200,11 +1249,16 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
         launch_transpose_bf16(static_cast<const uint16_t*>(p->W), Wt, pl.d_in, pl.d_out, st);
       }
       if (g_prof_on) launch_zero_fill(ws + pl.off_clock + 16, 16, st);
-      Timed t(TLORA_K_GEMM_BWD, st);
-      launch_seg_gemm(wt, tiles, dYb, wt ? Wt : static_cast<const uint16_t*>(p->W), dSx, wt ? atp : ap, pl.r_total,
-                      static_cast<uint16_t*>(dX), out_index, in_index, pl.T, pl.d_out, pl.d_in,
-                      g_prof_on ? (g_clock_slot[1] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock) + 2) : nullptr,
-                      pl.gemm_split_bwd, partial, st);
+      GemmCall g;
+      g.kernel = TLORA_K_GEMM_BWD;  g.w_is_kn = wt;
+      g.tiles = tiles;
+      g.op = {dYb, wt ? Wt : static_cast<const uint16_t*>(p->W), dSx, wt ? atp : ap, static_cast<uint16_t*>(dX)};
+      g.r_total = pl.r_total;  g.T = pl.T;  g.K = pl.d_out;  g.N = pl.d_in;
+      g.out_index = out_index;  g.in_index = in_index;
+      g.clk = g_prof_on ? (g_clock_slot[1] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock) + 2) : nullptr;
+      g.split = pl.gemm_split_bwd;  g.pair_split = pl.pair_split_bwd;  g.sums = partial;
+      if (later && g.pairs()) *later = g;
+      else launch_gemm(g, nullptr, st);
     }
   }
   if (want_grads) {
@@ -1435,13 +1489,14 @@ bool layer_bytes(const tlora_problem_t* p, LayerBytes& b) {
   b.sums = bf16 ? e->pl.partial_bytes : 0;
   return true;
 }
-int layer_fwd(const tlora_problem_t* p, void* Y, uint8_t* ws, size_t own, uint8_t* sums, void* hip_stream) {
-  return fwd_impl(p, Y, ws, own, hip_stream, false, nullptr, nullptr, false, p->dtype == TLORA_BF16 ? sums : nullptr);
+int layer_fwd(const tlora_problem_t* p, void* Y, uint8_t* ws, size_t own, uint8_t* sums, void* hip_stream,
+              GemmCall* later = nullptr) {
+  return fwd_impl(p, Y, ws, own, hip_stream, false, nullptr, nullptr, false, p->dtype == TLORA_BF16 ? sums : nullptr, later);
 }
 int layer_bwd(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags, uint8_t* ws,
-              size_t own, uint8_t* sums, void* hip_stream) {
+              size_t own, uint8_t* sums, void* hip_stream, GemmCall* later = nullptr) {
   return bwd_impl(p, dY, dX, dA, dB, flags, ws, own, hip_stream, nullptr, nullptr, false,
-                  p->dtype == TLORA_BF16 ? sums : nullptr);
+                  p->dtype == TLORA_BF16 ? sums : nullptr, 0, false, later);
 }
 
 struct MlpLayout {
@@ -1516,10 +1571,12 @@ int tlora_mlp_fwd(const tlora_mlp_t* p, void* Out, void* workspace, size_t ws_by
                        reinterpret_cast<float*>(ws + L.off_rstd), st);
   }
   L.gate.X = L.up.X = ws + L.off_xn;
-  rc = layer_fwd(&L.gate, ws + L.off_g, ws + L.off_ws_gate, L.ws_gate, ws + L.off_sums, hip_stream);
+  GemmCall gate, up;
+  rc = layer_fwd(&L.gate, ws + L.off_g, ws + L.off_ws_gate, L.ws_gate, ws + L.off_sums, hip_stream, &gate);
   if (rc != TLORA_OK) return rc;
-  rc = layer_fwd(&L.up, ws + L.off_u, ws + L.off_ws_up, L.ws_up, ws + L.off_sums, hip_stream);
+  rc = layer_fwd(&L.up, ws + L.off_u, ws + L.off_ws_up, L.ws_up, ws + L.off_sums, hip_stream, &up);
   if (rc != TLORA_OK) return rc;
+  launch_gemm_pair(gate, up, st);
   {
     Timed t(TLORA_K_GLUE, st);
     launch_swiglu_fwd(bf, ws + L.off_g, ws + L.off_u, ws + L.off_z, L.T * p->d_ff, st);
@@ -1561,10 +1618,12 @@ int tlora_mlp_bwd(const tlora_mlp_t* p, const void* dOut, void* dX, void* const*
     Timed t(TLORA_K_GLUE, st);
     launch_swiglu_bwd(bf, ws + L.off_g, ws + L.off_u, ws + L.off_dz, ws + L.off_dg, ws + L.off_du, L.T * p->d_ff, st);
   }
-  rc = layer_bwd(&L.gate, ws + L.off_dg, ws + L.off_dxa, dA_gate, dB_gate, lf, ws + L.off_ws_gate, L.ws_gate, ws + L.off_sums, hip_stream);
+  GemmCall gate, up;
+  rc = layer_bwd(&L.gate, ws + L.off_dg, ws + L.off_dxa, dA_gate, dB_gate, lf, ws + L.off_ws_gate, L.ws_gate, ws + L.off_sums, hip_stream, &gate);
   if (rc != TLORA_OK) return rc;
-  rc = layer_bwd(&L.up, ws + L.off_du, ws + L.off_dxb, dA_up, dB_up, lf, ws + L.off_ws_up, L.ws_up, ws + L.off_sums, hip_stream);
+  rc = layer_bwd(&L.up, ws + L.off_du, ws + L.off_dxb, dA_up, dB_up, lf, ws + L.off_ws_up, L.ws_up, ws + L.off_sums, hip_stream, &up);
   if (rc != TLORA_OK) return rc;
+  launch_gemm_pair(gate, up, st);
   if (L.T > 0) {
     Timed t(TLORA_K_GLUE, st);
     launch_rmsnorm_bwd(bf, p->X, p->gamma, reinterpret_cast<const float*>(ws + L.off_rstd), ws + L.off_dxa,
@@ -1812,9 +1871,11 @@ int tlora_attn_fwd(const tlora_attn_t* p, void* Out, void* workspace, size_t ws_
   }
   L.q.X = L.k.X = L.v.X = ws + L.off_xn;
   rc = layer_fwd(&L.q, ws + L.off_q, ws + L.off_ws[0], L.ws_l[0], ws + L.off_sums, hip_stream);
-  if (rc == TLORA_OK) rc = layer_fwd(&L.k, ws + L.off_k, ws + L.off_ws[1], L.ws_l[1], ws + L.off_sums, hip_stream);
-  if (rc == TLORA_OK) rc = layer_fwd(&L.v, ws + L.off_v, ws + L.off_ws[2], L.ws_l[2], ws + L.off_sums, hip_stream);
+  GemmCall k, v;
+  if (rc == TLORA_OK) rc = layer_fwd(&L.k, ws + L.off_k, ws + L.off_ws[1], L.ws_l[1], ws + L.off_sums, hip_stream, &k);
+  if (rc == TLORA_OK) rc = layer_fwd(&L.v, ws + L.off_v, ws + L.off_ws[2], L.ws_l[2], ws + L.off_sums, hip_stream, &v);
   if (rc != TLORA_OK) return rc;
+  launch_gemm_pair(k, v, st);
   const int32_t* pos = reinterpret_cast<const int32_t*>(aw + L.A.off_pos);
   {
     Timed t(TLORA_K_ROPE, st);
@@ -1883,9 +1944,11 @@ int tlora_attn_bwd(const tlora_attn_t* p, const void* dOut, void* dX, void* cons
     }
   }
   rc = layer_bwd(&L.q, ws + L.off_dq, ws + L.off_dxa, dA[0], dB[0], lf, ws + L.off_ws[0], L.ws_l[0], ws + L.off_sums, hip_stream);
-  if (rc == TLORA_OK) rc = layer_bwd(&L.k, ws + L.off_dk, ws + L.off_dxb, dA[1], dB[1], lf, ws + L.off_ws[1], L.ws_l[1], ws + L.off_sums, hip_stream);
-  if (rc == TLORA_OK) rc = layer_bwd(&L.v, ws + L.off_dv, ws + L.off_dxc, dA[2], dB[2], lf, ws + L.off_ws[2], L.ws_l[2], ws + L.off_sums, hip_stream);
+  GemmCall k, v;
+  if (rc == TLORA_OK) rc = layer_bwd(&L.k, ws + L.off_dk, ws + L.off_dxb, dA[1], dB[1], lf, ws + L.off_ws[1], L.ws_l[1], ws + L.off_sums, hip_stream, &k);
+  if (rc == TLORA_OK) rc = layer_bwd(&L.v, ws + L.off_dv, ws + L.off_dxc, dA[2], dB[2], lf, ws + L.off_ws[2], L.ws_l[2], ws + L.off_sums, hip_stream, &v);
   if (rc != TLORA_OK) return rc;
+  launch_gemm_pair(k, v, st);
   if (L.T > 0) {
     Timed t(TLORA_K_GLUE, st);
     launch_rmsnorm_bwd(true, p->X, p->gamma, reinterpret_cast<const float*>(ws + L.off_rstd), ws + L.off_dxa,
@@ -2282,6 +2345,8 @@ static int check_plan(const Plan& pl, bool fwd_only) {
           if (gemm_share(steps, g.splits) * (g.splits - 1) >= steps) return 69;
         }
         if (gemm_split_bytes(pl, g, d ? pl.d_in : pl.d_out) > pl.partial_bytes) return 68;
+        if (!fwd_only && gemm_split_bytes(pl, d ? pl.pair_split_bwd : pl.pair_split_fwd, d ? pl.d_in : pl.d_out, 2) > pl.partial_bytes)
+          return 68;
       }
       for (int d = 0; d < 2; ++d) {
         const int k = d ? pl.small_dy : pl.small_x, K = d ? pl.d_out : pl.d_in, N = d ? pl.d_in : pl.d_out;

@@ -50,6 +50,14 @@ struct GemmSplit {
   int32_t n_direct = 0;
   int32_t splits = 1;
 };
+// What a product of a shape has of its own (host pointers' device memory); out null: there is none.
+struct GemmOperands {
+  const uint16_t* act = nullptr;
+  const uint16_t* W = nullptr;
+  const uint16_t* Sx = nullptr;
+  const uint16_t* packed = nullptr;
+  uint16_t* out = nullptr;
+};
 // K-steps of a share of a tile of `steps` steps, the last share apart, which has what is left: an even number, which the GEMM's
 // ring of tile slots asks of a first step.
 __host__ __device__ inline int gemm_share(int steps, int splits) { return ((steps + splits - 1) / splits + 1) & ~1; }

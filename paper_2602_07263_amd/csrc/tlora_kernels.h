@@ -81,7 +81,10 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
                      unsigned long long* clk /* null, or 2 zeroed words: every 64th workgroup adds the shader
                                                 cycles and 100 MHz ticks of its K-loop */,
                      const GemmSplit& split /* taken when K % 32 == 0 */,
-                     float* part /* splits x cut tiles x min(T, 256) x 256 floats */, hipStream_t st);
+                     float* part /* splits x cut tiles x min(T, 256) x 256 floats */,
+                     const GemmOperands& second /* another product of the same T, K, N and tiles in the same launch, if any
+                                                   (K % 32 == 0, no indexes); `split` is then that of both */,
+                     hipStream_t st);
 
 // A direction of a small batch (T <= kSmallRows; K and N multiples of 64): S_j (dS_j) as hi / lo planes (null: not wanted) and,
 // unless out is null, Y (dX).  act: as fragments if small_frags(small_blocks(T)).  rank_rows: A_j^T (B_j) packed, [R + 32, K];  expand_rows: B_j (A_j^T) packed, [R + 32, N].  part:

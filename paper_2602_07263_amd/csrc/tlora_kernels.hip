@@ -931,6 +931,9 @@ struct GemmParams {
   // part[split][tile - n_direct][part_rows][256]
   int n_direct, splits, part_rows;
   float* part;
+  // a second product of the same shape behind the first in the walk, if n_tiles is twice tiles_m tiles_n
+  int n_tiles;
+  GemmOperands second;
 };
 
 // Tile L of the walk: groups of 4 row tiles, so that workgroups that run together share activation and weight panels.
@@ -980,10 +983,10 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   // Cut tiles: neighbours of an XCD are tiles of one split (they share its slices of the operands); n_direct is a
   // multiple of 8, so b & 7 is the XCD there too.
   int tm, tn;
-  bool cut = false;
+  bool cut = false, second;
   int split = 0, tail_tile = 0;
   {
-    const int nb = P.tiles_m * P.tiles_n, b = blockIdx.x;
+    const int nb = P.n_tiles, b = blockIdx.x;
     cut = SPLIT && b >= P.n_direct;
     const int first = cut ? P.n_direct : 0;
     const int n = !SPLIT ? nb : cut ? (nb - P.n_direct) * P.splits : P.n_direct;
@@ -994,6 +997,8 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
       tail_tile = __builtin_amdgcn_readfirstlane(L - split * (nb - first));
       L = first + tail_tile;
     }
+    second = L >= P.tiles_m * P.tiles_n;
+    if (second) L -= P.tiles_m * P.tiles_n;
     gemm_tile_of(L, P.tiles_m, P.tiles_n, tm, tn);
   }
   const int row0 = tm * BM, col0 = tn * BN;
@@ -1045,12 +1050,15 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
     const int lr = wave * 32 + (lane >> 3);                   // row / column of the tile for i = 0 (i adds 8)
     const int coff = ((lane & 3) ^ (lane >> 4)) * 16;         // byte offset of the lane's chunk inside its 32-k half
     const int h0 = (lane >> 2) & 1;                           // which half, for even i (odd i: the other one)
-    const char* const a_base = uniform_ptr(reinterpret_cast<const char*>(INDEXED ? P.act : P.act + (int64_t)row0 * P.K));
-    const char* const x_base = uniform_ptr(reinterpret_cast<const char*>(P.Sx + td.aoff) - (int64_t)nfull * 64);
-    const char* const w_base = uniform_ptr(reinterpret_cast<const char*>(KN ? P.W + col0 : P.W + (int64_t)col0 * P.K));
+    const uint16_t* const act = second ? P.second.act : P.act;
+    const uint16_t* const W = second ? P.second.W : P.W;
+    const uint16_t* const packed = second ? P.second.packed : P.packed;
+    const char* const a_base = uniform_ptr(reinterpret_cast<const char*>(INDEXED ? act : act + (int64_t)row0 * P.K));
+    const char* const x_base = uniform_ptr(reinterpret_cast<const char*>((second ? P.second.Sx : P.Sx) + td.aoff) - (int64_t)nfull * 64);
+    const char* const w_base = uniform_ptr(reinterpret_cast<const char*>(KN ? W + col0 : W + (int64_t)col0 * P.K));
     const char* const e_base = uniform_ptr(
-        KN ? reinterpret_cast<const char*>(P.packed + (int64_t)td.roff_first * P.N + col0) - (int64_t)nfull * 64 * P.N
-           : reinterpret_cast<const char*>(P.packed + (int64_t)col0 * P.ra + td.roff_first) - (int64_t)nfull * 64);
+        KN ? reinterpret_cast<const char*>(packed + (int64_t)td.roff_first * P.N + col0) - (int64_t)nfull * 64 * P.N
+           : reinterpret_cast<const char*>(packed + (int64_t)col0 * P.ra + td.roff_first) - (int64_t)nfull * 64);
     const uint32_t lds0 = lds_addr(lds);
     // Interior tiles (no row / column clamping) need two offsets per operand: the lane's row and chunk for even
     // and for odd i; the 8 i rows between consecutive loads go into the uniform base.
@@ -1271,7 +1279,7 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   }
 
   if (SPLIT && cut) {       // fp32 sums, rows of 256 columns: a wave's stores fill whole 256-byte runs across j
-    float* const dst = P.part + ((int64_t)split * (P.tiles_m * P.tiles_n - P.n_direct) + tail_tile) * P.part_rows * BN;
+    float* const dst = P.part + ((int64_t)split * (P.n_tiles - P.n_direct) + tail_tile) * P.part_rows * BN;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int R = wm * 128 + i * 16 + (lane & 15);
@@ -1287,21 +1295,30 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
   // ---- epilogue: accumulators -> bf16 -> LDS (slots 0-3 hold 64 output rows each, 512 B per row, 16-byte
   // chunk c of row R at slot c ^ (R & 31)) -> full 512-byte rows to global memory. -----------------------------
   __syncthreads();
+  int le = lane;
+  asm volatile("" : "+v"(le));               // (nothing that only the epilogue needs stays live through the loop)
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     // lane l holds token (l % 16) of block i, features 4 (l / 16) .. + 3 of each feature block
     uint8_t* const obuf = wm ? (i < 4 ? sl2 : sl3) : (i < 4 ? sl0 : sl1);
-    const int R = wm * 128 + i * 16 + (lane & 15);
-    uint8_t* const orow = obuf + (R & 63) * 512 + ((lane >> 4) & 1) * 8;
+    const int R = wm * 128 + i * 16 + (le & 15);
+    uint8_t* const orow = obuf + (R & 63) * 512 + ((le >> 4) & 1) * 8;
 #pragma unroll
     for (int j = 0; j < NFB; ++j) {
-      const int c = wn * 8 + j * 2 + (lane >> 5);
+      const int c = wn * 8 + j * 2 + (le >> 5);
       u32x2 v = {pack_bf16x2(acc[j][i][0], acc[j][i][1]), pack_bf16x2(acc[j][i][2], acc[j][i][3])};
       *reinterpret_cast<u32x2*>(orow + ((c ^ (R & 31)) << 4)) = v;
     }
   }
   __syncthreads();
   constexpr int RPI = NT / 32;              // output rows per iteration
+  uint16_t* out = P.out;
+  if (P.n_tiles > P.tiles_m * P.tiles_n) {  // (found again rather than kept: the loop has no scalar register to spare)
+    int b = blockIdx.x;
+    asm volatile("" : "+s"(b));
+    const int n = SPLIT ? P.n_direct : P.n_tiles;
+    if ((b & 7) * (n >> 3) + min(b & 7, n & 7) + (b >> 3) >= P.tiles_m * P.tiles_n) out = P.second.out;
+  }
 #pragma unroll
   for (int it = 0; it < 256 / RPI; ++it) {
     const uint8_t* const obuf = it * RPI < 64 ? sl0 : it * RPI < 128 ? sl1 : it * RPI < 192 ? sl2 : sl3;
@@ -1309,18 +1326,24 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
     const u32x4 v = *reinterpret_cast<const u32x4*>(obuf + (R & 63) * 512 + ((c ^ (R & 31)) << 4));
     if (R < rows_valid && col0 + c * 8 < P.N) {
       const int64_t orow = P.out_index ? P.out_index[row0 + R] : row0 + R;
-      *reinterpret_cast<u32x4*>(P.out + orow * P.N + col0 + c * 8) = v;
+      *reinterpret_cast<u32x4*>(out + orow * P.N + col0 + c * 8) = v;
     }
   }
 }
 
 // out = bf16(sum of the splits in order): one workgroup = 8 rows of a cut tile, 8 columns per thread
 __global__ void __launch_bounds__(256) gemm_reduce_kernel(const float* __restrict__ part, int n_direct, int splits,
-                                                          int part_rows, uint16_t* __restrict__ out,
+                                                          int part_rows, uint16_t* __restrict__ first,
+                                                          uint16_t* __restrict__ second,
                                                           const int32_t* __restrict__ out_index, int T, int N, int tiles_m,
                                                           int tiles_n) {
-  int tm, tn;
-  gemm_tile_of(n_direct + (int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+  int tm, tn, L = n_direct + (int)blockIdx.x;
+  uint16_t* out = first;
+  if (L >= tiles_m * tiles_n) {
+    L -= tiles_m * tiles_n;
+    out = second;
+  }
+  gemm_tile_of(L, tiles_m, tiles_n, tm, tn);
   const int R = (int)blockIdx.y * 8 + (int)(threadIdx.x >> 5), c = (int)(threadIdx.x & 31) * 8;
   const int t = tm * kGemmBM + R, col = tn * kGemmBN + c;
   if (t >= T || col >= N) return;
@@ -1339,7 +1362,7 @@ __global__ void __launch_bounds__(256) gemm_reduce_kernel(const float* __restric
 void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, const uint16_t* W, const uint16_t* Sx,
                      const uint16_t* packed, int r_total, uint16_t* out, const int32_t* out_index,
                      const int32_t* in_index, int T, int K, int N, unsigned long long* clk, const GemmSplit& split,
-                     float* part, hipStream_t st) {
+                     float* part, const GemmOperands& second, hipStream_t st) {
   GemmParams P;
   P.clk = clk;
   P.out_index = out_index;
@@ -1348,7 +1371,8 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
   P.T = T;  P.K = K;  P.N = N;  P.ra = r_total + 32;
   P.tiles_m = (T + kGemmBM - 1) / kGemmBM;
   P.tiles_n = (N + kGemmBN - 1) / kGemmBN;
-  const int nb = P.tiles_m * P.tiles_n;
+  P.second = second;
+  const int nb = P.n_tiles = P.tiles_m * P.tiles_n * (second.out ? 2 : 1);
   if (nb == 0) return;
   const bool tail = K % kGemmBK != 0;
   P.n_direct = split.n_direct;  P.splits = split.splits;  P.part_rows = std::min(T, kGemmBM);  P.part = part;
@@ -1360,7 +1384,7 @@ void launch_seg_gemm(bool w_is_kn, const TileDev* tiles, const uint16_t* act, co
     else         { if (in_index) TLORA_GEMM_CUT(false, true); else TLORA_GEMM_CUT(false, false); }
 #undef TLORA_GEMM_CUT
     hipLaunchKernelGGL(gemm_reduce_kernel, dim3(n_tail, (P.part_rows + 7) / 8), dim3(256), 0, st, part, P.n_direct, P.splits,
-                       P.part_rows, out, out_index, T, N, P.tiles_m, P.tiles_n);
+                       P.part_rows, out, second.out, out_index, T, N, P.tiles_m, P.tiles_n);
     return;
   }
 #define TLORA_GEMM_LAUNCH(KN, TAIL, IDX) \
