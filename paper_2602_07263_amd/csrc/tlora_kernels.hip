@@ -57,6 +57,13 @@ __device__ __forceinline__ void dma16s(uint32_t voff, const void* sbase, uint32_
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
                : "memory");
 }
+// The same for the lanes below `below` (any value) alone: the others load nothing and their LDS bytes stay as they are.
+__device__ __forceinline__ void dma16s_below(int lane, int below, uint32_t voff, const void* sbase, uint32_t lds_base) {
+  uint64_t all;
+  asm volatile("s_mov_b32 m0, %3\n\tv_cmp_gt_i32 vcc, %4, %5\n\ts_and_saveexec_b64 %0, vcc\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+               "s_mov_b64 exec, %0"
+               : "=&s"(all) : "v"(voff), "s"(sbase), "s"(lds_base), "s"(below), "v"(lane) : "vcc", "memory");
+}
 // A pointer the program knows to be wave-uniform, moved into scalar registers (64-bit products are computed on the
 // vector ALU, and the "s" operand of the load above must really be a scalar register pair).
 __device__ __forceinline__ const char* uniform_ptr(const char* p) {
@@ -1039,14 +1046,15 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
     // layout, so the source address is recomputed per load from the step index t of the lane's half of the
     // tile: t < K / 32 reads the backbone operands, later steps the tile's dense [256, kext] adapter operand
     // (rows of other jobs are stored zeros) against rows roff_first.. of b_all (forward) or columns roff_first..
-    // of a_all (backward).  Steps outside 0 .. ntot - 1 (first half of L_0, tiles past the end) and rows /
-    // columns beyond the problem edge are clamped to valid ones: they only fill LDS that is never read or feed
-    // outputs that are never stored.  Selects, not branches: a branch around a load would make the compiler
-    // wait for every outstanding load where the paths merge.
+    // of a_all (backward).  Steps outside 0 .. ntot - 1 (first half of L_0, tiles past the end) are clamped to valid
+    // ones: they only fill LDS that is never read.  Rows / columns beyond the problem edge are not loaded, or clamped
+    // to valid ones in the general path: they feed outputs that are never stored.
     //  k-contiguous tile ("row tile", 128 B rows): slot p -> row p / 8, 16-byte chunk (p % 8) ^ ((row / 2) % 8).
     // A tile whose two steps lie on the same side of the backbone / adapter boundary (all but one or two per
     // operand) is loaded as wave-uniform base + per-lane 32-bit offset; the offsets are loop constants.  The
-    // others take the general path, which derives each lane's address from scratch.
+    // others take the general path, which derives each lane's address from scratch.  While all tiles of the last,
+    // ragged row of tiles took it, 4095 tokens over 4096 -> 8192 ran 235 us forward where 4096 ran 216 (now 218 and
+    // 214), 12288 -> 8192 643 and 587 (now 585 and 565).
     const int lr = wave * 32 + (lane >> 3);                   // row / column of the tile for i = 0 (i adds 8)
     const int coff = ((lane & 3) ^ (lane >> 4)) * 16;         // byte offset of the lane's chunk inside its 32-k half
     const int h0 = (lane >> 2) & 1;                           // which half, for even i (odd i: the other one)
@@ -1060,14 +1068,16 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
         KN ? reinterpret_cast<const char*>(packed + (int64_t)td.roff_first * P.N + col0) - (int64_t)nfull * 64 * P.N
            : reinterpret_cast<const char*>(packed + (int64_t)col0 * P.ra + td.roff_first) - (int64_t)nfull * 64);
     const uint32_t lds0 = lds_addr(lds);
-    // Interior tiles (no row / column clamping) need two offsets per operand: the lane's row and chunk for even
-    // and for odd i; the 8 i rows between consecutive loads go into the uniform base.
-    const bool interior_m = rows_valid == BM, interior_n = col0 + BN <= P.N;
-    uint32_t k_off[2], x_off[2], kn_off[2];
+    // Two offsets per operand: the lane's row and chunk for even and for odd i; the 8 i rows between consecutive loads
+    // go into the uniform base.
+    // Steps in front of a_plain (w_plain) load without a look at the edges: the rows (columns) of this wave's loads all exist, and
+    // so do both steps of the tile.  (A forward weight tile past N reads on into the next rows: up to 255 elements, 32 rows of 8.)
+    const int a_plain = rows_valid >= wave * 32 + 32 ? nfull - 1 : 0;
+    const int w_plain = KN ? (col0 + BN <= P.N ? ntot : nfull - 1) : P.N - col0 >= wave * 32 + 32 ? max(nfull - 1, 0) : 0;
+    uint32_t k_off[2], kn_off[2];
 #pragma unroll
     for (int par = 0; par < 2; ++par) {
       k_off[par] = (uint32_t)lr * (uint32_t)(P.K * 2) + coff + (h0 ^ par) * 64;       // rows of K elements: act, NT weight
-      x_off[par] = INDEXED ? 0u : (uint32_t)lr * (uint32_t)(td.kext * 2) + coff + (h0 ^ par) * 64;   // rows of the adapter operand
       const int kl = wave * 8 + par * 2 + (lane >> 5);                                // forward weight: k-row of i = par
       const int c = (lane & 31) ^ ((kl & 3) << 2) ^ (((kl >> 3) & 1) << 1);
       kn_off[par] = KN ? (uint32_t)(kl & 31) * (uint32_t)(P.N * 2) + c * 16 : 0u;
@@ -1086,25 +1096,37 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
         const char* const sb = a_base + (int64_t)tq * 64;
 #pragma unroll
         for (int i = 0; i < 4; ++i) dma16s(g_off[i], sb, dst + i * 1024);
-      } else if (!INDEXED && interior_m && tq + 1 < nfull) {
+      } else if (!INDEXED && tq < a_plain) {
         const char* const sb = a_base + (int64_t)tq * 64;
 #pragma unroll
         for (int i = 0; i < 4; ++i) dma16s(k_off[i & 1], uniform_ptr(sb + (int64_t)i * 16 * P.K), dst + i * 1024);
+      } else if (!INDEXED && tq + 1 < nfull) {                 // the last row tile, ragged
+        const char* const sb = a_base + (int64_t)tq * 64;
+        int below = rows_valid;
+        asm volatile("" : "+s"(below));        // (four limits kept through the loop would spill)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          dma16s_below(lane, (below - wave * 32 - i * 8) * 8, k_off[i & 1], uniform_ptr(sb + (int64_t)i * 16 * P.K), dst + i * 1024);
       } else if (!INDEXED && tq >= nfull && tq + 1 < ntot) {   // (INDEXED keeps no offsets for these few steps: general path)
         const char* const sb = x_base + (int64_t)tq * 64;
+        int l0 = lane;
+        asm volatile("" : "+v"(l0));          // (rows of the adapter operand: found here rather than kept)
+        const uint32_t back = (uint32_t)(wave * 32 + (l0 >> 3)) * (uint32_t)((P.K - td.kext) * 2);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dma16s(x_off[i & 1], uniform_ptr(sb + (int64_t)i * 16 * td.kext), dst + i * 1024);
+        for (int i = 0; i < 4; ++i) dma16s(k_off[i & 1] - back, uniform_ptr(sb + (int64_t)i * 16 * td.kext), dst + i * 1024);
       } else {
-        int r0 = lr;
-        asm volatile("" : "+v"(r0));         // keep what this rare path derives out of the loop's live registers
+        int l0 = lane;
+        asm volatile("" : "+v"(l0));          // keep what this rare path derives out of the loop's live registers
+        const int r0 = wave * 32 + (l0 >> 3);
+        const int coff0 = ((l0 & 3) ^ (l0 >> 4)) * 16, h00 = (l0 >> 2) & 1;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int r = r0 + i * 8;
-          const int t = min(max(tq + (h0 ^ (i & 1)), 0), ntot - 1);
+          const int t = min(max(tq + (h00 ^ (i & 1)), 0), ntot - 1);
           const bool ext = t >= nfull;
           const uint32_t off = (ext ? (uint32_t)r * (uint32_t)(td.kext * 2)
-                                : INDEXED ? g_off[i] - coff - (h0 ^ (i & 1)) * 64
-                                          : (uint32_t)min(r, rows_valid - 1) * (uint32_t)(P.K * 2)) + t * 64 + coff;
+                                : INDEXED ? g_off[i] - coff0 - (h00 ^ (i & 1)) * 64
+                                          : (uint32_t)min(r, rows_valid - 1) * (uint32_t)(P.K * 2)) + t * 64 + coff0;
           dma16((ext ? x_base : a_base) + off, dst + i * 1024);
         }
       }
@@ -1116,7 +1138,7 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
         //  to one step, so base and step clamping are wave-uniform
         const int t = min(max(tq + (wave >> 2), 0), ntot - 1);
         const char* const sb = (t >= nfull ? e_base : w_base) + (int64_t)t * 64 * P.N;
-        if (interior_n) {
+        if (t < w_plain) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             dma16s(kn_off[i & 1], uniform_ptr(sb + (int64_t)(i >> 1) * 8 * P.N), dst + i * 1024);   // i / 2: 4 k-rows on
@@ -1130,19 +1152,28 @@ __global__ void __launch_bounds__(512) seg_gemm_kernel(GemmParams P) {
             dma16(sb + (int64_t)(kl & 31) * (P.N * 2) + min(c * 16, (P.N - 8 - col0) * 2), dst + i * 1024);
           }
         }
-      } else if (interior_n && tq >= 0 && tq + 1 < nfull) {
+      } else if ((uint32_t)tq < (uint32_t)w_plain) {       // (not the half tile in front of the first step)
         const char* const sb = w_base + (int64_t)tq * 64;
 #pragma unroll
         for (int i = 0; i < 4; ++i) dma16s(k_off[i & 1], uniform_ptr(sb + (int64_t)i * 16 * P.K), dst + i * 1024);
+      } else if (tq >= 0 && tq + 1 < nfull) {
+        const char* const sb = w_base + (int64_t)tq * 64;
+        int below = P.N - col0;
+        asm volatile("" : "+s"(below));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          dma16s_below(lane, (below - wave * 32 - i * 8) * 8, k_off[i & 1], uniform_ptr(sb + (int64_t)i * 16 * P.K), dst + i * 1024);
       } else {                                // the few adapter steps of the backward weight operand included
-        int r0 = lr;
-        asm volatile("" : "+v"(r0));
+        int l0 = lane;
+        asm volatile("" : "+v"(l0));
+        const int r0 = wave * 32 + (l0 >> 3);
+        const int coff0 = ((l0 & 3) ^ (l0 >> 4)) * 16, h00 = (l0 >> 2) & 1;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int n = min(r0 + i * 8, P.N - 1 - col0);
-          const int t = min(max(tq + (h0 ^ (i & 1)), 0), ntot - 1);
+          const int t = min(max(tq + (h00 ^ (i & 1)), 0), ntot - 1);
           const bool ext = t >= nfull;
-          const uint32_t off = (uint32_t)n * (uint32_t)((ext ? P.ra : P.K) * 2) + t * 64 + coff;
+          const uint32_t off = (uint32_t)n * (uint32_t)((ext ? P.ra : P.K) * 2) + t * 64 + coff0;
           dma16((ext ? e_base : w_base) + off, dst + i * 1024);
         }
       }
