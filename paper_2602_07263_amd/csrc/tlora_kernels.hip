@@ -1731,8 +1731,8 @@ void launch_small(bool w_is_kn, const JobDev* jobs, const TileDev* tiles, const 
 // in memory (token-major) and read through the transposing LDS read.  One workgroup (8 waves) owns
 // kGradCols = 256 feature columns x 32*MB rank rows for a chunk of tokens, so V is read from memory once for all
 // rank rows; a wave takes 64 columns and every other rank block.  Per step of 32 tokens a stage holds the V tile (32 x 256, 16 KB) and
-// the two U tiles (32 x 32*MB); four stages are filled by asynchronous global->LDS loads three steps
-// ahead.  V rows beyond the chunk are clamped to its last row: they meet the zero pad rows of U.
+// the two U tiles (32 x 32*MB); four stages (seven, for one block of ranks) are filled by asynchronous
+// global->LDS loads three (six) steps ahead.  V rows beyond the chunk are clamped to its last row: they meet the zero pad rows of U.
 // ---------------------------------------------------------------------------------------------------
 __device__ __forceinline__ bf16x8 frag_tr_u(const uint8_t* plane, int pitch, int sw_shift, int sw_mask, int nb, int kk,
                                             int lane) {
@@ -1756,61 +1756,54 @@ __device__ __forceinline__ bf16x8 frag_tr_u(const uint8_t* plane, int pitch, int
 // INDEXED: the rows of V are fetched through row_index (token-indexed calls).  A separate instantiation, so that the
 // plain one carries no trace of it: even a branch around a memory load inside the load loop would make the compiler
 // wait, where the paths merge, for every asynchronous load in flight.
-// One launch may run the units of dB_j and of dA_j (side, a_side).  A unit with all tokens of its job (part_off < 0) has the gradient
-// itself and stores it: dB rows leave the registers as runs of 128 bytes, dA is turned in LDS, half of the columns at a time.  The
-// others leave partial tiles.  With partial tiles for every job and a launch for each side, dA and dB took, reductions included (mlp
-// projections of 31744 tokens 797 us / now 723; 32 skewed jobs 1695 / 1501; four jobs of 7680 tokens, 4096 -> 4096, 54 / 43; three of
-// 9082, 4096 -> 5120, 94 / 58; 4198 tokens of eleven jobs, 10848 -> 1448, 77 / 52).
-template <bool INDEXED>
-__global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict__ jobs, GradSide side, GradSide a_side,
-                                                        float* __restrict__ partial, int accumulate,
-                                                        const int32_t* __restrict__ row_index) {
-  constexpr int MB = kGradMaxBlocks;                        // the U tile always has room for 4 blocks of 32 ranks;
-  constexpr int RP = kGradRanks * MB;                       // a unit multiplies only its u.mb live ones
-  constexpr int UPITCH = 2 * RP;                            // 256 bytes per token row of a U tile
+// ONE: the unit has one block of 32 rank rows (the whole job, up to rank 32).  Each wave then takes 32 columns of it, where four of
+// the eight would idle, and a stage's U planes are a quarter, so that seven stages fit: a launch of few units waits for its loads, and
+// six steps in flight instead of three bring them sooner (one job of 512 tokens, 64 units: 12.6 us with four stages, now 9.4; 576
+// units of 4096 tokens 50.2 / 44.4; same bits).
+template <bool ONE>
+struct GradShape {
+  static constexpr int MB = ONE ? 1 : kGradMaxBlocks;       // blocks of 32 ranks a U tile has room for;
+  static constexpr int RP = kGradRanks * MB;                // a unit multiplies only its u.mb live ones
+  static constexpr int UPLANE = kGradStep * 2 * RP;         // 2 KB * MB
+  static constexpr int VTILE = kGradStep * kGradCols * 2;   // 16 KB
+  static constexpr int STAGE = VTILE + 2 * UPLANE;
+  static constexpr int STAGES = ONE ? 7 : 4;
+};
+constexpr int kGradLds = std::max(GradShape<true>::STAGE * GradShape<true>::STAGES, GradShape<false>::STAGE * GradShape<false>::STAGES);
+
+template <bool INDEXED, bool ONE>
+__device__ __forceinline__ void rank_grad_unit(const GradUnit& u, const JobDev& jb, const GradSide& side, bool dA, float* partial,
+                                               int accumulate, const int32_t* row_index, uint8_t* lds, int32_t* srow) {
+  using G = GradShape<ONE>;
+  constexpr int MB = G::MB, RP = G::RP, UPLANE = G::UPLANE, VTILE = G::VTILE, STAGE = G::STAGE, STAGES = G::STAGES;
+  constexpr int UPITCH = 2 * RP;                            // 256 (64) bytes per token row of a U tile
   // 16-byte chunk c of token row k sits at slot c ^ ((k & 3) << 2) so that the four rows one transposing read
-  // touches start in four distinct 64-byte bank groups
+  // touches start in four distinct 64-byte bank groups (rows of 64 bytes do so as they lie)
   constexpr int SW_SHIFT = 0;
-  constexpr int SW_MASK = 3;
-  constexpr int UPLANE = kGradStep * UPITCH;                // 2 KB * MB
-  constexpr int VTILE = kGradStep * kGradCols * 2;          // 16 KB
+  constexpr int SW_MASK = ONE ? 0 : 3;
   constexpr int WAVES = 8;
   constexpr int V_LD = VTILE / 1024 / WAVES;                // 2 loads per wave: V tile
-  constexpr int U_LD = 2 * UPLANE / 1024 / WAVES;           // 2 loads per wave: hi and lo planes of U
+  constexpr int U_LD = ONE ? 1 : 2 * UPLANE / 1024 / WAVES; // 2 loads per wave: hi and lo planes of U (ONE: half of one)
   constexpr int LOADS = V_LD + U_LD;                        // asynchronous loads per wave per step
-  constexpr int MW = MB / 2;                                // rank blocks per wave
-  static_assert(V_LD * WAVES * 1024 == VTILE && U_LD * WAVES * 1024 == 2 * UPLANE && MB == 4, "load split over the waves");
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[4 * (VTILE + 2 * UPLANE)];
-  uint8_t* const g0 = lds;
-  uint8_t* const g1 = lds + VTILE;
-  uint8_t* const g2 = lds + 2 * VTILE;
-  uint8_t* const g3 = lds + 3 * VTILE;
-  uint8_t* const h0 = lds + 4 * VTILE;
-  uint8_t* const h1 = h0 + 2 * UPLANE;
-  uint8_t* const h2 = h0 + 4 * UPLANE;
-  uint8_t* const h3 = h0 + 6 * UPLANE;
-  // token-indexed calls: where in the batch each token row of the unit lies (row_index of the unit's chunk, staged
-  // once so that the load loop never waits for an index from memory; a unit has at most kGradMaxTokens tokens)
-  __shared__ int32_t srow[INDEXED ? kGradMaxTokens : 1];
+  constexpr int MW = ONE ? 1 : MB / 2;                      // rank blocks and blocks of 32 columns per wave
+  constexpr int NW = ONE ? 1 : 2;
+  static_assert(V_LD * WAVES * 1024 == VTILE && (ONE || U_LD * WAVES * 1024 == 2 * UPLANE) && (ONE || MB == 4), "load split over the waves");
 
-  const bool dA = (int)blockIdx.x >= side.count;
-  if (dA) side = a_side;
-  const GradUnit u = side.units[dA ? blockIdx.x - (gridDim.x - a_side.count) : blockIdx.x];
-  const JobDev jb = jobs[u.job];
   const uint16_t* const V = side.V;
   const int D = side.D;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cg = wave & 3, rh = wave >> 2;                  // column group, rank half
+  const int cg = wave & 3, rh = ONE ? 0 : wave >> 2;        // column group, rank half
+  const int wcol = ONE ? wave * 32 : cg * 64;               // first column of the wave
   const int col0 = u.cb * kGradCols;
-  const int pbase = u.pb * RP;
+  const int pbase = u.pb * (kGradMaxBlocks * kGradRanks);
   const int nsteps = (u.t1 - u.t0 + kGradStep - 1) / kGradStep;
 
-  f32x16 acc[MW][2];
+  f32x16 acc[MW][NW];
 #pragma unroll
   for (int m = 0; m < MW; ++m)
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < NW; ++n)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[m][n][e] = 0.f;
 
@@ -1832,21 +1825,23 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
 #pragma unroll
   for (int i = 0; i < U_LD; ++i) {
     const int q = wave * U_LD + i;                    // 0 .. 4 MB - 1
-    const int plane = q / (2 * MB), within = q % (2 * MB);
-    const int slot = within * 64 + lane;              // 16-byte slot inside the plane
-    const int k = slot / (RP / 8), cphys = slot % (RP / 8);
+    const int plane = ONE ? wave >> 2 : q / (2 * MB), within = q % (2 * MB);
+    const int slot = ONE ? (wave & 3) * 32 + lane : within * 64 + lane;       // 16-byte slot inside the plane
+    const int k = min(slot / (RP / 8), kGradStep - 1), cphys = slot % (RP / 8);
     const int c = cphys ^ (((k >> SW_SHIFT) & SW_MASK) << 2);
-    ulive[i] = pbase + c * 8 < jb.rpad || lane == 0;    // lane 0 keeps every wave's load count the same
+    ulive[i] = (pbase + c * 8 < jb.rpad && (!ONE || lane < 32)) || lane == 0;  // lane 0 keeps every wave's load count the same
     const int p = min(pbase + c * 8, jb.rpad - 8);
     usrc[i] = (plane ? side.Ulo : side.Uhi) + jb.soff + (int64_t)(u.t0 - jb.row0 + k) * jb.rpad + p;
-    udst[i] = plane * UPLANE + within * 1024;
+    udst[i] = plane * UPLANE + (ONE ? (wave & 3) * 512 : within * 1024);
   }
   if (INDEXED) {
     for (int i = tid; i < min(u.t1 - u.t0, kGradMaxTokens); i += WAVES * 64) srow[i] = row_index[u.t0 + i];
     __syncthreads();
   }
   int f_step = 0;                                     // next step to fetch
-  auto issue = [&](uint8_t* S, uint8_t* H) {
+  auto issue = [&](int stage) {
+    uint8_t* const S = lds + stage * STAGE;
+    uint8_t* const H = S + VTILE;
     const int st = min(f_step, nsteps - 1);           // trailing issues re-load the last step (uniform load count)
     const uint32_t sbase = lds_addr(S + wave * (V_LD * 1024)), hbase = lds_addr(H);
 #pragma unroll
@@ -1860,20 +1855,22 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
       if (ulive[i]) dma16(usrc[i] + (int64_t)st * kGradStep * jb.rpad, hbase + __builtin_amdgcn_readfirstlane(udst[i]));
     ++f_step;
   };
-  auto compute = [&](const uint8_t* S, const uint8_t* H) {
+  auto compute = [&](int stage) {
+    const uint8_t* const S = lds + stage * STAGE;
+    const uint8_t* const H = S + VTILE;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-      bf16x8 vf[2];
+      bf16x8 vf[NW];
 #pragma unroll
-      for (int n = 0; n < 2; ++n) vf[n] = frag_kn_tile(S, cg * 64 + n * 32, kk, lane);
+      for (int n = 0; n < NW; ++n) vf[n] = frag_kn_tile(S, wcol + n * 32, kk, lane);
 #pragma unroll
       for (int i = 0; i < MW; ++i) {
         const int m = rh + 2 * i;
-        if (m < u.mb) {
+        if (ONE || m < u.mb) {
           const bf16x8 hi = frag_tr_u(H, UPITCH, SW_SHIFT, SW_MASK, m * 32, kk, lane);
           const bf16x8 lo = frag_tr_u(H + UPLANE, UPITCH, SW_SHIFT, SW_MASK, m * 32, kk, lane);
 #pragma unroll
-          for (int n = 0; n < 2; ++n) {
+          for (int n = 0; n < NW; ++n) {
             acc[i][n] = mfma32(hi, vf[n], acc[i][n]);
             acc[i][n] = mfma32(lo, vf[n], acc[i][n]);
           }
@@ -1882,24 +1879,29 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
     }
   };
   auto landed = [&]() {
-    // loads complete in order: all but those of the two youngest steps have landed
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LOADS));
+    // loads complete in order: all but those of the youngest steps have landed
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((STAGES - 2) * LOADS));
     __builtin_amdgcn_s_barrier();
   };
   if (nsteps > 0) {
-    issue(g0, h0);
-    issue(g1, h1);
-    issue(g2, h2);
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i) issue(i);
     int kt = 0;
-    for (; kt + 4 <= nsteps; kt += 4) {
-      landed();  issue(g3, h3);  compute(g0, h0);
-      landed();  issue(g0, h0);  compute(g1, h1);
-      landed();  issue(g1, h1);  compute(g2, h2);
-      landed();  issue(g2, h2);  compute(g3, h3);
+    for (; kt + STAGES <= nsteps; kt += STAGES) {
+#pragma unroll
+      for (int i = 0; i < STAGES; ++i) {
+        landed();
+        issue((i + STAGES - 1) % STAGES);
+        compute(i);
+      }
     }
-    if (kt < nsteps)     { landed();  issue(g3, h3);  compute(g0, h0); }
-    if (kt + 1 < nsteps) { landed();  issue(g0, h0);  compute(g1, h1); }
-    if (kt + 2 < nsteps) { landed();  issue(g1, h1);  compute(g2, h2); }
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i)
+      if (kt + i < nsteps) {
+        landed();
+        issue((i + STAGES - 1) % STAGES);
+        compute(i);
+      }
     __builtin_amdgcn_s_waitcnt(0x0070);   // drain the trailing loads before the workgroup's LDS is released
   }
 
@@ -1910,10 +1912,10 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
 #pragma unroll
       for (int i = 0; i < MW; ++i)
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
+        for (int n = 0; n < NW; ++n)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int p = (rh + 2 * i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), c = col0 + cg * 64 + n * 32 + (lane & 31);
+            const int p = (rh + 2 * i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), c = col0 + wcol + n * 32 + (lane & 31);
             if (p < live && c < D) {
               float* const d = dst + (int64_t)p * D + c;
               const float v = jb.scale * acc[i][n][e];
@@ -1923,23 +1925,25 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
       return;
     }
     constexpr int PITCH = RP + 1;
-    static_assert(128 * PITCH * 4 <= 4 * (VTILE + 2 * UPLANE), "half of the columns fit into the stages' place");
+    constexpr int XC = kGradCols / NW;                                   // columns turned at a time
+    static_assert(XC * PITCH * 4 <= STAGES * STAGE, "they fit into the stages' place");
+    auto column = [&](int x, int n) { return col0 + (ONE ? x : (x >> 5) * 64 + n * 32 + (x & 31)); };
     float* const turn = reinterpret_cast<float*>(lds);
     float* const dst = static_cast<float*>(jb.dA) + pbase;
     const bool fours = (jb.rank & 3) == 0 && (reinterpret_cast<uintptr_t>(jb.dA) & 15) == 0;
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < NW; ++n) {
       __syncthreads();                                                   // the stages, or the first half, have been read
 #pragma unroll
       for (int i = 0; i < MW; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          turn[(cg * 32 + (lane & 31)) * PITCH + (rh + 2 * i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)] = jb.scale * acc[i][n][e];
+          turn[((ONE ? wave : cg) * 32 + (lane & 31)) * PITCH + (rh + 2 * i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)] = jb.scale * acc[i][n][e];
       __syncthreads();
       if (fours) {                                                       // four ranks of a column per thread
         const int per = live / 4;
-        for (int q = tid; q < 128 * per; q += WAVES * 64) {
-          const int x = q / per, p = (q - x * per) * 4, c = col0 + (x >> 5) * 64 + n * 32 + (x & 31);
+        for (int q = tid; q < XC * per; q += WAVES * 64) {
+          const int x = q / per, p = (q - x * per) * 4, c = column(x, n);
           if (c < D) {
             f32x4* const d = reinterpret_cast<f32x4*>(dst + (int64_t)c * jb.rank + p);
             const float* const t = turn + x * PITCH + p;
@@ -1949,8 +1953,8 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
           }
         }
       } else {
-        for (int q = tid; q < 128 * live; q += WAVES * 64) {
-          const int x = q / live, p = q - x * live, c = col0 + (x >> 5) * 64 + n * 32 + (x & 31);
+        for (int q = tid; q < XC * live; q += WAVES * 64) {
+          const int x = q / live, p = q - x * live, c = column(x, n);
           if (c < D) {
             float* const d = dst + (int64_t)c * jb.rank + p;
             const float v = turn[x * PITCH + p];
@@ -1967,16 +1971,37 @@ __global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict
 #pragma unroll
   for (int i = 0; i < MW; ++i) {
     const int m = rh + 2 * i;
-    if (m < u.mb) {
+    if (ONE || m < u.mb) {
 #pragma unroll
-      for (int n = 0; n < 2; ++n)
+      for (int n = 0; n < NW; ++n)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int pl = m * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-          out[pl * kGradCols + cg * 64 + n * 32 + (lane & 31)] = acc[i][n][e];
+          out[pl * kGradCols + wcol + n * 32 + (lane & 31)] = acc[i][n][e];
         }
     }
   }
+}
+
+// One launch may run the units of dB_j and of dA_j (side, a_side).  A unit with all tokens of its job (part_off < 0) has the gradient
+// itself and stores it: dB rows leave the registers as runs of 128 bytes, dA is turned in LDS, half of the columns at a time.  The
+// others leave partial tiles.  With partial tiles for every job and a launch for each side, dA and dB took, reductions included (mlp
+// projections of 31744 tokens 797 us / now 723; 32 skewed jobs 1695 / 1501; four jobs of 7680 tokens, 4096 -> 4096, 54 / 43; three of
+// 9082, 4096 -> 5120, 94 / 58; 4198 tokens of eleven jobs, 10848 -> 1448, 77 / 52).
+template <bool INDEXED>
+__global__ void __launch_bounds__(512) rank_grad_kernel(const JobDev* __restrict__ jobs, GradSide side, GradSide a_side,
+                                                        float* __restrict__ partial, int accumulate,
+                                                        const int32_t* __restrict__ row_index) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kGradLds];
+  // token-indexed calls: where in the batch each token row of the unit lies (row_index of the unit's chunk, staged
+  // once so that the load loop never waits for an index from memory; a unit has at most kGradMaxTokens tokens)
+  __shared__ int32_t srow[INDEXED ? kGradMaxTokens : 1];
+  const bool dA = (int)blockIdx.x >= side.count;
+  if (dA) side = a_side;
+  const GradUnit u = side.units[dA ? blockIdx.x - (gridDim.x - a_side.count) : blockIdx.x];
+  const JobDev jb = jobs[u.job];
+  if (u.mb == 1) rank_grad_unit<INDEXED, true>(u, jb, side, dA, partial, accumulate, row_index, lds, srow);
+  else           rank_grad_unit<INDEXED, false>(u, jb, side, dA, partial, accumulate, row_index, lds, srow);
 }
 
 void launch_rank_grad(const JobDev* jobs, const GradSide& b, const GradSide& a, float* partial, bool accumulate,

@@ -14,6 +14,7 @@ CASES = [
     ("two_blocks_and_idle_jobs", 1032, 3080, [256, 7, 129], [500, 0, 33]),
     ("a_long_job_beside_short_ones", 2048, 2304, [8, 40, 5], [6000, 40, 300]),
     ("long_jobs_of_full_height", 4096, 1024, [128, 64], [4100, 700]),
+    ("around_seven_steps", 1024, 1032, [32, 8, 25], [192, 224, 250]),
     ("two_launches", 264, 520, [8, 33, 2], [700, 0, 4500]),
 ]
 
