@@ -567,7 +567,7 @@ constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 
 // (128 x 32); NS stages are filled NS - 1 steps ahead by raw asynchronous global->LDS loads, so several KB
 // per wave stay in flight without holding registers -- the kernel is bound by how fast X (or dY) streams in.
 // ---------------------------------------------------------------------------------------------------
-// PCOLS: rank columns staged per step.  A unit whose job has at most 32 padded rank columns stages a 32-column
+// PCOLS: rank columns staged per step.  A unit whose job has at most 32 (64) padded rank columns stages such an
 // adapter tile and spends the LDS it saves on more stages: the kernel is bound by the bytes of X in flight.
 // WAVES: 4, or 8 for the 128-row units.  A CU runs one workgroup (the stages fill its LDS), so with four waves every
 // SIMD has a single wave whose LDS reads, MFMAs and waits follow one another; for a 128-column unit that serial
@@ -585,10 +585,10 @@ __device__ __forceinline__ void shrink_stream_body(uint8_t* lds, const ShrinkUni
                                                    uint16_t* __restrict__ Shi, uint16_t* __restrict__ Slo,
                                                    uint16_t* __restrict__ Sx, const int32_t* __restrict__ row_index,
                                                    int step0, int nsteps, float* __restrict__ part) {
-  constexpr int CW = PCOLS == 32 ? 4 : WAVES;      // waves that multiply
-  constexpr int WM = PCOLS == 32 ? 4 : ROWS / 32;  // waves along token rows
+  constexpr int WM = ROWS / 32;                    // waves along token rows
+  constexpr int CW = PCOLS == 128 ? WAVES : WM * (PCOLS / 32);   // waves that multiply
   constexpr int WN = CW / WM;                      // waves along rank columns
-  static_assert(WM * 32 == ROWS || PCOLS != 32, "a 32-column unit needs 128 token rows for its four waves");
+  static_assert(CW <= WAVES, "a wave multiplies blocks of 32 x 32");
   constexpr int PW = PCOLS / WN, NPB = PW / 32;    // rank columns (and 32-wide blocks) per wave
   static_assert(WN >= 1 && PW % 32 == 0 && NPB >= 1, "wave layout");
   constexpr int RB = KS * 2;                       // bytes per tile row: 64 (K-steps of 32) or 128 (of 64)
@@ -643,11 +643,13 @@ __device__ __forceinline__ void shrink_stream_body(uint8_t* lds, const ShrinkUni
   auto issue = [&]() {
     const int st = min(f_step, nsteps - 1);        // trailing issues re-load the last step (uniform load count)
     const uint32_t base = lds0 + (f_step % NS) * STAGE;
+    const bool needed = !SPLIT || f_step < nsteps || lane == 0;      // (a split has few steps)
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) dma16(asrc[i] + st * KS, base + (wave * A_LD + i) * 1024);
+    for (int i = 0; i < A_LD; ++i)
+      if (needed) dma16(asrc[i] + st * KS, base + (wave * A_LD + i) * 1024);
 #pragma unroll
     for (int i = 0; i < P_LD; ++i)
-      if (plive[i]) dma16(psrc[i] + st * KS, base + A_BYTES + __builtin_amdgcn_readfirstlane(pslot[i]) * 1024);
+      if (plive[i] && needed) dma16(psrc[i] + st * KS, base + A_BYTES + __builtin_amdgcn_readfirstlane(pslot[i]) * 1024);
     ++f_step;
   };
   for (int i = 0; i < NS - 1; ++i) issue();
@@ -777,7 +779,9 @@ __global__ void __launch_bounds__(WAVES * 64) shrink_stream_kernel(const JobDev*
 // units of 32 rows leave half the workgroup slots empty and one 512-token job fills 16 of 256 CUs for the whole
 // 12288-long contraction.  blockIdx.y = split: each takes an even share of the K-steps, all splits run at once, and
 // shrink_emit_kernel adds their fp32 sums in split order (a fixed order: bit-reproducible) and writes what the direct
-// kernel writes.
+// kernel writes.  A stage holds as many rank columns as the unit's job has, in 32s up to 64: what that leaves of the LDS keeps
+// nine (five) steps of X in flight instead of three.  With stages of 128 columns for all, a shrink of three jobs of ranks up to 16
+// took 18.0 us (1900 tokens, 12288 features; now 12.8), of ranks 8 to 64 20.9 (7680, 4096; 18.3); same bits.
 // ---------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) shrink_split_kernel(const JobDev* __restrict__ jobs, const ShrinkUnit* __restrict__ units,
                                                            const uint16_t* __restrict__ act, int K,
@@ -789,8 +793,16 @@ __global__ void __launch_bounds__(256) shrink_split_kernel(const JobDev* __restr
   const JobDev jb = jobs[u.job];
   const int total = K / 64;
   const int s0 = (int)((int64_t)blockIdx.y * total / gridDim.y), s1 = (int)((int64_t)(blockIdx.y + 1) * total / gridDim.y);
-  shrink_stream_body<32, 4, 64, 128, 4, true>(lds, u, jb, nullptr, act, K, packed, packed_is_atp, nullptr, nullptr, nullptr,
-                                              row_index, s0, s1 - s0, part + (int64_t)blockIdx.y * part_stride);
+  float* const sums = part + (int64_t)blockIdx.y * part_stride;
+  if (jb.rpad <= 32)
+    shrink_stream_body<32, 10, 64, 32, 4, true>(lds, u, jb, nullptr, act, K, packed, packed_is_atp, nullptr, nullptr, nullptr,
+                                                row_index, s0, s1 - s0, sums);
+  else if (jb.rpad <= 64)
+    shrink_stream_body<32, 6, 64, 64, 4, true>(lds, u, jb, nullptr, act, K, packed, packed_is_atp, nullptr, nullptr, nullptr,
+                                               row_index, s0, s1 - s0, sums);
+  else
+    shrink_stream_body<32, 4, 64, 128, 4, true>(lds, u, jb, nullptr, act, K, packed, packed_is_atp, nullptr, nullptr, nullptr,
+                                                row_index, s0, s1 - s0, sums);
 }
 
 // One workgroup = 8 rows of a GEMM tile, threads along the 16-byte chunks of the rows of its K-extension operand: own
