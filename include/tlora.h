@@ -95,7 +95,7 @@ typedef struct {
 /* Bytes of device workspace that tlora_fwd / tlora_bwd need for this problem (depends only on
  * dtype, J, d_in, d_out, ranks, offsets).  It grows with sum_j T_j * r_j and with r_j * (d_in + d_out), plus
  * one bf16 d_in x d_out buffer (the transposed W of the backward, shared by all jobs), plus one block that the partial
- * tiles of dA / dB (at most 2046 tiles of 32 KB per 32 ranks of a job while there are few tokens, then linear in T) and the
+ * tiles of dA and dB (of each at most 2046 tiles of 32 KB per 32 ranks of a job while there are few tokens, then linear in T) and the
  * fp32 sums of launches whose contraction is cut (at most 128 MiB, at most 12 T (d_in + d_out) bytes
  * or 128 bytes per element of the packed S_j) use in turn; no d_in x d_out per-job buffer is ever used (Sec. 3.3: the
  * merged adapter weight is not materialised).  It never falls when tokens are added: the workspace of a batch serves
@@ -421,7 +421,8 @@ int tlora_plan_check(const tlora_problem_t* p, int32_t fwd_only, int32_t* failed
 /* How the plan of `p` (of the forward alone if fwd_only != 0) cuts contractions into shares whose fp32 sums are added by a
  * launch of their own (host only): cuts[0], cuts[1] = shares of S_j = X_j.A_j and of dS_j = dY_j.B_j^T; cuts[2], cuts[3] =
  * whole tiles of the forward's backbone product and shares of each of the others; cuts[4], cuts[5] = the same of dX.  One
- * share means not cut (every tile is whole). */
+ * share means not cut (every tile is whole).  A batch of at most 128 tokens may run in the two-launch form instead, whose shares these are
+ * not, and a block runs gate and up, or k and v, as one product of twice the tiles. */
 int tlora_plan_cuts(const tlora_problem_t* p, int32_t fwd_only, int32_t* cuts);
 
 /* Tuning knobs (process-wide, for experiments and for the tiling-independence tests).
