@@ -1091,15 +1091,22 @@ int tlora_fwd_noalloc(const tlora_problem_t* p, void* Y, void* hip_stream) {
 
 namespace tlora {
 namespace {
-// later: as there; the product then follows the gradients.
+// What the nano-batches of one call have left in its workspace for those after them.  The copies of the adapters are known one by
+// one: a nano-batch in the two-launch form packs no a_all, and a later one of another form may read it.
+struct Packed {
+  bool adapters = false;                                // A_j^T and B_j
+  bool a_all = false;                                   // A_j side by side
+};
 // The backward's launch sequence (out_index / in_index as in fwd_impl: dX rows are scattered; X and dY are fetched
-// through the list; packed and shared_sums as there, the latter also for the partial tiles of dA / dB).
+// through the list; shared_sums as there, also for the partial tiles of dA / dB; later as there, the product then follows the
+// gradients).
+// packed: of the nano-batches before this one, brought up to date (null: no nano-batch).
 // batch_tokens: of the whole batch, if the call is one of its nano-batches, which share one copy of W^T or do without alike.
 // wt_there: the same entry point has made the copy for an earlier nano-batch.
 int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags,
              void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index,
-             bool packed = false, uint8_t* shared_sums = nullptr, int64_t batch_tokens = 0, bool wt_there = false,
-             GemmCall* later = nullptr) {
+             uint8_t* shared_sums = nullptr, GemmCall* later = nullptr, Packed* packed = nullptr, int64_t batch_tokens = 0,
+             bool wt_there = false) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, false, shared_sums != nullptr);
@@ -1215,10 +1222,11 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace, and a_all,
     // which only a dX product against W as it lies reads, if the forward's batch is one for it
     const bool need_a_all = dX && !wt && !small;
-    const bool have_a_all = reuse_S ? packs_a_all(pl) : packed;
-    if (!(reuse_S || packed) || (need_a_all && !have_a_all))
+    const Packed have = reuse_S ? Packed{true, packs_a_all(pl)} : packed ? *packed : Packed();
+    if (!have.adapters || (need_a_all && !have.a_all))
       launch_pack_adapters(reinterpret_cast<JobDev*>(tb), pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp,
                            need_a_all ? ap : nullptr, bp, FragPack(), nullptr, 0, st);
+    if (packed) *packed = {true, have.a_all || need_a_all};
   }
   if (pl.T > 0) {
     if (redo_S) {
@@ -1408,7 +1416,8 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
   if (!workspace || ws_bytes < need) return TLORA_EWORKSPACE;
   const size_t elt = p->dtype == TLORA_F32 ? 4 : 2;
   const int64_t T = p->offsets[p->num_jobs];
-  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0, wt_there = false, packed = false;
+  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0, wt_there = false;
+  Packed packed;
   for (int32_t n = 0; n < n_nano; ++n) {
     NanoSub s;
     int rc = make_sub(p, n_nano, granule, n, s);
@@ -1418,9 +1427,8 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
     int f = (first ? (flags & TLORA_BWD_ACCUMULATE) : TLORA_BWD_ACCUMULATE) | (wt_made ? TLORA_BWD_REUSE_WT : 0);
     rc = bwd_impl(&s.p, dY ? static_cast<const uint8_t*>(dY) + (size_t)s.b0 * p->d_out * elt : nullptr,
                   dX ? static_cast<uint8_t*>(dX) + (size_t)s.b0 * p->d_in * elt : nullptr, dA, dB, f, workspace, ws_bytes,
-                  hip_stream, nullptr, nullptr, packed, nullptr, T, wt_there);
+                  hip_stream, nullptr, nullptr, nullptr, nullptr, &packed, T, wt_there);
     if (rc != TLORA_OK) return rc;
-    packed = true;
     first = false;
     // (a batch that does without the copy does so in every nano-batch)
     if (dX && s.b1 > s.b0 && (wt_made || !dx_direct(T, p->d_in, p->d_out))) wt_made = wt_there = true;
@@ -1495,8 +1503,8 @@ int layer_fwd(const tlora_problem_t* p, void* Y, uint8_t* ws, size_t own, uint8_
 }
 int layer_bwd(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags, uint8_t* ws,
               size_t own, uint8_t* sums, void* hip_stream, GemmCall* later = nullptr) {
-  return bwd_impl(p, dY, dX, dA, dB, flags, ws, own, hip_stream, nullptr, nullptr, false,
-                  p->dtype == TLORA_BF16 ? sums : nullptr, 0, false, later);
+  return bwd_impl(p, dY, dX, dA, dB, flags, ws, own, hip_stream, nullptr, nullptr,
+                  p->dtype == TLORA_BF16 ? sums : nullptr, later);
 }
 
 struct MlpLayout {

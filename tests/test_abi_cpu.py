@@ -359,6 +359,14 @@ def test_problems_of_the_cut_tests_are_cut():
     assert cuts(na.FIRST)["fwd"][1] == 1 and cuts(na.SECOND)["fwd"][1] == 1
 
 
+def test_problems_of_the_mixed_nano_batches_are_mixed():
+    """The GPU tests of nano-batches in both forms name which are which: so it must be, whatever the cost model becomes."""
+    from tests import test_nano_gpu as nano
+    for name, d_in, d_out, ranks, tokens, n_nano, granule, small in nano.MIXED:
+        prob, _keep = _problem(ranks, tokens, d_in=d_in, d_out=d_out)
+        assert nano.small_nano_batches(prob, n_nano, granule) == small, name
+
+
 @pytest.mark.parametrize("cfg", [0, 1, 2, 3, 4])
 def test_planner_self_check_on_the_five_configurations(cfg):
     wl = wk.config(cfg)

@@ -74,6 +74,50 @@ def test_accumulate_flag_adds_to_the_existing_gradients(dtype):
     _assert_ok(res, f"accumulate plain/{dtype}")
 
 
+# Nano-batches of which some run in the two-launch form of small batches and others in the general one: by their sizes, or by
+# the ranks that are idle in them.  d_in d_out >= 2^19, so that dX runs against W as it lies in both.
+MIXED = [
+    # name, d_in, d_out, ranks, tokens, n_nano, granule, which nano-batches are small
+    ("larger_last", 1024, 1024, [16], [700], 6, 100, [1, 1, 1, 1, 1, 0]),
+    ("larger_in_between", 1024, 1024, [32, 30], [200, 250], 4, 75, [1, 0, 1, 0]),
+    ("idle_ranks_later", 1024, 1024, [64, 16], [256, 256], 4, 128, [1, 1, 0, 0]),
+    ("idle_ranks_first", 1024, 2048, [16, 64], [128, 256], 3, 128, [0, 1, 1]),
+]
+
+
+def small_nano_batches(prob, n_nano, granule):
+    """Which nano-batches' backward runs in the two-launch form."""
+    from paper_2602_07263_amd import tlora
+    out = []
+    for n in range(n_nano):
+        _, _, off = tlora.tlora_nano_split(prob, n_nano, granule, n)
+        sub, _keep = tlora.make_problem(tlora.TLORA_BF16, prob.d_in, prob.d_out, list(prob.ranks[:prob.num_jobs]), off,
+                                        [1.0] * prob.num_jobs, 0x1000, 0x2000, [0x3000] * prob.num_jobs, [0x4000] * prob.num_jobs)
+        c = tlora.tlora_plan_cuts(sub)
+        out.append(int(c["bwd"] == (0, c["shrink_dy"])))
+    return out
+
+
+@pytest.mark.parametrize("case", MIXED, ids=[c[0] for c in MIXED])
+def test_small_and_general_nano_batches_of_one_call(case):
+    """dX of the general ones reads copies of the adapters that the small ones do without."""
+    import torch
+    from paper_2602_07263_amd import tlora
+    name, d_in, d_out, ranks, tokens, n_nano, granule, small = case
+    p = wk.generate(wk.custom(name, "bf16", d_in, d_out, ranks, tokens, [2.0] * len(ranks)), seed=12)
+    lp = tlora.LayerProblem.from_numpy(p)
+    assert small_nano_batches(lp.prob, n_nano, granule) == small
+    lp._nano_ws(n_nano, granule)
+    lp.ws.fill_(255)                                                    # (NaN in bf16 and fp32)
+    dY = torch.from_numpy(p.dY).to(device="cuda", dtype=torch.bfloat16)
+    Y, dX, dA, dB = lp.new_outputs()
+    lp.fwd_nano(n_nano, granule, Y)
+    lp.bwd_nano(n_nano, granule, dY, dX, dA, dB)
+    torch.cuda.synchronize()
+    n = lambda t: t.float().cpu().numpy()
+    _assert_ok(pu.compare(p, n(Y), n(dX), [n(a) for a in dA], [n(b) for b in dB]), name)
+
+
 def test_reuse_of_the_transposed_weight():
     """A second backward with TLORA_BWD_REUSE_WT on the same workspace and W finds the copy."""
     import torch
