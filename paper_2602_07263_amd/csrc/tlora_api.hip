@@ -1091,22 +1091,21 @@ int tlora_fwd_noalloc(const tlora_problem_t* p, void* Y, void* hip_stream) {
 
 namespace tlora {
 namespace {
-// What the nano-batches of one call have left in its workspace for those after them.  The copies of the adapters are known one by
-// one: a nano-batch in the two-launch form packs no a_all, and a later one of another form may read it.
-struct Packed {
-  bool adapters = false;                                // A_j^T and B_j
+// What the nano-batches of one call have left in its workspace for those after them, copy by copy: a nano-batch in the two-launch
+// form makes neither a_all nor W^T, and a later one of the other form may read either.
+struct Copies {
+  bool adapters = false;                                // A_j^T and B_j, packed
   bool a_all = false;                                   // A_j side by side
+  bool wt = false;                                      // W^T
 };
 // The backward's launch sequence (out_index / in_index as in fwd_impl: dX rows are scattered; X and dY are fetched
 // through the list; shared_sums as there, also for the partial tiles of dA / dB; later as there, the product then follows the
 // gradients).
-// packed: of the nano-batches before this one, brought up to date (null: no nano-batch).
-// batch_tokens: of the whole batch, if the call is one of its nano-batches, which share one copy of W^T or do without alike.
-// wt_there: the same entry point has made the copy for an earlier nano-batch.
+// copies: of the nano-batches before this one, brought up to date (null: no nano-batch).
+// batch_tokens: of the whole batch, if the call is one of its nano-batches.  It decides whether dX has use for a copy of W^T.
 int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA, void* const* dB, int flags,
              void* workspace, size_t ws_bytes, void* hip_stream, const int32_t* out_index, const int32_t* in_index,
-             uint8_t* shared_sums = nullptr, GemmCall* later = nullptr, Packed* packed = nullptr, int64_t batch_tokens = 0,
-             bool wt_there = false) {
+             uint8_t* shared_sums = nullptr, GemmCall* later = nullptr, Copies* copies = nullptr, int64_t batch_tokens = 0) {
   const PlanEntry* entry = nullptr;
   std::vector<JobDev> hjobs;
   int rc = common_checks(p, &entry, hjobs, workspace, ws_bytes, false, shared_sums != nullptr);
@@ -1185,15 +1184,17 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
   }
 
   const bool direct = dx_direct(std::max<int64_t>(batch_tokens, pl.T), pl.d_in, pl.d_out);
-  const bool reuse_wt = (flags & TLORA_BWD_REUSE_WT) != 0;
   // (the nano-batches of a large batch share its copy)
   const bool small = pl.small_dy && (batch_tokens <= pl.T || direct);
-  const bool wt = g_opt.dx_transposed_w != 0 && !small && (reuse_wt || !direct);
+  const bool promised = (flags & TLORA_BWD_REUSE_WT) != 0, wt_there = copies && copies->wt;
+  const bool wt = g_opt.dx_transposed_w != 0 && !small && (promised || !direct);
+  const bool wt_made = wt && !promised && !wt_there;    // by a launch of its own, below
   uint16_t* Wt = reinterpret_cast<uint16_t*>(ws + pl.off_wt);
   WtCall wc;
   if (dX && pl.T > 0) {
-    if (!reuse_wt) wc.action = wt ? kWtMade : kWtNone;
-    else if (wt && !wt_there) wc.action = kWtEnsure;
+    if (wt_there) wc.action = kWtKeep;
+    else if (promised) wc.action = wt ? kWtEnsure : kWtKeep;
+    else wc.action = wt ? kWtMade : kWtNone;
     wc.state = reinterpret_cast<WtState*>(ws + pl.off_wt_state);
     wc.W = static_cast<const uint16_t*>(p->W);
     wc.Wt = Wt;
@@ -1222,11 +1223,11 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     // with TLORA_BWD_REUSE_S the forward's packed copies of the (unchanged) adapters are still in the workspace, and a_all,
     // which only a dX product against W as it lies reads, if the forward's batch is one for it
     const bool need_a_all = dX && !wt && !small;
-    const Packed have = reuse_S ? Packed{true, packs_a_all(pl)} : packed ? *packed : Packed();
+    const Copies have = reuse_S ? Copies{true, packs_a_all(pl)} : copies ? *copies : Copies();
     if (!have.adapters || (need_a_all && !have.a_all))
       launch_pack_adapters(reinterpret_cast<JobDev*>(tb), pl.J, pl.d_in, pl.d_out, pl.max_rpad, pl.r_total, atp,
                            need_a_all ? ap : nullptr, bp, FragPack(), nullptr, 0, st);
-    if (packed) *packed = {true, have.a_all || need_a_all};
+    if (copies) *copies = {true, have.a_all || need_a_all, wt_there || (dX && pl.T > 0 && wt)};
   }
   if (pl.T > 0) {
     if (redo_S) {
@@ -1252,7 +1253,7 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
       // dX = dY . W^T contracts over W's contiguous dimension.  Against a transposed copy of W the weight tiles
       // are 64 rows of 512 contiguous bytes instead of 256 rows of 128, which the load stream handles markedly
       // better (the copy costs one read and one write of W; W is frozen, so REUSE_WT skips it).
-      if (wt && !reuse_wt) {
+      if (wt_made) {
         Timed t(TLORA_K_WT, st);
         launch_transpose_bf16(static_cast<const uint16_t*>(p->W), Wt, pl.d_in, pl.d_out, st);
       }
@@ -1416,22 +1417,20 @@ int tlora_bwd_nano(const tlora_problem_t* p, int32_t n_nano, int64_t granule, co
   if (!workspace || ws_bytes < need) return TLORA_EWORKSPACE;
   const size_t elt = p->dtype == TLORA_F32 ? 4 : 2;
   const int64_t T = p->offsets[p->num_jobs];
-  bool first = true, wt_made = (flags & TLORA_BWD_REUSE_WT) != 0, wt_there = false;
-  Packed packed;
+  bool first = true;
+  Copies copies;
   for (int32_t n = 0; n < n_nano; ++n) {
     NanoSub s;
     int rc = make_sub(p, n_nano, granule, n, s);
     if (rc != TLORA_OK) return rc;
     if (s.b1 == s.b0 && !(first && n == n_nano - 1)) continue;      // (an all-empty batch still zeroes dA / dB once)
     // the adapter gradients are sums over the job's tokens: the first nano-batch overwrites, the others add
-    int f = (first ? (flags & TLORA_BWD_ACCUMULATE) : TLORA_BWD_ACCUMULATE) | (wt_made ? TLORA_BWD_REUSE_WT : 0);
+    const int f = first ? flags : flags | TLORA_BWD_ACCUMULATE;
     rc = bwd_impl(&s.p, dY ? static_cast<const uint8_t*>(dY) + (size_t)s.b0 * p->d_out * elt : nullptr,
                   dX ? static_cast<uint8_t*>(dX) + (size_t)s.b0 * p->d_in * elt : nullptr, dA, dB, f, workspace, ws_bytes,
-                  hip_stream, nullptr, nullptr, nullptr, nullptr, &packed, T, wt_there);
+                  hip_stream, nullptr, nullptr, nullptr, nullptr, &copies, T);
     if (rc != TLORA_OK) return rc;
     first = false;
-    // (a batch that does without the copy does so in every nano-batch)
-    if (dX && s.b1 > s.b0 && (wt_made || !dx_direct(T, p->d_in, p->d_out))) wt_made = wt_there = true;
   }
   return TLORA_OK;
 }

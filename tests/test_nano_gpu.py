@@ -118,6 +118,33 @@ def test_small_and_general_nano_batches_of_one_call(case):
     _assert_ok(pu.compare(p, n(Y), n(dX), [n(a) for a in dA], [n(b) for b in dB]), name)
 
 
+def test_the_flag_after_small_nano_batches_makes_the_copy():
+    """TLORA_BWD_REUSE_WT after a call that did without the copy of W^T: it is made where the first general nano-batch needs it,
+    though the small ones before have no use for it, and found by the next call."""
+    import torch
+    from paper_2602_07263_amd import tlora
+    for name, d_in, d_out, ranks, tokens, n_nano, granule, small in MIXED:
+        p = wk.generate(wk.custom(name, "bf16", d_in, d_out, ranks, tokens, [2.0] * len(ranks)), seed=13)
+        lp = tlora.LayerProblem.from_numpy(p)
+        lp._nano_ws(n_nano, granule)
+        lp.ws.fill_(255)
+        dY = torch.from_numpy(p.dY).to(device="cuda", dtype=torch.bfloat16)
+        first = None
+        for flags in (0, tlora.TLORA_BWD_REUSE_WT, tlora.TLORA_BWD_REUSE_WT):
+            Y, dX, dA, dB = lp.new_outputs()
+            for t in (Y, dX, *dA, *dB):
+                t.fill_(float("nan"))
+            lp.fwd_nano(n_nano, granule, Y)
+            lp.bwd_nano(n_nano, granule, dY, dX, dA, dB, flags)
+            torch.cuda.synchronize()
+            if first is None:
+                first = [dX, *dA, *dB]
+                n = lambda t: t.float().cpu().numpy()
+                _assert_ok(pu.compare(p, n(Y), n(dX), [n(a) for a in dA], [n(b) for b in dB]), name)
+            else:
+                assert all(torch.equal(a, b) for a, b in zip(first, [dX, *dA, *dB])), (name, flags)
+
+
 def test_reuse_of_the_transposed_weight():
     """A second backward with TLORA_BWD_REUSE_WT on the same workspace and W finds the copy."""
     import torch
