@@ -96,6 +96,7 @@ struct Plan {
   GemmSplit gemm_split_fwd, gemm_split_bwd;             // tiles of the two GEMMs that are cut along the contraction
   GemmSplit pair_split_fwd, pair_split_bwd;             // and of two such GEMMs in one launch
   int small_x = 0, small_dy = 0;                        // splits of a small batch's two-launch form (0: not taken), X and dY side
+  bool frags_wait = false;                              // dY's fragments lie behind the sums that making S again writes
   size_t partial_bytes = 0;                             // what off_partial holds: dA / dB tiles, or sums of split launches
   // workspace byte offsets
   size_t off_tables = 0, off_S = 0, off_dS = 0, off_Shi = 0, off_Slo = 0, off_dShi = 0, off_dSlo = 0, off_Sx = 0, off_dSx = 0, off_atp = 0, off_wt = 0, off_wt_state = 0, off_ap = 0,
@@ -340,15 +341,20 @@ size_t small_frag_bytes(const Plan& pl, int K) {
   const int rb = small_blocks(pl.T);
   return small_frags(rb) ? align_up((size_t)rb * 32 * (size_t)K, 256) : 0;
 }
-// Where the fragments of X (side 0) and dY (side 1) lie in the room of the sums: behind those of either direction.
+// Where the fragments of X (side 0) and dY (side 1) lie in the room of the sums: behind those of the two-launch form of either
+// direction, and those of dY, which a backward writes with its first launch, also behind the sums of a general S = X.A if that
+// backward may make S again first (frags_wait; where the room does not hold both, they are written after S).
+size_t small_frag_at(const Plan& pl, int side) {
+  const size_t shrink = pl.small_x || pl.shrink_splits_x < 2 ? 0 : sizeof(float) * (size_t)pl.s_elems * (size_t)pl.shrink_splits_x;
+  const size_t sums = std::max({pl.small_x ? small_part_bytes(pl, pl.d_out, pl.small_x) : 0,
+                                pl.small_dy ? small_part_bytes(pl, pl.d_in, pl.small_dy) : 0, pl.frags_wait ? shrink : 0});
+  return align_up(sums, 256) + (side ? small_frag_bytes(pl, pl.d_in) : 0);
+}
 FragPack small_frag_pack(const Plan& pl, int side, const void* act, const int32_t* in_index, void* sums) {
   FragPack f;
   f.act = static_cast<const uint16_t*>(act);  f.in_index = in_index;
   f.T = pl.T;  f.K = side ? pl.d_out : pl.d_in;  f.rb = small_blocks(pl.T);
-  if (!small_frags(f.rb)) return f;
-  const size_t x = std::max(pl.small_x ? small_part_bytes(pl, pl.d_out, pl.small_x) : 0,
-                            pl.small_dy ? small_part_bytes(pl, pl.d_in, pl.small_dy) : 0);
-  f.out = reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(sums) + align_up(x, 256) + (side ? small_frag_bytes(pl, pl.d_in) : 0));
+  if (small_frags(f.rb)) f.out = reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(sums) + small_frag_at(pl, side));
   return f;
 }
 // Splits of the two-launch form of a small batch over [T, K] x [K, N] (0: the general kernels); kn: against a weight as the
@@ -611,6 +617,8 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
       pl.pair_split_bwd = gemm_split(pl, pl.d_out, pl.d_in, sums_room(pl), 2);
       pl.small_dy = small_splits(pl, pl.d_out, pl.d_in, false, sums_room(pl));
       pl.partial_bytes = res.partial;
+      pl.frags_wait = true;
+      pl.frags_wait = small_frag_at(pl, 1) + small_frag_bytes(pl, pl.d_out) <= pl.partial_bytes;
       pl.off_partial = wplace(pl.partial_bytes);
     }
   }
@@ -1201,8 +1209,10 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     wc.rows = pl.d_in;  wc.cols = pl.d_out;
   }
   float* partial = reinterpret_cast<float*>(shared_sums ? shared_sums : ws + pl.off_partial);
+  const bool redo_S = want_grads && !reuse_S;
   const FragPack frags = small && pl.T > 0 ? small_frag_pack(pl, 1, dY, in_index, partial) : FragPack();
-  rc = upload_tables(blob, tb, st, wc, frags);
+  const bool frags_late = redo_S && !pl.frags_wait;
+  rc = upload_tables(blob, tb, st, wc, frags_late ? FragPack() : frags);
   if (rc != TLORA_OK) return rc;
   uint16_t* Sx = reinterpret_cast<uint16_t*>(ws + pl.off_Sx);
   uint16_t* dSx = reinterpret_cast<uint16_t*>(ws + pl.off_dSx);
@@ -1216,7 +1226,6 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
   const TileDev* tiles = reinterpret_cast<const TileDev*>(tb + pl.tb_tiles);
   const uint16_t* Xb = static_cast<const uint16_t*>(p->X);
   const uint16_t* dYb = static_cast<const uint16_t*>(dY);
-  const bool redo_S = want_grads && !reuse_S;
 
   {
     Timed t(TLORA_K_PACK, st);
@@ -1243,6 +1252,7 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     }
     if (small) {
       Timed t(dX ? TLORA_K_GEMM_BWD : TLORA_K_SHRINK, st);
+      if (frags_late) launch_frag_pack(frags, st);
       launch_small(false, jobs, tiles, frags.out ? frags.out : dYb, static_cast<const uint16_t*>(p->W), bp, atp, pl.r_total, static_cast<uint16_t*>(dX),
                    out_index, in_index, pl.T, pl.d_out, pl.d_in, pl.small_dy, partial, dShi, dSlo, st);
     } else {
@@ -2360,10 +2370,14 @@ static int check_plan(const Plan& pl, bool fwd_only) {
         if (k == 0) continue;
         if (pl.T < 1 || pl.T > kSmallRows || pl.tile_jobs.size() != 1 || K % 64 || N % 64 || k < 1 || k > K / 64) return 71;
         if (small_part_bytes(pl, N, k) > pl.partial_bytes) return 72;
-        uint8_t* const none = nullptr;                   // (offsets)
-        const FragPack f = small_frag_pack(pl, d, nullptr, nullptr, none);
-        if (f.out && (size_t)(reinterpret_cast<uint8_t*>(f.out) - none) + small_frag_bytes(pl, K) > pl.partial_bytes) return 73;
-        if (f.out && (size_t)(reinterpret_cast<uint8_t*>(f.out) - none) < small_part_bytes(pl, N, k)) return 74;
+        if (!small_frags(small_blocks(pl.T))) continue;
+        const size_t at = small_frag_at(pl, d);
+        if (at % 256 || at + small_frag_bytes(pl, K) > pl.partial_bytes) return 73;
+        if (at < small_part_bytes(pl, N, k)) return 74;
+        // dY's beside what making S again writes
+        if (d && pl.small_x &&
+            at < std::max(small_part_bytes(pl, pl.d_out, pl.small_x), small_frag_at(pl, 0) + small_frag_bytes(pl, pl.d_in))) return 75;
+        if (d && !pl.small_x && pl.frags_wait && pl.shrink_splits_x > 1 && at < 4 * se * (size_t)pl.shrink_splits_x) return 76;
       }
       if (!fwd_only) w.push_back({pl.off_partial, pl.partial_bytes});
       else if (pl.total != forward_bytes(pl)) return 70;

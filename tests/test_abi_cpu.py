@@ -359,6 +359,29 @@ def test_problems_of_the_cut_tests_are_cut():
     assert cuts(na.FIRST)["fwd"][1] == 1 and cuts(na.SECOND)["fwd"][1] == 1
 
 
+def test_self_check_of_small_batches_of_high_ranks():
+    """Plans whose backward of dY runs in the two-launch form and whose forward does not: S made again and dY's fragments share the
+    room of the sums.  The GPU tests' problems are of this kind, whatever the cost model becomes."""
+    from tests import test_small_batches_gpu as sb
+    small = lambda c, product, shrink: c[product] == (0, c[shrink])
+    rng = np.random.default_rng(77)
+    problems = [c[1:] for c in sb.HALF_SMALL]
+    for _ in range(1500):
+        J = int(rng.integers(1, 13))
+        tokens = 1 + rng.multinomial(int(rng.integers(33, 129)) - J, np.ones(J) / J)
+        problems.append((int(64 * rng.integers(8, 193)), int(64 * rng.integers(8, 193)),
+                         [int(r) for r in rng.choice([64, 100, 128, 256, 512, 1024], J)], [int(t) for t in tokens]))
+    half = 0
+    for i, (d_in, d_out, ranks, tokens) in enumerate(problems):
+        prob, _keep = _problem(ranks, tokens, d_in=d_in, d_out=d_out)
+        c = tlora.tlora_plan_cuts(prob)
+        mixed = small(c, "bwd", "shrink_dy") and not small(c, "fwd", "shrink_x")
+        assert mixed or i >= len(sb.HALF_SMALL), (sb.HALF_SMALL[i], c)
+        half += mixed
+        assert tlora.tlora_plan_check(prob) == (0, 0), (d_in, d_out, ranks, tokens, tlora.tlora_plan_check(prob))
+    assert half > 100
+
+
 def test_problems_of_the_mixed_nano_batches_are_mixed():
     """The GPU tests of nano-batches in both forms name which are which: so it must be, whatever the cost model becomes."""
     from tests import test_nano_gpu as nano

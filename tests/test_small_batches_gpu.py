@@ -39,6 +39,29 @@ def test_small_batches_meet_the_oracle(case):
         assert all(v <= 1.0 for v in res.values()), f"{name} reuse={reuse}: worst error / tolerance ratios {res}"
 
 
+# The backward of dY is small while the forward is not, so a backward that makes S again runs both forms in one room of sums:
+# dY's fragments (33 tokens on) lie behind whichever sums are more.
+HALF_SMALL = [
+    # name, d_in, d_out, ranks, tokens
+    ("twelve_short_jobs", 12288, 4096, [128] * 12, [3] * 12),
+    ("three_jobs", 5248, 512, [768, 128, 512], [28, 33, 24]),
+    ("four_jobs_110_tokens", 4672, 576, [256, 1024, 512, 64], [27, 28, 27, 28]),
+]
+
+
+@pytest.mark.parametrize("case", HALF_SMALL, ids=[c[0] for c in HALF_SMALL])
+def test_small_backward_of_a_general_forward(case):
+    from paper_2602_07263_amd import tlora
+    name, d_in, d_out, ranks, tokens = case
+    p = wk.generate(wk.custom(name, "bf16", d_in, d_out, ranks, tokens, [2.0] * len(ranks)), seed=63)
+    cuts = tlora.tlora_plan_cuts(tlora.LayerProblem.from_numpy(p).prob)
+    assert cuts["fwd"] != (0, cuts["shrink_x"]) and cuts["bwd"] == (0, cuts["shrink_dy"]), cuts
+    for reuse in (True, False):
+        Y, dX, dA, dB, _ = pu.run_gpu(p, reuse_S=reuse)
+        res = pu.compare(p, Y, dX, dA, dB)
+        assert all(v <= 1.0 for v in res.values()), f"{name} reuse={reuse}: worst error / tolerance ratios {res}"
+
+
 def test_row_lists_scratch_and_partial_outputs_give_the_same_bits():
     """Through a row list, without an allocation, without dX and without gradients: the plain call's bits."""
     import torch
