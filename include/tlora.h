@@ -475,7 +475,8 @@ int tlora_profile_read(int kernel_class, double* total_ms, int64_t* launches);
 /* Shader clock (GHz) that a sample of workgroups (every 64th) of the most recent profiled forward / backward
  * segmented GEMM saw across their K-loops (summed cycle counter over summed 100 MHz real-time counter): the
  * clock the chip actually sustained under that kernel's power draw, which scales the attainable MFMA rate.  Synchronises the device.  Either output may be NULL;
- * 0.0 = no profiled launch yet.  The workspace of that call must still be allocated. */
+ * 0.0 = no profiled launch yet, or the most recent product ran in the two-launch form of small batches, which takes no
+ * sample.  Two products of a block in one launch are one sample.  The workspace of that call must still be allocated. */
 int tlora_profile_clock(double* ghz_fwd, double* ghz_bwd);
 
 /* Static description of an error code. */

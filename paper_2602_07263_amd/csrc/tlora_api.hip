@@ -753,7 +753,12 @@ struct GemmCall {
   }
 };
 // second: another one over the same jobs, in the same launch; their sums have one place.
+// A profiled one is counted, the pair as a whole, into the clock slot of the first.
 void launch_gemm(const GemmCall& g, const GemmCall* second, hipStream_t st) {
+  if (g.clk) {
+    launch_zero_fill(g.clk, 16, st);
+    g_clock_slot[g.kernel == TLORA_K_GEMM_FWD ? 0 : 1] = g.clk;
+  }
   Timed t(g.kernel, st, g.timed);
   launch_seg_gemm(g.w_is_kn, g.tiles, g.op.act, g.op.W, g.op.Sx, g.op.packed, g.r_total, g.op.out, g.out_index, g.in_index, g.T,
                   g.K, g.N, g.clk, second ? g.pair_split : g.split, g.sums, second ? second->op : GemmOperands(), st);
@@ -1053,6 +1058,7 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
   }
   if (pl.small_x) {
     Timed tg(TLORA_K_GEMM_FWD, st, timed);
+    if (timed) g_clock_slot[0] = nullptr;             // (it takes no sample)
     launch_small(true, jobs, tiles, frags.out ? frags.out : static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), atp, bp, pl.r_total,
                  static_cast<uint16_t*>(Y), out_index, in_index, pl.T, pl.d_in, pl.d_out, pl.small_x, sums,
                  no_alloc ? nullptr : reinterpret_cast<uint16_t*>(ws + pl.off_Shi), reinterpret_cast<uint16_t*>(ws + pl.off_Slo), st);
@@ -1064,14 +1070,13 @@ int fwd_impl(const tlora_problem_t* p, void* Y, void* workspace, size_t ws_bytes
                reinterpret_cast<uint16_t*>(ws + pl.off_Shi), reinterpret_cast<uint16_t*>(ws + pl.off_Slo), Sx, in_index,
                sums, st);
   }
-  if (timed) launch_zero_fill(ws + pl.off_clock, 16, st);
   GemmCall g;
   g.kernel = TLORA_K_GEMM_FWD;  g.w_is_kn = true;  g.timed = timed;
   g.tiles = tiles;
   g.op = {static_cast<const uint16_t*>(p->X), static_cast<const uint16_t*>(p->W), Sx, bp, static_cast<uint16_t*>(Y)};
   g.r_total = pl.r_total;  g.T = pl.T;  g.K = pl.d_in;  g.N = pl.d_out;
   g.out_index = out_index;  g.in_index = in_index;
-  g.clk = timed ? (g_clock_slot[0] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock)) : nullptr;
+  g.clk = timed ? reinterpret_cast<unsigned long long*>(ws + pl.off_clock) : nullptr;
   g.split = pl.gemm_split_fwd;  g.pair_split = pl.pair_split_fwd;  g.sums = sums;
   if (later && g.pairs()) *later = g;
   else launch_gemm(g, nullptr, st);
@@ -1252,6 +1257,7 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     }
     if (small) {
       Timed t(dX ? TLORA_K_GEMM_BWD : TLORA_K_SHRINK, st);
+      if (g_prof_on && dX) g_clock_slot[1] = nullptr;
       if (frags_late) launch_frag_pack(frags, st);
       launch_small(false, jobs, tiles, frags.out ? frags.out : dYb, static_cast<const uint16_t*>(p->W), bp, atp, pl.r_total, static_cast<uint16_t*>(dX),
                    out_index, in_index, pl.T, pl.d_out, pl.d_in, pl.small_dy, partial, dShi, dSlo, st);
@@ -1267,14 +1273,13 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
         Timed t(TLORA_K_WT, st);
         launch_transpose_bf16(static_cast<const uint16_t*>(p->W), Wt, pl.d_in, pl.d_out, st);
       }
-      if (g_prof_on) launch_zero_fill(ws + pl.off_clock + 16, 16, st);
       GemmCall g;
       g.kernel = TLORA_K_GEMM_BWD;  g.w_is_kn = wt;
       g.tiles = tiles;
       g.op = {dYb, wt ? Wt : static_cast<const uint16_t*>(p->W), dSx, wt ? atp : ap, static_cast<uint16_t*>(dX)};
       g.r_total = pl.r_total;  g.T = pl.T;  g.K = pl.d_out;  g.N = pl.d_in;
       g.out_index = out_index;  g.in_index = in_index;
-      g.clk = g_prof_on ? (g_clock_slot[1] = reinterpret_cast<unsigned long long*>(ws + pl.off_clock) + 2) : nullptr;
+      g.clk = g_prof_on ? reinterpret_cast<unsigned long long*>(ws + pl.off_clock) + 2 : nullptr;
       g.split = pl.gemm_split_bwd;  g.pair_split = pl.pair_split_bwd;  g.sums = partial;
       if (later && g.pairs()) *later = g;
       else launch_gemm(g, nullptr, st);
