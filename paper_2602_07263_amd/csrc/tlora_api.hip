@@ -173,10 +173,10 @@ bool grad_bounds(const Plan& pl, int D, GradBounds& bounds) {
   };
   double shrink = 1.0;
   while (shrink > 1.0 / 64 && count(shrink).units < kGradUnitsWanted) shrink *= 0.5;
-  if (count(shrink).units > kMaxUnits || grad_tiles(pl, D) > kMaxUnits) return false;
+  if (count(shrink).units > kMaxUnits) return false;
   // Grows with every job's tokens: what chunks of 1024 tokens per live block give, or, of each tile height at most what the
   // shortest chunks give, the tallest tiles first, 2046 units.  The chunks below are chosen within it (those of 4096 tokens always
-  // are); the units of idle jobs, which store zeros, come on top.
+  // are); the output tiles of idle jobs, which are zeros, come on top.
   const GradBounds whole = count(1.0);
   int64_t by_height[kGradMaxBlocks + 1] = {}, left = 2 * (kGradUnitsWanted - 1);
   for (const JobDev& jb : pl.jobs)
@@ -188,7 +188,7 @@ bool grad_bounds(const Plan& pl, int D, GradBounds& bounds) {
     const int64_t u = std::min(by_height[mb], left);
     bounds.units += u;  bounds.floats += u * mb * kGradRanks * kGradCols;  left -= u;
   }
-  bounds.units = std::max(whole.units, bounds.units) + grad_tiles(pl, D);
+  bounds.units = std::max(whole.units, bounds.units);
   bounds.floats = std::max(whole.floats, bounds.floats);
   return true;
 }
@@ -210,7 +210,7 @@ GradCost grad_cost(const Plan& pl, int D, double limit) {
       g.longest = std::max(g.longest, fixed + step * ((std::min(T, chunk) + kGradStep - 1) / kGradStep));
       g.sum += ncb * (n * fixed + step * ((T + kGradStep - 1) / kGradStep));
       g.bytes += (double)ncb * T * kGradCols * 2;
-      g.units += (int64_t)n * ncb;
+      if (T > 0) g.units += (int64_t)n * ncb;
       if (n > 1) g.floats += (int64_t)n * ncb * mb * kGradRanks * kGradCols;
     }
   }
@@ -234,8 +234,9 @@ double grad_limit(const Plan& pl, const int* widths, const GradBounds* bounds, i
   }
   return best;
 }
-void build_grad_units(const Plan& pl, int D, double limit, std::vector<GradUnit>& units, std::vector<GradGroup>& groups,
-                      int64_t& partial_floats /* in: first free float, out: past the last */) {
+// idle_units: the output tiles of jobs without tokens are units, which store zeros; else groups of no partial tiles, which do too.
+void build_grad_units(const Plan& pl, int D, double limit, bool idle_units, std::vector<GradUnit>& units,
+                      std::vector<GradGroup>& groups, int64_t& partial_floats /* in: first free float, out: past the last */) {
   const int ncb = (D + kGradCols - 1) / kGradCols;
   for (int j = 0; j < pl.J; ++j) {
     const JobDev& jb = pl.jobs[j];
@@ -245,12 +246,16 @@ void build_grad_units(const Plan& pl, int D, double limit, std::vector<GradUnit>
       const int mb = grad_live_blocks(jb, pb), chunk = grad_chunk_of(mb, limit);
       const int nchunks = std::max(1, (Tj + chunk - 1) / chunk);
       for (int cb = 0; cb < ncb; ++cb) {
-        if (nchunks == 1) {
+        if (nchunks == 1 && (Tj > 0 || idle_units)) {
           units.push_back(GradUnit{j, jb.row0, jb.row1, cb, pb, mb, -1});
           continue;
         }
         GradGroup g{};
-        g.job = j;  g.cb = cb;  g.pb = pb;  g.mb = mb;  g.nunits = nchunks;  g.part_off = partial_floats;
+        g.job = j;  g.cb = cb;  g.pb = pb;  g.mb = mb;  g.nunits = Tj > 0 ? nchunks : 0;  g.part_off = partial_floats;
+        if (Tj == 0) {
+          groups.push_back(g);
+          continue;
+        }
         for (int c = 0; c < nchunks; ++c) {
           const int t0 = jb.row0 + c * chunk;
           units.push_back(GradUnit{j, t0, std::min(jb.row1, t0 + chunk), cb, pb, mb, partial_floats});
@@ -433,7 +438,7 @@ Reserve reserve_of(const Plan& pl, const GradBounds& gB, const GradBounds& gA) {
   table(sizeof(ShrinkUnit) * (size_t)stream);
   for (int d = 0; d < 2; ++d) {
     const int64_t tiles = grad_tiles(pl, d ? pl.d_in : pl.d_out);
-    table(sizeof(GradUnit) * (size_t)(d ? gA.units : gB.units));
+    table(sizeof(GradUnit) * (size_t)((d ? gA.units : gB.units) + tiles));
     table(sizeof(GradGroup) * (size_t)tiles);
   }
   r.partial = std::max(sums_room(pl), sizeof(float) * (size_t)(gB.floats + gA.floats));
@@ -527,14 +532,18 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     }
     if (!fwd_only) {
       if (!grad_bounds(pl, pl.d_out, gB) || !grad_bounds(pl, pl.d_in, gA)) return TLORA_EINVAL;
-      // One launch for both from 32 output tiles on; with fewer either way is a few workgroups.
-      pl.grads_merged = grad_tiles(pl, pl.d_out) + grad_tiles(pl, pl.d_in) >= 32;
+      // One launch for both from 32 output tiles on; with fewer either way is a few workgroups.  A launch has at most kMaxUnits units
+      // (2^31 threads): with more, which takes tens of thousands of jobs, the idle ones go with the reduction and each side has a
+      // launch of its own, as both did for all sizes once.
+      const int64_t tiles = grad_tiles(pl, pl.d_out) + grad_tiles(pl, pl.d_in);
+      const bool one_launch_holds = gB.units + gA.units + tiles <= kMaxUnits;
+      pl.grads_merged = tiles >= 32 && one_launch_holds;
       const int widths[2] = {pl.d_out, pl.d_in};
       const GradBounds bounds[2] = {gB, gA};
       const double limit = grad_limit(pl, widths, bounds, pl.grads_merged ? 2 : 1);
-      build_grad_units(pl, pl.d_out, limit, pl.gradB_units, pl.gradB_groups, pl.grad_partial);
-      build_grad_units(pl, pl.d_in, pl.grads_merged ? limit : grad_limit(pl, widths + 1, bounds + 1, 1), pl.gradA_units, pl.gradA_groups,
-                       pl.grad_partial);
+      build_grad_units(pl, pl.d_out, limit, one_launch_holds, pl.gradB_units, pl.gradB_groups, pl.grad_partial);
+      build_grad_units(pl, pl.d_in, pl.grads_merged ? limit : grad_limit(pl, widths + 1, bounds + 1, 1), one_launch_holds, pl.gradA_units,
+                       pl.gradA_groups, pl.grad_partial);
     }
   }
 
@@ -2286,15 +2295,18 @@ static int check_plan(const Plan& pl, bool fwd_only) {
         spans.push_back({u.part_off, n});
       }
       // every output tile (job with a rank, column block, rank block) has a unit of its own, or one group whose partial tiles are
-      // the units of the same (job, cb, pb), consecutive in memory and covering the job's tokens
+      // the units of the same (job, cb, pb), consecutive in memory and covering the job's tokens (none, if it has no tokens)
+      if ((int64_t)units.size() > kMaxUnits) return 56;
       size_t alone = 0;
+      for (const GradGroup& g : groups)
+        if (g.nunits == 0) by_tile[{g.job, g.cb, g.pb}];
       for (const auto& t : by_tile) alone += t.second.size() == 1 && t.second[0]->part_off < 0;
       if ((int64_t)by_tile.size() != grad_tiles(pl, D) || alone + groups.size() != by_tile.size()) return 47;
       for (const GradGroup& g : groups) {
         if (g.job < 0 || g.job >= pl.J) return 48;
         const JobDev& jb = pl.jobs[g.job];
         auto& us = by_tile[{g.job, g.cb, g.pb}];
-        if ((int)us.size() != g.nunits || g.nunits < 2) return 49;
+        if ((int)us.size() != g.nunits || (g.nunits < 2 && (g.nunits != 0 || jb.row1 != jb.row0))) return 49;
         std::sort(us.begin(), us.end(), [](const GradUnit* a, const GradUnit* b) { return a->t0 < b->t0; });
         int t = jb.row0;
         for (int k = 0; k < g.nunits; ++k) {
@@ -2312,6 +2324,7 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       std::sort(spans.begin(), spans.end());                         // (both may be in use at a time)
       for (size_t i = 1; i < spans.size(); ++i)
         if (spans[i - 1].first + spans[i - 1].second > spans[i].first) return 46;
+      if (pl.grads_merged && (int64_t)(pl.gradB_units.size() + pl.gradA_units.size()) > kMaxUnits) return 56;
     } else if (!pl.gradA_units.empty() || !pl.gradB_units.empty()) {
       return 55;
     }

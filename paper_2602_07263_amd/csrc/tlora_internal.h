@@ -97,12 +97,13 @@ struct GradUnit {
   int64_t part_off;        // < 0: the unit has all tokens of its job and stores the gradient itself
 };
 
-// One output tile of dA_j / dB_j whose tokens are several units: the run of nunits consecutive partial tiles that sum to it.
+// One output tile of dA_j / dB_j whose tokens are several units: the run of nunits consecutive partial tiles that sum to it.  Or
+// one of a job without tokens, if those are too many to be units.
 struct GradGroup {
   int32_t job;
   int32_t cb, pb;
   int32_t mb;
-  int32_t nunits;          // number of partial tiles (token chunks), at least two
+  int32_t nunits;          // number of partial tiles (token chunks): two or more, or 0 without tokens
   int32_t pad_;
   int64_t part_off;        // float offset of the first partial tile
 };

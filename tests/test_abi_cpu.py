@@ -427,6 +427,13 @@ def test_sizes_beyond_the_stated_limits_are_refused_on_the_host():
     prob, _keep = tlora.make_problem(tlora.TLORA_BF16, 64, 64, [1024] * J, list(range(J + 1)), [1.0] * J, 0x1000, 0x2000,
                                      [0x3000] * J, [0x4000] * J)
     assert tlora.tlora_workspace_bytes(prob) == 0 and tlora.tlora_plan_check(prob)[0] == tlora.TLORA_EINVAL
+    J = 32768                                        # jobs without tokens: their 5.2 million gradient tiles are no work units
+    prob, _keep = tlora.make_problem(tlora.TLORA_BF16, 8, 40960, [1] * J, [0] * 1001 + [1] * (J - 1000), [1.0] * J, 0x1000, 0x2000,
+                                     [0x3000] * J, [0x4000] * J)
+    try:
+        assert tlora.tlora_workspace_bytes(prob) > 0
+    finally:
+        tlora.tlora_set_option("plan_cache", 1)      # (a large entry)
     J = 32769
     prob, _keep = tlora.make_problem(tlora.TLORA_BF16, 64, 64, [1] * J, list(range(J + 1)), [1.0] * J, 0x1000, 0x2000,
                                      [0x3000] * J, [0x4000] * J)
