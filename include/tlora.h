@@ -95,7 +95,7 @@ typedef struct {
 /* Bytes of device workspace that tlora_fwd / tlora_bwd need for this problem (depends only on
  * dtype, J, d_in, d_out, ranks, offsets).  It grows with sum_j T_j * r_j and with r_j * (d_in + d_out), plus
  * one bf16 d_in x d_out buffer (the transposed W of the backward, shared by all jobs), plus one block that the partial
- * tiles of dA and dB (of each at most 2046 tiles of 32 KB per 32 ranks of a job while there are few tokens, then linear in T) and the
+ * tiles of dA / dB (at most 2046 tiles of 32 KB per 32 ranks of a job while there are few tokens, then linear in T) and the
  * fp32 sums of launches whose contraction is cut (at most 128 MiB, at most 12 T (d_in + d_out) bytes
  * or 128 bytes per element of the packed S_j) use in turn; no d_in x d_out per-job buffer is ever used (Sec. 3.3: the
  * merged adapter weight is not materialised).  It never falls when tokens are added: the workspace of a batch serves

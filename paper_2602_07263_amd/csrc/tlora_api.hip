@@ -86,7 +86,7 @@ struct Plan {
   std::vector<GradUnit> gradB_units, gradA_units;      // dB: columns over d_out;  dA: columns over d_in;
 
   bool grads_merged = false;                            // dB and dA share a launch
-  int64_t grad_partial = 0;                             // floats of partial tiles, those of dB first
+  int64_t grad_partial = 0;                             // floats of partial tiles in use at a time (merged: those of dB first)
   std::vector<GradGroup> gradB_groups, gradA_groups;
   int64_t s_elems = 0;                                  // elements of the packed S (= dS) buffer
   int64_t atp_elems = 0;
@@ -105,10 +105,11 @@ struct Plan {
   size_t tables_bytes = 0;
   // offsets of each table inside the table blob
   size_t tb_jobs = 0, tb_tiles = 0, tb_shrink = 0, tb_stream = 0, tb_gBu = 0, tb_gBg = 0, tb_gAu = 0, tb_gAg = 0, tb_f32 = 0;
-  size_t off_clock = 0;                                 // 4 words outside the uploaded tables: GEMM clock probe
+  size_t off_clock = 0;                                 // kClockBytes outside the uploaded tables: GEMM clock probe
   size_t f32_reserved = 0;
 };
 
+constexpr size_t kClockBytes = 64;
 constexpr int64_t kMaxUnits = (int64_t)1 << 22;   // most GEMM tiles / work units of one kind in a launch
 
 int validate(const tlora_problem_t* p) {
@@ -217,20 +218,23 @@ GradCost grad_cost(const Plan& pl, int D, double limit) {
   return g;
 }
 // The limit for one launch over the given widths: the cheapest of a few, by the longest unit, the units' sum over 256 CUs, the bytes
-// of the activations at 5 TB/s, and for the partial tiles a launch of 5 us and their bytes, written and read, at 4 TB/s.
-double grad_limit(const Plan& pl, const int* widths, const GradBounds* bounds, int n) {
-  double best = 1e9, best_us = 0.0;
+// of the activations at 5 TB/s, and for the partial tiles a launch of 5 us and their bytes, written and read, at 4 TB/s.  Negative:
+// none whose partial tiles, room floats of them, have a place (for one width there always is one, see grad_bounds).
+double grad_limit(const Plan& pl, const int* widths, const GradBounds* bounds, int n, int64_t room) {
+  double best = -1.0, best_us = 0.0;
   for (double limit : {1e9, 96.0, 64.0, 48.0, 32.0, 24.0, 16.0, 12.0, 8.0, 6.0}) {
     double longest = 0.0, sum = 0.0, bytes = 0.0, extra = 0.0;
+    int64_t floats = 0;
     bool fits = true;
     for (int i = 0; i < n; ++i) {
       const GradCost g = grad_cost(pl, widths[i], limit);
-      fits = fits && g.units <= bounds[i].units && g.floats <= bounds[i].floats;
+      fits = fits && g.units <= bounds[i].units;
+      floats += g.floats;
       longest = std::max(longest, g.longest);  sum += g.sum;  bytes += g.bytes;
       if (g.floats > 0) extra += 5.0 + (double)g.floats * 8 / 4.0e6;
     }
     const double us = std::max({longest, sum / 256, bytes / 5.0e6}) + 0.5 * longest * (sum > 256 * longest) + extra;
-    if (limit == 1e9 || (fits && us < best_us)) { best = limit;  best_us = us; }
+    if (fits && floats <= room && (best < 0.0 || us < best_us)) { best = limit;  best_us = us; }
   }
   return best;
 }
@@ -401,11 +405,17 @@ size_t sums_room(const Plan& pl) {
   const size_t shrink = sizeof(float) * (size_t)pl.s_elems * kShrinkMaxSplits;
   return std::min<size_t>(std::max(gemm, shrink), 2 * (size_t)TLORA_NOALLOC_SUM_BYTES);
 }
+// Room for the partial tiles of dA / dB and those sums, which use it in turn: what either gradient may leave alone.  One launch for
+// both needs less than both bounds together nearly always (a job of one unit leaves none): while the room was their sum, workspaces
+// grew by up to 70 % (one job of rank 512, 6812 tokens, 5120 -> 5120: 381 to 649 MB).
+size_t grads_room(const Plan& pl, const GradBounds& gB, const GradBounds& gA) {
+  return std::max(sums_room(pl), sizeof(float) * (size_t)std::max(gB.floats, gA.floats));
+}
 // Bytes of the forward-only plan's workspace (the self-check holds the layout to this sum).
 size_t forward_bytes(const Plan& pl) {
   auto a = [](size_t bytes) { return align_up(bytes, 256); };
   return a(sizeof(JobDev) * pl.jobs.size()) + a(sizeof(TileDev) * pl.tile_jobs.size()) +
-         a(sizeof(ShrinkUnit) * pl.shrink_units.size()) + a(sizeof(ShrinkUnit) * pl.stream_units.size()) + a(64) +
+         a(sizeof(ShrinkUnit) * pl.shrink_units.size()) + a(sizeof(ShrinkUnit) * pl.stream_units.size()) + a(kClockBytes) +
          2 * a(2 * (size_t)pl.s_elems) + a(2 * (size_t)pl.sx_elems + 256) + a(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)) +
          (a(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)) + a(2 * (size_t)pl.d_out * (size_t)(pl.r_total + 32)));
 }
@@ -436,12 +446,11 @@ Reserve reserve_of(const Plan& pl, const GradBounds& gB, const GradBounds& gA) {
   table(sizeof(TileDev) * pl.tile_jobs.size());
   table(sizeof(ShrinkUnit) * pl.shrink_units.size());
   table(sizeof(ShrinkUnit) * (size_t)stream);
-  for (int d = 0; d < 2; ++d) {
-    const int64_t tiles = grad_tiles(pl, d ? pl.d_in : pl.d_out);
-    table(sizeof(GradUnit) * (size_t)((d ? gA.units : gB.units) + tiles));
-    table(sizeof(GradGroup) * (size_t)tiles);
-  }
-  r.partial = std::max(sums_room(pl), sizeof(float) * (size_t)(gB.floats + gA.floats));
+  // (an output tile is units and a group, or one unit or a group if its job is idle)
+  static_assert(sizeof(GradUnit) == sizeof(GradGroup), "they share a table's room");
+  for (int d = 0; d < 2; ++d)
+    table(sizeof(GradUnit) * (size_t)((d ? gA.units : gB.units) + grad_tiles(pl, d ? pl.d_in : pl.d_out)));
+  r.partial = grads_room(pl, gB, gA);
   return r;
 }
 
@@ -532,18 +541,28 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     }
     if (!fwd_only) {
       if (!grad_bounds(pl, pl.d_out, gB) || !grad_bounds(pl, pl.d_in, gA)) return TLORA_EINVAL;
-      // One launch for both from 32 output tiles on; with fewer either way is a few workgroups.  A launch has at most kMaxUnits units
-      // (2^31 threads): with more, which takes tens of thousands of jobs, the idle ones go with the reduction and each side has a
-      // launch of its own, as both did for all sizes once.
+      // One launch for both from 32 output tiles on, with fewer either way is a few workgroups; and if the partial tiles of both have
+      // room at a time.  Where they have not, either has rounds of units of its own and two launches take as long (backward of 20000
+      // and 24000 tokens at ranks 512 and 1024, 4096 -> 12288: one 6.80 ms, two 6.84; 25000 at rank 1024, 5120 -> 17408: 7.00, 6.98).
+      // A launch has at most kMaxUnits units (2^31 threads): with more, which takes tens of thousands of jobs, the idle ones go with
+      // the reduction and each side has a launch of its own.
       const int64_t tiles = grad_tiles(pl, pl.d_out) + grad_tiles(pl, pl.d_in);
       const bool one_launch_holds = gB.units + gA.units + tiles <= kMaxUnits;
       pl.grads_merged = tiles >= 32 && one_launch_holds;
       const int widths[2] = {pl.d_out, pl.d_in};
       const GradBounds bounds[2] = {gB, gA};
-      const double limit = grad_limit(pl, widths, bounds, pl.grads_merged ? 2 : 1);
-      build_grad_units(pl, pl.d_out, limit, one_launch_holds, pl.gradB_units, pl.gradB_groups, pl.grad_partial);
-      build_grad_units(pl, pl.d_in, pl.grads_merged ? limit : grad_limit(pl, widths + 1, bounds + 1, 1), one_launch_holds, pl.gradA_units,
-                       pl.gradA_groups, pl.grad_partial);
+      const int64_t room = (int64_t)(grads_room(pl, gB, gA) / sizeof(float));
+      double limit[2] = {-1.0, -1.0};
+      if (pl.grads_merged) limit[0] = limit[1] = grad_limit(pl, widths, bounds, 2, room);
+      pl.grads_merged = limit[0] >= 0.0;
+      int64_t used[2] = {};
+      for (int d = 0; d < 2; ++d) {
+        if (!pl.grads_merged) limit[d] = grad_limit(pl, widths + d, bounds + d, 1, room);
+        else if (d) used[1] = used[0];
+        build_grad_units(pl, widths[d], limit[d], one_launch_holds, d ? pl.gradA_units : pl.gradB_units,
+                         d ? pl.gradA_groups : pl.gradB_groups, used[d]);
+      }
+      pl.grad_partial = std::max(used[0], used[1]);
     }
   }
 
@@ -554,10 +573,13 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
   pl.tb_tiles = place(sizeof(TileDev) * pl.tile_jobs.size());
   pl.tb_shrink = place(sizeof(ShrinkUnit) * pl.shrink_units.size());
   pl.tb_stream = place(sizeof(ShrinkUnit) * pl.stream_units.size());
-  pl.tb_gBu = place(sizeof(GradUnit) * pl.gradB_units.size());
-  pl.tb_gBg = place(sizeof(GradGroup) * pl.gradB_groups.size());
-  pl.tb_gAu = place(sizeof(GradUnit) * pl.gradA_units.size());
-  pl.tb_gAg = place(sizeof(GradGroup) * pl.gradA_groups.size());
+  for (int d = 0; d < 2; ++d) {                         // the groups right behind the units
+    const size_t units = sizeof(GradUnit) * (d ? pl.gradA_units : pl.gradB_units).size();
+    const size_t groups = sizeof(GradGroup) * (d ? pl.gradA_groups : pl.gradB_groups).size();
+    size_t& at = d ? pl.tb_gAu : pl.tb_gBu;
+    at = place(units + groups);
+    (d ? pl.tb_gAg : pl.tb_gBg) = at + units;
+  }
   if (pl.dtype == TLORA_F32) {
     // the fp32 path needs at most 3 J + 1 products per launch, two launches per pass
     const size_t max_units = 2 * (size_t)(3 * pl.J + 1);
@@ -580,12 +602,11 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
   const Reserve res = full ? reserve_of(pl, gB, gA) : Reserve();
   size_t w = 0;
   auto wplace = [&](size_t bytes) { const size_t at = w;  w = align_up(w + bytes, 256);  return at; };
-  // the transposed W first: its place depends on nothing but d_in x d_out, so a copy made by one call is found
+  // the transposed W first, then its state: their place depends on nothing but d_in x d_out, so a copy made by one call is found
   // by later calls on other token batches (nano-batches) that share the workspace
-  if (full) {
-    pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
-    pl.off_wt_state = wplace(sizeof(WtState));
-  }
+  if (full) pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
+  pl.off_clock = wplace(kClockBytes + (full ? sizeof(WtState) : 0));
+  pl.off_wt_state = pl.off_clock + kClockBytes;         // (what is known about the copy, in the rest of the clock's 256 bytes)
   // so do the packed adapters, whose places depend on the feature sizes and ranks
   if (pl.dtype == TLORA_BF16) {
     pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
@@ -593,7 +614,6 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
   }
   pl.off_tables = wplace(full ? res.tables : pl.tables_bytes);
-  pl.off_clock = wplace(64);
   if (pl.dtype == TLORA_F32) {
     pl.off_S = wplace(sizeof(float) * (size_t)pl.s_elems);
     if (!fwd_only) pl.off_dS = wplace(sizeof(float) * (size_t)pl.s_elems);
@@ -1298,24 +1318,18 @@ int bwd_impl(const tlora_problem_t* p, const void* dY, void* dX, void* const* dA
     const GradSide b = {reinterpret_cast<const GradUnit*>(tb + pl.tb_gBu), Shi, Slo, dYb, pl.d_out, (int)pl.gradB_units.size()};
     const GradSide a = {reinterpret_cast<const GradUnit*>(tb + pl.tb_gAu), dShi, dSlo, Xb, pl.d_in, (int)pl.gradA_units.size()};
     const GradSide none;
-    {
+    auto gradients = [&](const GradSide& dB_side, const GradSide& dA_side) {
       Timed t(TLORA_K_RANK_GRAD, st);
-      launch_rank_grad(jobs, b, pl.grads_merged ? a : none, partial, accumulate, in_index, st);
-    }
-    if (!pl.grads_merged) {
-      Timed t(TLORA_K_RANK_GRAD, st);
-      launch_rank_grad(jobs, none, a, partial, accumulate, in_index, st);
-    }
-    {
+      launch_rank_grad(jobs, dB_side, dA_side, partial, accumulate, in_index, st);
+    };
+    auto reduce = [&](size_t groups, size_t count, int D, bool out_is_dA) {
       Timed t(TLORA_K_GRAD_REDUCE, st);
-      launch_grad_reduce(jobs, reinterpret_cast<const GradGroup*>(tb + pl.tb_gBg), (int)pl.gradB_groups.size(), partial,
-                         pl.d_out, false, accumulate, st);
-    }
-    {
-      Timed t(TLORA_K_GRAD_REDUCE, st);
-      launch_grad_reduce(jobs, reinterpret_cast<const GradGroup*>(tb + pl.tb_gAg), (int)pl.gradA_groups.size(), partial,
-                         pl.d_in, true, accumulate, st);
-    }
+      launch_grad_reduce(jobs, reinterpret_cast<const GradGroup*>(tb + groups), (int)count, partial, D, out_is_dA, accumulate, st);
+    };
+    gradients(b, pl.grads_merged ? a : none);
+    reduce(pl.tb_gBg, pl.gradB_groups.size(), pl.d_out, false);
+    if (!pl.grads_merged) gradients(none, a);           // (its partial tiles take the place of those of dB)
+    reduce(pl.tb_gAg, pl.gradA_groups.size(), pl.d_in, true);
   }
   return launches_ok(__LINE__);
 }
@@ -2274,7 +2288,7 @@ static int check_plan(const Plan& pl, bool fwd_only) {
     if (int rc = check_shrink(pl.shrink_units, 64, kShrinkCols)) return rc;
     if (int rc = check_shrink(pl.stream_units, pl.shrink_rows, 128)) return rc + 100;
     // 4x: dA / dB work units and their partial tiles
-    std::vector<std::pair<int64_t, int64_t>> spans;
+    std::vector<std::pair<int64_t, int64_t>> spans;                  // of partial tiles in use at a time
     auto check_grad = [&](const std::vector<GradUnit>& units, const std::vector<GradGroup>& groups, int D) -> int {
       std::map<std::tuple<int, int, int>, std::vector<const GradUnit*>> by_tile;
       for (const GradUnit& u : units) {
@@ -2319,11 +2333,17 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       return 0;
     };
     if (!fwd_only) {
+      auto disjoint = [&] {
+        std::sort(spans.begin(), spans.end());
+        for (size_t i = 1; i < spans.size(); ++i)
+          if (spans[i - 1].first + spans[i - 1].second > spans[i].first) return false;
+        return true;
+      };
       if (int rc = check_grad(pl.gradB_units, pl.gradB_groups, pl.d_out)) return rc;
+      if (!disjoint()) return 46;
+      if (!pl.grads_merged) spans.clear();
       if (int rc = check_grad(pl.gradA_units, pl.gradA_groups, pl.d_in)) return rc + 100;
-      std::sort(spans.begin(), spans.end());                         // (both may be in use at a time)
-      for (size_t i = 1; i < spans.size(); ++i)
-        if (spans[i - 1].first + spans[i - 1].second > spans[i].first) return 46;
+      if (!disjoint()) return 146;
       if (pl.grads_merged && (int64_t)(pl.gradB_units.size() + pl.gradA_units.size()) > kMaxUnits) return 56;
     } else if (!pl.gradA_units.empty() || !pl.gradB_units.empty()) {
       return 55;
@@ -2339,7 +2359,7 @@ static int check_plan(const Plan& pl, bool fwd_only) {
     if (pl.dtype == TLORA_F32) t.push_back({pl.tb_f32, pl.f32_reserved});
     size_t end = 0;
     for (auto& r : t) {
-      if (r.first % 256 || r.first < end) return 60;
+      if (r.first % (r.first == pl.tb_gBg || r.first == pl.tb_gAg ? sizeof(GradGroup) : 256) || r.first < end) return 60;
       end = r.first + r.second;
     }
     if (end > pl.tables_bytes) return 61;
@@ -2349,7 +2369,10 @@ static int check_plan(const Plan& pl, bool fwd_only) {
     const size_t se = (size_t)pl.s_elems, sx = 2 * (size_t)pl.sx_elems + 256;
     if (bf16 && !fwd_only) {
       w.push_back({pl.off_wt, 2 * (size_t)pl.d_in * (size_t)pl.d_out});
-      w.push_back({pl.off_wt_state, sizeof(WtState)});
+      if (pl.off_wt_state != pl.off_clock + kClockBytes) return 77;
+      w.push_back({pl.off_clock, kClockBytes + sizeof(WtState)});
+    } else {
+      w.push_back({pl.off_clock, kClockBytes});
     }
     if (bf16) {
       w.push_back({pl.off_atp, 2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)});
@@ -2357,7 +2380,6 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       w.push_back({pl.off_ap, 2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)});
     }
     w.push_back({pl.off_tables, pl.tables_bytes});
-    w.push_back({pl.off_clock, 64});
     if (!bf16) {
       w.push_back({pl.off_S, 4 * se});
       if (!fwd_only) w.push_back({pl.off_dS, 4 * se});

@@ -155,6 +155,18 @@ def test_workspace_of_a_batch_serves_every_smaller_one():
             tokens[int(rng.integers(0, J))] += int(rng.choice([1, 37, 256, 1000, 3000]))
 
 
+def test_a_kept_workspace_stays_large_enough():
+    """Buffers of these sizes are in callers' hands: a faster plan has to find its place in them."""
+    for ranks, tokens, d_in, d_out, dtype, kept in [
+            ([256] * 16, [2000] * 16, 5120, 17408, tlora.TLORA_BF16, 799932928), ([512], [6812], 5120, 5120, tlora.TLORA_BF16, 380962560),
+            ([8, 16, 32, 64], [2048, 1024, 4096, 512], 4096, 12288, tlora.TLORA_BF16, 244649728),
+            ([16], [512], 4096, 12288, tlora.TLORA_BF16, 203480832), ([3, 0, 130], [5, 0, 700], 72, 136, tlora.TLORA_BF16, 13849600),
+            ([1024], [52011], 64, 5120, tlora.TLORA_BF16, 932804352), ([4, 8], [64, 64], 256, 256, tlora.TLORA_F32, 12032)]:
+        prob, _keep = _problem(ranks, tokens, d_in=d_in, d_out=d_out, dtype=dtype)
+        assert 0 < tlora.tlora_workspace_bytes(prob) <= kept, (ranks, tokens, d_in, d_out)
+        assert tlora.tlora_plan_check(prob) == (0, 0)
+
+
 def test_a_block_has_one_place_for_its_projections_sums():
     """The projections of an MLP block run one after the other: their partial tiles and sums (64 MiB at this size) are
     reserved once, so the block needs less than its activations and three whole workspaces by two such places."""

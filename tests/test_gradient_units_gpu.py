@@ -38,3 +38,22 @@ def test_gradients_meet_the_oracle(case):
     for got, g in zip(dA2 + dB2, list(dA) + list(dB)):
         want = torch.from_numpy(g).to("cuda") + 3.0
         assert torch.equal(got, want), name
+
+
+def test_gradients_whose_partial_tiles_have_no_room_together():
+    """A long job of the highest rank: dB and dA in a launch each, one after the other through the same room."""
+    import torch
+    from paper_2602_07263_amd import tlora
+    d_in, d_out, r, T, scale = 64, 5120, 1024, 52011, 2.0
+    g = torch.Generator(device="cuda").manual_seed(82)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=g) * std).to(torch.bfloat16)
+    X, W, A, B, dY = rnd(T, d_in), rnd(d_in, d_out), rnd(d_in, r, std=d_in ** -0.5), rnd(r, d_out, std=0.01), rnd(T, d_out)
+    lp = tlora.LayerProblem("bf16", d_in, d_out, [r], [0, T], [scale], X, W, [A], [B])
+    dA, dB = torch.full((d_in, r), 1.0, device="cuda"), torch.full((r, d_out), 1.0, device="cuda")
+    for flags, add in ((0, 0.0), (tlora.TLORA_BWD_ACCUMULATE, 1.0)):
+        lp.bwd(dY, None, [dA], [dB], flags=flags)
+        x, dy, a, b = (t.double() for t in (X, dY, A, B))
+        dA_r, dB_r = scale * x.T @ (dy @ b.T), scale * (x @ a).T @ dy
+        # S and dS as two bf16 planes: 2^-17 of themselves at most; fp32 sums of at most 4096 tokens, then of 13: 2^-24 sqrt(4096)
+        for got, want in ((dA, dA_r), (dB, dB_r)):
+            assert float((got.double() - (1.0 + add) * want).norm() / want.norm()) <= 2 * (2.0 ** -17 + 2.0 ** -18), (flags, want.shape)
