@@ -604,9 +604,11 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
   auto wplace = [&](size_t bytes) { const size_t at = w;  w = align_up(w + bytes, 256);  return at; };
   // the transposed W first, then its state: their place depends on nothing but d_in x d_out, so a copy made by one call is found
   // by later calls on other token batches (nano-batches) that share the workspace
-  if (full) pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
-  pl.off_clock = wplace(kClockBytes + (full ? sizeof(WtState) : 0));
-  pl.off_wt_state = pl.off_clock + kClockBytes;         // (what is known about the copy, in the rest of the clock's 256 bytes)
+  if (full) {
+    pl.off_wt = wplace(2 * (size_t)pl.d_in * (size_t)pl.d_out);
+    pl.off_clock = wplace(kClockBytes + sizeof(WtState));
+    pl.off_wt_state = pl.off_clock + kClockBytes;       // (in the rest of the clock's 256 bytes)
+  }
   // so do the packed adapters, whose places depend on the feature sizes and ranks
   if (pl.dtype == TLORA_BF16) {
     pl.off_atp = wplace(2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in));
@@ -614,6 +616,7 @@ int build_plan(const tlora_problem_t* p, Plan& pl, bool fwd_only = false) {
     pl.off_ap = wplace(2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32));
   }
   pl.off_tables = wplace(full ? res.tables : pl.tables_bytes);
+  if (!full) pl.off_clock = wplace(kClockBytes);
   if (pl.dtype == TLORA_F32) {
     pl.off_S = wplace(sizeof(float) * (size_t)pl.s_elems);
     if (!fwd_only) pl.off_dS = wplace(sizeof(float) * (size_t)pl.s_elems);
@@ -2371,8 +2374,6 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       w.push_back({pl.off_wt, 2 * (size_t)pl.d_in * (size_t)pl.d_out});
       if (pl.off_wt_state != pl.off_clock + kClockBytes) return 77;
       w.push_back({pl.off_clock, kClockBytes + sizeof(WtState)});
-    } else {
-      w.push_back({pl.off_clock, kClockBytes});
     }
     if (bf16) {
       w.push_back({pl.off_atp, 2 * ((size_t)pl.atp_elems + 32 * (size_t)pl.d_in)});
@@ -2380,6 +2381,7 @@ static int check_plan(const Plan& pl, bool fwd_only) {
       w.push_back({pl.off_ap, 2 * (size_t)pl.d_in * (size_t)(pl.r_total + 32)});
     }
     w.push_back({pl.off_tables, pl.tables_bytes});
+    if (!bf16 || fwd_only) w.push_back({pl.off_clock, kClockBytes});
     if (!bf16) {
       w.push_back({pl.off_S, 4 * se});
       if (!fwd_only) w.push_back({pl.off_dS, 4 * se});
