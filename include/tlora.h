@@ -412,9 +412,9 @@ int tlora_plan_dump(const tlora_problem_t* p, int32_t* rpad, int64_t* soff, int3
  * fwd_only != 0 -- and verifies what the kernels rely on: job segments, padded ranks and packed offsets add up; every
  * row tile's adapter range holds all jobs with a row inside it and fits the packed operands; the shrink work units tile
  * each job's [tokens x padded ranks] exactly once; every dA / dB work unit lies inside its job, starts on the token
- * step, owns a partial tile that overlaps no other, and each output tile's partial tiles are consecutive and cover the
- * job's tokens; all tables fit the table block and all workspace regions are disjoint and inside
- * tlora_workspace_bytes().  Returns TLORA_OK, the validation error of `p`, or TLORA_EINVAL with the number of the
+ * step, owns a partial tile that overlaps no other in use with it, and each output tile's partial tiles are consecutive and
+ * cover the job's tokens; sums of cut launches and the fragments of a small batch have their places; all tables fit the table
+ * block and all workspace regions are disjoint and inside tlora_workspace_bytes().  Returns TLORA_OK, the validation error of `p`, or TLORA_EINVAL with the number of the
  * first failed check in *failed_check (may be NULL; 0 when nothing failed).  Used by the CPU tests on random problems. */
 int tlora_plan_check(const tlora_problem_t* p, int32_t fwd_only, int32_t* failed_check);
 
