@@ -179,9 +179,10 @@ void launch_frag_pack(const FragPack& f, hipStream_t st) {
 constexpr int kPackPiece = 1024;               // 16-byte chunks of B_j a workgroup copies at a time
 // ARGS: the call's tables, the job table first, travel as an argument of this launch, which also leaves them in the workspace for the
 // launches that follow: a launch of their own took 2 to 4 us of a forward (13 % of one of 61 tokens).
-struct PackTables {
+struct alignas(8) PackTables {               // (read as JobDev where it lies among the arguments)
   uint32_t w[kPackArgBytes / 4];
 };
+static_assert(alignof(PackTables) >= alignof(JobDev), "the job table is read in place");
 struct NoTables {};
 template <bool ARGS>
 __global__ void __launch_bounds__(256) pack_adapters_kernel(JobDev* job_table, int num_jobs, int d_in, int d_out, int r_total,
